@@ -1,0 +1,311 @@
+"""Workloads of the library for timing: what a program that trains, prunes or serves coupled-sparse models asks of it,
+through the public entry points of `paper_2511_11641_amd` (`binding`, `layer`, `stack`).
+
+A case is a dict of plain values.  Kinds:
+  ffn_f32   steps 1-5 on one fp32 FFN pair: score, select, gather, forward, backward
+  layer     an attention block followed by an FFN block, bf16; `task` is
+              forward   forward only, nothing kept for a backward pass
+              train     forward and backward (saved activations, input gradient, every weight and bias gradient)
+              step      the importance estimated again first: score + select, gather with transposed copies and rotary
+                        tables, then forward and backward
+  prune     steps 1-3 over a stack of layers, one batched call each (what a re-estimation of a whole model does)
+  stack     a whole model: `task` forward gives the logits of every position, train is one training step (forward,
+            cross-entropy, backward, AdamW on the compact tensors, refreshed transposed copies)
+keep = num / den of every pair's inner dimensions.  Weights are N(0, 0.02^2) with every inner dimension scaled by its own
+log-normal factor (the spread of pair norms that trained weights show), activations and upstream gradients N(0, 1).
+"""
+import math
+
+import torch
+
+from paper_2511_11641_amd import binding as B
+from paper_2511_11641_amd.layer import AttnBlock, FfnBlock, rows_aligned
+from paper_2511_11641_amd.stack import DecoderStack
+
+# the two layer shapes of the paper's pre-training runs that the benchmark is quoted on, and the wide one
+GPT2M = {"d": 1024, "h": 16, "h_kv": 16, "d_h": 64, "d_ff": 4096, "gated": False, "rope": False, "bias": True, "causal": True}
+LLAMA1B = {"d": 2048, "h": 32, "h_kv": 32, "d_h": 64, "d_ff": 5461, "gated": True, "rope": True, "bias": False, "causal": True}
+LLAMA7B = {"d": 4096, "h": 32, "h_kv": 32, "d_h": 128, "d_ff": 11008, "gated": True, "rope": True, "bias": False, "causal": True}
+DEIT_S = {"d": 384, "h": 6, "h_kv": 6, "d_h": 64, "d_ff": 1536, "gated": False, "rope": False, "bias": True, "causal": False}
+
+
+def listed():
+    return [
+        # the single fp32 FFN pair of the first benchmark configuration: ten short launches, nothing but latency
+        {"name": "ffn_f32", "kind": "ffn_f32", "T": 512, "d": 256, "n": 1024, "num": 1, "den": 2},
+        # prefill of one short prompt through a half-kept layer: a few dozen tokens, so weights and launches are the cost
+        {"name": "prompt_61", "kind": "layer", "task": "forward", **LLAMA1B, "B": 1, "L": 61, "num": 1, "den": 2},
+        # forward of the whole 24-layer model at batch 1 (the inference benchmark's latency point)
+        {"name": "stack_infer_b1", "kind": "stack", "task": "forward", **GPT2M, "layers": 24, "vocab": 50304, "B": 1, "L": 1024, "num": 1, "den": 2},
+        # forward at batch 32 and the smallest keep ratio of the sweep (throughput serving, scoring of a corpus)
+        {"name": "infer_b32", "kind": "layer", "task": "forward", **GPT2M, "B": 32, "L": 1024, "num": 3, "den": 10},
+        # fine-tuning a small vision model: 197 tokens per image, no mask, narrow matrices, token count off every tile
+        {"name": "vit_train", "kind": "layer", "task": "train", **DEIT_S, "B": 61, "L": 197, "num": 1, "den": 2},
+        # the two layer configurations of the headline metric, importance estimated again in front of the pass
+        {"name": "gpt2m_step", "kind": "layer", "task": "step", **GPT2M, "B": 8, "L": 1024, "num": 1, "den": 2},
+        {"name": "llama1b_step", "kind": "layer", "task": "step", **LLAMA1B, "B": 16, "L": 256, "num": 1, "den": 2},
+        # the dense layer through the same code (the first stage of every schedule)
+        {"name": "llama1b_dense", "kind": "layer", "task": "train", **LLAMA1B, "B": 16, "L": 256, "num": 1, "den": 1},
+        # shared key/value heads, ragged batch: sequences of 381 tokens, eleven of them
+        {"name": "gqa_ragged", "kind": "layer", "task": "train", **LLAMA1B, "h_kv": 8, "B": 11, "L": 381, "num": 3, "den": 8},
+        # the wide layer early in a schedule: 96 of 128 head dims kept
+        {"name": "llama7b_train", "kind": "layer", "task": "train", **LLAMA7B, "B": 4, "L": 512, "num": 3, "den": 4},
+        # re-estimation of a 24-layer model (every couple of hundred steps)
+        {"name": "prune_24", "kind": "prune", **GPT2M, "layers": 24, "num": 1, "den": 2},
+        # one training step of a model: embedding, layers, vocabulary projection, loss, optimizer
+        {"name": "stack_train", "kind": "stack", "task": "train", **LLAMA1B, "layers": 4, "vocab": 32000, "B": 32, "L": 256, "num": 1, "den": 2},
+    ]
+
+
+KEEPS = ((1, 1), (7, 8), (3, 4), (5, 8), (1, 2), (3, 8), (3, 10), (1, 4))
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _shape(rng, d_hi):
+    d = 64 * _log(rng, 3, d_hi // 64)
+    d_h = rng.choice((32, 48, 64, 64, 96, 128))
+    h = max(2, round(d / d_h))
+    gated = rng.random() < 0.5
+    return {"d": d, "h": h, "h_kv": h // 2 if h % 2 == 0 and rng.random() < 0.25 else h, "d_h": d_h, "d_ff": int(d * rng.uniform(2.5, 4.0)),
+            "gated": gated, "rope": gated, "bias": not gated, "causal": rng.random() < 0.8}
+
+
+def draw(rng):
+    """One more case of the same kinds; sizes over the whole range, any integers where the library takes any."""
+    most = 0.8 * work(listed()[-1])["flops"]
+    while True:
+        kind = rng.choice(("ffn_f32", "forward", "forward", "train", "train", "train", "step", "step", "prune", "stack_f", "stack_t"))
+        num, den = rng.choice(KEEPS)
+        L = _log(rng, 17, 1500)
+        if kind == "ffn_f32":
+            c = {"kind": "ffn_f32", "T": _log(rng, 64, 2048), "d": 8 * _log(rng, 8, 96), "n": _log(rng, 128, 3000), "num": num, "den": den}
+        elif kind in ("forward", "train", "step"):
+            tokens = _log(rng, 32 if kind == "forward" else 512, 32768 if kind == "forward" else 16384)
+            c = {"kind": "layer", "task": kind, **_shape(rng, 4096), "B": max(1, round(tokens / L)), "L": L, "num": num, "den": den}
+        elif kind == "prune":
+            c = {"kind": "prune", **_shape(rng, 2048), "layers": rng.randint(1, 24), "num": num, "den": den}
+        else:
+            task = "train" if kind == "stack_t" else "forward"
+            L = min(L, 1024)
+            c = {"kind": "stack", "task": task, **_shape(rng, 2048), "causal": True, "layers": rng.randint(2, 4 if task == "train" else 12),
+                 "vocab": 8 * _log(rng, 500, 6000), "B": max(1, round(_log(rng, 256, 8192) / L)), "L": L, "num": num, "den": den}
+        w = work(c)
+        if w["flops"] <= most and w["bytes"] < 6e9:
+            return c
+
+
+# ---- preparation ------------------------------------------------------------------------------------------------------
+def _weights(c, gen, dtype, w2_rows):
+    d, hd, kvd, n = c["d"], c["h"] * c["d_h"], c["h_kv"] * c["d_h"], c["d_ff"]
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen)
+    spread = lambda m: torch.exp(0.5 * rnd(m))[:, None]
+    w = {"wq": rnd(hd, d) * spread(hd), "wk": rnd(kvd, d) * spread(kvd), "wv": rnd(kvd, d) * spread(kvd), "wo": rnd(hd, d) * spread(hd),
+         "w1": rnd(n, d) * spread(n), "w2": rnd(n, d) * spread(n)}
+    if c["gated"]:
+        w["w1b"] = rnd(n, d)
+    if c["bias"]:
+        w.update(bq=rnd(hd), bk=rnd(kvd), bv=rnd(kvd), bo=rnd(d), b1=rnd(n), b2=rnd(d))
+    w = {k: (v * 0.02).to(dtype) for k, v in w.items()}
+    if not w2_rows:      # the Linear layout: units of the second members as columns
+        w["wo"], w["w2"] = w["wo"].t().contiguous(), rows_aligned(w["w2"].t().contiguous())
+    return w
+
+
+def _blocks(ctx, c, w, rows, transposed):
+    act = B.ACT_SWIGLU if c["gated"] else B.ACT_GELU_ERF
+    attn = AttnBlock(ctx, w["wq"], w["wk"], w["wv"], w["wo"], w.get("bq"), w.get("bk"), w.get("bv"), w.get("bo"), c["h"], c["d_h"],
+                     rope=c["rope"], causal=c["causal"], transposed=transposed, h_kv=c["h_kv"], wo_rows=rows)
+    ffn = FfnBlock(ctx, w["w1"], w.get("b1"), w["w2"], w.get("b2"), act, w.get("w1b"), transposed=transposed, w2_rows=rows)
+    return attn, ffn
+
+
+def _kept(c):
+    unit = 2 if c["rope"] else 1
+    return (c["d_h"] // unit) * c["num"] // c["den"], c["d_h"] * c["num"] // c["den"], c["d_ff"] * c["num"] // c["den"]
+
+
+def _prepare_layer(c, gen):
+    ctx = B.Context()
+    train = c["task"] != "forward"
+    rows = c["task"] == "step"
+    attn, ffn = _blocks(ctx, c, _weights(c, gen, torch.bfloat16, rows), rows, train)
+    k = _kept(c)
+    idx = [torch.empty((c["h_kv"] if i < 2 else 1, kk), dtype=torch.int32, device="cuda") for i, kk in enumerate(k)]
+    pairs = attn.pairs() + [ffn.pair()]
+    arr = (B.Pair * 3)(*pairs)
+    scores, _ = ctx.ecospa_score_select(arr, k, idx=idx)
+    attn.compact(idx[0], idx[1])
+    ffn.compact(idx[2])
+    attn.alloc(c["B"], c["L"])
+    ffn.alloc(c["B"], c["L"])
+    st = {"ctx": ctx, "attn": attn, "ffn": ffn, "pairs": arr, "k": k, "scores": scores, "idx": idx}
+    if rows:
+        items = attn.compact(idx[0], idx[1], defer=True) + ffn.compact(idx[2], defer=True)
+        st["items"], st["rope"] = (B.MapItem * len(items))(*items), attn.rope_item()
+        post = attn.post_gather_items() + ffn.post_gather_items()
+        st["post"] = (B.TransposeItem * len(post))(*post) if post else None
+    T = c["B"] * c["L"]
+    st["x"] = torch.randn(T, c["d"], device="cuda", generator=gen).to(torch.bfloat16)
+    if train:
+        st["dy"] = torch.randn(T, c["d"], device="cuda", generator=gen).to(torch.bfloat16)
+    return st
+
+
+def _prepare_ffn(c, gen):
+    ctx = B.Context()
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen)
+    n, d, T = c["n"], c["d"], c["T"]
+    w1 = rnd(n, d) * torch.exp(0.5 * rnd(n))[:, None] * 0.02
+    w2 = (rnd(d, n) * torch.exp(0.5 * rnd(n)) * 0.02).contiguous()
+    blk = FfnBlock(ctx, w1, rnd(n) * 0.02, w2, rnd(d) * 0.02, B.ACT_GELU_ERF)
+    idx = torch.empty((1, n * c["num"] // c["den"]), dtype=torch.int32, device="cuda")
+    pair = (B.Pair * 1)(blk.pair())
+    scores = ctx.ecospa_coupled_score(pair)
+    ctx.ecospa_select_topk(scores[0], idx.shape[1], out=idx)
+    blk.compact(idx)
+    blk.alloc(1, T)
+    return {"ctx": ctx, "blk": blk, "pair": pair, "scores": scores, "idx": idx, "x": rnd(T, d), "dy": rnd(T, d)}
+
+
+def _prepare_prune(c, gen):
+    ctx = B.Context()
+    layers = [_blocks(ctx, c, _weights(c, gen, torch.bfloat16, True), True, True) for _ in range(c["layers"])]
+    k = _kept(c)
+    pairs = [p for a, f in layers for p in a.pairs() + [f.pair()]]
+    arr = (B.Pair * len(pairs))(*pairs)
+    scores = ctx.ecospa_coupled_score(arr)
+    idx = [torch.empty((s.shape[0], k[i % 3]), dtype=torch.int32, device="cuda") for i, s in enumerate(scores)]
+    sel = [ctx.select_item(s, o.shape[1], o) for s, o in zip(scores, idx)]
+    sel = (B.SelectItem * len(sel))(*sel)
+    ctx.ecospa_select_topk_batch(sel)
+    items = []
+    for i, (a, f) in enumerate(layers):
+        items += a.compact(idx[3 * i], idx[3 * i + 1], defer=True) + f.compact(idx[3 * i + 2], defer=True)
+    post = [t for a, f in layers for t in a.post_gather_items() + f.post_gather_items()]
+    return {"ctx": ctx, "layers": layers, "pairs": arr, "scores": scores, "idx": idx, "sel": sel, "items": (B.MapItem * len(items))(*items),
+            "post": (B.TransposeItem * len(post))(*post) if post else None}
+
+
+def _prepare_stack(c, gen, seed):
+    ctx = B.Context()
+    st = DecoderStack(ctx, c, c["layers"], c["vocab"], keep=(c["num"], c["den"]), seed=seed, train=c["task"] == "train")
+    # token ids as text has them: a few frequent ones, a long tail
+    ids = (c["vocab"] * torch.rand(c["B"] * c["L"] + 1, device="cuda", generator=gen) ** 3).long().clamp_(max=c["vocab"] - 1)
+    return {"stack": st, "ids": ids[:-1].contiguous(), "targets": ids[1:].contiguous()}
+
+
+def prepare(case, seed):
+    c = dict(case)
+    c["kind"] = case["kind"]
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    if c["kind"] == "ffn_f32":
+        st = _prepare_ffn(c, gen)
+    elif c["kind"] == "layer":
+        st = _prepare_layer(c, gen)
+    elif c["kind"] == "prune":
+        st = _prepare_prune(c, gen)
+    else:
+        st = _prepare_stack(c, gen, seed)
+    st["case"] = c
+    return st
+
+
+# ---- one pass -----------------------------------------------------------------------------------------------------------
+def run(state):
+    c = state["case"]
+    if c["kind"] == "ffn_f32":
+        ctx, blk = state["ctx"], state["blk"]
+        ctx.ecospa_coupled_score(state["pair"], out=state["scores"])
+        ctx.ecospa_select_topk(state["scores"][0], state["idx"].shape[1], out=state["idx"])
+        blk.compact(state["idx"])
+        y = blk.fwd(state["x"])
+        dx = blk.bwd(state["x"], state["dy"])
+        return {"scores": state["scores"], "idx": state["idx"], "y": y, "dx": dx, "dw1": blk.dw1_c, "db1": blk.db1_c, "dw2": blk.dw2_c, "db2": blk.db2}
+    if c["kind"] == "layer":
+        attn, ffn = state["attn"], state["ffn"]
+        if c["task"] == "forward":
+            return ffn.fwd(attn.fwd(state["x"], save=False), save=False)
+        out = {}
+        if c["task"] == "step":
+            ctx = state["ctx"]
+            ctx.ecospa_score_select(state["pairs"], state["k"], state["scores"], state["idx"])
+            ctx.ecospa_compact_batch(state["items"], state["rope"])
+            if state["post"] is not None:
+                ctx.ecospa_transpose_batch(state["post"])
+            out = {"scores": state["scores"], "idx": state["idx"]}
+        x = state["x"]
+        y1 = attn.fwd(x)
+        y = ffn.fwd(y1)
+        d1 = ffn.bwd(y1, state["dy"])
+        dx = attn.bwd(x, d1)
+        out.update(y=y, dx=dx, dwqkv=attn.dwqkv_c, dwo=attn.dwo_c, dw1=ffn.dw1_c, dw2=ffn.dw2_c)
+        if c["bias"]:
+            out.update(dbqkv=attn.dbqkv_c, dbo=attn.dbo, db1=ffn.db1_c, db2=ffn.db2)
+        return out
+    if c["kind"] == "prune":
+        ctx = state["ctx"]
+        ctx.ecospa_coupled_score(state["pairs"], out=state["scores"])
+        ctx.ecospa_select_topk_batch(state["sel"])
+        ctx.ecospa_compact_batch(state["items"])
+        if state["post"] is not None:
+            ctx.ecospa_transpose_batch(state["post"])
+        ends = state["layers"][:1] + state["layers"][-1:]        # (64 outputs at most: the first and the last layer's matrices)
+        return {"idx": state["idx"][:20], "compact": [[a.wqkv_c, a.wqkv_t, a.wo_c, a.wo_t, f.w1_c, f.w1_t, f.w2_c, f.w2_t] for a, f in ends],
+                "scores": state["scores"][:20]}
+    st = state["stack"]
+    if c["task"] == "forward":
+        return st.forward(state["ids"])
+    loss = st.train_step(state["ids"], state["targets"])
+    blk = [(ly.attn["w"], ly.ffn["w"]) for ly in st.layers]
+    glue = [p for ly in st.layers for ps in ly.norm for p in ps] + st.norm_f + [st.emb, st.lm] + ([st.pos] if st.pos is not None else [])
+    return {"loss": loss, "dlogits": st.logits, "grads": [[a.dwqkv_c, a.dwo_c, f.dw1_c, f.dw2_c] for a, f in blk],
+            "weights": [[a.wqkv_c, a.wo_c, f.w1_c, f.w2_c] for a, f in blk[:2]], "glue": [p.g for p in glue][:20], "table": st.emb.w}
+
+
+# ---- what a pass cannot do without -----------------------------------------------------------------------------------------
+def _layer_work(c, T, L, kq, kv, kf):
+    """(kept weights of a layer, forward flops of a layer): kept dimensions, causal attention at half."""
+    g = 2 if c["gated"] else 1
+    params = c["d"] * ((c["h"] + c["h_kv"]) * kq + (c["h"] + c["h_kv"]) * kv + (g + 1) * kf)
+    return params, 2.0 * T * params + 2.0 * T * L * c["h"] * (kq + kv) * (0.5 if c["causal"] else 1.0)
+
+
+def work(case):
+    c = case
+    if c["kind"] == "ffn_f32":
+        k, T, d, n = c["n"] * c["num"] // c["den"], c["T"], c["d"], c["n"]
+        return {"bytes": 4.0 * (2 * n * d + 4 * T * d + 4 * k * d + n), "flops": 12.0 * T * d * k + 4.0 * n * d}
+    kq, kv, kf = _kept(c)
+    kq *= 2 if c["rope"] else 1
+    d, g = c["d"], 2 if c["gated"] else 1
+    full = d * (2 * (c["h"] + c["h_kv"]) * c["d_h"] + (g + 1) * c["d_ff"])
+    if c["kind"] == "prune":
+        params, _ = _layer_work(c, 1, 1, kq, kv, kf)
+        return {"bytes": c["layers"] * 2.0 * (full + 2 * params), "flops": c["layers"] * 2.0 * full}
+    T = c["B"] * c["L"]
+    params, fwd = _layer_work(c, T, c["L"], kq, kv, kf)
+    if c["kind"] == "layer":
+        if c["task"] == "forward":
+            return {"bytes": 2.0 * (params + 2 * T * d), "flops": fwd}
+        prune = 2.0 * (full + 2 * params) if c["task"] == "step" else 0.0
+        return {"bytes": 2.0 * (2 * params + 4 * T * d) + prune, "flops": 3.0 * fwd + (2.0 * full if prune else 0.0)}
+    head = d * c["vocab"]
+    flops = c["layers"] * fwd + 2.0 * T * head
+    if c["task"] == "forward":
+        return {"bytes": 2.0 * (c["layers"] * params + head + 2 * T * d + T * c["vocab"]), "flops": flops}
+    n = c["layers"] * params + 2 * head
+    return {"bytes": 2.0 * T * c["vocab"] + 28.0 * n, "flops": 3.0 * flops}
+
+
+def tolerance(case):
+    """About four times what the path differs by from the same arithmetic in fp64 (fp32 pair: 5e-7 on every output; scores:
+    below 3e-7, gathered matrices bit for bit) or, in bf16, from fp32 arithmetic without its roundings (outputs of a layer: 4e-3 to 5e-3,
+    worst element 0.12 of the root mean square)."""
+    if case["kind"] == "ffn_f32":
+        return {"rel": 2e-6}
+    if case["kind"] == "prune":
+        return {"rel": 1e-6}
+    return {"rel": 2e-2, "max": 0.5}
