@@ -260,9 +260,10 @@ def run(state):
         return st.forward(state["ids"])
     loss = st.train_step(state["ids"], state["targets"])
     blk = [(ly.attn["w"], ly.ffn["w"]) for ly in st.layers]
-    glue = [p for ly in st.layers for ps in ly.norm for p in ps] + st.norm_f + [st.emb, st.lm] + ([st.pos] if st.pos is not None else [])
+    norms = [p.g for ly in st.layers for ps in ly.norm for p in ps] + [p.g for p in st.norm_f]
+    # the two tables as updated: a table's gradient is a few frequent rows that dwarf, and cancel to, the others
     return {"loss": loss, "dlogits": st.logits, "grads": [[a.dwqkv_c, a.dwo_c, f.dw1_c, f.dw2_c] for a, f in blk],
-            "weights": [[a.wqkv_c, a.wo_c, f.w1_c, f.w2_c] for a, f in blk[:2]], "glue": [p.g for p in glue][:20], "table": st.emb.w}
+            "weights": [[a.wqkv_c, a.wo_c, f.w1_c, f.w2_c] for a, f in blk[:2]], "norms": norms[:20], "tables": [st.emb.w, st.lm.w]}
 
 
 # ---- what a pass cannot do without -----------------------------------------------------------------------------------------
@@ -303,9 +304,12 @@ def work(case):
 def tolerance(case):
     """About four times what the path differs by from the same arithmetic in fp64 (fp32 pair: 5e-7 on every output; scores:
     below 3e-7, gathered matrices bit for bit) or, in bf16, from fp32 arithmetic without its roundings (outputs of a layer: 4e-3 to 5e-3,
-    worst element 0.12 of the root mean square)."""
+    worst element 0.12 of the root mean square).  Whole models: products added in another order give logits of 24 layers that differ
+    by 1.2e-2, and after one update gradients of four layers by 1.7e-2 (worst element 0.15)."""
     if case["kind"] == "ffn_f32":
         return {"rel": 2e-6}
     if case["kind"] == "prune":
         return {"rel": 1e-6}
+    if case["kind"] == "stack":
+        return {"rel": 3e-2, "max": 0.6}
     return {"rel": 2e-2, "max": 0.5}
