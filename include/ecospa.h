@@ -420,14 +420,10 @@ int ecospa_coupled_bwd(ecospa_ctx* ctx, const ecospa_block_desc* desc /*host*/, 
  *   C[m, n] = sum_k A(m, k) * B(n, k) (+ bias[n]),   m < M, n < N, k < K,   fp32 accumulation,
  *   A(m, k) = A[m*lda + k] (trans_a = 0) or A[k*lda + m] (trans_a = 1); B(n, k) likewise with ldb.
  * So x W^T is (0, 0), dY W is (0, 1) and dY^T X is (1, 1).  bias may be NULL.
- * tile (bf16 only; for tests and tuning): 0 = library's choice; 1 / 2 = 128x128 / 256x256 workgroup
- * tiles staged through registers, K-slow operands transposed on the way to LDS; 3 / 4 = the same with
- * K-slow operands read by transposing LDS reads; 10..19 and 21 = configurations 0..9 and 10 of the
- * software-pipelined kernel (direct global->LDS ring; needs K and K/splits to be multiples of its slab
- * depth, else the library falls back to its own choice); 20 = the register-prefetch kernel (256x256 tiles) for long
- * contractions with a K-slow B; 30..38 = the same kernel for dY^T X (both operands K-slow) with tiles 256x256,
- * 192x256, 256x192, 128x256, 256x128, 192x192, 128x192, 192x128, 128x128 (needs K and the K range of a split to be
- * multiples of 64).
+ * tile (bf16 only; for tests and tuning): 0 = library's choice; any other code names a workgroup tile (rows x columns of C; where
+ * that tile is not built for the operand form, the library chooses): 1, 3 = 128x128; 2, 4, 20 = 256x256; 10 .. 19 = 256x256, 256x256,
+ * 256x128, 128x256, 128x128, 256x256, 128x128, 256x256, 256x256, 256x128; 21 = 256x192; 30 .. 38 = 256x256, 192x256, 256x192,
+ * 128x256, 256x128, 192x192, 128x192, 192x128, 128x128.
  * splits: 0 = library's choice, otherwise the number of K splits (partials come from the
  * workspace and are added in a fixed order).
  * bf16 needs 16-byte aligned pointers, N % 8 == 0, leading dimensions % 8 == 0 and the

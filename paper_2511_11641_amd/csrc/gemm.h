@@ -46,7 +46,7 @@ struct GemmDesc {
   const void* B;
   long long ldb;
   int trans_b;
-  int tile;          // 0 = choose, 1 = 128x128 workgroup tiles, 2 = 256x256
+  int tile;          // 0 = choose, otherwise a tile code of ecospa_contract
   int splits;        // > 1: split K, fp32 partials in `partial`, reduced in a fixed order
   float* partial;    // [splits][M][N] when splits > 1
   int defer_reduce;  // splits > 1: only write the partials; the caller runs ecospa_gemm_reduce later
@@ -66,31 +66,15 @@ int ecospa_gemm_reduce(ecospa_ctx* ctx, const GemmDesc& d);
 // How many K splits a (M, N, K) problem should use to fill the chip, and the bytes of partials.
 int ecospa_gemm_splits(int M, int N, int K);
 // The same question for the contractions whose M is the token count (x W^T and dY W): with few tokens (inference
-// at batch 1) their output has too few tiles for the chip, and K is split until the 128x128 tiles reach a
-// workgroup per compute unit, keeping at least 1024 of K per split (shorter splits lose more to the partial sums
-// than they gain: measured on the batch-1 forward of the 24-layer stack); 1 for the training shapes.
+// at batch 1) their output has too few tiles for the chip; 1 for the training shapes.
 int ecospa_gemm_token_splits(int M, int N, int K);
 
-// Software-pipelined kernel for full K slabs (gemm_pipe.hip): configurations 0 .. GEMM_PIPE_CONFIGS-1
-// differ in workgroup tile, slab depth and LDS ring length; d.tile = 10 + configuration forces one.
-#define GEMM_PIPE_CONFIGS 11
-bool gemm_pipe_ok(const GemmDesc& d, int cfg, int k_chunk);
-hipError_t gemm_pipe_launch(ecospa_ctx* ctx, const GemmDesc& d, int cfg, int k_chunk);
-int gemm_pipe_bk(int cfg);
-
-// Register-staged kernel with a two-slab prefetch (gemm_rs.hip): bm x bn x 64 tiles, four wavefronts.
-// 256 x 256: A K-contiguous with B either way, or both K-slow; the narrower shapes (bm, bn from 128, 192, 256)
-// are built for dY^T X only.  d.tile = 20 forces 256 x 256, d.tile = 30 + i shape i of GEMM_RS_SHAPES.
-bool gemm_rs_ok(const GemmDesc& d, int k_chunk);
-bool gemm_rs_shape_ok(int bm, int bn);
-hipError_t gemm_rs_launch(ecospa_ctx* ctx, const GemmDesc& d, int k_chunk, int bm, int bn);
-#define GEMM_RS_NSHAPES 9
-static const int GEMM_RS_SHAPES[GEMM_RS_NSHAPES][2] = {{256, 256}, {192, 256}, {256, 192}, {128, 256}, {256, 128},
-                                                       {192, 192}, {128, 192}, {192, 128}, {128, 128}};
-// Plan of a weight-gradient contraction dY^T X (M x N outputs, K = tokens): tile shape and number of K splits that
-// finish soonest on 256 compute units by a cost model fitted to measurements; false if the problem does not suit
-// the kernel (K not a multiple of 64, too short).
-bool gemm_tt_plan(int M, int N, int K, int* bm, int* bn, int* splits);
+// The bf16 kernel (gemm_ring.h): launch of tile shape `shape` (index into the table in gemm.hip; not every shape is built for every
+// form).  k_chunk: K range of a split, a multiple of 64.
+#define GEMM_RING_NSHAPES 12
+hipError_t gemm_ring_launch_nt(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk);
+hipError_t gemm_ring_launch_tt(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk);
+hipError_t gemm_ring_launch_mixed(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk);
 
 // The small jobs that follow the contractions of a backward pass, batched into ONE launch (each of
 // them alone would be bound by the fixed cost of a launch): fixed-order reductions of split-K

@@ -1,327 +1,10 @@
-// Dense contractions of the reduced forward/backward pass.
+// Dense contractions of the reduced forward/backward pass: choice of kernel, tile shape and K split, the fp32 kernel, and the
+// reductions of split contractions.
 //
-// bf16: 128x128x64 workgroup tiles, 4 wavefronts of 64x64, v_mfma_f32_32x32x16_bf16, operands
-//       staged through XOR-swizzled LDS with register double buffering; operands whose K index
-//       is the slow storage axis (dY W, dY^T X) are transposed in registers on the way to LDS.
-// fp32: 64x64x16 vector-ALU tiles (the fp32 configuration is small and launch bound).
+// bf16: the kernel of gemm_ring.h (MFMA, direct global -> LDS loads).
+// fp32: 64x64x32 vector-ALU tiles (the fp32 configuration is small and launch bound).
 // Split-K writes fp32 partials that a second kernel adds in a fixed order (deterministic dW).
-#include "gemm_lds.h"
-
-// ---------------------------------------------------------------------------------------------
-// bf16 MFMA kernel, parametrised by the workgroup tile BM x BN and the WGM x WGN grid of wavefronts
-// ---------------------------------------------------------------------------------------------
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-// LDS operand tiles are [rows][BK] bf16 with the 16-byte chunks of a row XOR-swizzled by the row
-// index, so that the 32 lanes that read one k-chunk of 32 consecutive rows spread over the banks.
-template <int BK>
-__device__ __forceinline__ int lds_off(int row, int chunk) {
-  constexpr int CPR = BK / 8;                       // chunks per row (8 for BK = 64, 4 for BK = 32)
-  const int f = BK == 64 ? (row ^ (row >> 3)) : ((row >> 1) ^ (row >> 3));
-  return row * BK + ((chunk ^ (f & (CPR - 1))) << 3);
-}
-
-// Loads are unconditional (straight-line code that the scheduler can interleave with MFMAs): row
-// indices beyond the matrix are clamped - such rows only feed outputs that are never stored - and
-// only a K slab that crosses k_end (FULL = false) zero-fills its out-of-range chunks.
-// K-contiguous operand: the tile is ROWS x BK/8 chunks of 8 elements.
-template <int ROWS, int BK, int THREADS, bool FULL>
-__device__ __forceinline__ void gload_kc(const bf16_t* __restrict__ base, long long ld, int row0, int R, int k0,
-                                         int k_end, u32x4 (&reg)[(ROWS * BK / 8 / THREADS < 4 ? 4 : ROWS * BK / 8 / THREADS)]) {
-  constexpr int CPR = BK / 8;
-#pragma unroll
-  for (int i = 0; i < ROWS * CPR / THREADS; ++i) {
-    const int c = threadIdx.x + i * THREADS;
-    const int gr = min(row0 + c / CPR, R - 1), gk = k0 + (c % CPR) * 8;
-    if (FULL) {
-      reg[i] = *reinterpret_cast<const u32x4*>(base + static_cast<long long>(gr) * ld + gk);
-    } else {
-      const u32x4 v = *reinterpret_cast<const u32x4*>(base + static_cast<long long>(gr) * ld + min(gk, k_end - 8));
-      reg[i] = gk < k_end ? v : u32x4{0u, 0u, 0u, 0u};
-    }
-  }
-}
-template <int ROWS, int BK, int THREADS>
-__device__ __forceinline__ void sstore_kc(bf16_t* lds, const u32x4 (&reg)[(ROWS * BK / 8 / THREADS < 4 ? 4 : ROWS * BK / 8 / THREADS)]) {
-  constexpr int CPR = BK / 8;
-#pragma unroll
-  for (int i = 0; i < ROWS * CPR / THREADS; ++i) {
-    const int c = threadIdx.x + i * THREADS;
-    *reinterpret_cast<u32x4*>(lds + lds_off<BK>(c / CPR, c % CPR)) = reg[i];
-  }
-}
-// K-contiguous operand, full K slab, BK = 64: global -> LDS without passing through registers.
-// One global_load_lds_dwordx4 of a wavefront fills 64 consecutive 16-byte chunks of LDS (lane i
-// writes chunk i of the 1 KB block the wave-uniform base points at) = 8 tile rows.  The swizzle is
-// applied on the global side: the lane that owns physical chunk pc of row r fetches the logical
-// k-chunk that lds_off() maps there.
-template <int ROWS, int THREADS>
-__device__ __forceinline__ void dload_kc(const bf16_t* __restrict__ base, long long ld, int row0, int R, int k0,
-                                         lds_bf16_t* tile) {
-  constexpr int PER = ROWS / 8 / (THREADS / 64);     // 8-row groups per wavefront
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r = lane >> 3, pc = lane & 7;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int group = wave * PER + i;
-    const int row = group * 8 + r;
-    const int kc = pc ^ ((row ^ (row >> 3)) & 7);
-    const int gr = min(row0 + row, R - 1);
-    __builtin_amdgcn_global_load_lds(base + static_cast<long long>(gr) * ld + k0 + kc * 8, tile + group * 8 * 64, 16, 0, 0);
-  }
-}
-// K-slow operand (storage [K][R]): 4(k) x 8(r) blocks, transposed in registers on the way to LDS
-template <int ROWS, int BK, int THREADS, bool FULL>
-__device__ __forceinline__ void gload_tr(const bf16_t* __restrict__ base, long long ld, int row0, int R, int k0,
-                                         int k_end, u32x4 (&reg)[(ROWS * BK / 8 / THREADS < 4 ? 4 : ROWS * BK / 8 / THREADS)]) {
-  constexpr int NSUB = ROWS * BK / 32;            // 4 x 8 sub-blocks in the tile
-#pragma unroll
-  for (int b = 0; b < (NSUB + THREADS - 1) / THREADS; ++b) {
-    const int sb = threadIdx.x + b * THREADS;
-    if (NSUB % THREADS != 0 && sb >= NSUB) break;
-    const int rblk = sb % (ROWS / 8), kblk = sb / (ROWS / 8);
-    const int gr = min(row0 + rblk * 8, R - 8);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int gk = k0 + kblk * 4 + i;
-      if (FULL) {
-        reg[b * 4 + i] = *reinterpret_cast<const u32x4*>(base + static_cast<long long>(gk) * ld + gr);
-      } else {
-        const u32x4 v = *reinterpret_cast<const u32x4*>(base + static_cast<long long>(min(gk, k_end - 1)) * ld + gr);
-        reg[b * 4 + i] = gk < k_end ? v : u32x4{0u, 0u, 0u, 0u};
-      }
-    }
-  }
-}
-template <int ROWS, int BK, int THREADS>
-__device__ __forceinline__ void sstore_tr(bf16_t* lds, const u32x4 (&reg)[(ROWS * BK / 8 / THREADS < 4 ? 4 : ROWS * BK / 8 / THREADS)]) {
-  constexpr int NSUB = ROWS * BK / 32;
-#pragma unroll
-  for (int b = 0; b < (NSUB + THREADS - 1) / THREADS; ++b) {
-    const int sb = threadIdx.x + b * THREADS;
-    if (NSUB % THREADS != 0 && sb >= NSUB) break;
-    const int rblk = sb % (ROWS / 8), kblk = sb / (ROWS / 8);
-    const int kc = kblk >> 1, half = kblk & 1;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int r = rblk * 8 + j;
-      uint32_t e[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) e[i] = (j & 1) ? (reg[b * 4 + i][j >> 1] >> 16) : (reg[b * 4 + i][j >> 1] & 0xffffu);
-      u32x2 v;
-      v.x = e[0] | (e[1] << 16);
-      v.y = e[2] | (e[3] << 16);
-      *reinterpret_cast<u32x2*>(lds + lds_off<BK>(r, kc) + half * 4) = v;
-    }
-  }
-}
-
-// K-slow operand kept as it lies in memory, [BK][ROWS] (fragments then come from transposing LDS
-// reads): the four 16-byte pieces of a thread's 4(k) x 8(r) block go to four k rows - no shuffling.
-template <int ROWS, int BK, int THREADS>
-__device__ __forceinline__ void sstore_ks(bf16_t* lds, const u32x4 (&reg)[(ROWS * BK / 8 / THREADS < 4 ? 4 : ROWS * BK / 8 / THREADS)]) {
-  constexpr int NSUB = ROWS * BK / 32;
-#pragma unroll
-  for (int b = 0; b < (NSUB + THREADS - 1) / THREADS; ++b) {
-    const int sb = threadIdx.x + b * THREADS;
-    if (NSUB % THREADS != 0 && sb >= NSUB) break;
-    const int rblk = sb % (ROWS / 8), kblk = sb / (ROWS / 8);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(lds + ks_off<ROWS>(kblk * 4 + i, rblk)) = reg[b * 4 + i];
-  }
-}
-
-// LDS traffic of one wavefront with itself (its private staging area): order only, no s_barrier
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Workgroup tile BM x BN x BK, WGM x WGN wavefronts; WPE = wavefronts per SIMD the register
-// allocation is tuned for (occupancy hides the LDS and global latencies between MFMAs).
-// TRR: K-slow operands stay untransposed in LDS and are read with ds_read_b64_tr_b16.
-template <int BM, int BN, int BK, int WGM, int WGN, int WPE, bool TA, bool TB, bool TRR>
-__global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
-void gemm_bf16_mfma_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
-  constexpr int THREADS = 64 * WGM * WGN;
-  constexpr int WTM = BM / WGM, WTN = BN / WGN, FM = WTM / 32, FN = WTN / 32;
-  constexpr int STAGE = (BM + BN) * BK;            // elements of one LDS buffer (A tile then B tile)
-  constexpr int NA = BM * BK / 8 / THREADS < 4 ? 4 : BM * BK / 8 / THREADS;
-  constexpr int NB = BN * BK / 8 / THREADS < 4 ? 4 : BN * BK / 8 / THREADS;
-  static_assert(WTN == 64 || WTN == 128, "epilogue handles 64 or 128 columns per wavefront");
-  static_assert((BM * BK / 8) % THREADS == 0 && (BN * BK / 8) % THREADS == 0, "loader shape");
-  extern __shared__ __attribute__((aligned(16))) bf16_t lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
-
-  // XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs, so give each XCD a
-  // contiguous range of tiles (neighbouring tiles share operand rows in that XCD's L2).
-  int id, zsplit;
-  gemm_work_item(d.splits > 1 ? d.splits : 1, id, zsplit);
-  const int m0 = (id / tiles_n) * BM, n0 = (id % tiles_n) * BN;
-  const int k_begin = zsplit * k_chunk;
-  const int k_end = min(d.K, k_begin + k_chunk);
-  const int nk = (k_end - k_begin + BK - 1) / BK;
-
-  const bf16_t* A = static_cast<const bf16_t*>(d.A);
-  const bf16_t* B = static_cast<const bf16_t*>(d.B);
-  u32x4 ra[NA], rb[NB];
-  // Column sums of a K-slow A operand (bias gradient, GemmDesc::colsum): a thread's 4(k) x 8(m) sub-blocks keep their
-  // m across the K loop, so it adds up its own eight columns; only the first tile column of the grid does it.
-  constexpr bool CS = TA && TB;                      // the dY^T X form, the only one that asks for it
-  constexpr int NCS = CS ? NA / 4 : 1;
-  const bool do_cs = CS && d.colsum != nullptr && n0 == 0;
-  float cs_acc[NCS][8];
-#pragma unroll
-  for (int b = 0; b < NCS; ++b)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) cs_acc[b][j] = 0.f;
-  floatx16 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // Operand staging for K slab k0 into LDS buffer `buf`.  K-contiguous operands whose slab lies
-  // fully inside [k_begin, k_end) go straight to LDS (BK = 64 only); K-slow operands and the ragged
-  // last slab travel through registers (FETCH now, STORE after the MFMAs of the current slab).
-  constexpr bool DIRECT_OK = BK == 64;
-  lds_bf16_t* lds3 = (lds_bf16_t*)lds;   // same array, LDS address space for the direct loads
-#define GEMM_FETCH(k0, buf)                                                                        \
-  do {                                                                                             \
-    const bool full_ = (k0) + BK <= k_end;                                                         \
-    if (!TA && DIRECT_OK && full_) dload_kc<BM, THREADS>(A, d.lda, m0, d.M, (k0), lds3 + (buf) * STAGE);          \
-    else if (TA) { if (full_) gload_tr<BM, BK, THREADS, true>(A, d.lda, m0, d.M, (k0), k_end, ra);                \
-                   else gload_tr<BM, BK, THREADS, false>(A, d.lda, m0, d.M, (k0), k_end, ra); }                   \
-    else { if (full_) gload_kc<BM, BK, THREADS, true>(A, d.lda, m0, d.M, (k0), k_end, ra);                        \
-           else gload_kc<BM, BK, THREADS, false>(A, d.lda, m0, d.M, (k0), k_end, ra); }                           \
-    if (!TB && DIRECT_OK && full_) dload_kc<BN, THREADS>(B, d.ldb, n0, d.N, (k0), lds3 + (buf) * STAGE + BM * BK); \
-    else if (TB) { if (full_) gload_tr<BN, BK, THREADS, true>(B, d.ldb, n0, d.N, (k0), k_end, rb);                \
-                   else gload_tr<BN, BK, THREADS, false>(B, d.ldb, n0, d.N, (k0), k_end, rb); }                   \
-    else { if (full_) gload_kc<BN, BK, THREADS, true>(B, d.ldb, n0, d.N, (k0), k_end, rb);                        \
-           else gload_kc<BN, BK, THREADS, false>(B, d.ldb, n0, d.N, (k0), k_end, rb); }                           \
-  } while (0)
-#define GEMM_STORE(k0, buf)                                                                        \
-  do {                                                                                             \
-    const bool full_ = (k0) + BK <= k_end;                                                         \
-    bf16_t* as_ = lds + (buf) * STAGE;                                                             \
-    if (CS && do_cs) {                                                                             \
-      _Pragma("unroll") for (int q_ = 0; q_ < NCS * 4; ++q_) {                                     \
-        const uint32_t w_[4] = {ra[q_].x, ra[q_].y, ra[q_].z, ra[q_].w};                           \
-        _Pragma("unroll") for (int i_ = 0; i_ < 4; ++i_) {                                         \
-          cs_acc[q_ / 4][2 * i_] += __uint_as_float(w_[i_] << 16);                                 \
-          cs_acc[q_ / 4][2 * i_ + 1] += __uint_as_float(w_[i_] & 0xffff0000u);                     \
-        }                                                                                          \
-      }                                                                                            \
-    }                                                                                              \
-    if (TA && TRR) sstore_ks<BM, BK, THREADS>(as_, ra);                                            \
-    else if (TA) sstore_tr<BM, BK, THREADS>(as_, ra);                                              \
-    else if (!(DIRECT_OK && full_)) sstore_kc<BM, BK, THREADS>(as_, ra);                           \
-    if (TB && TRR) sstore_ks<BN, BK, THREADS>(as_ + BM * BK, rb);                                  \
-    else if (TB) sstore_tr<BN, BK, THREADS>(as_ + BM * BK, rb);                                    \
-    else if (!(DIRECT_OK && full_)) sstore_kc<BN, BK, THREADS>(as_ + BM * BK, rb);                 \
-  } while (0)
-
-  if (nk > 0) {
-    GEMM_FETCH(k_begin, 0);
-    GEMM_STORE(k_begin, 0);
-  }
-  __builtin_amdgcn_s_waitcnt(0);     // direct-to-LDS loads are counted by vmcnt
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    const int k_next = k_begin + (kt + 1) * BK;
-    if (kt + 1 < nk) GEMM_FETCH(k_next, cur ^ 1);
-    const bf16_t* As = lds + cur * STAGE;
-    const bf16_t* Bs = As + BM * BK;
-#pragma unroll
-    for (int s = 0; s < BK / 16; ++s) {
-      bf16x8_t a[FM], b[FN];
-      const int kc = s * 2 + (lane >> 5);
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-        a[i] = (TA && TRR) ? read_frag<BM, BK, true>(As, wm * WTM + i * 32, s)
-                           : *reinterpret_cast<const bf16x8_t*>(As + lds_off<BK>(wm * WTM + i * 32 + (lane & 31), kc));
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-        b[j] = (TB && TRR) ? read_frag<BN, BK, true>(Bs, wn * WTN + j * 32, s)
-                           : *reinterpret_cast<const bf16x8_t*>(Bs + lds_off<BK>(wn * WTN + j * 32 + (lane & 31), kc));
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    if (kt + 1 < nk) GEMM_STORE(k_next, cur ^ 1);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-  }
-#undef GEMM_FETCH
-#undef GEMM_STORE
-
-  if (CS && d.colsum != nullptr) {       // uniform over the grid; the operand buffers are idle now
-    float* red = reinterpret_cast<float*>(lds);      // [BK / 4 k-blocks][BM]
-    if (do_cs) {
-#pragma unroll
-      for (int b = 0; b < NCS; ++b) {
-        const int sb = tid + b * THREADS;
-        const int rblk = sb % (BM / 8), kblk = sb / (BM / 8);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) red[kblk * BM + rblk * 8 + j] = cs_acc[b][j];
-      }
-    }
-    __syncthreads();
-    if (do_cs)
-      for (int r = tid; r < BM; r += THREADS) {
-        float s = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < BK / 4; ++kb) s += red[kb * BM + r];     // fixed order
-        if (m0 + r < d.M) d.colsum[static_cast<long long>(zsplit) * d.M + m0 + r] = s;
-      }
-    __syncthreads();
-  }
-
-  // Epilogue through LDS: each wavefront parks 32 rows x WTN columns of fp32 at a time in its own
-  // slice of the (now idle) operand buffers, then every lane handles 8 consecutive columns of a
-  // row, so global traffic is 16-byte vectors.  Accumulator layout of a 32x32 MFMA tile:
-  // column = lane % 32, row = 8*(r/4) + 4*(lane/32) + r%4.
-  float* cs = reinterpret_cast<float*>(lds) + wave * (32 * WTN);
-  const bool split = d.splits > 1;
-  float* part = split ? d.partial + static_cast<long long>(zsplit) * d.M * d.N : nullptr;
-  constexpr int LPR = WTN / 8;          // lanes per row
-  constexpr int RPI = 64 / LPR;         // rows per pass
-  const int n = n0 + wn * WTN + (lane % LPR) * 8;
-#pragma unroll
-  for (int i = 0; i < FM; ++i) {
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        cs[((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * WTN + j * 32 + (lane & 31)] = acc[i][j][r];
-    wave_lds_sync();
-#pragma unroll 1
-    for (int it = 0; it < 32 / RPI; ++it) {
-      const int row = it * RPI + lane / LPR;
-      const int m = m0 + wm * WTM + i * 32 + row;
-      if (m >= d.M || n >= d.N) continue;
-      float v[8];
-      const float4 lo = *reinterpret_cast<const float4*>(cs + row * WTN + (lane % LPR) * 8);
-      const float4 hi = *reinterpret_cast<const float4*>(cs + row * WTN + (lane % LPR) * 8 + 4);
-      v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w; v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
-      if (split) {
-        float* p = part + static_cast<long long>(m) * d.N + n;
-        *reinterpret_cast<float4*>(p) = lo;
-        *reinterpret_cast<float4*>(p + 4) = hi;
-      } else {
-        epi_apply_vec8(d.epi, m, n, v);
-      }
-    }
-    wave_lds_sync();
-  }
-}
+#include "gemm_epi.h"
 
 // ---------------------------------------------------------------------------------------------
 // fp32 (and generic fallback) vector-ALU kernel: 64x64 tile, 16x16 threads, 4x4 per thread
@@ -435,179 +118,98 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_vec8_kernel(const Gemm
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tile choice: 256x256 tiles (8 wavefronts, 128 KB LDS, one workgroup per CU) need about twice
-// fewer operand bytes per flop than 128x128 tiles (4 wavefronts, two workgroups per CU), but only
-// pay off when there are enough of them to occupy the 256 CUs.
-static bool gemm_prefers_big_tile(int M, int N, int splits) {
-  const long long big = static_cast<long long>((M + 255) / 256) * ((N + 255) / 256) * splits;
-  const long long small = static_cast<long long>((M + 127) / 128) * ((N + 127) / 128) * splits;
-  // 256x256 tiles when they fill three quarters of the compute units - or two thirds, if the 128x128 tiles
-  // would need more than one round of 512
-  return big >= 192 || (big >= 168 && small > 512);
+// Tile shape and K split of a bf16 contraction.
+//
+// One workgroup per compute unit: a launch takes rounds = ceil(tiles * splits / 256) of (slabs of 64 k) * slab + rest, with both
+// times measured per shape on full rounds of 256 tiles (us; `rest`: first slabs from memory and the epilogue; 2 us more once
+// per launch).  The K-slow forms read 8 bytes per LDS instruction instead of 16, which the narrow tiles feel most.  A split adds
+// its partial sums: 3 us and their bytes at 4 TB/s; a split keeps at least 4 slabs.
+struct RingShape {
+  int bm, bn;
+  float slab_nt, slab_tt, rest;
+};
+static const RingShape RING_SHAPES[GEMM_RING_NSHAPES] = {
+    {256, 256, 1.50f, 1.37f, 6.5f}, {192, 256, 1.10f, 1.03f, 6.0f}, {256, 192, 1.07f, 1.02f, 6.5f}, {128, 256, 0.73f, 0.74f, 5.2f},
+    {256, 128, 0.71f, 0.73f, 5.4f}, {192, 192, 0.80f, 0.81f, 5.5f}, {128, 192, 0.54f, 0.57f, 4.3f}, {192, 128, 0.54f, 0.57f, 4.1f},
+    {128, 128, 0.39f, 0.40f, 3.1f}, {64, 128, 0.26f, 0.29f, 2.2f},  {128, 64, 0.25f, 0.29f, 2.2f},  {64, 64, 0.165f, 0.20f, 1.7f}};
+// Shapes that are built per form (bit i: shape i); see gemm_ring_*.hip.
+static unsigned ring_shapes_built(int trans_a, int trans_b) {
+  if (!trans_a && !trans_b) return 0xfffu;
+  if (trans_a && trans_b) return 0x3ffu;        // at least 128 columns: the partial column sums have a row per tile column
+  return trans_b ? 0x391u : 0x101u;
 }
-
-// Which configuration of the software-pipelined kernel (gemm_pipe.hip) suits a problem, or -1 for the
-// register-staged kernel above.  Measured on the layer shapes (M = tokens = 8192, N and K between 512
-// and 4096) inside the layer step: for K-contiguous operands (x W^T) the largest workgroup tile that
-// still yields about one tile per compute unit wins; with a K-slow B operand (dY W) that holds only
-// for the 256x256 configuration (its two wavefronts per SIMD cover the transposing reads); dY^T X
-// stays on the register-staged kernel.
-static int gemm_pipe_choice(const GemmDesc& d) {
-  if (d.trans_a) return -1;
-  const long long tm256 = (d.M + 255) / 256, t256 = tm256 * ((d.N + 255) / 256), t256x128 = tm256 * ((d.N + 127) / 128);
-  if (t256 >= 192) {
-    // 256x256 with 8 wavefronts - unless its tiles fill the last round over the 256 compute units so badly that
-    // narrower tiles finish sooner.  Cost of a choice: rounds of work times the area of a tile, the 256x128 tiles
-    // taken as 7 % and the 256x192 tiles (two ring slots only) as 17 % less efficient per flop (fitted to cold-cache
-    // timings of the layer shapes); 256x192 serves the widths that are multiples of 192 (the fused Q|K|V
-    // projections of both layers) and K-contiguous operands only.
-    if (!d.trans_b) {
-      const long long t256x192 = tm256 * ((d.N + 191) / 192);
-      const long long c256 = (t256 + 255) / 256 * 256 * 100, c192 = (t256x192 + 255) / 256 * 192 * 117,
-                      c128 = (t256x128 + 255) / 256 * 128 * 107;
-      if (c192 < c256 && c192 <= c128) return 10;
-      if (c128 < c256) return 9;
-    }
-    return 5;
-  }
-  if (d.trans_b) return -1;
-  if (t256x128 >= 192) {
-    // 256x128 (8 wavefronts, 3-deep ring) - or 256x192 when its tiles fit one round where the narrower ones need
-    // two (output widths a little above a multiple of 256: what an FFN keeps at a keep ratio like 3/10)
-    const long long t256x192 = tm256 * ((d.N + 191) / 192);
-    const long long c192 = (t256x192 + 255) / 256 * 192 * 117, c128 = (t256x128 + 255) / 256 * 128 * 107;
-    return c192 < c128 ? 10 : 9;
-  }
-  return 6;                       // 128x128 with 32-deep slabs in a ring of four: more loads in flight than two 64-deep slabs, which
-                                  // matters when a compute unit holds one such workgroup (measured on the few-token shapes)
-}
-// Long contractions with a K-slow B operand (K of several thousand, at least a tile per compute unit)
-// run fastest on the two-slab register prefetch of gemm_rs.hip.
-static bool gemm_prefers_rs_nt(const GemmDesc& d) {
-  const long long t256 = static_cast<long long>((d.M + 255) / 256) * ((d.N + 255) / 256);
-  return !d.trans_a && d.trans_b && d.splits <= 1 && d.K >= 4096 && t256 >= 192;
-}
-
-template <int BM, int BN, int BK, int WGM, int WGN, int WPE, bool TRR>
-static hipError_t launch_tile(ecospa_ctx* ctx, const GemmDesc& d, int k_chunk) {
-  const int tm = (d.M + BM - 1) / BM, tn = (d.N + BN - 1) / BN;
-  const int splits = d.splits > 1 ? d.splits : 1;
-  const dim3 grid(tm * tn * splits), block(64 * WGM * WGN);
-  const size_t operand_bytes = 2ull * (BM + BN) * BK * sizeof(bf16_t);
-  const size_t staging_bytes = static_cast<size_t>(WGM) * WGN * 32 * (BN / WGN) * 4;   // epilogue tiles
-  const size_t lds_bytes = operand_bytes > staging_bytes ? operand_bytes : staging_bytes;
-#define LAUNCH_TT(TA, TB)                                                                                      \
-  do {                                                                                                         \
-    auto kern = gemm_bf16_mfma_kernel<BM, BN, BK, WGM, WGN, WPE, TA, TB, (TRR && (TA || TB))>;                         \
-    static LdsAttrOnce attr_once;                                                                              \
-    if (lds_bytes > 64 * 1024) {                                                                               \
-      hipError_t e = attr_once.ensure(reinterpret_cast<const void*>(kern), static_cast<int>(lds_bytes));       \
-      if (e != hipSuccess) return e;                                                                           \
-    }                                                                                                          \
-    hipLaunchKernelGGL(kern, grid, block, lds_bytes, ctx->stream, d, tn, k_chunk);                             \
-  } while (0)
-  if (!d.trans_a && !d.trans_b) LAUNCH_TT(false, false);
-  else if (!d.trans_a && d.trans_b) LAUNCH_TT(false, true);
-  else if (d.trans_a && d.trans_b) LAUNCH_TT(true, true);
-  else LAUNCH_TT(true, false);
-#undef LAUNCH_TT
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------------------------
-// Weight-gradient contractions (dY^T X: K = tokens, few output tiles) on the register-prefetch kernel of
-// gemm_rs.hip: one workgroup per compute unit, so the tile shape (bm, bn from 128, 192, 256) and the number of K
-// splits are chosen together to finish soonest on 256 compute units.  Cost of a choice, in microseconds, fitted to
-// per-workgroup timings of every shape on this GPU (both operands K-slow; the loop is bound by moving the operands,
-// hence the term in bm + bn beside the one in bm * bn):
-//   slab (64 of K)  = 0.05 + 0.9 (bm + bn) / 512 + 0.73 bm bn / 256^2
-//   epilogue        = 0.3 + 8.1 bm bn / 256^2          (all workgroups of a round write at once)
-//   rounds          = ceil(tiles * splits / 256), each round = slabs per split * slab + epilogue
-//   split K         = a later pass over the partial sums: 3 + (splits * M * N * 4 + M * N * 2) bytes at 4 TB/s
-// A split keeps at least 512 of K.
-bool gemm_tt_plan(int M, int N, int K, int* bm_out, int* bn_out, int* splits_out) {
-  if (K % 64 || K < 1024 || M < 8 || N < 8) return false;
-  const int slabs = K / 64;
+// Shape and split that finish soonest; splits > 0: that many, else 1 .. max_splits.
+static void ring_plan(int trans_a, int trans_b, int M, int N, int K, int splits, int max_splits, int* shape_out, int* splits_out) {
+  const int slabs = (K + 63) / 64;
+  const unsigned built = ring_shapes_built(trans_a, trans_b);
   double best = 0.0;
-  bool found = false;
-  for (int q = 0; q < GEMM_RS_NSHAPES; ++q) {
-    const int bm = GEMM_RS_SHAPES[q][0], bn = GEMM_RS_SHAPES[q][1];
-    const long long tiles = static_cast<long long>((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-    const double area = static_cast<double>(bm) * bn / 65536.0;
-    const double slab = 0.05 + 0.9 * (bm + bn) / 512.0 + 0.73 * area, epi = 0.3 + 8.1 * area;
-    for (int sp = 1; sp <= 8; ++sp) {
+  int bs = -1, bq = 1;
+  for (int q = 0; q < GEMM_RING_NSHAPES; ++q) {
+    if (!((built >> q) & 1)) continue;
+    const RingShape& r = RING_SHAPES[q];
+    const long long tiles = static_cast<long long>((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn);
+    const double slab = trans_a || trans_b ? r.slab_tt : r.slab_nt;
+    for (int sp = splits > 0 ? splits : 1; sp <= (splits > 0 ? splits : max_splits); ++sp) {
       const int per = (slabs + sp - 1) / sp;                 // slabs of the first splits; the last one takes the rest
-      if (per * (sp - 1) >= slabs || (sp > 1 && per < 8)) continue;
-      const long long wg = tiles * sp, rounds = (wg + 255) / 256;
+      if (splits <= 0 && sp > 1 && (per < 4 || per * (sp - 1) >= slabs)) break;
       const double mn = static_cast<double>(M) * N;
       const double red = sp > 1 ? 3.0 + (sp * mn * 4.0 + mn * 2.0) / 4.0e6 : 0.0;
-      const double t = 3.0 + rounds * (per * slab + epi) + red;
-      if (!found || t < best) {
-        found = true;
-        best = t;
-        *bm_out = bm; *bn_out = bn; *splits_out = sp;
-      }
+      const double t = static_cast<double>((tiles * sp + 255) / 256) * (per * slab + r.rest) + red;
+      if (bs < 0 || t < best) { best = t; bs = q; bq = sp; }
     }
   }
-  return found;
+  *shape_out = bs;
+  *splits_out = bq;
 }
 
 int ecospa_gemm_splits(int M, int N, int K) {
-  int bm, bn, sp;
-  if (gemm_tt_plan(M, N, K, &bm, &bn, &sp)) return sp;
-  const long long tiles = static_cast<long long>((M + 127) / 128) * ((N + 127) / 128);
-  int s = 1;
-  // Two 128x128 workgroups fit a compute unit, so 512 of them run at once: split K while all splits still fit
-  // that one round and every split keeps at least 512 of K, eight ways at most.  More splits than that only add
-  // partial sums to write and reduce (measured on the weight-gradient shapes of both layers, inside their steps).
-  while (tiles * s * 2 <= 512 && K / (s * 2) >= 512 && s < 8) s *= 2;
-  return s;
+  int shape, sp;
+  ring_plan(1, 1, M, N, K, 0, 8, &shape, &sp);
+  return sp;
 }
 
 int ecospa_gemm_token_splits(int M, int N, int K) {
-  const long long tiles = static_cast<long long>((M + 127) / 128) * ((N + 127) / 128);
-  int s = 1;
-  while (tiles * s * 2 <= 256 && K / (s * 2) >= 1024 && s < 8) s *= 2;
-  return s;
+  int shape, sp;
+  ring_plan(0, 0, M, N, K, 0, 8, &shape, &sp);
+  return sp;
 }
 
-// Which kernel a bf16 contraction goes to: the register-prefetch kernel with tile rs_bm x rs_bn (rs_bm = 0: not that
-// one), else configuration cfg of the pipelined kernel (cfg < 0: neither - the register-staged kernel).
-// tile codes: 10-19 and 21 name the configurations 0-9 and 10 of the pipelined kernel, 20 the register-prefetch
-// kernel with 256 x 256 tiles, 30 + i the same kernel with shape i of GEMM_RS_SHAPES (dY^T X only).
-static void gemm_route(const GemmDesc& d, int splits, int* k_split_out, int* cfg_out, int* rs_bm_out, int* rs_bn_out) {
-  // K range of a split: whole 64-deep slabs, the first splits take one slab more when the slabs do not divide
-  const int k_split = d.K % 64 == 0 ? (d.K / 64 + splits - 1) / splits * 64 : (d.K + splits - 1) / splits;
-  const bool no_empty_split = static_cast<long long>(k_split) * (splits - 1) < d.K;
-  int cfg = d.tile >= 10 && d.tile < 20 ? d.tile - 10 : (d.tile == 21 ? 10 : (d.tile == 0 ? gemm_pipe_choice(d) : -1));
-  int rs_bm = 0, rs_bn = 0;
-  if (d.tile == 20) { rs_bm = rs_bn = 256; }
-  else if (d.tile >= 30 && d.tile < 30 + GEMM_RS_NSHAPES && d.trans_a && d.trans_b) { rs_bm = GEMM_RS_SHAPES[d.tile - 30][0]; rs_bn = GEMM_RS_SHAPES[d.tile - 30][1]; }
-  else if (d.tile == 0 && d.trans_a && d.trans_b) {
-    int sp;      // dY^T X: the planned shape, when the caller split K as planned
-    if (!(gemm_tt_plan(d.M, d.N, d.K, &rs_bm, &rs_bn, &sp) && sp == splits)) rs_bm = rs_bn = 0;
-  } else if (d.tile == 0 && gemm_prefers_rs_nt(d)) { rs_bm = rs_bn = 256; }
-  if (!(rs_bm && gemm_rs_ok(d, k_split) && no_empty_split)) rs_bm = rs_bn = 0;
-  if (!(cfg >= 0 && gemm_pipe_ok(d, cfg, k_split) && no_empty_split)) cfg = -1;
-  *k_split_out = k_split; *cfg_out = cfg; *rs_bm_out = rs_bm; *rs_bn_out = rs_bn;
+// Workgroup tile that a tile code of the contraction entry point names, or 0.
+static void ring_forced_tile(int tile, int* bm, int* bn) {
+  static const int cfg[11][2] = {{256, 256}, {256, 256}, {256, 128}, {128, 256}, {128, 128}, {256, 256}, {128, 128}, {256, 256}, {256, 256}, {256, 128}, {256, 192}};
+  static const int wg[9][2] = {{256, 256}, {192, 256}, {256, 192}, {128, 256}, {256, 128}, {192, 192}, {128, 192}, {192, 128}, {128, 128}};
+  *bm = *bn = 0;
+  if (tile >= 1 && tile <= 4) { *bm = *bn = tile & 1 ? 128 : 256; }
+  else if (tile >= 10 && tile <= 19) { *bm = cfg[tile - 10][0]; *bn = cfg[tile - 10][1]; }
+  else if (tile == 20) { *bm = *bn = 256; }
+  else if (tile == 21) { *bm = cfg[10][0]; *bn = cfg[10][1]; }
+  else if (tile >= 30 && tile < 39) { *bm = wg[tile - 30][0]; *bn = wg[tile - 30][1]; }
 }
 
-// Rows of the partial column-sum matrix (GemmDesc::colsum) that the launch of d writes, M floats each: one per K split,
-// times the tile columns when the register-prefetch kernel runs it (there every tile column adds up its share of the
-// slabs).  The caller sizes the buffer with it and adds the rows up in order.
+static int ring_route(const GemmDesc& d, int splits) {
+  int shape, sp, bm, bn;
+  ring_forced_tile(d.tile, &bm, &bn);
+  const unsigned built = ring_shapes_built(d.trans_a, d.trans_b);
+  for (int q = 0; q < GEMM_RING_NSHAPES && bm; ++q)
+    if (((built >> q) & 1) && RING_SHAPES[q].bm == bm && RING_SHAPES[q].bn == bn) return q;
+  ring_plan(d.trans_a, d.trans_b, d.M, d.N, d.K, splits, splits, &shape, &sp);
+  return shape;
+}
+
+// Rows of the partial column-sum matrix (GemmDesc::colsum) that the launch of d writes, M floats each: one per K split and
+// tile column.  The caller sizes the buffer with it and adds the rows up in order.
 int ecospa_gemm_colsum_rows(const GemmDesc& d) {
   const int splits = d.splits > 1 ? d.splits : 1;
   if (d.dtype != ECOSPA_BF16) return splits;
-  int k_split, cfg, rs_bm, rs_bn;
-  gemm_route(d, splits, &k_split, &cfg, &rs_bm, &rs_bn);
-  return rs_bm ? splits * ((d.N + rs_bn - 1) / rs_bn) : splits;
+  const int bn = RING_SHAPES[ring_route(d, splits)].bn;
+  return splits * ((d.N + bn - 1) / bn);
 }
 
 int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d) {
   if (d.M < 1 || d.N < 1 || d.K < 1) return ECOSPA_ERR_SHAPE;
   if (!d.A || !d.B || (!d.epi.c && d.epi.kind != EPI_SWIGLU)) return ECOSPA_ERR_NULL;      // the gated epilogue may skip its first output
   if (d.splits > 1 && !d.partial) return ECOSPA_ERR_WORKSPACE;
-  // column sums of the A operand: the dY^T X form on the kernels that stage A through registers (not the pipelined one)
+  // column sums of the A operand: the dY^T X form
   if (d.colsum && !(d.dtype == ECOSPA_BF16 && d.trans_a && d.trans_b && (d.tile <= 4 || d.tile == 20 || d.tile >= 30))) return ECOSPA_ERR_SHAPE;
   const int splits = d.splits > 1 ? d.splits : 1;
   if (d.dtype == ECOSPA_BF16) {
@@ -626,33 +228,21 @@ int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d) {
       return ECOSPA_ERR_ALIGN;
     if (d.epi.kind == EPI_DSWIGLU && d.epi.kp % 8) return ECOSPA_ERR_ALIGN;
     if (d.splits > 1 && !aligned16(d.partial)) return ECOSPA_ERR_ALIGN;
-    int k_chunk = (d.K + splits - 1) / splits;
-    k_chunk = (k_chunk + 63) / 64 * 64;
-    const bool big = d.tile == 2 || (d.tile == 0 && gemm_prefers_big_tile(d.M, d.N, splits));
     const bool prof = ctx->prof_on && ctx->prof_n < ctx->prof_cap;
     if (prof) (void)hipEventRecord(ctx->prof_ev[2 * ctx->prof_n], ctx->stream);
+    // K range of a split: whole 64-deep slabs, the last split takes what is left
+    const int k_chunk = ((d.K + 63) / 64 + splits - 1) / splits * 64;
+    const int shape = ring_route(d, splits);
     hipError_t le;
-    int k_split, cfg, rs_bm, rs_bn;
-    gemm_route(d, splits, &k_split, &cfg, &rs_bm, &rs_bn);
-    if (rs_bm) le = gemm_rs_launch(ctx, d, k_split, rs_bm, rs_bn);
-    else if (cfg >= 0) le = gemm_pipe_launch(ctx, d, cfg, k_split);
-    else {
-      // register-staged kernel; tile 1/2 = 128/256 tiles with K-slow operands transposed on the way to
-      // LDS, 3/4 = the same tiles with K-slow operands read by transposing LDS reads.  Measured: the
-      // transposing reads win only when BOTH operands are K-slow (dY^T X).
-      int t = d.tile >= 1 && d.tile <= 4 ? d.tile : (big ? 2 : 1);
-      if (d.tile == 0 && d.trans_a && d.trans_b) t += 2;
-      if (t == 4) le = launch_tile<256, 256, 64, 2, 4, 2, true>(ctx, d, k_chunk);
-      else if (t == 3) le = launch_tile<128, 128, 64, 2, 2, 2, true>(ctx, d, k_chunk);
-      else if (t == 2) le = launch_tile<256, 256, 64, 2, 4, 2, false>(ctx, d, k_chunk);
-      else le = launch_tile<128, 128, 64, 2, 2, 2, false>(ctx, d, k_chunk);
-    }
+    if (d.trans_a && d.trans_b) le = gemm_ring_launch_tt(ctx, d, shape, k_chunk);
+    else if (d.trans_a || d.trans_b) le = gemm_ring_launch_mixed(ctx, d, shape, k_chunk);
+    else le = gemm_ring_launch_nt(ctx, d, shape, k_chunk);
     if (le != hipSuccess) return hip_fail(ctx, le, "gemm launch");
     if (prof) {
       (void)hipEventRecord(ctx->prof_ev[2 * ctx->prof_n + 1], ctx->stream);
       ctx->prof_flop[ctx->prof_n++] = 2.0 * d.M * d.N * d.K;
     }
-    ECOSPA_CHECK_LAUNCH(ctx, "gemm_bf16_mfma_kernel");
+    ECOSPA_CHECK_LAUNCH(ctx, "gemm_bf16_ring_kernel");
   } else if (d.dtype == ECOSPA_F32) {
     if (d.epi.kind == EPI_ROPE || d.epi.kind == EPI_SWIGLU) return ECOSPA_ERR_DTYPE;
     const int tm = (d.M + 63) / 64, tn = (d.N + 63) / 64;

@@ -102,65 +102,50 @@ __device__ __forceinline__ bool epi_bias_load(const GemmEpi& e, int n, float (&b
   unpack8(*reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(e.bias) + n), b);
   return true;
 }
-// Columns n .. n+7 of row m with the bias and the side inputs already in registers.
+// Eight consecutive columns of one row with the bias already added and the side inputs in registers: what goes to c (and c2).
+// DSWIGLU fills both words of o, the others the first; a2: second output (BIAS_ACT, SWIGLU's four units in .x and .y).
+struct EpiOut { uint4 o[2]; uint4 a2; };
 template <int KIND>
-__device__ __forceinline__ void epi_apply_vec8_k(const GemmEpi& e, int m, int n, float (&v)[8], bool has_bias, const float (&b)[8],
-                                                 const EpiSide& sd) {
-  bf16_t* c = static_cast<bf16_t*>(e.c) + static_cast<long long>(m) * e.ldc + n;
-  if constexpr (KIND != EPI_DACT && KIND != EPI_DSWIGLU) {
-    if (has_bias) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] += b[i];
-    }
-  }
+__device__ __forceinline__ void epi_math_k(int act, float (&v)[8], const EpiSide& sd, bool rope_on, EpiOut& out) {
   if constexpr (KIND == EPI_ROPE) {
-    if (n < e.rope_cols) rope_turn8(__builtin_bit_cast(float4, sd.a), __builtin_bit_cast(float4, sd.b), 1.f, v);
-    *reinterpret_cast<uint4*>(c) = pack8(v);
+    if (rope_on) rope_turn8(__builtin_bit_cast(float4, sd.a), __builtin_bit_cast(float4, sd.b), 1.f, v);
+    out.o[0] = pack8(v);
   } else if constexpr (KIND == EPI_STORE) {
-    *reinterpret_cast<uint4*>(c) = pack8(v);
-  } else if constexpr (KIND == EPI_BIAS_ACT) {
-    *reinterpret_cast<uint4*>(c) = pack8(v);
+    out.o[0] = pack8(v);
+  } else if constexpr (KIND == EPI_BIAS_ACT || KIND == EPI_ACT) {
+    if constexpr (KIND == EPI_BIAS_ACT) out.o[0] = pack8(v);
     float a[8];
-    if (e.act == ECOSPA_ACT_GELU_TANH) {
+    if (act == ECOSPA_ACT_GELU_TANH) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) a[i] = act_gelu(v[i], ECOSPA_ACT_GELU_TANH);
     } else {
 #pragma unroll
       for (int i = 0; i < 8; ++i) a[i] = act_gelu(v[i], ECOSPA_ACT_GELU_ERF);
     }
-    *reinterpret_cast<uint4*>(static_cast<bf16_t*>(e.c2) + static_cast<long long>(m) * e.ldc2 + n) = pack8(a);
-  } else if constexpr (KIND == EPI_ACT) {
-    if (e.act == ECOSPA_ACT_GELU_TANH) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = act_gelu(v[i], ECOSPA_ACT_GELU_TANH);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = act_gelu(v[i], ECOSPA_ACT_GELU_ERF);
-    }
-    *reinterpret_cast<uint4*>(c) = pack8(v);
+    (KIND == EPI_ACT ? out.o[0] : out.a2) = pack8(a);
   } else if constexpr (KIND == EPI_DACT) {
     float h[8];
     unpack8(sd.a, h);
-    if (e.act == ECOSPA_ACT_GELU_TANH) {
+    if (act == ECOSPA_ACT_GELU_TANH) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) v[i] *= act_gelu_grad(h[i], ECOSPA_ACT_GELU_TANH);
     } else {
 #pragma unroll
       for (int i = 0; i < 8; ++i) v[i] *= act_gelu_grad(h[i], ECOSPA_ACT_GELU_ERF);
     }
-    *reinterpret_cast<uint4*>(c) = pack8(v);
+    out.o[0] = pack8(v);
   } else if constexpr (KIND == EPI_SWIGLU) {
     // columns n .. n+7 are four (gate, up) pairs: units n/2 .. n/2+3
-    if (e.c) *reinterpret_cast<uint4*>(c) = pack8(v);
+    out.o[0] = pack8(v);
     typedef float floatx4 __attribute__((ext_vector_type(4)));
     typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
     floatx4 a;
 #pragma unroll
     for (int i = 0; i < 4; ++i) a[i] = v[2 * i] * act_sigmoid(v[2 * i]) * v[2 * i + 1];
-    *reinterpret_cast<bf16x4_t*>(static_cast<bf16_t*>(e.c2) + static_cast<long long>(m) * e.ldc2 + (n >> 1)) = __builtin_convertvector(a, bf16x4_t);
+    const uint2 p = __builtin_bit_cast(uint2, __builtin_convertvector(a, bf16x4_t));
+    out.a2.x = p.x; out.a2.y = p.y;
   } else {  // EPI_DSWIGLU: units n .. n+7, their (gate, up) pairs in columns 2n .. 2n+15 of h and of c
     static_assert(KIND == EPI_DSWIGLU, "epilogue kind");
-    bf16_t* cp = static_cast<bf16_t*>(e.c) + static_cast<long long>(m) * e.ldc + 2 * n;
     float p[2][8], o[2][8];
     unpack8(sd.a, p[0]);
     unpack8(sd.b, p[1]);
@@ -171,9 +156,28 @@ __device__ __forceinline__ void epi_apply_vec8_k(const GemmEpi& e, int m, int n,
       o[i >> 2][2 * (i & 3)] = v[i] * u * sg * (1.f + g * (1.f - sg));
       o[i >> 2][2 * (i & 3) + 1] = v[i] * g * sg;
     }
-    *reinterpret_cast<uint4*>(cp) = pack8(o[0]);
-    *reinterpret_cast<uint4*>(cp + 8) = pack8(o[1]);
+    out.o[0] = pack8(o[0]);
+    out.o[1] = pack8(o[1]);
   }
+}
+// Columns n .. n+7 of row m, addresses and all.
+template <int KIND>
+__device__ __forceinline__ void epi_apply_vec8_k(const GemmEpi& e, int m, int n, float (&v)[8], bool has_bias, const float (&b)[8],
+                                                 const EpiSide& sd) {
+  if constexpr (KIND != EPI_DACT && KIND != EPI_DSWIGLU) {
+    if (has_bias) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] += b[i];
+    }
+  }
+  EpiOut out;
+  epi_math_k<KIND>(e.act, v, sd, KIND == EPI_ROPE && n < e.rope_cols, out);
+  bf16_t* c = static_cast<bf16_t*>(e.c) + static_cast<long long>(m) * e.ldc + (KIND == EPI_DSWIGLU ? 2 * n : n);
+  if (KIND != EPI_SWIGLU || e.c) *reinterpret_cast<uint4*>(c) = out.o[0];
+  if constexpr (KIND == EPI_DSWIGLU) *reinterpret_cast<uint4*>(c + 8) = out.o[1];
+  if constexpr (KIND == EPI_BIAS_ACT) *reinterpret_cast<uint4*>(static_cast<bf16_t*>(e.c2) + static_cast<long long>(m) * e.ldc2 + n) = out.a2;
+  if constexpr (KIND == EPI_SWIGLU)
+    *reinterpret_cast<uint2*>(static_cast<bf16_t*>(e.c2) + static_cast<long long>(m) * e.ldc2 + (n >> 1)) = make_uint2(out.a2.x, out.a2.y);
 }
 // Calls f with the epilogue kind as a compile-time constant (std::integral_constant).
 template <typename F>

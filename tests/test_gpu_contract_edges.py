@@ -1,0 +1,54 @@
+"""GPU parity of the bf16 contraction kernel where it can go wrong: K that is no multiple of the 64-deep slab (the first slab takes
+the remainder, zeroed in LDS beyond it), fewer slabs than the LDS ring holds, K splits with an uneven or empty last range, and
+every tile shape with remainders of one 8-column group and one row - against a plain fp64 product of the same bf16 operands."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_11641_amd import binding as B
+from paper_2511_11641_amd import synth
+from util import assert_close, dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    return B.Context("cuda:0")
+
+
+def _case(seed, M, N, K, ta, tb):
+    a = synth.round_to(synth.normal(seed, 300, (K, M) if ta else (M, K)), "bf16")
+    b = synth.round_to(synth.normal(seed, 301, (K, N) if tb else (N, K)), "bf16")
+    want = (a.T if ta else a).astype(np.float64) @ (b if tb else b.T).astype(np.float64)
+    return dev(a, "bf16"), dev(b, "bf16"), a, want
+
+
+# tile codes: 30 .. 38 name the nine shapes of at least 128 x 128; 0 with few rows or columns takes the 64-wide ones
+@pytest.mark.parametrize("tile", [0, 30, 31, 32, 33, 34, 35, 36, 37, 38])
+@pytest.mark.parametrize("ta,tb,M,N,K", [
+    (False, False, 257, 264, 8), (False, False, 129, 136, 72), (False, False, 61, 200, 456), (False, False, 385, 392, 200),
+    (True, True, 264, 264, 1), (True, True, 136, 392, 63), (True, True, 264, 136, 191), (True, True, 392, 264, 257),
+    (False, True, 257, 264, 72), (False, True, 70, 136, 200), (True, False, 264, 136, 136)])
+def test_contract_k_remainders(ctx, ta, tb, M, N, K, tile):
+    ga, gb, _, want = _case(61, M, N, K, ta, tb)
+    got = ctx.ecospa_contract(ga, ta, gb, tb, tile=tile, splits=1)
+    assert_close(got, want, "bf16", f"{M}x{N}x{K} tile {tile}")
+
+
+@pytest.mark.parametrize("M,N,K,splits", [(64, 128, 4191, 0), (384, 768, 1379, 0), (264, 136, 191, 3), (136, 264, 70, 4),     # the last splits are empty
+                                           (1000, 264, 1379, 5)])
+def test_weight_gradient_with_column_sums_any_token_count(ctx, M, N, K, splits):
+    ga, gb, a, want = _case(62, M, N, K, True, True)
+    got, cs = ctx.ecospa_contract_colsum(ga, gb, splits=splits)
+    assert_close(got, want, "bf16", "product")
+    assert_close(cs, a.astype(np.float64).sum(axis=0), "f32", "column sums")
+    again, cs2 = ctx.ecospa_contract_colsum(ga, gb, splits=splits)
+    assert torch.equal(got, again) and torch.equal(cs, cs2)
+
+
+@pytest.mark.parametrize("M,N,K", [(8, 64, 2048), (61, 2048, 1024), (65, 72, 3000), (129, 5504, 520)])
+def test_few_tokens_own_plan(ctx, M, N, K):
+    ga, gb, _, want = _case(63, M, N, K, False, False)
+    assert_close(ctx.ecospa_contract(ga, False, gb, False, splits=1), want, "bf16", "unsplit")
+    assert_close(ctx.ecospa_contract(ga, False, gb, False), want, "bf16", "library's split")
