@@ -848,7 +848,7 @@ static int attn_backward_body(ecospa_ctx* ctx, const ecospa_block_desc& d, const
   int rc;
   // dW_o = dY^T O (partials),  dO = dY W_o
   GemmDesc go = mk_gemm(d.dtype, dm, nvo, T, dy, dm, 1, sv.o, nvo, 1, gr.dw_o, gr.ld_dwo, nullptr);
-  go.splits = ecospa_gemm_splits(dm, nvo, T); go.partial = w.partial; go.defer_reduce = 1;
+  go.splits = ecospa_gemm_splits(d.dtype, dm, nvo, T); go.partial = w.partial; go.defer_reduce = 1;
   // the bias gradients are column sums of dY and dQKV, the K-slow operands of the two weight-gradient
   // contractions: those add them up on the way
   if (gr.dw_o && gr.db_o) go.colsum = w.colsum;
@@ -871,7 +871,7 @@ static int attn_backward_body(ecospa_ctx* ctx, const ecospa_block_desc& d, const
 
   // dW_qkv = dQKV^T X (partials)
   GemmDesc gq = mk_gemm(d.dtype, nqkv, dm, T, w.dqkv, nqkv, 1, x, dm, 1, gr.dw_qkv, gr.ld_dwqkv, nullptr);
-  gq.splits = ecospa_gemm_splits(nqkv, dm, T); gq.partial = w.partial2; gq.defer_reduce = 1;
+  gq.splits = ecospa_gemm_splits(d.dtype, nqkv, dm, T); gq.partial = w.partial2; gq.defer_reduce = 1;
   if (gr.dw_qkv && gr.db_qkv) gq.colsum = w.colsum2;
   if (gr.dw_qkv && (rc = ecospa_gemm(ctx, gq))) return rc;
 

@@ -46,7 +46,7 @@ int block_colsum_rows(int dtype, int M, int N, int K) {
   GemmDesc g;
   memset(&g, 0, sizeof(g));
   g.dtype = dtype; g.M = M; g.N = N; g.K = K; g.lda = M; g.ldb = N; g.trans_a = g.trans_b = 1;
-  g.splits = ecospa_gemm_splits(M, N, K);
+  g.splits = ecospa_gemm_splits(dtype, M, N, K);
   return ecospa_gemm_colsum_rows(g);
 }
 
@@ -57,7 +57,7 @@ void block_ws_layout(const ecospa_block_desc& d, void* base, BlockWs& w) {
   size_t part = 0, part2 = 0, cs = 0, cs2 = 0, px = 0;
   const int Ti = static_cast<int>(T);
   auto splitk_bytes = [&](int M, int N, int K) {
-    const int s = ecospa_gemm_splits(M, N, K);
+    const int s = ecospa_gemm_splits(d.dtype, M, N, K);
     return s > 1 ? static_cast<size_t>(s) * M * N * 4 : static_cast<size_t>(0);
   };
   auto colsum_bytes = [&](int M, int N, int K) { return static_cast<size_t>(block_colsum_rows(d.dtype, M, N, K)) * M * 4; };
@@ -189,7 +189,7 @@ static int ffn_backward_body(ecospa_ctx* ctx, const ecospa_block_desc& d, const 
   }
   // dW_2 = dY^T A,  dW_1 = dH^T X
   GemmDesc g2 = gemm_desc(d.dtype, dm, kp, T, dy, dm, 1, sv.act, kp, 1);
-  g2.splits = ecospa_gemm_splits(dm, kp, T); g2.partial = w.partial; g2.defer_reduce = 1;
+  g2.splits = ecospa_gemm_splits(d.dtype, dm, kp, T); g2.partial = w.partial; g2.defer_reduce = 1;
   g2.epi.kind = EPI_STORE; g2.epi.c = gr.dw_2; g2.epi.ldc = gr.ld_dw2;
   // the bias gradients are column sums of dY and dH: the weight-gradient contractions read exactly these as
   // their K-slow operand and add them up on the way (bf16 kernels; otherwise a column-sum job below)
@@ -197,7 +197,7 @@ static int ffn_backward_body(ecospa_ctx* ctx, const ecospa_block_desc& d, const 
   if (fused_db && gr.dw_2 && gr.db_2) g2.colsum = w.colsum;
   if (gr.dw_2 && (rc = ecospa_gemm(ctx, g2))) return rc;
   GemmDesc g1 = gemm_desc(d.dtype, nh, dm, T, w.dh, nh, 1, x, dm, 1);
-  g1.splits = ecospa_gemm_splits(nh, dm, T); g1.partial = w.partial2; g1.defer_reduce = 1;
+  g1.splits = ecospa_gemm_splits(d.dtype, nh, dm, T); g1.partial = w.partial2; g1.defer_reduce = 1;
   g1.epi.kind = EPI_STORE; g1.epi.c = gr.dw_1; g1.epi.ldc = gr.ld_dw1;
   if (fused_db && gr.dw_1 && gr.db_1) g1.colsum = w.colsum2;
   if (gr.dw_1 && (rc = ecospa_gemm(ctx, g1))) return rc;
@@ -261,7 +261,7 @@ extern "C" int ecospa_coupled_bwd(ecospa_ctx* ctx, const ecospa_block_desc* desc
 // ---------------------------------------------------------------------------------------------
 extern "C" size_t ecospa_contract_workspace_bytes(int dtype, int M, int N, int K, int splits) {
   if (!dtype_ok(dtype) || M < 1 || N < 1 || K < 1 || splits < 0 || splits > 64) return 0;
-  const int s = splits == 0 ? ecospa_gemm_splits(M, N, K) : splits;
+  const int s = splits == 0 ? ecospa_gemm_splits(dtype, M, N, K) : splits;
   return s > 1 ? static_cast<size_t>(s) * M * N * 4 : 0;
 }
 
@@ -274,7 +274,7 @@ extern "C" int ecospa_contract(ecospa_ctx* ctx, int dtype, int M, int N, int K, 
   if (lda < (trans_a ? M : K) || ldb < (trans_b ? N : K) || ldc < N) return ECOSPA_ERR_SHAPE;
   GemmDesc g = gemm_desc(dtype, M, N, K, A, lda, trans_a ? 1 : 0, B, ldb, trans_b ? 1 : 0);
   g.tile = tile;
-  g.splits = splits == 0 ? ecospa_gemm_splits(M, N, K) : splits;
+  g.splits = splits == 0 ? ecospa_gemm_splits(dtype, M, N, K) : splits;
   g.epi.kind = EPI_STORE; g.epi.c = C; g.epi.ldc = ldc; g.epi.bias = bias;
   if (g.splits > 1) {
     const size_t need = static_cast<size_t>(g.splits) * M * N * 4;
@@ -292,7 +292,7 @@ extern "C" int ecospa_contract_colsum(ecospa_ctx* ctx, int M, int N, int K, cons
   if (M < 1 || N < 1 || K < 1 || tile < 0 || tile > 38 || (tile > 21 && tile < 30) || splits < 0 || splits > 64) return ECOSPA_ERR_SHAPE;
   if (lda < M || ldb < N || ldc < N) return ECOSPA_ERR_SHAPE;
   GemmDesc g = gemm_desc(ECOSPA_BF16, M, N, K, A, lda, 1, B, ldb, 1);
-  g.splits = splits == 0 ? ecospa_gemm_splits(M, N, K) : splits;
+  g.splits = splits == 0 ? ecospa_gemm_splits(ECOSPA_BF16, M, N, K) : splits;
   const int sp = g.splits > 1 ? g.splits : 1;
   g.epi.kind = EPI_STORE; g.epi.c = C; g.epi.ldc = ldc;
   g.tile = tile;

@@ -64,7 +64,7 @@ int ecospa_gemm_colsum_rows(const GemmDesc& d);
 // then the epilogue.  Same descriptor as the first half.
 int ecospa_gemm_reduce(ecospa_ctx* ctx, const GemmDesc& d);
 // How many K splits a (M, N, K) problem should use to fill the chip, and the bytes of partials.
-int ecospa_gemm_splits(int M, int N, int K);
+int ecospa_gemm_splits(int dtype, int M, int N, int K);
 // The same question for the contractions whose M is the token count (x W^T and dY W): with few tokens (inference
 // at batch 1) their output has too few tiles for the chip; 1 for the training shapes.
 int ecospa_gemm_token_splits(int M, int N, int K);

@@ -2,93 +2,125 @@
 // reductions of split contractions.
 //
 // bf16: the kernel of gemm_ring.h (MFMA, direct global -> LDS loads).
-// fp32: 64x64x32 vector-ALU tiles (the fp32 configuration is small and launch bound).
+// fp32: MFMA on fragments loaded straight from memory (the fp32 configuration is small and latency bound).
 // Split-K writes fp32 partials that a second kernel adds in a fixed order (deterministic dW).
 #include "gemm_epi.h"
 
 // ---------------------------------------------------------------------------------------------
-// fp32 (and generic fallback) vector-ALU kernel: 64x64 tile, 16x16 threads, 4x4 per thread
-// ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void gemm_valu_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
-  // 64 x 64 tile, 32-deep slabs; the 16 operand elements a thread moves per slab are fetched one slab ahead with
-  // unconditional loads from clamped addresses (all in flight together, none behind a branch) and dropped by a
-  // select where they lie outside the problem: these problems are small, so nothing but the loads' own
-  // parallelism hides their latency.
-  constexpr int BK = 32, NL = 64 * BK / 256;
-  __shared__ float As[BK][64 + 4];
-  __shared__ float Bs[BK][64 + 4];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = (blockIdx.x / tiles_n) * 64, n0 = (blockIdx.x % tiles_n) * 64;
-  const int k_begin = blockIdx.z * k_chunk;
-  const int k_end = min(d.K, k_begin + k_chunk);
-  const T* A = static_cast<const T*>(d.A);
-  const T* B = static_cast<const T*>(d.B);
-  float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+// fp32: v_mfma_f32_32x32x2_f32 on fragments that every lane loads straight from memory.  The fp32 problems are small: what bounds
+// them is how many wavefronts there are and the latency of their loads, so nothing is staged through LDS.  A wavefront owns 32 x 32
+// outputs; WK wavefronts of a workgroup share a tile's K and add up through LDS in a fixed order (WM = WN = 1), or the four form a
+// 64 x 64 tile (WK = 1), whose operand rows are shared in the L1.
+// 512 x 512 x 256 (x W^T): vector-ALU kernel of 64 x 64 tiles through LDS 27 us, this one 6 us; 256 x 512 x 512 (dY^T X): 42 -> 8 us.
+typedef float floatx16_f32 __attribute__((ext_vector_type(16)));
+typedef float floatx4_f32 __attribute__((ext_vector_type(4), aligned(4)));
 
-  float ra[NL], rb[NL];
-  auto fetch = [&](int k0) {
+// 32 k of one operand row per lane pair: step j of lane half hh is k = 8 (j / 4) + 4 hh + j % 4 (both operands the same way)
+template <bool KSLOW>
+struct F32Frags {
+  const float* p;      // this lane's row, k = 0
+  long long ld;
+  __device__ __forceinline__ void init(const void* mat, long long l, int row, int R) {
+    ld = l;
+    const int r = min(row, R - 1);
+    p = static_cast<const float*>(mat) + (KSLOW ? r : r * l);
+  }
+  __device__ __forceinline__ void load(float (&v)[16], int k0, int hh) const {
+    if constexpr (KSLOW) {
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int e = tid + i * 256;
-      {
-        const int kk = d.trans_a ? e >> 6 : e & (BK - 1), r = d.trans_a ? e & 63 : e / BK;
-        const int gm = m0 + r, gk = k0 + kk;
-        const long long cm = min(gm, d.M - 1), ck = min(gk, k_end - 1);
-        const float v = load_f32<T>(A + (d.trans_a ? ck * d.lda + cm : cm * d.lda + ck));
-        ra[i] = (gm < d.M && gk < k_end) ? v : 0.f;
+      for (int j = 0; j < 16; ++j) v[j] = p[(k0 + 8 * (j / 4) + 4 * hh + j % 4) * ld];
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const floatx4_f32 t = *reinterpret_cast<const floatx4_f32*>(p + k0 + 8 * q + 4 * hh);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[4 * q + i] = t[i];
       }
-      {
-        const int kk = d.trans_b ? e >> 6 : e & (BK - 1), r = d.trans_b ? e & 63 : e / BK;
-        const int gn = n0 + r, gk = k0 + kk;
-        const long long cn = min(gn, d.N - 1), ck = min(gk, k_end - 1);
-        const float v = load_f32<T>(B + (d.trans_b ? ck * d.ldb + cn : cn * d.ldb + ck));
-        rb[i] = (gn < d.N && gk < k_end) ? v : 0.f;
-      }
+    }
+  }
+  __device__ __forceinline__ void load_tail(float (&v)[16], int k0, int k_end, int hh) const {     // zeros from k_end on
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int k = k0 + 8 * (j / 4) + 4 * hh + j % 4, kc = min(k, k_end - 1);
+      const float t = KSLOW ? p[kc * ld] : p[kc];
+      v[j] = k < k_end ? t : 0.f;
+    }
+  }
+};
+
+template <int WM, int WN, int WK, bool TA, bool TB>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
+  static_assert(WM * WN * WK == 4 && (WK == 1 || WK == 4), "four wavefronts");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hh = lane >> 5;
+  const int wk = wave % WK, wmn = wave / WK, wm = wmn / WN, wn = wmn % WN;
+  const int m0 = (static_cast<int>(blockIdx.x) / tiles_n) * (32 * WM) + wm * 32, n0 = (static_cast<int>(blockIdx.x) % tiles_n) * (32 * WN) + wn * 32;
+  const int z0 = blockIdx.z * k_chunk, z1 = min(d.K, z0 + k_chunk);
+  const int per = ((z1 - z0 + WK - 1) / WK + 31) / 32 * 32;       // K range of a wavefront: whole groups of 32
+  const int k_begin = min(z0 + wk * per, z1), k_end = min(k_begin + per, z1);
+  F32Frags<TA> fa;
+  F32Frags<TB> fb;
+  fa.init(d.A, d.lda, m0 + l32, d.M);
+  fb.init(d.B, d.ldb, n0 + l32, d.N);
+  floatx16_f32 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  float a[2][16], b[2][16];
+  const int nc = (k_end - k_begin) / 32;
+  auto products = [&](const float (&x)[16], const float (&y)[16]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[j], y[j], acc, 0, 0, 0);
+  };
+  if (nc > 0) { fa.load(a[0], k_begin, hh); fb.load(b[0], k_begin, hh); }
+  int c = 0;
+  for (; c + 2 <= nc; c += 2) {
+    fa.load(a[1], k_begin + (c + 1) * 32, hh);
+    fb.load(b[1], k_begin + (c + 1) * 32, hh);
+    products(a[0], b[0]);
+    const int kn = k_begin + min(c + 2, nc - 1) * 32;       // the last group again when there is no further one
+    fa.load(a[0], kn, hh);
+    fb.load(b[0], kn, hh);
+    products(a[1], b[1]);
+  }
+  if (c < nc) products(a[0], b[0]);
+  if (k_begin + nc * 32 < k_end) {
+    fa.load_tail(a[0], k_begin + nc * 32, k_end, hh);
+    fb.load_tail(b[0], k_begin + nc * 32, k_end, hh);
+    products(a[0], b[0]);
+  }
+  float* part = d.splits > 1 ? d.partial + static_cast<long long>(blockIdx.z) * d.M * d.N : nullptr;
+  auto put = [&](int m, int n, float v) __attribute__((always_inline)) {
+    if (m < d.M && n < d.N) {
+      if (part) part[static_cast<long long>(m) * d.N + n] = v;
+      else epi_apply<float>(d.epi, m, n, v);
     }
   };
-  if (k_begin < k_end) fetch(k_begin);
-  for (int k0 = k_begin; k0 < k_end; k0 += BK) {
+  // accumulator layout: column lane % 32, row 8 (r / 4) + 4 (lane / 32) + r % 4
+  if constexpr (WK == 4) {
+    __shared__ float red[4][32][33];
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int e = tid + i * 256;
-      As[d.trans_a ? e >> 6 : e & (BK - 1)][d.trans_a ? e & 63 : e / BK] = ra[i];
-      Bs[d.trans_b ? e >> 6 : e & (BK - 1)][d.trans_b ? e & 63 : e / BK] = rb[i];
-    }
+    for (int r = 0; r < 16; ++r) red[wave][8 * (r / 4) + 4 * hh + r % 4][l32] = acc[r];
     __syncthreads();
-    if (k0 + BK < k_end) fetch(k0 + BK);      // the same for the whole workgroup
+    const int n = threadIdx.x & 31;
 #pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+    for (int q = 0; q < 4; ++q) {
+      const int m = (threadIdx.x >> 5) + 8 * q;
+      put(m0 + m, n0 + n, (red[0][m][n] + red[1][m][n]) + (red[2][m][n] + red[3][m][n]));
     }
-    __syncthreads();
-  }
-  const bool split = d.splits > 1;
-  float* part = split ? d.partial + static_cast<long long>(blockIdx.z) * d.M * d.N : nullptr;
+  } else {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m >= d.M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= d.N) continue;
-      if (split) part[static_cast<long long>(m) * d.N + n] = acc[i][j];
-      else epi_apply<T>(d.epi, m, n, acc[i][j]);
-    }
+    for (int r = 0; r < 16; ++r) put(m0 + 8 * (r / 4) + 4 * hh + r % 4, n0 + l32, acc[r]);
   }
+}
+
+template <bool TA, bool TB>
+static void launch_f32(ecospa_ctx* ctx, const GemmDesc& d, int splits) {
+  const int k_chunk = (d.K + splits - 1) / splits;
+  const int tm = (d.M + 63) / 64, tn = (d.N + 63) / 64, sm = (d.M + 31) / 32, sn = (d.N + 31) / 32;
+  // 64 x 64 tiles once they fill the compute units (half the operand traffic per product); below that K is what there is to share out
+  if (static_cast<long long>(tm) * tn * splits >= 512)
+    hipLaunchKernelGGL((gemm_f32_kernel<2, 2, 1, TA, TB>), dim3(tm * tn, 1, splits), dim3(256), 0, ctx->stream, d, tn, k_chunk);
+  else
+    hipLaunchKernelGGL((gemm_f32_kernel<1, 1, 4, TA, TB>), dim3(sm * sn, 1, splits), dim3(256), 0, ctx->stream, d, sn, k_chunk);
 }
 
 // fixed-order sum of the K-split partials, then the epilogue
@@ -162,7 +194,8 @@ static void ring_plan(int trans_a, int trans_b, int M, int N, int K, int splits,
   *splits_out = bq;
 }
 
-int ecospa_gemm_splits(int M, int N, int K) {
+int ecospa_gemm_splits(int dtype, int M, int N, int K) {
+  if (dtype != ECOSPA_BF16) return 1;      // the fp32 kernel shares K out inside a workgroup
   int shape, sp;
   ring_plan(1, 1, M, N, K, 0, 8, &shape, &sp);
   return sp;
@@ -245,11 +278,11 @@ int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d) {
     ECOSPA_CHECK_LAUNCH(ctx, "gemm_bf16_ring_kernel");
   } else if (d.dtype == ECOSPA_F32) {
     if (d.epi.kind == EPI_ROPE || d.epi.kind == EPI_SWIGLU) return ECOSPA_ERR_DTYPE;
-    const int tm = (d.M + 63) / 64, tn = (d.N + 63) / 64;
-    int k_chunk = (d.K + splits - 1) / splits;
-    k_chunk = (k_chunk + 31) / 32 * 32;
-    hipLaunchKernelGGL((gemm_valu_kernel<float>), dim3(tm * tn, 1, splits), dim3(256), 0, ctx->stream, d, tn, k_chunk);
-    ECOSPA_CHECK_LAUNCH(ctx, "gemm_valu_kernel");
+    if (!d.trans_a && !d.trans_b) launch_f32<false, false>(ctx, d, splits);
+    else if (!d.trans_a) launch_f32<false, true>(ctx, d, splits);
+    else if (d.trans_b) launch_f32<true, true>(ctx, d, splits);
+    else launch_f32<true, false>(ctx, d, splits);
+    ECOSPA_CHECK_LAUNCH(ctx, "gemm_f32_kernel");
   } else {
     return ECOSPA_ERR_DTYPE;
   }

@@ -1,4 +1,4 @@
-"""GPU parity of the bf16 contraction kernel where it can go wrong: K that is no multiple of the 64-deep slab (the first slab takes
+"""GPU parity of the contraction kernels where they can go wrong: K that is no multiple of the 64-deep slab (the first slab takes
 the remainder, zeroed in LDS beyond it), fewer slabs than the LDS ring holds, K splits with an uneven or empty last range, and
 every tile shape with remainders of one 8-column group and one row - against a plain fp64 product of the same bf16 operands."""
 import numpy as np
@@ -52,3 +52,16 @@ def test_few_tokens_own_plan(ctx, M, N, K):
     ga, gb, _, want = _case(63, M, N, K, False, False)
     assert_close(ctx.ecospa_contract(ga, False, gb, False, splits=1), want, "bf16", "unsplit")
     assert_close(ctx.ecospa_contract(ga, False, gb, False), want, "bf16", "library's split")
+
+
+# 32 x 32 tiles with K shared out over a workgroup, and 64 x 64 tiles once 512 of them exist; K below, at and beyond the groups of 32
+# of a wavefront; rows and columns off every tile; fp32 sums of K products of N(0, 1) values: relative error about K^0.5 2^-24 < 3e-6
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, True), (True, False)])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 31, 5), (64, 65, 127), (130, 70, 128), (97, 200, 1025), (1473, 1409, 70)])
+def test_contract_f32_edges(ctx, ta, tb, M, N, K):
+    a = synth.normal(64, 300, (K, M) if ta else (M, K))
+    b = synth.normal(64, 301, (K, N) if tb else (N, K))
+    want = (a.T if ta else a).astype(np.float64) @ (b if tb else b.T).astype(np.float64)
+    assert_close(ctx.ecospa_contract(dev(a), ta, dev(b), tb, splits=1), want, "f32", f"{M}x{N}x{K}")
+    if K > 64:
+        assert_close(ctx.ecospa_contract(dev(a), ta, dev(b), tb, splits=3), want, "f32", f"{M}x{N}x{K} in three parts")
