@@ -45,40 +45,50 @@ __global__ __launch_bounds__(GLUE_NORM_THREADS) void norm_fwd_kernel(const NormF
   if (row >= a.T) return;
   const int nc = a.d >> 3;                          // 16-byte chunks per row
   const long long base = static_cast<long long>(row) * a.d;
+  // Every load is out before the first value is used, and none sits behind a branch per chunk (a lane beyond the row
+  // takes the row's last chunk and drops it): a few rows are a chain of latencies and nothing else (1024 x 1024 with the
+  // residual, LayerNorm: loads where they are used 6.4 us, this 5.6 us; 8192 x 2048 25.2 -> 24.5 us, 5.5 TB/s).
+  uint4 xr[MAXC], rr[MAXC], gr[MAXC], br[MAXC];
+#pragma unroll
+  for (int c = 0; c < MAXC; ++c) xr[c] = *reinterpret_cast<const uint4*>(a.x + base + min(c * 64 + lane, nc - 1) * 8);
+  if (a.res) {
+#pragma unroll
+    for (int c = 0; c < MAXC; ++c) rr[c] = *reinterpret_cast<const uint4*>(a.res + base + min(c * 64 + lane, nc - 1) * 8);
+  }
+#pragma unroll
+  for (int c = 0; c < MAXC; ++c) gr[c] = *reinterpret_cast<const uint4*>(a.gain + min(c * 64 + lane, nc - 1) * 8);
+  if (a.bias) {
+#pragma unroll
+    for (int c = 0; c < MAXC; ++c) br[c] = *reinterpret_cast<const uint4*>(a.bias + min(c * 64 + lane, nc - 1) * 8);
+  }
   float v[MAXC][8];
   float s = 0.f;
 #pragma unroll
   for (int c = 0; c < MAXC; ++c) {
     const int ch = c * 64 + lane;
-    if (ch < nc) {
-      glue_unpack8(*reinterpret_cast<const uint4*>(a.x + base + ch * 8), v[c]);
-      if (a.res) {
-        float r[8];
-        glue_unpack8(*reinterpret_cast<const uint4*>(a.res + base + ch * 8), r);
+    glue_unpack8(xr[c], v[c]);
+    if (a.res) {
+      float r[8];
+      glue_unpack8(rr[c], r);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[c][i] += r[i];
-        const uint4 packed = glue_pack8(v[c]);
-        *reinterpret_cast<uint4*>(a.x_out + base + ch * 8) = packed;
-        glue_unpack8(packed, v[c]);
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) s += v[c][i];
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[c][i] = 0.f;
+      for (int i = 0; i < 8; ++i) v[c][i] += r[i];
+      const uint4 packed = glue_pack8(v[c]);
+      if (ch < nc) *reinterpret_cast<uint4*>(a.x_out + base + ch * 8) = packed;
+      glue_unpack8(packed, v[c]);
     }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s += ch < nc ? v[c][i] : 0.f;
   }
   const float inv_d = 1.f / static_cast<float>(a.d);
   const float mean = a.layer ? wave_sum(s) * inv_d : 0.f;
   float q = 0.f;
 #pragma unroll
   for (int c = 0; c < MAXC; ++c) {
-    if (c * 64 + lane < nc) {
+    const bool on = c * 64 + lane < nc;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float t = v[c][i] - mean;
-        q += t * t;
-      }
+    for (int i = 0; i < 8; ++i) {
+      const float t = on ? v[c][i] - mean : 0.f;
+      q += t * t;
     }
   }
   const float rstd = rsqrtf(wave_sum(q) * inv_d + a.eps);
@@ -89,19 +99,17 @@ __global__ __launch_bounds__(GLUE_NORM_THREADS) void norm_fwd_kernel(const NormF
 #pragma unroll
   for (int c = 0; c < MAXC; ++c) {
     const int ch = c * 64 + lane;
-    if (ch < nc) {
-      float g[8], o[8];
-      glue_unpack8(*reinterpret_cast<const uint4*>(a.gain + ch * 8), g);
+    float g[8], o[8];
+    glue_unpack8(gr[c], g);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) o[i] = (v[c][i] - mean) * rstd * g[i];
-      if (a.bias) {
-        float b[8];
-        glue_unpack8(*reinterpret_cast<const uint4*>(a.bias + ch * 8), b);
+    for (int i = 0; i < 8; ++i) o[i] = (v[c][i] - mean) * rstd * g[i];
+    if (a.bias) {
+      float b[8];
+      glue_unpack8(br[c], b);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) o[i] += b[i];
-      }
-      *reinterpret_cast<uint4*>(a.y + base + ch * 8) = glue_pack8(o);
+      for (int i = 0; i < 8; ++i) o[i] += b[i];
     }
+    if (ch < nc) *reinterpret_cast<uint4*>(a.y + base + ch * 8) = glue_pack8(o);
   }
 }
 
