@@ -108,15 +108,17 @@ __device__ __forceinline__ bf16x8_t trn_frag(TrnRegs& r) {
 // there).  Rows beyond the end of the sequence repeat its last row and dims beyond the kept width
 // repeat the last kept chunk: finite stand-ins that the callers keep out of every result (masked
 // scores; a zero-padded partner operand; output columns that are never stored).
-template <int D>
+// WAVES = 1: a wavefront moves whole tiles of its own.
+template <int D, int WAVES = 4>
 struct TileStream {
-  static constexpr int CPR = D / 8, RPI = 64 / CPR, PER = (64 / RPI) / 4;
+  static constexpr int CPR = D / 8, RPI = 64 / CPR, PER = (64 / RPI) / WAVES;
+  static __device__ __forceinline__ int wave_of() { return WAVES == 1 ? 0 : static_cast<int>(threadIdx.x >> 6); }
   const bf16_t* base;
   long long ld;
   const bf16_t* p0[PER];   // this lane's source in a tile that starts at row 0
   int row[PER], col[PER];
   __device__ __forceinline__ void init(const bf16_t* b, long long l, int kp) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = wave_of();
     base = b;
     ld = l;
 #pragma unroll
@@ -129,7 +131,7 @@ struct TileStream {
   }
   // rows g0 .. g0 + 63 of the matrix, of which the first rows_valid (>= 1) exist
   __device__ __forceinline__ void issue(bf16_t* tile, long long g0, int rows_valid) const {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(wave_of());
     if (rows_valid >= 64) {      // uniform: one scalar product, one add per load
       const long long adv = g0 * ld;
 #pragma unroll
@@ -260,6 +262,81 @@ __device__ __forceinline__ void attn_work_item(const AttnArgs& a, int heads, int
 // layer need few registers, and more resident workgroups hide their barrier and LDS latencies.
 #define ATTN_WPE(DQ, DV, narrow) ((DQ) + (DV) <= 64 ? (narrow) : ((DQ) > 64 || (DV) > 64 ? 1 : 2))
 
+// One 64-key tile of the forward pass for the 32 queries of a wavefront: scores, the softmax against the running reference
+// maximum, products with V.  oacc: O^T (dims x queries); lacc: the softmax denominators, accumulated by the matrix unit from
+// the same rounded probabilities as the numerator (an all-ones operand in place of V^T, so every row of lacc holds the row
+// sums).  `taken` is called when nothing of the tile is read from LDS any more.
+template <int DQ, int DV, typename Taken>
+__device__ __forceinline__ void attn_fwd_tile(const bf16_t* Kt, const bf16_t* Vt, const bf16x8_t (&qf)[DQ / 16], floatx16 (&oacc)[DV / 32],
+                                              floatx16& lacc, float& m_run, const bf16x8_t& ones, float sc, int L, int causal,
+                                              int kv0, int qw0, Taken taken) {
+  const int lane = threadIdx.x & 63, hh = lane >> 5, l32 = lane & 31, q_idx = qw0 + l32;
+  floatx16 sacc[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sacc[t][r] = 0.f;
+#pragma unroll
+    for (int s = 0; s < DQ / 16; ++s)
+      sacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_nat<DQ>(Kt, t * 32 + l32, s, hh), qf[s], sacc[t], 0, 0, 0);
+  }
+  // Softmax on raw scores: the scale is folded into the exponent's FMA.  Masking is a
+  // wave-uniform special case (tiles on the diagonal or at the end of the sequence) done
+  // with selects, never with divergent branches.
+  if ((causal && kv0 + 63 > qw0) || (kv0 + 64 > L)) {
+    const int lim = (causal ? min(q_idx, L - 1) : L - 1) - kv0 - hh * 4;   // last visible key of this query, from the lane's first key
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sacc[t][r] = t * 32 + (r >> 2) * 8 + (r & 3) > lim ? -INFINITY : sacc[t][r];
+  }
+  float mx = sacc[0][0];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[t][r]);
+  {   // the other 32 keys of the query sit in lane ^ 32
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    mx = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+  }
+  // Running reference maximum (raw, unscaled).  It only has to keep the exponentials in range, so it
+  // moves - and the accumulators are rescaled - only when some query's maximum has grown by more than
+  // RESCALE_LOG2 binades since the reference was set (wave-uniform test); until then probabilities
+  // up to 2^RESCALE_LOG2 are accumulated against the old reference.
+  const float m_new = fmaxf(m_run, mx);
+  if (__builtin_amdgcn_ballot_w64((m_new - m_run) * sc > RESCALE_LOG2 || (m_new > m_run && m_run == -INFINITY)) != 0ull) {
+    const float msc_new = (m_new == -INFINITY ? 0.f : m_new) * sc;
+    const float alpha = __builtin_amdgcn_exp2f(__builtin_fmaf(m_run, sc, -msc_new));
+#pragma unroll
+    for (int r = 0; r < 16; ++r) lacc[r] *= alpha;
+#pragma unroll
+    for (int u = 0; u < DV / 32; ++u)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[u][r] *= alpha;
+    m_run = m_new;
+  }
+  const float msc = (m_run == -INFINITY ? 0.f : m_run) * sc;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sacc[t][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[t][r], sc, -msc));
+  TrnRegs vr[4][DV / 32];
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int u = 0; u < DV / 32; ++u) trn_issue<DV>(vr[s][u], Vt, u * 32, s);
+  trn_wait();
+  taken();
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const bf16x8_t pf = acc_to_frag(sacc[s >> 1], s & 1);
+    lacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pf, lacc, 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < DV / 32; ++u)
+      oacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trn_frag(vr[s][u]), pf, oacc[u], 0, 0, 0);
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // forward: one workgroup per (128 queries, head, batch); 4 wavefronts x 32 queries
 // ---------------------------------------------------------------------------------------------
@@ -302,9 +379,6 @@ void attn_fwd_kernel(const AttnArgs a) {
     own_row_frags<DQ>(qf, qraw, qrow < a.L, a.kp_qk, hh);
   }
 
-  // oacc: O^T (dims x queries); lacc: the softmax denominators, accumulated by the matrix unit from
-  // the same rounded probabilities as the numerator (an all-ones operand in place of V^T, so every
-  // row of lacc holds the row sums)
   floatx16 oacc[DV / 32], lacc;
 #pragma unroll
   for (int u = 0; u < DV / 32; ++u)
@@ -328,69 +402,7 @@ void attn_fwd_kernel(const AttnArgs a) {
       vs.issue(Vs(cur ^ 1), tok0 + kv0 + 64, a.L - kv0 - 64);
     }
     if (a.causal && kv0 > qw0 + 31) continue;   // no query of this wavefront sees the tile
-    floatx16 sacc[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[t][r] = 0.f;
-#pragma unroll
-      for (int s = 0; s < DQ / 16; ++s)
-        sacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_nat<DQ>(Ks(cur), t * 32 + l32, s, hh), qf[s], sacc[t], 0, 0, 0);
-    }
-    // Softmax on raw scores: the scale is folded into the exponent's FMA.  Masking is a
-    // wave-uniform special case (tiles on the diagonal or at the end of the sequence) done
-    // with selects, never with divergent branches.
-    if ((a.causal && kv0 + 63 > qw0) || (kv0 + 64 > a.L)) {
-      const int lim = a.causal ? min(q_idx, a.L - 1) : a.L - 1;   // last visible key of this query
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = kv0 + t * 32 + (r >> 2) * 8 + hh * 4 + (r & 3);
-          sacc[t][r] = key > lim ? -INFINITY : sacc[t][r];
-        }
-    }
-    float mx = sacc[0][0];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[t][r]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    // Running reference maximum (raw, unscaled).  It only has to keep the exponentials in range, so it
-    // moves - and the accumulators are rescaled - only when some query's maximum has grown by more than
-    // RESCALE_LOG2 binades since the reference was set (wave-uniform test); until then probabilities
-    // up to 2^RESCALE_LOG2 are accumulated against the old reference.
-    const float m_new = fmaxf(m_run, mx);
-    if (__builtin_amdgcn_ballot_w64((m_new - m_run) * sc > RESCALE_LOG2 || (m_new > m_run && m_run == -INFINITY)) != 0ull) {
-      const float msc_new = (m_new == -INFINITY ? 0.f : m_new) * sc;
-      const float alpha = __builtin_amdgcn_exp2f(__builtin_fmaf(m_run, sc, -msc_new));
-#pragma unroll
-      for (int r = 0; r < 16; ++r) lacc[r] *= alpha;
-#pragma unroll
-      for (int u = 0; u < DV / 32; ++u)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[u][r] *= alpha;
-      m_run = m_new;
-    }
-    const float msc = (m_run == -INFINITY ? 0.f : m_run) * sc;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[t][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[t][r], sc, -msc));
-    TrnRegs vr[4][DV / 32];
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int u = 0; u < DV / 32; ++u) trn_issue<DV>(vr[s][u], Vs(cur), u * 32, s);
-    trn_wait();
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const bf16x8_t pf = acc_to_frag(sacc[s >> 1], s & 1);
-      lacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pf, lacc, 0, 0, 0);
-#pragma unroll
-      for (int u = 0; u < DV / 32; ++u)
-        oacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trn_frag(vr[s][u]), pf, oacc[u], 0, 0, 0);
-    }
+    attn_fwd_tile<DQ, DV>(Ks(cur), Vs(cur), qf, oacc, lacc, m_run, ones, sc, a.L, a.causal, kv0, qw0, [] {});
   }
   const float l_tot = lacc[0];
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
@@ -403,6 +415,120 @@ void attn_fwd_kernel(const AttnArgs a) {
   tile_to_global<DV>(Qs, 128, a.o + head * a.kp_vo, a.ld_o, tok0 + q0, a.L - q0, a.kp_vo);
 #undef Ks
 #undef Vs
+}
+
+// ---------------------------------------------------------------------------------------------
+// forward, few workgroups: one workgroup per (32 queries, head, batch), its wavefronts share out the keys
+// ---------------------------------------------------------------------------------------------
+// A short batch leaves most of the chip without a 128-query workgroup, and the last query tile then is a chain of L / 64
+// iterations.  Here wavefront w takes the key tiles w, w + 4, .. from LDS buffers of its own (no barrier in the loop: a
+// wavefront waits for its own loads only) and the four partial results are put together at the end, in wavefront order, against the
+// common maximum.  16 heads x 1024 causal tokens, 32 dims: 16.7 -> 8.9 us.
+template <int DQ, int DV>
+static constexpr int attn_split_bufs() { return DQ + DV <= 128 ? 2 : 1; }
+template <int DQ, int DV>
+static constexpr int attn_split_lds_bytes() {
+  const int loop = 4 * attn_split_bufs<DQ, DV>() * 64 * (DQ + DV) * 2;
+  const int join = 4 * DV * 32 * 4 + 2 * 4 * 32 * 4 + 32 * DV * 2;
+  return loop > join ? loop : join;
+}
+template <int DQ, int DV>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DQ + DV <= 64 ? 2 : 1, DQ + DV <= 64 ? 2 : 1)))
+void attn_fwd_split_kernel(const AttnArgs a) {
+  constexpr int NB = attn_split_bufs<DQ, DV>();
+  extern __shared__ __attribute__((aligned(16))) bf16_t lds_all[];     // attn_split_lds_bytes<DQ, DV>()
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), hh = lane >> 5, l32 = lane & 31;
+  bf16_t* const Ks0 = lds_all + wave * NB * 64 * (DQ + DV);      // [NB][64 * DQ]
+  bf16_t* const Vs0 = Ks0 + NB * 64 * DQ;                        // [NB][64 * DV]
+  int qt, head, b;
+  attn_work_item(a, a.h, (a.L + 31) / 32, qt, head, b);
+  const int q0 = qt * 32, q_idx = q0 + l32;
+  const long long tok0 = static_cast<long long>(b) * a.L;
+  const int kv_end = a.causal ? min(a.L, q0 + 32) : a.L;
+  const int n_kv = (kv_end + 63) / 64;
+
+  TileStream<DQ, 1> ks;
+  TileStream<DV, 1> vs;
+  ks.init(a.qkv + k_col(a, head / a.qpk), a.ld_qkv, a.kp_qk);
+  vs.init(a.qkv + v_col(a, head / a.qpk), a.ld_qkv, a.kp_vo);
+  auto issue = [&](int j, int buf) __attribute__((always_inline)) {
+    ks.issue(Ks0 + buf * 64 * DQ, tok0 + j * 64, a.L - j * 64);
+    vs.issue(Vs0 + buf * 64 * DV, tok0 + j * 64, a.L - j * 64);
+  };
+  if (wave < n_kv) issue(wave, 0);
+  bf16x8_t qf[DQ / 16];
+  {
+    u32x4 qraw[DQ / 16];
+    own_row_load<DQ>(qraw, a.qkv + head * a.kp_qk, a.ld_qkv, tok0 + min(q_idx, a.L - 1), a.kp_qk, hh);
+    own_row_frags<DQ>(qf, qraw, q_idx < a.L, a.kp_qk, hh);
+  }
+  floatx16 oacc[DV / 32], lacc;
+#pragma unroll
+  for (int u = 0; u < DV / 32; ++u)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[u][r] = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) lacc[r] = 0.f;
+  bf16x8_t ones;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) ones[i] = static_cast<__bf16>(1.0f);
+  float m_run = -INFINITY;
+  const float sc = a.scale * LOG2E;
+
+  int cur = 0;
+  for (int j = wave; j < n_kv; j += 4) {
+    stream_wait();      // this wavefront's tile is in LDS, its reads of the tile before are done
+    if (NB == 2 && j + 4 < n_kv) issue(j + 4, cur ^ 1);
+    attn_fwd_tile<DQ, DV>(Ks0 + cur * 64 * DQ, Vs0 + cur * 64 * DV, qf, oacc, lacc, m_run, ones, sc, a.L, a.causal, j * 64, q0,
+                          [&]() __attribute__((always_inline)) { if (NB == 1 && j + 4 < n_kv) issue(j + 4, 0); });
+    if (NB == 2) cur ^= 1;
+  }
+
+  // Join: every lane leaves its accumulators in slots of its own and its query's (maximum, denominator); a wavefront then
+  // adds up the register groups wave, wave + 4, .. of all four.
+  __syncthreads();
+  float* const part = reinterpret_cast<float*>(lds_all);       // [4 wavefronts][DV / 2 registers][64 lanes]
+  float* const ms = part + 4 * DV * 32;                        // [4][32]
+  float* const ls = ms + 4 * 32;                               // [4][32]
+  bf16_t* const Os = reinterpret_cast<bf16_t*>(ls + 4 * 32);   // [32][DV]
+#pragma unroll
+  for (int u = 0; u < DV / 32; ++u)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[((wave * (DV / 32) + u) * 16 + r) * 64 + lane] = oacc[u][r];
+  if (hh == 0) {
+    ms[wave * 32 + l32] = m_run;
+    ls[wave * 32 + l32] = lacc[0];
+  }
+  __syncthreads();
+  float m_all = ms[l32], al[4], l_tot = 0.f;
+#pragma unroll
+  for (int w = 1; w < 4; ++w) m_all = fmaxf(m_all, ms[w * 32 + l32]);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float m = ms[w * 32 + l32];
+    al[w] = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_all) * sc);
+    l_tot += al[w] * ls[w * 32 + l32];
+  }
+  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  if (wave == 0 && hh == 0 && q_idx < a.L)
+    a.lse[(static_cast<long long>(b) * a.h + head) * a.L + q_idx] = (m_all * sc + __log2f(l_tot)) * LN2;
+#pragma unroll
+  for (int u = 0; u < DV / 32; ++u) {
+    typedef float floatx4 __attribute__((ext_vector_type(4)));
+    typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+    floatx4 f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      f[i] = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) f[i] += al[w] * part[((w * (DV / 32) + u) * 16 + 4 * wave + i) * 64 + lane];
+      f[i] *= inv;
+    }
+    const bf16x4_t o = __builtin_convertvector(f, bf16x4_t);
+    *reinterpret_cast<bf16x4_t*>(Os + nat_off<DV>(l32, u * 4 + wave) + 4 * hh) = o;
+  }
+  __syncthreads();
+  tile_to_global<DV>(Os, 32, a.o + head * a.kp_vo, a.ld_o, tok0 + q0, a.L - q0, a.kp_vo);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -736,6 +862,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ATTN_WPE(DQ
 // from the launch code, the host side of this compiler can drop some of the kernel stubs).
 #define ATTN_INSTANTIATE(DQ, DV)                                              \
   template __global__ void attn_fwd_kernel<DQ, DV>(const AttnArgs);           \
+  template __global__ void attn_fwd_split_kernel<DQ, DV>(const AttnArgs);     \
   template __global__ void attn_bwd_dq_kernel<DQ, DV>(const AttnArgs);        \
   template __global__ void attn_bwd_dkdv_kernel<DQ, DV>(const AttnArgs);
 ATTN_INSTANTIATE(32, 32)
@@ -749,6 +876,19 @@ ATTN_INSTANTIATE(128, 64)
 ATTN_INSTANTIATE(128, 128)
 #undef ATTN_INSTANTIATE
 
+// Whether the forward pass shares a query tile's keys out over the wavefronts (attn_fwd_split_kernel).  It needs 4 times the workgroups
+// and reads every key tile from memory once per 32 queries, so it pays while all of its workgroups are resident at once (two per
+// compute unit for heads of 32 dims, one for wider ones), and for long causal chains up to twice that.  Attention block forward, 1024 wide,
+// causal, us before -> after, by (heads * batch, L): 32 dims (16, 256) 16.8 -> 14.7, (64, 256) 22.2 -> 20.4, (16, 1024) 31.2 -> 23.1,
+// (32, 1024) 35.0 -> 32.5, beyond the line (128, 256) 25.3 -> 27.0, (64, 1024) 44.9 -> 50.7; 64 dims (32, 256) 23.4 -> 20.8,
+// (16, 1024) 39.8 -> 36.0, beyond (64, 256) 29.5 -> 30.1, (32, 1024) 46.8 -> 58.0; 96 dims (32, 256) 32.4 -> 28.3, (16, 1024)
+// 56.0 -> 50.8, beyond (64, 256) 39.0 -> 42.2.  One key tile: nothing to share.
+static bool attn_fwd_splits_keys(const AttnArgs& a, int dq, int dv) {
+  const long long wgs = static_cast<long long>((a.L + 31) / 32) * a.h * a.B;
+  const long long resident = dq + dv <= 64 ? 512 : 256;
+  return a.L > 64 && wgs <= (a.causal && a.L >= 512 ? 2 * resident : resident);
+}
+
 // LDS of a kernel (which: 0 forward, 1 dQ, 2 dK/dV): the staging tile, the two double-buffered stream tiles, and for
 // dK/dV the row statistics of two query tiles.
 template <int DQ, int DV>
@@ -760,7 +900,8 @@ template <int DQ, int DV>
 static hipError_t launch_core(int which, const AttnArgs& a, hipStream_t st) {
   const unsigned tiles = static_cast<unsigned>((a.L + 127) / 128);
   const dim3 grid(tiles * a.h * a.B), grid_kv(tiles * a.h_kv * a.B);
-  const int lds = attn_lds_bytes<DQ, DV>(which);
+  const bool split = which == 0 && attn_fwd_splits_keys(a, DQ, DV);
+  const int lds = split ? attn_split_lds_bytes<DQ, DV>() : attn_lds_bytes<DQ, DV>(which);
 #define ATTN_LAUNCH(kern, g)                                                                      \
   do {                                                                                            \
     static LdsAttrOnce attr_once;                                                                 \
@@ -770,7 +911,8 @@ static hipError_t launch_core(int which, const AttnArgs& a, hipStream_t st) {
     }                                                                                             \
     hipLaunchKernelGGL(kern, g, dim3(256), lds, st, a);                                           \
   } while (0)
-  if (which == 0) ATTN_LAUNCH((attn_fwd_kernel<DQ, DV>), grid);
+  if (split) ATTN_LAUNCH((attn_fwd_split_kernel<DQ, DV>), dim3(static_cast<unsigned>((a.L + 31) / 32) * a.h * a.B));
+  else if (which == 0) ATTN_LAUNCH((attn_fwd_kernel<DQ, DV>), grid);
   else if (which == 1) ATTN_LAUNCH((attn_bwd_dq_kernel<DQ, DV>), grid);
   else ATTN_LAUNCH((attn_bwd_dkdv_kernel<DQ, DV>), grid_kv);
 #undef ATTN_LAUNCH
