@@ -79,20 +79,21 @@ __device__ __forceinline__ bf16x8_t frag_nat(const bf16_t* tile, int row, int s,
 // 4 * (i % 4) ..+3) and receives dim i of the group's four rows.
 // The reads are issued through inline assembly: the compiler would hold the builtin form back until
 // every direct global->LDS load in flight has landed (it cannot tell the stream buffers apart), which
-// would undo the prefetch.  trn_issue() starts the two reads of a fragment, trn_wait() waits for all LDS
+// would undo the prefetch.  The step is an offset in the instruction: these kernels are bound by their vector instructions (62 % of the
+// cycles at 32 dims and 1024 tokens, the matrix units 25 %), and addresses were a tenth of them.  trn_issue() starts the two reads of a fragment, trn_wait() waits for all LDS
 // reads issued so far, trn_frag() then hands a fragment over (its empty asm statements keep the uses
 // behind the wait).
 struct TrnRegs { shortx4_t lo, hi; };
 template <int D>
 __device__ __forceinline__ void trn_issue(TrnRegs& r, const bf16_t* tile, int dim0, int s) {
   const int lane = threadIdx.x & 63, g = lane >> 4, i = lane & 15;
-  const int row = 16 * s + 4 * (g >> 1) + (i >> 2);
+  const int row = 4 * (g >> 1) + (i >> 2);      // the swizzles look at the low four bits of a row: step s is a constant offset
   const int col = dim0 + 16 * (g & 1) + 4 * (i & 3);
   const lds_bf16_t* t3 = (const lds_bf16_t*)tile;
   const unsigned a0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>(t3 + nat_off<D>(row, col >> 3) + (col & 7)));
   const unsigned a1 = static_cast<unsigned>(reinterpret_cast<uintptr_t>(t3 + nat_off<D>(row + 8, col >> 3) + (col & 7)));
-  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(r.lo) : "v"(a0) : "memory");
-  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(r.hi) : "v"(a1) : "memory");
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.lo) : "v"(a0), "i"(s * 32 * D) : "memory");
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.hi) : "v"(a1), "i"(s * 32 * D) : "memory");
 }
 __device__ __forceinline__ void trn_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ bf16x8_t trn_frag(TrnRegs& r) {
@@ -613,7 +614,7 @@ void attn_bwd_dq_kernel(const AttnArgs a) {
     }
     if (a.causal && kv0 > qw0 + 31) continue;
     const bool need_mask = (a.causal && kv0 + 63 > qw0) || (kv0 + 64 > a.L);
-    const int lim = a.causal ? min(q_idx, a.L - 1) : a.L - 1;       // last visible key of this query
+    const int lim = (a.causal ? min(q_idx, a.L - 1) : a.L - 1) - kv0 - hh * 4;       // last visible key of this query, from the lane's first key
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       floatx16 sacc, pacc;
@@ -627,10 +628,7 @@ void attn_bwd_dq_kernel(const AttnArgs a) {
         pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_nat<DV>(Vs(cur), t * 32 + l32, s, hh), dof[s], pacc, 0, 0, 0);
       if (need_mask) {        // wave-uniform; selects only
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = kv0 + t * 32 + (r >> 2) * 8 + hh * 4 + (r & 3);
-          sacc[r] = key > lim ? -INFINITY : sacc[r];
-        }
+        for (int r = 0; r < 16; ++r) sacc[r] = t * 32 + (r >> 2) * 8 + (r & 3) > lim ? -INFINITY : sacc[r];
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -762,11 +760,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ATTN_WPE(DQ
       floatx16 pr;
       if (need_mask) {        // wave-uniform: only tiles on the diagonal or at the end of the sequence pay for the selects
         // a query sees this lane's key if key <= q (causal) and both are inside the sequence
-        const int q_min = key_idx >= a.L ? 0x7fffffff : (a.causal ? key_idx : 0);
+        const int q_first = qb0 + hh * 4;       // the lane's first query; both limits are counted from it
+        const int q_min = key_idx >= a.L ? 64 : (a.causal ? key_idx : 0) - q_first, q_end = a.L - q_first;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int q = qb0 + t * 32 + (r >> 2) * 8 + hh * 4 + (r & 3);
-          sacc[r] = (q < q_min || q >= a.L) ? -INFINITY : sacc[r];
+          const int q = t * 32 + (r >> 2) * 8 + (r & 3);
+          sacc[r] = (q < q_min || q >= q_end) ? -INFINITY : sacc[r];
         }
       }
 #pragma unroll
