@@ -56,7 +56,7 @@ struct GemmDesc {
   GemmEpi epi;
 };
 
-// Launch on ctx->stream.  bf16 runs on MFMA tiles; fp32 on a vector-ALU tile kernel.
+// Launch on ctx->stream.  bf16 and fp32 both run on MFMA tiles.
 int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d);
 // Rows (of M floats) of the partial column sums that the launch of d writes to d.colsum.
 int ecospa_gemm_colsum_rows(const GemmDesc& d);
