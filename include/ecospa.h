@@ -424,8 +424,8 @@ int ecospa_coupled_bwd(ecospa_ctx* ctx, const ecospa_block_desc* desc /*host*/, 
  * that tile is not built for the operand form, the library chooses): 1, 3 = 128x128; 2, 4, 20 = 256x256; 10 .. 19 = 256x256, 256x256,
  * 256x128, 128x256, 128x128, 256x256, 128x128, 256x256, 256x256, 256x128; 21 = 256x192; 30 .. 38 = 256x256, 192x256, 256x192,
  * 128x256, 256x128, 192x192, 128x192, 192x128, 128x128.
- * splits: 0 = library's choice, otherwise the number of K splits (partials come from the
- * workspace and are added in a fixed order).
+ * splits: 0 = library's choice, of the numbers whose partials the attached workspace holds (none attached: 1);
+ * otherwise the number of K splits (-> ERR_WORKSPACE where they do not fit).  The partials are added in a fixed order.
  * bf16 needs 16-byte aligned pointers, N % 8 == 0, leading dimensions % 8 == 0 and the
  * contiguous extent of each operand % 8 == 0 (-> ERR_ALIGN otherwise).
  * ------------------------------------------------------------------------------------------ */

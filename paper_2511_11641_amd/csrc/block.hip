@@ -259,10 +259,12 @@ extern "C" int ecospa_coupled_bwd(ecospa_ctx* ctx, const ecospa_block_desc* desc
 }
 
 // ---------------------------------------------------------------------------------------------
+static size_t split_bytes(int splits, int M, int N) { return splits > 1 ? static_cast<size_t>(splits) * M * N * 4 : 0; }
+
 extern "C" size_t ecospa_contract_workspace_bytes(int dtype, int M, int N, int K, int splits) {
   if (!dtype_ok(dtype) || M < 1 || N < 1 || K < 1 || splits < 0 || splits > 64) return 0;
   const int s = splits == 0 ? ecospa_gemm_splits(dtype, M, N, K) : splits;
-  return s > 1 ? static_cast<size_t>(s) * M * N * 4 : 0;
+  return split_bytes(s, M, N);
 }
 
 extern "C" int ecospa_contract(ecospa_ctx* ctx, int dtype, int M, int N, int K, const void* A, long long lda,
@@ -275,10 +277,11 @@ extern "C" int ecospa_contract(ecospa_ctx* ctx, int dtype, int M, int N, int K, 
   GemmDesc g = gemm_desc(dtype, M, N, K, A, lda, trans_a ? 1 : 0, B, ldb, trans_b ? 1 : 0);
   g.tile = tile;
   g.splits = splits == 0 ? ecospa_gemm_splits(dtype, M, N, K) : splits;
+  // the library's own choice is one of time only: K is split as far as the workspace goes, which may be none
+  while (splits == 0 && g.splits > 1 && ctx->ws_bytes < split_bytes(g.splits, M, N)) --g.splits;
   g.epi.kind = EPI_STORE; g.epi.c = C; g.epi.ldc = ldc; g.epi.bias = bias;
   if (g.splits > 1) {
-    const size_t need = static_cast<size_t>(g.splits) * M * N * 4;
-    if (!ctx->ws || ctx->ws_bytes < need) return ECOSPA_ERR_WORKSPACE;
+    if (!ctx->ws || ctx->ws_bytes < split_bytes(g.splits, M, N)) return ECOSPA_ERR_WORKSPACE;
     g.partial = static_cast<float*>(ctx->ws);
   }
   return ecospa_gemm(ctx, g);

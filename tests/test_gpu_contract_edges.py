@@ -65,3 +65,24 @@ def test_contract_f32_edges(ctx, ta, tb, M, N, K):
     assert_close(ctx.ecospa_contract(dev(a), ta, dev(b), tb, splits=1), want, "f32", f"{M}x{N}x{K}")
     if K > 64:
         assert_close(ctx.ecospa_contract(dev(a), ta, dev(b), tb, splits=3), want, "f32", f"{M}x{N}x{K} in three parts")
+
+
+# no workspace, one that holds fewer splits than the library would take (8 for this shape), and enough
+@pytest.mark.parametrize("parts", [0, 2, 8])
+@pytest.mark.parametrize("ta,tb", [(False, False), (True, True)])
+def test_own_split_is_limited_to_the_workspace(ta, tb, parts):
+    M, N, K = 16, 24, 2048
+    ga, gb, _, want = _case(65, M, N, K, ta, tb)
+    ctx = B.Context("cuda:0")          # a context of its own: nothing attached yet
+    assert ctx.lib.ecospa_contract_workspace_bytes(B.BF16, M, N, K, 0) == 8 * M * N * 4
+    if parts:
+        ctx.reserve(parts * M * N * 4)
+    out = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+
+    def call(splits):
+        return ctx.lib.ecospa_contract(ctx.h, B.BF16, M, N, K, ga.data_ptr(), ga.stride(0), int(ta), gb.data_ptr(), gb.stride(0), int(tb),
+                                       out.data_ptr(), N, None, 0, splits)
+
+    assert call(0) == B.OK
+    assert_close(out, want, "bf16", f"{parts} parts held")
+    assert torch.equal(out, ctx.ecospa_contract(ga, ta, gb, tb, splits=max(parts, 1)))
