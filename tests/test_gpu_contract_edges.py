@@ -86,3 +86,16 @@ def test_own_split_is_limited_to_the_workspace(ta, tb, parts):
     assert call(0) == B.OK
     assert_close(out, want, "bf16", f"{parts} parts held")
     assert torch.equal(out, ctx.ecospa_contract(ga, ta, gb, tb, splits=max(parts, 1)))
+
+
+# Rounding against fp64.  The error of n additions in one chain is about 1.8e-8 n^0.5 of a sum of N(0, 1) products; chains of 256 and
+# the chain of their K / 256 (at most 128) sums: 1.8e-8 (256 + 128)^0.5 = 3.5e-7, whatever K is.
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, True)])
+@pytest.mark.parametrize("M,N,K", [(1536, 1472, 8192), (768, 2704, 1500), (96, 80, 32768)])
+def test_contract_f32_error_does_not_grow_with_k(ctx, ta, tb, M, N, K):
+    gen = torch.Generator(device="cuda").manual_seed(68)
+    a = torch.randn((K, M) if ta else (M, K), device="cuda", generator=gen)
+    b = torch.randn((K, N) if tb else (N, K), device="cuda", generator=gen)
+    want = (a.t() if ta else a).double() @ (b if tb else b.t()).double()
+    got = ctx.ecospa_contract(a, ta, b, tb)
+    assert float((got.double() - want).norm() / want.norm()) < 4.5e-7
