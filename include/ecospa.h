@@ -436,8 +436,9 @@ int ecospa_contract(ecospa_ctx* ctx, int dtype, int M, int N, int K, const void*
 /* The dY^T X form of ecospa_contract (bf16, both operands K-slow: A[K, M], B[K, N]) together with the column sums of
  * its A operand, colsum[m] = sum_k A(m, k) (float[M]) - the bias gradient that a backward pass gets from the weight-
  * gradient contraction that reads dY anyway.  Exposed for tests of every tile shape (tile: 0, 1..4, 20, 30..38 as in
- * ecospa_contract).  Workspace: splits * M floats (256-byte rounded) plus the partial products of a split contraction.
- * Errors as ecospa_contract. */
+ * ecospa_contract).  Workspace: at least splits * M floats (256-byte rounded) plus the partial products of a split contraction
+ * (splits = 0: as many as fit); with splits * ceil(N / 128) * M floats in front of them the sums come from the contraction itself,
+ * with less A is read a second time for them.  Errors as ecospa_contract. */
 int ecospa_contract_colsum(ecospa_ctx* ctx, int M, int N, int K, const void* A, long long lda, const void* B,
                            long long ldb, void* C, long long ldc, float* colsum, int tile, int splits);
 

@@ -294,23 +294,28 @@ extern "C" int ecospa_contract_colsum(ecospa_ctx* ctx, int M, int N, int K, cons
   if (!ctx || !A || !B || !C || !colsum) return ECOSPA_ERR_NULL;
   if (M < 1 || N < 1 || K < 1 || tile < 0 || tile > 38 || (tile > 21 && tile < 30) || splits < 0 || splits > 64) return ECOSPA_ERR_SHAPE;
   if (lda < M || ldb < N || ldc < N) return ECOSPA_ERR_SHAPE;
+  if ((tile >= 10 && tile < 20) || tile == 21) return ECOSPA_ERR_SHAPE;      // not codes of this entry point
   GemmDesc g = gemm_desc(ECOSPA_BF16, M, N, K, A, lda, 1, B, ldb, 1);
   g.splits = splits == 0 ? ecospa_gemm_splits(ECOSPA_BF16, M, N, K) : splits;
-  const int sp = g.splits > 1 ? g.splits : 1;
+  // the least that the caller attaches: `splits` rows of M floats and the partial products
+  const auto least = [&](int s) { return align_up(static_cast<size_t>(s > 1 ? s : 1) * M * 4, 256) + split_bytes(s, M, N); };
+  while (splits == 0 && g.splits > 1 && ctx->ws_bytes < least(g.splits)) --g.splits;
+  if (!ctx->ws || ctx->ws_bytes < least(g.splits)) return ECOSPA_ERR_WORKSPACE;
   g.epi.kind = EPI_STORE; g.epi.c = C; g.epi.ldc = ldc;
   g.tile = tile;
-  // workspace: [rows][M] partial column sums, then the fp32 partial products of a split contraction
+  // The contraction leaves a row of partial column sums per split and tile column: [rows][M], then the partial products.  Where
+  // the workspace is too small for that many rows, the last launch adds up A's rows instead.
   const int rows = ecospa_gemm_colsum_rows(g);
   const size_t cs_bytes = align_up(static_cast<size_t>(rows) * M * 4, 256);
-  const size_t need = cs_bytes + (sp > 1 ? static_cast<size_t>(sp) * M * N * 4 : 0);
-  if (!ctx->ws || ctx->ws_bytes < need) return ECOSPA_ERR_WORKSPACE;
-  g.colsum = static_cast<float*>(ctx->ws);
-  if (sp > 1) { g.partial = reinterpret_cast<float*>(static_cast<char*>(ctx->ws) + cs_bytes); g.defer_reduce = 1; }
+  const bool fused = ctx->ws_bytes >= cs_bytes + split_bytes(g.splits, M, N);
+  if (fused) g.colsum = static_cast<float*>(ctx->ws);
+  if (g.splits > 1) { g.partial = reinterpret_cast<float*>(static_cast<char*>(ctx->ws) + (fused ? cs_bytes : 0)); g.defer_reduce = 1; }
   const int rc = ecospa_gemm(ctx, g);
   if (rc) return rc;
   AuxBatch aux;
   memset(&aux, 0, sizeof(aux));
-  if (sp > 1) aux.reduce[aux.n_reduce++] = g;
-  aux.colsum[aux.n_colsum++] = AuxColsum{g.colsum, M, rows, M, ECOSPA_F32, colsum, ECOSPA_F32};
+  if (g.splits > 1) aux.reduce[aux.n_reduce++] = g;
+  aux.colsum[aux.n_colsum++] = fused ? AuxColsum{g.colsum, M, rows, M, ECOSPA_F32, colsum, 0}
+                                     : AuxColsum{A, lda, K, M, ECOSPA_BF16, colsum, AUX_OUT_F32};
   return ecospa_aux_launch(ctx, aux);
 }

@@ -81,12 +81,13 @@ hipError_t gemm_ring_launch_mixed(ecospa_ctx* ctx, const GemmDesc& d, int shape,
 // partials (a GemmDesc launched with defer_reduce) and bias gradients out[n] = sum_m X[m, n].
 // A column sum is done by one workgroup per strip of columns over all rows - no second pass.
 #define AUX_MAX_JOBS 4
+#define AUX_OUT_F32 (-1)
 struct AuxColsum {
   const void* X;
   long long ldx;
   int M, N, dtype;
   void* out;
-  int out_dtype;     // 0: as X; otherwise the type of `out` (fp32 partial sums reduced into a bf16 gradient)
+  int out_dtype;     // 0: as X; ECOSPA_BF16 (fp32 partial sums reduced into a bf16 gradient); AUX_OUT_F32 (fp32 sums of a bf16 X)
 };
 struct AuxBatch {
   int n_reduce, n_colsum;

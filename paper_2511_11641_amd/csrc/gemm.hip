@@ -252,8 +252,7 @@ int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d) {
   if (d.M < 1 || d.N < 1 || d.K < 1) return ECOSPA_ERR_SHAPE;
   if (!d.A || !d.B || (!d.epi.c && d.epi.kind != EPI_SWIGLU)) return ECOSPA_ERR_NULL;      // the gated epilogue may skip its first output
   if (d.splits > 1 && !d.partial) return ECOSPA_ERR_WORKSPACE;
-  // column sums of the A operand: the dY^T X form
-  if (d.colsum && !(d.dtype == ECOSPA_BF16 && d.trans_a && d.trans_b && (d.tile <= 4 || d.tile == 20 || d.tile >= 30))) return ECOSPA_ERR_SHAPE;
+  if (d.colsum && !(d.dtype == ECOSPA_BF16 && d.trans_a && d.trans_b)) return ECOSPA_ERR_SHAPE;      // column sums of A: the dY^T X form
   const int splits = d.splits > 1 ? d.splits : 1;
   if (d.dtype == ECOSPA_BF16) {
     // 16-byte vector loads along the contiguous axis of each operand
@@ -438,7 +437,8 @@ __global__ __launch_bounds__(AUX_THREADS) void bwd_aux_kernel(const AuxBatchDev 
   if (j < a.b.n_colsum) {
     const AuxColsum& c = a.b.colsum[j];
     const int od = c.out_dtype ? c.out_dtype : c.dtype;
-    if (c.dtype == ECOSPA_BF16) aux_colsum_block<bf16_t, bf16_t>(c, local, lds);
+    if (c.dtype == ECOSPA_BF16 && od == AUX_OUT_F32) aux_colsum_block<bf16_t, float>(c, local, lds);
+    else if (c.dtype == ECOSPA_BF16) aux_colsum_block<bf16_t, bf16_t>(c, local, lds);
     else if (od == ECOSPA_BF16) aux_colsum_block<float, bf16_t>(c, local, lds);
     else aux_colsum_block<float, float>(c, local, lds);
   } else {

@@ -99,3 +99,26 @@ def test_contract_f32_error_does_not_grow_with_k(ctx, ta, tb, M, N, K):
     want = (a.t() if ta else a).double() @ (b if tb else b.t()).double()
     got = ctx.ecospa_contract(a, ta, b, tb)
     assert float((got.double() - want).norm() / want.norm()) < 4.5e-7
+
+
+# the workspace that the header asks for holds a row of sums per split; the contraction would leave one per split and tile column
+@pytest.mark.parametrize("M,N,K,splits", [(136, 1048, 200, 1), (64, 392, 1379, 3), (72, 264, 4191, 0), (24, 8, 5, 1)])
+def test_column_sums_in_the_least_workspace(M, N, K, splits):
+    ga, gb, a, want = _case(66, M, N, K, True, True)
+    ctx = B.Context("cuda:0")
+    lib = ctx.lib
+    parts = lib.ecospa_contract_workspace_bytes(B.BF16, M, N, K, splits)
+    sp = max(1, parts // (M * N * 4))
+    least = (sp * M * 4 + 255) // 256 * 256 + parts
+    out, cs = torch.empty((M, N), dtype=torch.bfloat16, device="cuda"), torch.empty((M,), dtype=torch.float32, device="cuda")
+
+    def call(tile=0, splits=splits):
+        return lib.ecospa_contract_colsum(ctx.h, M, N, K, ga.data_ptr(), M, gb.data_ptr(), N, out.data_ptr(), N, cs.data_ptr(), tile, splits)
+
+    assert call() == B.ERR_WORKSPACE
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+    assert lib.ecospa_set_workspace(ctx.h, ws.data_ptr(), least) == B.OK
+    assert call() == B.OK
+    assert_close(out, want, "bf16", "product")
+    assert_close(cs, a.astype(np.float64).sum(axis=0), "f32", "column sums")
+    assert call(tile=14) == B.ERR_SHAPE and call(splits=sp + 1) == B.ERR_WORKSPACE
