@@ -41,13 +41,11 @@ static int validate_block(const ecospa_block_desc* dp) {
 
 static size_t max_sz(size_t a, size_t b) { return a > b ? a : b; }
 
-// Rows of partial column sums that the weight-gradient contraction dY^T X of this shape writes (library's own plan).
+// Rows of partial column sums that the weight-gradient contraction dY^T X of this shape writes at most: one per split and tile
+// column, and no tile of that form has fewer than 128 columns (which one runs depends on the leading dimensions, not known here).
 int block_colsum_rows(int dtype, int M, int N, int K) {
-  GemmDesc g;
-  memset(&g, 0, sizeof(g));
-  g.dtype = dtype; g.M = M; g.N = N; g.K = K; g.lda = M; g.ldb = N; g.trans_a = g.trans_b = 1;
-  g.splits = ecospa_gemm_splits(dtype, M, N, K);
-  return ecospa_gemm_colsum_rows(g);
+  const int splits = ecospa_gemm_splits(dtype, M, N, K);
+  return dtype == ECOSPA_BF16 ? splits * ((N + 127) / 128) : splits;
 }
 
 void block_ws_layout(const ecospa_block_desc& d, void* base, BlockWs& w) {

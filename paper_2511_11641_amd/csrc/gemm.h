@@ -72,6 +72,12 @@ int ecospa_gemm_token_splits(int M, int N, int K);
 // The bf16 kernel (gemm_ring.h): launch of tile shape `shape` (index into the table in gemm.hip; not every shape is built for every
 // form).  k_chunk: K range of a split, a multiple of 64.
 #define GEMM_RING_NSHAPES 12
+// Leading dimensions from 2^23 on (256 rows of them are 4 GB): lane offsets of 64 bits, built for 128 x 128 tiles alone.
+#define GEMM_RING_WIDE_SHAPE 8
+static inline bool ring_wide(const GemmDesc& d) {
+  const long long lim = 1ll << 23;
+  return d.lda >= lim || d.ldb >= lim || d.epi.ldc >= lim || d.epi.ldc2 >= lim || d.epi.ldh >= lim;
+}
 hipError_t gemm_ring_launch_nt(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk);
 hipError_t gemm_ring_launch_tt(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk);
 hipError_t gemm_ring_launch_mixed(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk);

@@ -231,6 +231,7 @@ static void ring_forced_tile(int tile, int* bm, int* bn) {
 
 static int ring_route(const GemmDesc& d, int splits) {
   int shape, sp, bm, bn;
+  if (ring_wide(d)) return GEMM_RING_WIDE_SHAPE;
   ring_forced_tile(d.tile, &bm, &bn);
   const unsigned built = ring_shapes_built(d.trans_a, d.trans_b);
   for (int q = 0; q < GEMM_RING_NSHAPES && bm; ++q)

@@ -57,13 +57,15 @@ template <int RT>
 __device__ __forceinline__ int ring_ks_swz(int k) { return RT % 128 == 0 ? ((k & 3) << 2) : RT == 64 ? ((k & 1) << 2) : (((k >> 1) & 1) << 2); }
 
 // Direct loads of one operand tile of RT rows: PER instructions per slab and wavefront, each moving 64 x 16 bytes to consecutive LDS.
-// Addresses are a wavefront-uniform base (scalar registers, advanced by scalar adds) plus a lane offset that never changes.
-template <int RT, bool KSLOW>
+// Addresses are a wavefront-uniform base (scalar registers, advanced by scalar adds) plus a lane offset that never changes: 32 bits, or
+// 64 (WIDE) for leading dimensions whose tiles reach over 4 GB.
+template <bool WIDE> using ring_off = std::conditional_t<WIDE, unsigned long long, unsigned>;
+template <int RT, bool KSLOW, bool WIDE>
 struct RingLoads {
   static constexpr int PER = RT * RING_BK * 2 / 1024 / 4;
   static_assert(PER * 4096 == RT * RING_BK * 2, "whole load instructions per wavefront");
   const char* base;
-  unsigned off[PER];
+  ring_off<WIDE> off[PER];
   long long step;        // bytes per slab
   // first slab: kv (1 .. 64) of k, loaded here into `tile`; single: there is no other slab (the offsets then stay the clamped ones)
   __device__ __forceinline__ void init(const bf16_t* mat, long long ld, int r0, int R, int k0, int kv, bool single, bf16_t* tile) {
@@ -82,8 +84,8 @@ struct RingLoads {
       }
       const int gr = min(r0 + r, KSLOW ? R - 8 : R - 1) - r0;          // rows beyond the matrix repeat its last ones (never stored)
       const int gk = min(k, KSLOW ? kv - 1 : kv - 8);
-      const unsigned o0 = static_cast<unsigned>((KSLOW ? static_cast<long long>(gk) * ld + gr : static_cast<long long>(gr) * ld + gk) * 2);
-      off[i] = single ? o0 : static_cast<unsigned>((KSLOW ? static_cast<long long>(k) * ld + gr : static_cast<long long>(gr) * ld + k) * 2);
+      const ring_off<WIDE> o0 = static_cast<ring_off<WIDE>>((KSLOW ? static_cast<long long>(gk) * ld + gr : static_cast<long long>(gr) * ld + gk) * 2);
+      off[i] = single ? o0 : static_cast<ring_off<WIDE>>((KSLOW ? static_cast<long long>(k) * ld + gr : static_cast<long long>(gr) * ld + k) * 2);
       __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(base + o0), (lds_bf16_t*)tile + (wave * PER + i) * 512, 16, 0, 0);
     }
     if (!single) base += KSLOW ? static_cast<long long>(kv) * ld * 2 : kv * 2;
@@ -93,7 +95,7 @@ struct RingLoads {
   // last slab is then loaded again, into buffers that nobody reads any more, which keeps the loop free of branches
   __device__ __forceinline__ void issue(int i, lds_bf16_t* tile, long long adv) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    asm volatile("" : "+v"(off[i]));     // keeps the offset a 32-bit register at the load
+    asm volatile("" : "+v"(off[i]));     // keeps the offset a lane register at the load
     __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(base + off[i]), tile + (wave * PER + i) * 512, 16, 0, 0);
     if (i == PER - 1) base += adv;
   }
@@ -174,9 +176,9 @@ __device__ __forceinline__ void gemm_work_item(int splits, int& tile, int& z) {
   }
 }
 
-// EPIS: bit mask of the epilogue kinds the instantiation carries; CS: column sums of a K-slow A (GemmDesc::colsum).
-template <int BM, int BN, int NS, bool TA, bool TB, bool CS, int EPIS, int WPE = 1>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
+// EPIS: bit mask of the epilogue kinds the instantiation carries; CS: column sums of a K-slow A (GemmDesc::colsum); WIDE: see ring_off.
+template <int BM, int BN, int NS, bool TA, bool TB, bool CS, int EPIS, bool WIDE = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void gemm_bf16_ring_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
   constexpr int WTM = BM / 2, WTN = BN / 2, FM = WTM / 16, FN = WTN / 16, S = RING_BK / 32, NM = FM * FN, NR = FM + FN;
   constexpr int STAGE = (BM + BN) * RING_BK;
@@ -229,9 +231,9 @@ void gemm_bf16_ring_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
 #pragma unroll
   for (int i = 0; i < (CS ? FM : 1); ++i) cs[i] = 0.f;
 
-  RingLoads<BM, TA> la;
-  RingLoads<BN, TB> lb;
-  constexpr int PA = RingLoads<BM, TA>::PER, PB = RingLoads<BN, TB>::PER, LPW = PA + PB;
+  RingLoads<BM, TA, WIDE> la;
+  RingLoads<BN, TB, WIDE> lb;
+  constexpr int PA = RingLoads<BM, TA, WIDE>::PER, PB = RingLoads<BN, TB, WIDE>::PER, LPW = PA + PB;
   static_assert(LPW * (NS - 1) < 64, "vmcnt range");
   la.init(static_cast<const bf16_t*>(d.A), d.lda, m0, d.M, k_begin, kv, nk == 1, lds);
   lb.init(static_cast<const bf16_t*>(d.B), d.ldb, n0, d.N, k_begin, kv, nk == 1, lds + BM * RING_BK);
@@ -257,8 +259,8 @@ void gemm_bf16_ring_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   if (kv < RING_BK) {
-    RingLoads<BM, TA>::zero_tail(lds, kv);
-    RingLoads<BN, TB>::zero_tail(lds + BM * RING_BK, kv);
+    RingLoads<BM, TA, WIDE>::zero_tail(lds, kv);
+    RingLoads<BN, TB, WIDE>::zero_tail(lds + BM * RING_BK, kv);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -425,16 +427,17 @@ void gemm_bf16_ring_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
       for (int q = 0; q < 8; ++q) v[q] += b[q];
     }
   };
-  // Addresses: a base per workgroup (scalar) plus 32-bit lane offsets; lane rows beyond the matrix read its last row and store nothing.
+  // Addresses: a base per workgroup (scalar) plus lane offsets; lane rows beyond the matrix read its last row and store nothing.
   const bool cols_in = n0 + BN <= d.N;
   const int row_l = wm * WTM + l16, rows_in = d.M - m0, nl = nw - n0, n_last = d.N - 8 - n0;
   char* const cb = reinterpret_cast<char*>(static_cast<bf16_t*>(d.epi.c) + static_cast<long long>(m0) * d.epi.ldc + (d.epi.kind == EPI_DSWIGLU ? 2 * n0 : n0));
-  const unsigned ldc2b = static_cast<unsigned>(d.epi.ldc) * 2u;      // bytes per row of c
+  typedef ring_off<WIDE> off_t;
+  const off_t ldc2b = static_cast<off_t>(d.epi.ldc) * 2u;      // bytes per row of c
   if (d.epi.kind == EPI_STORE) {
     ring_for<0, FM>([&](auto i_) __attribute__((always_inline)) {
       constexpr int i = decltype(i_)::value;
       const int row = row_l + i * 16;
-      const unsigned off = static_cast<unsigned>(row) * ldc2b + nl * 2;
+      const off_t off = static_cast<off_t>(row) * ldc2b + nl * 2;
       uint4 o[JP];
       ring_for<0, JP>([&](auto jp_) __attribute__((always_inline)) {
         float v[8];
@@ -486,7 +489,7 @@ void gemm_bf16_ring_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
             nxt[jp].a = *reinterpret_cast<const uint4*>(d.epi.rope_cos + rope_off[jp] + tpos);
             nxt[jp].b = *reinterpret_cast<const uint4*>(d.epi.rope_sin + rope_off[jp] + tpos);
           } else if constexpr (epi_has_side(KIND)) {
-            const char* p = hb + static_cast<unsigned>(row) * (static_cast<unsigned>(d.epi.ldh) * 2u) + (cols_in ? nl + jp * 32 : min(nl + jp * 32, n_last)) * CM;
+            const char* p = hb + static_cast<off_t>(row) * (static_cast<off_t>(d.epi.ldh) * 2u) + (cols_in ? nl + jp * 32 : min(nl + jp * 32, n_last)) * CM;
             nxt[jp].a = *reinterpret_cast<const uint4*>(p);
             if constexpr (KIND == EPI_DSWIGLU) nxt[jp].b = *reinterpret_cast<const uint4*>(p + 16);
           }
@@ -521,7 +524,7 @@ void gemm_bf16_ring_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
             add_bias(jp, v);
             epi_math_k<KIND>(d.epi.act, v, sd[jp], KIND == EPI_ROPE && rope_on[jp], out[jp]);
           }
-          const unsigned off = static_cast<unsigned>(row) * ldc2b + nl * CM;
+          const off_t off = static_cast<off_t>(row) * ldc2b + nl * CM;
           if (row < rows_in) {
 #pragma unroll
             for (int jp = 0; jp < JP; ++jp) {
@@ -529,9 +532,9 @@ void gemm_bf16_ring_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
                 if (KIND != EPI_SWIGLU || d.epi.c) *reinterpret_cast<uint4*>(cb + off + jp * (32 * CM)) = out[jp].o[0];
                 if constexpr (KIND == EPI_DSWIGLU) *reinterpret_cast<uint4*>(cb + off + jp * (32 * CM) + 16) = out[jp].o[1];
                 if constexpr (KIND == EPI_BIAS_ACT)
-                  *reinterpret_cast<uint4*>(c2b + static_cast<unsigned>(row) * (static_cast<unsigned>(d.epi.ldc2) * 2u) + nl * 2 + jp * 64) = out[jp].a2;
+                  *reinterpret_cast<uint4*>(c2b + static_cast<off_t>(row) * (static_cast<off_t>(d.epi.ldc2) * 2u) + nl * 2 + jp * 64) = out[jp].a2;
                 if constexpr (KIND == EPI_SWIGLU)
-                  *reinterpret_cast<uint2*>(c2b + static_cast<unsigned>(row) * (static_cast<unsigned>(d.epi.ldc2) * 2u) + nl + jp * 32) = make_uint2(out[jp].a2.x, out[jp].a2.y);
+                  *reinterpret_cast<uint2*>(c2b + static_cast<off_t>(row) * (static_cast<off_t>(d.epi.ldc2) * 2u) + nl + jp * 32) = make_uint2(out[jp].a2.x, out[jp].a2.y);
               }
             }
           }
@@ -543,13 +546,13 @@ void gemm_bf16_ring_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
 
 // ---------------------------------------------------------------------------------------------
 // launch
-template <int BM, int BN, int NS, bool TA, bool TB, bool CS, int EPIS>
+template <int BM, int BN, int NS, bool TA, bool TB, bool CS, int EPIS, bool WIDE = false>
 static hipError_t ring_launch_shape(ecospa_ctx* ctx, const GemmDesc& d, int k_chunk) {
   const int tm = (d.M + BM - 1) / BM, tn = (d.N + BN - 1) / BN;
   const int splits = d.splits > 1 ? d.splits : 1;
   constexpr int lds_bytes = NS * (BM + BN) * RING_BK * static_cast<int>(sizeof(bf16_t));
   static_assert(lds_bytes <= 160 * 1024, "LDS of a compute unit");
-  auto kern = gemm_bf16_ring_kernel<BM, BN, NS, TA, TB, CS, EPIS>;
+  auto kern = gemm_bf16_ring_kernel<BM, BN, NS, TA, TB, CS, EPIS, WIDE>;
   static LdsAttrOnce attr_once;
   if (lds_bytes > 64 * 1024) {
     const hipError_t e = attr_once.ensure(reinterpret_cast<const void*>(kern), lds_bytes);

@@ -7,11 +7,16 @@
   template __global__ void gemm_bf16_ring_kernel<BM, BN, NS, true, true, false, EPIS_TT>(const GemmDesc, int, int); \
   template __global__ void gemm_bf16_ring_kernel<BM, BN, NS, true, true, true, EPIS_TT>(const GemmDesc, int, int);
 TT_SHAPES(TT_INST)
+template __global__ void gemm_bf16_ring_kernel<128, 128, 4, true, true, false, EPIS_TT, true>(const GemmDesc, int, int);
+template __global__ void gemm_bf16_ring_kernel<128, 128, 4, true, true, true, EPIS_TT, true>(const GemmDesc, int, int);
 
 hipError_t gemm_ring_launch_tt(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk) {
 #define TT_CASE(I, BM, BN, NS)                                                                                   \
   if (shape == I) return d.colsum ? ring_launch_shape<BM, BN, NS, true, true, true, EPIS_TT>(ctx, d, k_chunk)   \
                                   : ring_launch_shape<BM, BN, NS, true, true, false, EPIS_TT>(ctx, d, k_chunk);
+  if (ring_wide(d) && shape == GEMM_RING_WIDE_SHAPE)
+    return d.colsum ? ring_launch_shape<128, 128, 4, true, true, true, EPIS_TT, true>(ctx, d, k_chunk)
+                    : ring_launch_shape<128, 128, 4, true, true, false, EPIS_TT, true>(ctx, d, k_chunk);
   TT_SHAPES(TT_CASE)
   return hipErrorInvalidValue;
 }

@@ -122,3 +122,22 @@ def test_column_sums_in_the_least_workspace(M, N, K, splits):
     assert_close(out, want, "bf16", "product")
     assert_close(cs, a.astype(np.float64).sum(axis=0), "f32", "column sums")
     assert call(tile=14) == B.ERR_SHAPE and call(splits=sp + 1) == B.ERR_WORKSPACE
+
+
+# rows more than 4 GB / 64 apart: a tile of 128 rows (K-contiguous) or 64 k (K-slow) spans more than 32 bits of offset
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, True), (True, False)])
+def test_contract_leading_dimensions_beyond_32_bits(ctx, ta, tb):
+    M, N, K = 104, 120, 112
+    big = torch.empty((120, (1 << 26) + 8), dtype=torch.bfloat16, device="cuda")     # 16 GB; A, B and C are strips of its columns
+    ga, gb, a, want = _case(67, M, N, K, ta, tb)
+    sa, sb, sc = big[:ga.shape[0], 1000:1000 + ga.shape[1]], big[:gb.shape[0], 1 << 22:(1 << 22) + gb.shape[1]], big[:M, 1 << 25:(1 << 25) + N]
+    sa.copy_(ga)
+    sb.copy_(gb)
+    for splits in (1, 2):
+        sc.zero_()
+        ctx.ecospa_contract(sa, ta, sb, tb, splits=splits, out=sc)
+        assert_close(sc, want, "bf16", f"{splits} parts")
+    if ta and tb:
+        got, cs = ctx.ecospa_contract_colsum(sa, sb, splits=1)
+        assert_close(got, want, "bf16", "product")
+        assert_close(cs, a.astype(np.float64).sum(axis=0), "f32", "column sums")
