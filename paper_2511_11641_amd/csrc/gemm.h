@@ -72,6 +72,15 @@ int ecospa_gemm_token_splits(int M, int N, int K);
 // The bf16 kernel (gemm_ring.h): launch of tile shape `shape` (index into the table in gemm.hip; not every shape is built for every
 // form).  k_chunk: K range of a split, a multiple of 64.
 #define GEMM_RING_NSHAPES 12
+// Epilogue kinds that are built, as bit masks: x W^T carries all of them, dY W the activation derivatives, the forms with a K-slow A
+// only the plain store.  (A split contraction leaves partial sums; the reduction behind it knows every kind.)
+#define GEMM_EPIS_NT 0x7f
+#define GEMM_EPIS_NN ((1 << EPI_STORE) | (1 << EPI_DACT) | (1 << EPI_DSWIGLU))
+#define GEMM_EPIS_TX (1 << EPI_STORE)
+static inline bool gemm_epi_built(int trans_a, int trans_b, int kind) {
+  const int mask = trans_a ? GEMM_EPIS_TX : (trans_b ? GEMM_EPIS_NN : GEMM_EPIS_NT);
+  return kind >= 0 && kind < 31 && ((mask >> kind) & 1);
+}
 // Leading dimensions from 2^23 on (256 rows of them are 4 GB): lane offsets of 64 bits, built for 128 x 128 tiles alone.
 #define GEMM_RING_WIDE_SHAPE 8
 static inline bool ring_wide(const GemmDesc& d) {

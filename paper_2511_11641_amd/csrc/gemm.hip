@@ -271,6 +271,7 @@ int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d) {
       return ECOSPA_ERR_ALIGN;
     if (d.epi.kind == EPI_DSWIGLU && d.epi.kp % 8) return ECOSPA_ERR_ALIGN;
     if (d.splits > 1 && !aligned16(d.partial)) return ECOSPA_ERR_ALIGN;
+    if (!gemm_epi_built(splits > 1 ? 0 : d.trans_a, splits > 1 ? 0 : d.trans_b, d.epi.kind)) return ECOSPA_ERR_DTYPE;
     const bool prof = ctx->prof_on && ctx->prof_n < ctx->prof_cap;
     if (prof) (void)hipEventRecord(ctx->prof_ev[2 * ctx->prof_n], ctx->stream);
     // K range of a split: whole 64-deep slabs, the last split takes what is left
@@ -287,7 +288,7 @@ int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d) {
     }
     ECOSPA_CHECK_LAUNCH(ctx, "gemm_bf16_ring_kernel");
   } else if (d.dtype == ECOSPA_F32) {
-    if (d.epi.kind == EPI_ROPE || d.epi.kind == EPI_SWIGLU) return ECOSPA_ERR_DTYPE;
+    if (d.epi.kind < EPI_STORE || d.epi.kind > EPI_ACT) return ECOSPA_ERR_DTYPE;      // the rotary and gated forms are bf16 only
     if (!d.trans_a && !d.trans_b) launch_f32<false, false>(ctx, d, splits);
     else if (!d.trans_a) launch_f32<false, true>(ctx, d, splits);
     else if (d.trans_b) launch_f32<true, true>(ctx, d, splits);

@@ -2,23 +2,21 @@
 // epilogues), and the combination no layer uses (A K-slow, B K-contiguous), which the contraction entry point offers.
 #include "gemm_ring.h"
 
-#define EPIS_NN ((1 << EPI_STORE) | (1 << EPI_DACT) | (1 << EPI_DSWIGLU))
-#define EPIS_TN (1 << EPI_STORE)
 #define NN_SHAPES(X) X(0, 256, 256, 2) X(4, 256, 128, 3) X(7, 192, 128, 3) X(8, 128, 128, 4) X(9, 64, 128, 4)
 #define TN_SHAPES(X) X(0, 256, 256, 2) X(8, 128, 128, 4)
-#define NN_INST(I, BM, BN, NS) template __global__ void gemm_bf16_ring_kernel<BM, BN, NS, false, true, false, EPIS_NN>(const GemmDesc, int, int);
-#define TN_INST(I, BM, BN, NS) template __global__ void gemm_bf16_ring_kernel<BM, BN, NS, true, false, false, EPIS_TN>(const GemmDesc, int, int);
+#define NN_INST(I, BM, BN, NS) template __global__ void gemm_bf16_ring_kernel<BM, BN, NS, false, true, false, GEMM_EPIS_NN>(const GemmDesc, int, int);
+#define TN_INST(I, BM, BN, NS) template __global__ void gemm_bf16_ring_kernel<BM, BN, NS, true, false, false, GEMM_EPIS_TX>(const GemmDesc, int, int);
 NN_SHAPES(NN_INST)
 TN_SHAPES(TN_INST)
-template __global__ void gemm_bf16_ring_kernel<128, 128, 4, false, true, false, EPIS_NN, true>(const GemmDesc, int, int);
-template __global__ void gemm_bf16_ring_kernel<128, 128, 4, true, false, false, EPIS_TN, true>(const GemmDesc, int, int);
+template __global__ void gemm_bf16_ring_kernel<128, 128, 4, false, true, false, GEMM_EPIS_NN, true>(const GemmDesc, int, int);
+template __global__ void gemm_bf16_ring_kernel<128, 128, 4, true, false, false, GEMM_EPIS_TX, true>(const GemmDesc, int, int);
 
 hipError_t gemm_ring_launch_mixed(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk) {
-#define NN_CASE(I, BM, BN, NS) if (shape == I) return ring_launch_shape<BM, BN, NS, false, true, false, EPIS_NN>(ctx, d, k_chunk);
-#define TN_CASE(I, BM, BN, NS) if (shape == I) return ring_launch_shape<BM, BN, NS, true, false, false, EPIS_TN>(ctx, d, k_chunk);
+#define NN_CASE(I, BM, BN, NS) if (shape == I) return ring_launch_shape<BM, BN, NS, false, true, false, GEMM_EPIS_NN>(ctx, d, k_chunk);
+#define TN_CASE(I, BM, BN, NS) if (shape == I) return ring_launch_shape<BM, BN, NS, true, false, false, GEMM_EPIS_TX>(ctx, d, k_chunk);
   if (ring_wide(d) && shape == GEMM_RING_WIDE_SHAPE) {
-    if (d.trans_b) return ring_launch_shape<128, 128, 4, false, true, false, EPIS_NN, true>(ctx, d, k_chunk);
-    return ring_launch_shape<128, 128, 4, true, false, false, EPIS_TN, true>(ctx, d, k_chunk);
+    if (d.trans_b) return ring_launch_shape<128, 128, 4, false, true, false, GEMM_EPIS_NN, true>(ctx, d, k_chunk);
+    return ring_launch_shape<128, 128, 4, true, false, false, GEMM_EPIS_TX, true>(ctx, d, k_chunk);
   }
   if (d.trans_b) { NN_SHAPES(NN_CASE) }
   else { TN_SHAPES(TN_CASE) }

@@ -238,3 +238,31 @@ def test_glue_validation(lib, ctx):
     assert xe(ctx, 4, 70000, B.BF16, p, 70000, p, None, 0, p, p) == B.ERR_SHAPE
     assert xe(ctx, 4, 100, B.BF16, p, 100, p, None, 0, p, p) == B.ERR_ALIGN                           # leading dimension % 8
     assert xe(ctx, 4, 100, B.F32, p, 104, p, None, 0, p, p) == B.ERR_DTYPE
+
+
+class _Epi(C.Structure):      # GemmEpi and GemmDesc of csrc/gemm.h
+    _fields_ = [("kind", C.c_int), ("act", C.c_int), ("c", C.c_void_p), ("ldc", C.c_longlong), ("bias", C.c_void_p), ("c2", C.c_void_p),
+                ("ldc2", C.c_longlong), ("h", C.c_void_p), ("ldh", C.c_longlong), ("kp", C.c_int), ("rope_cos", C.c_void_p), ("rope_sin", C.c_void_p),
+                ("rope_cols", C.c_int), ("rope_kp", C.c_int), ("rope_L", C.c_int), ("rope_hq", C.c_int), ("rope_qpk", C.c_int)]
+
+
+class _Gemm(C.Structure):
+    _fields_ = [("dtype", C.c_int), ("M", C.c_int), ("N", C.c_int), ("K", C.c_int), ("A", C.c_void_p), ("lda", C.c_longlong), ("trans_a", C.c_int),
+                ("B", C.c_void_p), ("ldb", C.c_longlong), ("trans_b", C.c_int), ("tile", C.c_int), ("splits", C.c_int), ("partial", C.c_void_p),
+                ("defer_reduce", C.c_int), ("colsum", C.c_void_p), ("epi", _Epi)]
+
+
+STORE, BIAS_ACT, DACT, DSWIGLU, ACT, ROPE, SWIGLU = range(7)
+
+
+@pytest.mark.parametrize("dtype,ta,tb,kinds", [
+    (B.BF16, 0, 1, (BIAS_ACT, ACT, ROPE, SWIGLU, 7, -1)), (B.BF16, 1, 1, (BIAS_ACT, DACT, DSWIGLU, ACT, ROPE, SWIGLU, 7)),
+    (B.BF16, 1, 0, (DACT, SWIGLU)), (B.BF16, 0, 0, (7, -1)), (B.F32, 0, 0, (ROPE, SWIGLU, 7, -1))])
+def test_contraction_refuses_epilogues_that_are_not_built(lib, ctx, dtype, ta, tb, kinds):
+    """An epilogue kind that a kernel was not built with would leave its output unwritten."""
+    f = lib._Z11ecospa_gemmP10ecospa_ctxRK8GemmDesc
+    p = 4096      # never followed: refused on the host
+    for kind in kinds:
+        e = _Epi(kind, 0, p, 64, None, p, 64, p, 128, 64, p, p, 64, 16, 8, 4, 1)
+        g = _Gemm(dtype, 64, 64, 64, p, 64, ta, p, 64, tb, 0, 1, None, 0, None, e)
+        assert f(ctx, C.byref(g)) == B.ERR_DTYPE, kind
