@@ -71,7 +71,11 @@ def test_gather_with_a_shared_index_list(ctx):
                                                               (6, 3, 192, 64, 64, False, False, 197), (4, 1, 128, 20, 32, True, True, 300),
                                                               (32, 8, 2048, 32, 32, True, True, 256)])
 def test_gqa_attention_block(ctx, h, hkv, d, k_qk, k_vo, rope, causal, L):
-    Bsz, dh, dtype = 2, 64, "bf16"
+    run_gqa_case(ctx, h, hkv, d, k_qk, k_vo, rope, causal, L, 2)
+
+
+def run_gqa_case(ctx, h, hkv, d, k_qk, k_vo, rope, causal, L, Bsz):
+    dh, dtype = 64, "bf16"
     m, unit = h // hkv, 2 if rope else 1
     bias = not rope
     t = _gqa_layer(120 + h, Bsz, L, d, h, hkv, dh, dtype, bias)
