@@ -217,16 +217,17 @@ int ecospa_gemm_token_splits(int M, int N, int K) {
   return sp;
 }
 
-// Workgroup tile that a tile code of the contraction entry point names, or 0.
+// Workgroup tile that a tile code names, or 0: those of the contraction entry point, and 39 .. 41 for the 64-wide shapes.
 static void ring_forced_tile(int tile, int* bm, int* bn) {
   static const int cfg[11][2] = {{256, 256}, {256, 256}, {256, 128}, {128, 256}, {128, 128}, {256, 256}, {128, 128}, {256, 256}, {256, 256}, {256, 128}, {256, 192}};
-  static const int wg[9][2] = {{256, 256}, {192, 256}, {256, 192}, {128, 256}, {256, 128}, {192, 192}, {128, 192}, {192, 128}, {128, 128}};
+  static const int wg[12][2] = {{256, 256}, {192, 256}, {256, 192}, {128, 256}, {256, 128}, {192, 192},
+                                {128, 192}, {192, 128}, {128, 128}, {64, 128}, {128, 64}, {64, 64}};
   *bm = *bn = 0;
   if (tile >= 1 && tile <= 4) { *bm = *bn = tile & 1 ? 128 : 256; }
   else if (tile >= 10 && tile <= 19) { *bm = cfg[tile - 10][0]; *bn = cfg[tile - 10][1]; }
   else if (tile == 20) { *bm = *bn = 256; }
   else if (tile == 21) { *bm = cfg[10][0]; *bn = cfg[10][1]; }
-  else if (tile >= 30 && tile < 39) { *bm = wg[tile - 30][0]; *bn = wg[tile - 30][1]; }
+  else if (tile >= 30 && tile < 42) { *bm = wg[tile - 30][0]; *bn = wg[tile - 30][1]; }
 }
 
 static int ring_route(const GemmDesc& d, int splits) {

@@ -7,6 +7,7 @@ import re
 import pytest
 
 from paper_2511_11641_amd import binding as B
+from util import GemmDesc, GemmEpi
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -240,18 +241,6 @@ def test_glue_validation(lib, ctx):
     assert xe(ctx, 4, 100, B.F32, p, 104, p, None, 0, p, p) == B.ERR_DTYPE
 
 
-class _Epi(C.Structure):      # GemmEpi and GemmDesc of csrc/gemm.h
-    _fields_ = [("kind", C.c_int), ("act", C.c_int), ("c", C.c_void_p), ("ldc", C.c_longlong), ("bias", C.c_void_p), ("c2", C.c_void_p),
-                ("ldc2", C.c_longlong), ("h", C.c_void_p), ("ldh", C.c_longlong), ("kp", C.c_int), ("rope_cos", C.c_void_p), ("rope_sin", C.c_void_p),
-                ("rope_cols", C.c_int), ("rope_kp", C.c_int), ("rope_L", C.c_int), ("rope_hq", C.c_int), ("rope_qpk", C.c_int)]
-
-
-class _Gemm(C.Structure):
-    _fields_ = [("dtype", C.c_int), ("M", C.c_int), ("N", C.c_int), ("K", C.c_int), ("A", C.c_void_p), ("lda", C.c_longlong), ("trans_a", C.c_int),
-                ("B", C.c_void_p), ("ldb", C.c_longlong), ("trans_b", C.c_int), ("tile", C.c_int), ("splits", C.c_int), ("partial", C.c_void_p),
-                ("defer_reduce", C.c_int), ("colsum", C.c_void_p), ("epi", _Epi)]
-
-
 STORE, BIAS_ACT, DACT, DSWIGLU, ACT, ROPE, SWIGLU = range(7)
 
 
@@ -263,6 +252,6 @@ def test_contraction_refuses_epilogues_that_are_not_built(lib, ctx, dtype, ta, t
     f = lib._Z11ecospa_gemmP10ecospa_ctxRK8GemmDesc
     p = 4096      # never followed: refused on the host
     for kind in kinds:
-        e = _Epi(kind, 0, p, 64, None, p, 64, p, 128, 64, p, p, 64, 16, 8, 4, 1)
-        g = _Gemm(dtype, 64, 64, 64, p, 64, ta, p, 64, tb, 0, 1, None, 0, None, e)
+        e = GemmEpi(kind, 0, p, 64, None, p, 64, p, 128, 64, p, p, 64, 16, 8, 4, 1)
+        g = GemmDesc(dtype, 64, 64, 64, p, 64, ta, p, 64, tb, 0, 1, None, 0, None, e)
         assert f(ctx, C.byref(g)) == B.ERR_DTYPE, kind

@@ -1,13 +1,17 @@
 """GPU parity of the contraction kernels where they can go wrong: K that is no multiple of the 64-deep slab (the first slab takes
 the remainder, zeroed in LDS beyond it), fewer slabs than the LDS ring holds, K splits with an uneven or empty last range, and
 every tile shape with remainders of one 8-column group and one row - against a plain fp64 product of the same bf16 operands."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
 
 from paper_2511_11641_amd import binding as B
 from paper_2511_11641_amd import synth
-from util import assert_close, dev
+from test_gpu_attn import run_attn_case
+from test_gpu_ffn import run_ffn_case
+from util import GemmDesc, assert_close, dev
 
 pytestmark = pytest.mark.gpu
 
@@ -24,7 +28,7 @@ def _case(seed, M, N, K, ta, tb):
     return dev(a, "bf16"), dev(b, "bf16"), a, want
 
 
-# tile codes: 30 .. 38 name the nine shapes of at least 128 x 128; 0 with few rows or columns takes the 64-wide ones
+# tile codes: 30 .. 38 name the nine shapes of at least 128 x 128; 0 is the library's choice
 @pytest.mark.parametrize("tile", [0, 30, 31, 32, 33, 34, 35, 36, 37, 38])
 @pytest.mark.parametrize("ta,tb,M,N,K", [
     (False, False, 257, 264, 8), (False, False, 129, 136, 72), (False, False, 61, 200, 456), (False, False, 385, 392, 200),
@@ -47,11 +51,50 @@ def test_weight_gradient_with_column_sums_any_token_count(ctx, M, N, K, splits):
     assert torch.equal(got, again) and torch.equal(cs, cs2)
 
 
-@pytest.mark.parametrize("M,N,K", [(8, 64, 2048), (61, 2048, 1024), (65, 72, 3000), (129, 5504, 520)])
-def test_few_tokens_own_plan(ctx, M, N, K):
+# the shapes with a 64-wide side, which have no code at the entry point: 39 = 64x128, 40 = 128x64, 41 = 64x64 inside the library
+@pytest.mark.parametrize("ta,tb,tile", [(0, 0, 39), (0, 0, 40), (0, 0, 41), (0, 1, 39), (1, 1, 39)])
+@pytest.mark.parametrize("M,N,K,splits", [(64, 128, 8, 1), (72, 136, 72, 1), (8, 8, 200, 1), (200, 264, 456, 1), (136, 72, 1096, 3), (64, 64, 320, 1)])
+def test_64_wide_shapes(ctx, ta, tb, tile, M, N, K, splits):
+    if ta:
+        K += 3 if K > 64 else -3          # K-slow operands take any K
+    ga, gb, a, want = _case(69, M, N, K, ta, tb)
+    out = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    parts = torch.empty((splits, M, N), dtype=torch.float32, device="cuda")
+    g = GemmDesc(B.BF16, M, N, K, ga.data_ptr(), ga.stride(0), ta, gb.data_ptr(), gb.stride(0), tb, tile, splits, parts.data_ptr())
+    g.epi.c, g.epi.ldc = out.data_ptr(), N
+    rows = ctx.lib._Z23ecospa_gemm_colsum_rowsRK8GemmDesc(C.byref(g))
+    assert rows == splits * -(-N // (64 if tile >= 40 else 128))
+    cs = torch.full((rows, M), float("nan"), dtype=torch.float32, device="cuda")
+    if ta and tb:
+        g.colsum = cs.data_ptr()
+    assert ctx.lib._Z11ecospa_gemmP10ecospa_ctxRK8GemmDesc(ctx.h, C.byref(g)) == B.OK
+    assert_close(out, want, "bf16", f"{M}x{N}x{K}")
+    if ta and tb:
+        assert_close(cs.sum(dim=0), a.astype(np.float64).sum(axis=0), "f32", "column sums")
+
+
+@pytest.mark.parametrize("M,N,K,split", [(8, 64, 2048, True), (61, 2048, 1024, False), (65, 72, 3000, True), (129, 5504, 520, False)])
+def test_few_rows(ctx, M, N, K, split):
+    assert (ctx.lib.ecospa_contract_workspace_bytes(B.BF16, M, N, K, 0) > 0) == split
     ga, gb, _, want = _case(63, M, N, K, False, False)
     assert_close(ctx.ecospa_contract(ga, False, gb, False, splits=1), want, "bf16", "unsplit")
-    assert_close(ctx.ecospa_contract(ga, False, gb, False), want, "bf16", "library's split")
+    assert_close(ctx.ecospa_contract(ga, False, gb, False), want, "bf16", "library's choice")
+
+
+# a layer of 61 tokens: the contractions over the tokens' rows are split along K, so every epilogue runs behind the sum of the parts
+def test_few_tokens_rotary_projection_in_parts(ctx):
+    assert min(ctx.lib._Z24ecospa_gemm_token_splitsiii(61, n, k) for n, k in ((3072, 2048), (1024, 2048), (2048, 3072))) > 1
+    run_attn_case(ctx, 75, 1, 61, 2048, 32, 64, 32, 32, rope=True, causal=True, bias=False, structure="pretrained", transposed=True)
+    run_attn_case(ctx, 76, 1, 61, 2048, 32, 64, 32, 32, rope=False, causal=True, structure="pretrained")
+
+
+@pytest.mark.parametrize("act,n,k", [("swiglu", 2800, 1400), ("gelu", 5461, 2730)])
+def test_few_tokens_activations_in_parts(ctx, act, n, k):
+    kp = (k + 63) // 64 * 64
+    nh = 2 * kp if act == "swiglu" else kp
+    assert min(ctx.lib._Z24ecospa_gemm_token_splitsiii(61, *nk) for nk in ((nh, 2048), (kp, 2048), (2048, nh))) > 1
+    run_ffn_case(ctx, 77, 1, 61, 2048, n, k, act, "bf16", structure="pretrained")
+    run_ffn_case(ctx, 78, 1, 61, 2048, n, k, act, "bf16", structure="pretrained", transposed=True)
 
 
 # 32 x 32 tiles with K shared out over a workgroup, and 64 x 64 tiles once 512 of them exist; K below, at and beyond the groups of 32

@@ -1,4 +1,6 @@
-"""Helpers shared by the GPU parity tests (uploads, comparisons); no method arithmetic."""
+"""Helpers shared by the parity tests (uploads, comparisons, descriptors); no method arithmetic."""
+import ctypes as C
+
 import numpy as np
 import torch
 
@@ -76,3 +78,15 @@ def interleave_rows(a, b):
     out = np.empty((2 * a.shape[0],) + a.shape[1:], dtype=a.dtype)
     out[0::2], out[1::2] = a, b
     return out
+
+
+class GemmEpi(C.Structure):      # the contraction descriptors of csrc/gemm.h, for tests of what no entry point asks for
+    _fields_ = [("kind", C.c_int), ("act", C.c_int), ("c", C.c_void_p), ("ldc", C.c_longlong), ("bias", C.c_void_p), ("c2", C.c_void_p),
+                ("ldc2", C.c_longlong), ("h", C.c_void_p), ("ldh", C.c_longlong), ("kp", C.c_int), ("rope_cos", C.c_void_p), ("rope_sin", C.c_void_p),
+                ("rope_cols", C.c_int), ("rope_kp", C.c_int), ("rope_L", C.c_int), ("rope_hq", C.c_int), ("rope_qpk", C.c_int)]
+
+
+class GemmDesc(C.Structure):
+    _fields_ = [("dtype", C.c_int), ("M", C.c_int), ("N", C.c_int), ("K", C.c_int), ("A", C.c_void_p), ("lda", C.c_longlong), ("trans_a", C.c_int),
+                ("B", C.c_void_p), ("ldb", C.c_longlong), ("trans_b", C.c_int), ("tile", C.c_int), ("splits", C.c_int), ("partial", C.c_void_p),
+                ("defer_reduce", C.c_int), ("colsum", C.c_void_p), ("epi", GemmEpi)]
