@@ -367,8 +367,8 @@ __device__ __forceinline__ void aux_reduce_block(const GemmDesc& d, int blk) {
 // workgroups to hide the latency; the four strips of a line are mapped to workgroup ids that differ
 // by 8, 16 and 24, i.e. to the same XCD, so that the line is fetched into one L2 only.
 #define AUX_LANES 2
-template <typename T, typename TO>
-__device__ __forceinline__ void aux_colsum_block(const AuxColsum& c, int blk, float* lds) {
+template <typename T>
+__device__ __forceinline__ void aux_colsum_block(const AuxColsum& c, int blk, float* lds, bool out_bf16) {
   static_assert(AUX_LANES == 2, "four strips of AUX_LANES x 16 bytes make one 128-byte line");
   constexpr int V = 16 / sizeof(T);          // columns per lane
   constexpr int W = AUX_LANES * V;           // strip width
@@ -427,7 +427,10 @@ __device__ __forceinline__ void aux_colsum_block(const AuxColsum& c, int blk, fl
   part = wave_sum(part);     // lanes of a wavefront = the 64 groups of one column; fixed order
   if (colw < W && grp == 0) {
     const int col = blk * W + colw;
-    if (col < c.N) store_f32<TO>(static_cast<TO*>(c.out) + col, part);
+    if (col < c.N) {
+      if (out_bf16) store_f32<bf16_t>(static_cast<bf16_t*>(c.out) + col, part);
+      else store_f32<float>(static_cast<float*>(c.out) + col, part);
+    }
   }
 }
 
@@ -439,11 +442,9 @@ __global__ __launch_bounds__(AUX_THREADS) void bwd_aux_kernel(const AuxBatchDev 
   const int local = blk - a.blk_begin[j];
   if (j < a.b.n_colsum) {
     const AuxColsum& c = a.b.colsum[j];
-    const int od = c.out_dtype ? c.out_dtype : c.dtype;
-    if (c.dtype == ECOSPA_BF16 && od == AUX_OUT_F32) aux_colsum_block<bf16_t, float>(c, local, lds);
-    else if (c.dtype == ECOSPA_BF16) aux_colsum_block<bf16_t, bf16_t>(c, local, lds);
-    else if (od == ECOSPA_BF16) aux_colsum_block<float, bf16_t>(c, local, lds);
-    else aux_colsum_block<float, float>(c, local, lds);
+    const bool out_bf16 = (c.out_dtype ? c.out_dtype : c.dtype) == ECOSPA_BF16;
+    if (c.dtype == ECOSPA_BF16) aux_colsum_block<bf16_t>(c, local, lds, out_bf16);
+    else aux_colsum_block<float>(c, local, lds, out_bf16);
   } else {
     const GemmDesc& d = a.b.reduce[j - a.b.n_colsum];
     if (d.dtype == ECOSPA_BF16) aux_reduce_block<bf16_t>(d, local);
