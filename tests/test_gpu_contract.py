@@ -65,8 +65,8 @@ def test_contract_model_shapes_auto_tile(ctx):
         assert_close(got, want, "bf16", f"{M}x{N}x{K}")
 
 
-@pytest.mark.parametrize("M,N,K,ta,tb", [(5504, 2048, 8192, True, True),      # gate|up weight gradient of the LLaMA-1B-shaped FFN: register-prefetch kernel
-                                          (2048, 2752, 8192, True, True),      # W_down gradient: the same kernel, K split in two
+@pytest.mark.parametrize("M,N,K,ta,tb", [(5504, 2048, 8192, True, True),      # gate|up weight gradient of the LLaMA-1B-shaped FFN
+                                          (2048, 2752, 8192, True, True),      # W_down gradient
                                           (8192, 1280, 1024, False, False),    # FFN kept at 3/10: 256x192 tiles
                                           (8192, 2048, 2752, False, False)])   # contraction over 2752 kept units (43 whole slabs)
 def test_contract_stack_shapes_sampled(ctx, M, N, K, ta, tb):
@@ -115,16 +115,16 @@ def test_contract_alignment_errors(ctx):
 @pytest.mark.parametrize("cfg", range(11))
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, True)])
 @pytest.mark.parametrize("M,N,K", [(520, 264, 192), (256, 512, 64), (304, 136, 512)])
-def test_contract_bf16_pipelined_tiles(ctx, M, N, K, ta, tb, cfg):
-    """Every configuration of the software-pipelined kernel (tile = 10 + cfg): ragged M and N, one slab
-    (shorter than the LDS ring), a few slabs (ring wrap-around) and many."""
+def test_contract_bf16_tile_codes_10_to_21(ctx, M, N, K, ta, tb, cfg):
+    """Tile codes 10 .. 19 and 21 (five tile shapes, several codes name one): ragged M and N, one slab (shorter than the LDS
+    ring), a few slabs (ring wrap-around) and many."""
     a, b, bias, want = _operands(45, M, N, K, ta, tb, "bf16")
     got = ctx.ecospa_contract(dev(a, "bf16"), ta, dev(b, "bf16"), tb, dev(bias, "bf16"), tile=21 if cfg == 10 else 10 + cfg, splits=1)
-    assert_close(got, want, "bf16", f"pipelined cfg {cfg}")
+    assert_close(got, want, "bf16", f"code {cfg}")
 
 
 @pytest.mark.parametrize("cfg", [0, 1, 2, 4])
-def test_contract_bf16_pipelined_split_k(ctx, cfg):
+def test_contract_bf16_tile_codes_10_to_14_split_k(ctx, cfg):
     a, b, bias, want = _operands(46, 264, 520, 1024, True, True, "bf16")
     got = ctx.ecospa_contract(dev(a, "bf16"), True, dev(b, "bf16"), True, dev(bias, "bf16"), tile=10 + cfg, splits=4)
     assert_close(got, want, "bf16", "split k")
@@ -134,40 +134,40 @@ def test_contract_bf16_pipelined_split_k(ctx, cfg):
 
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, True)])
 @pytest.mark.parametrize("M,N,K", [(520, 264, 192), (256, 512, 64), (304, 136, 512), (1000, 520, 128)])
-def test_contract_bf16_register_staged_prefetch(ctx, M, N, K, ta, tb):
-    """The two-slab register-prefetch kernel (tile = 20): ragged M and N, one slab, two, three (odd count:
-    the unrolled slab pair plus a tail) and many; x W^T, dY W and dY^T X operand forms."""
+def test_contract_bf16_tile_code_20(ctx, M, N, K, ta, tb):
+    """256x256 tiles (code 20): ragged M and N, one slab, two (all of the ring), three and many; x W^T, dY W and dY^T X operand
+    forms."""
     a, b, bias, want = _operands(47, M, N, K, ta, tb, "bf16")
     got = ctx.ecospa_contract(dev(a, "bf16"), ta, dev(b, "bf16"), tb, dev(bias, "bf16"), tile=20, splits=1)
-    assert_close(got, want, "bf16", "register-staged prefetch")
+    assert_close(got, want, "bf16", "256x256")
     if ta:      # split along K: fp32 partial sums added in a fixed order
         got = ctx.ecospa_contract(dev(a, "bf16"), ta, dev(b, "bf16"), tb, dev(bias, "bf16"), tile=20, splits=2 if K >= 128 else 1)
-        assert_close(got, want, "bf16", "register-staged prefetch, split")
+        assert_close(got, want, "bf16", "256x256, split")
 
 
-def test_contract_bf16_register_staged_prefetch_split_k(ctx):
+def test_contract_bf16_tile_code_20_split_k(ctx):
     a, b, bias, want = _operands(48, 264, 520, 1024, False, True, "bf16")
     got = ctx.ecospa_contract(dev(a, "bf16"), False, dev(b, "bf16"), True, dev(bias, "bf16"), tile=20, splits=4)
     assert_close(got, want, "bf16", "split k")
 
 
-RS_SHAPES = [(256, 256), (192, 256), (256, 192), (128, 256), (256, 128), (192, 192), (128, 192), (192, 128), (128, 128)]
+TILE_SHAPES = [(256, 256), (192, 256), (256, 192), (128, 256), (256, 128), (192, 192), (128, 192), (192, 128), (128, 128)]
 
 
-@pytest.mark.parametrize("shape", range(9), ids=[f"{a}x{b}" for a, b in RS_SHAPES])
-@pytest.mark.parametrize("M,N,K,splits", [(520, 264, 192, 1),      # ragged M and N, three slabs (slab pair + tail)
+@pytest.mark.parametrize("shape", range(9), ids=[f"{a}x{b}" for a, b in TILE_SHAPES])
+@pytest.mark.parametrize("M,N,K,splits", [(520, 264, 192, 1),      # ragged M and N, three slabs
                                            (256, 512, 64, 1),       # one slab
                                            (304, 136, 128, 1),      # two slabs
                                            (1000, 776, 640, 1),     # several tiles on both axes, ten slabs
                                            (392, 648, 320, 3),      # five slabs split 2 + 2 + 1
                                            (200, 1048, 1024, 4)])
 def test_contract_bf16_weight_gradient_tile_shapes(ctx, M, N, K, splits, shape):
-    """dY^T X (both operands K-slow) on every tile shape of the register-prefetch kernel (tile = 30 + shape), with the
+    """dY^T X (both operands K-slow) on the tile shapes of at least 128 x 128 (tile = 30 + shape), with the
     column sums of the A operand that the backward passes take from the same launch (the bias gradient)."""
     a, b, _, _ = _operands(51, M, N, K, True, True, "bf16")
     want = a.astype(np.float64).T @ b.astype(np.float64)
     got, cs = ctx.ecospa_contract_colsum(dev(a, "bf16"), dev(b, "bf16"), tile=30 + shape, splits=splits)
-    assert_close(got, want, "bf16", f"{RS_SHAPES[shape]} x{splits}")
+    assert_close(got, want, "bf16", f"{TILE_SHAPES[shape]} x{splits}")
     assert_close(cs, a.astype(np.float64).sum(axis=0), "f32", "column sums of A")
     again, cs2 = ctx.ecospa_contract_colsum(dev(a, "bf16"), dev(b, "bf16"), tile=30 + shape, splits=splits)
     assert torch.equal(got, again) and torch.equal(cs, cs2)

@@ -80,8 +80,7 @@ def test_ffn_small_ragged(ctx, act, dtype):
 @pytest.mark.parametrize("act,bias,transposed", [("gelu", True, False), ("swiglu", False, True)])
 def test_ffn_long_token_axis_wide_weight_gradients(ctx, act, bias, transposed):
     """4096 tokens, 3072 kept units of 3200, d = 1024: weight gradients with enough 256x256 tiles that their
-    contraction over the tokens runs on the register-prefetch kernel (split two or four ways), where the bias
-    gradients are the column sums that kernel adds up on the way."""
+    contraction over the tokens fills the chip; the bias gradients are the column sums that it adds up on the way."""
     errs = run_ffn_case(ctx, 29, 4, 1024, 1024, 3200, 3072, act, "bf16", bias=bias, wscale=4.0, transposed=transposed)
     assert max(errs.values()) <= 2e-2
 
@@ -140,26 +139,32 @@ def test_ffn_backward_with_optional_outputs(ctx, act):
 
 
 def test_ffn_weight_gradients_with_a_ragged_tile_row(ctx):
-    """1100 kept units (padded to 1152 = 4.5 tiles of 256) at d = 2304 over 4096 tokens: the weight gradients run split
-    four ways on the register-prefetch kernel with a half-empty last tile row, whose bias-gradient column sums must
-    not count the columns beyond the edge twice."""
+    """1100 kept units (padded to 1152 = 4.5 tiles of 256) at d = 2304 over 4096 tokens: the last tile row of the
+    weight gradients is half empty, and its bias-gradient column sums must not count the columns beyond the edge twice."""
     errs = run_ffn_case(ctx, 32, 4, 1024, 2304, 1500, 1100, "gelu", "bf16", wscale=4.0)
     assert max(errs.values()) <= 2e-2
 
 
+@pytest.mark.parametrize("act,bias", [("gelu", True), ("swiglu", True), ("swiglu", False)])
+def test_ffn_weight_gradients_in_parts(ctx, act, bias):
+    """1203 tokens, narrow matrices: both weight gradients are split along the tokens, their parts and the partial column sums of the
+    bias gradients added up by the last launch."""
+    nh = 800 if act == "swiglu" else 400
+    assert min(ctx.lib._Z18ecospa_gemm_splitsiiii(B.BF16, m, n, 1203) for m, n in ((264, 400), (nh, 264))) > 1
+    run_ffn_case(ctx, 35, 3, 401, 264, 700, 390, act, "bf16", bias=bias, wscale=4.0)
+
+
 def test_ffn_wide_units_long_model_dimension(ctx):
     """4096 tokens, d = 2048, all 4096 units kept: x W_1^T and dY W_2 have a full round of 256x256 tiles with the bias +
-    GELU epilogue (both outputs) and the GELU-derivative epilogue, and the weight gradients run split two ways on the
-    register-prefetch kernel."""
+    GELU epilogue (both outputs) and the GELU-derivative epilogue."""
     errs = run_ffn_case(ctx, 31, 4, 1024, 2048, 4096, 4096, "gelu", "bf16", wscale=3.0, transposed=True)
     assert max(errs.values()) <= 2e-2
 
 
 @pytest.mark.parametrize("act,transposed", [("gelu", False), ("gelu", True), ("swiglu", True)])
 def test_ffn_few_tokens_split_contractions(ctx, act, transposed):
-    """256 tokens at d = 2048, 2048 kept units (inference at batch 1 and the like): the forward and input-gradient
-    contractions have too few output tiles for the chip and run split along K (two splits of 1024), partial sums added
-    in a fixed order before the epilogue (bias, activation and its stored input, activation derivative)."""
+    """256 tokens at d = 2048, 2048 kept units (inference at batch 1 and the like): the contractions have too few output tiles
+    for the chip; the input gradient of the gated form (K = 4096) runs split along K, partial sums added in a fixed order."""
     run_ffn_case(ctx, 30, 1, 256, 2048, 4096, 2048, act, "bf16", wscale=4.0, transposed=transposed)
 
 
