@@ -46,13 +46,13 @@ struct GemmDesc {
   const void* B;
   long long ldb;
   int trans_b;
-  int tile;          // 0 = choose, otherwise a tile code of ecospa_contract
+  int tile;          // 0 = choose, otherwise a tile code of ecospa_contract, or 39 .. 41 (64x128, 128x64, 64x64)
   int splits;        // > 1: split K, fp32 partials in `partial`, reduced in a fixed order
   float* partial;    // [splits][M][N] when splits > 1
   int defer_reduce;  // splits > 1: only write the partials; the caller runs ecospa_gemm_reduce later
   float* colsum;     // optional, bf16 contractions with a K-slow A operand (dY^T X): [ecospa_gemm_colsum_rows(d)][M] partial
                      // column sums of A, sum_k A(m, k) over disjoint parts of K - the bias gradient that belongs to the
-                     // weight gradient, taken from the operand on its way through the registers; the rows add up to the sums
+                     // weight gradient, added up from the operand's fragments; the rows add up to the sums
   GemmEpi epi;
 };
 

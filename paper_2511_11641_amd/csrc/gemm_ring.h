@@ -16,17 +16,19 @@
 //     LDS read; the reads are therefore inline assembly, with the waits written out.  The products are inline assembly where the
 //     accumulators fill the AGPRs, or copies between the two register files appear in the loop.
 // Against the kernels it replaced (direct loads with compiler-placed waits for x W^T, a register-staged one for dY^T X):
-// 4096x2048x2752 x W^T 59 -> 45 us (256x128), dY^T X 2048x2752x4096 59.5 -> 44.6 us, 5504x2048x4096 99 -> 76 us,
-// 2048x1024x4096 (K split in two) 33 -> 22 us.
+// 4096x2048x2752 x W^T 59 -> 45 us (256x128), dY^T X 2048x2752x4096 59.5 -> 44.6 us, 5504x2048x4096 99 -> 76 us.
+// dY^T X 2048x1024x4096 takes 33 us as it did, on 64x128 tiles unsplit (128x128, K split in two, operands warm: 22 us).
 //
 // K need not be a multiple of anything in the K-slow forms (8 in the K-contiguous ones): the FIRST slab takes the remainder,
 // with clamped addresses, and its k beyond the remainder are zeroed in LDS before the loop starts.
 //
 // LDS layout: 16-byte chunks, XOR-swizzled on the GLOBAL side of the direct load (the lane that owns a physical chunk fetches the
-// logical chunk that maps there), so that the lanes of one LDS access fall on different banks:
-//   K-contiguous tile [rows][64]:  chunk ^ (row % 8)
+// logical chunk that maps there):
+//   K-contiguous tile [rows][64]:  chunk ^ (row % 8): the lanes of an access fall on different banks (no conflicts counted)
 //   K-slow tile [64][rows]:        chunk ^ 4 (k % 4), or chunk ^ 4 (k / 2 % 2) for rows of 192 (which start half-way round the banks
-//                                  for odd k, and whose 24 chunks only allow a swizzle inside groups of eight)
+//                                  for odd k, and whose 24 chunks only allow a swizzle inside groups of eight), chunk ^ 4 (k % 2)
+//                                  for rows of 64.  This parts the four k of one group of 16 lanes; groups read 8 k apart from each
+//                                  other and still meet on the same banks (conflicts counted in 49-62 % of the LDS cycles).
 #pragma once
 #include "gemm_epi.h"
 

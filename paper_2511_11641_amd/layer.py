@@ -68,8 +68,8 @@ class FfnBlock:
             raise ValueError("ragged compaction needs k_max: the kept count lives on the device")
         k = idx.shape[1] if k_group is None else int(k_max)
         self.idx, self.k, self.k_group = idx, k, k_group
-        # padded width: a multiple of the contraction kernels' slab depth (64) once that costs little, so that the
-        # contractions over the kept units (the second FFN matrix, the input gradient) can take the pipelined kernel
+        # padded width: a multiple of the contraction kernel's slab depth (64) once that costs little (any multiple of 8 would
+        # do for the kernel; a remainder slab is zeroed in LDS in front of the loop)
         self.kp = kp = B.round_up(k, 64 if k >= 512 else 16)
         nh = 2 * kp if self.gated else kp
         dt, dev = self.w1.dtype, self.w1.device
