@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch of the MFMA contraction kernels, averaged over the contraction launches of one sparse
 # step of the headline workload, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (see profiles/):
 # (sha256 prefix of csrc/gemm*, bytes).  Reported only while the kernel sources still have that hash; otherwise null.
-GEMM_TRAFFIC = ("e60043d358feaa32", 143.8e6)
+GEMM_TRAFFIC = ("e6cb08a98703f552", 143.8e6)
 HEADLINE = "c3_llama1b_layer"
 SECOND = "c2_gpt2m_layer"
 
@@ -284,8 +284,8 @@ def prune_stack(ctx, cfg, n_layers, keep_num, keep_den, steps, rows=True, extras
 
 def fp32_pair_workload(ctx, steps):
     """The fp32 single FFN pair (512 tokens, d = 256, 1024 inner dimensions, half kept): score, select, gather,
-    forward and backward.  0.8 GFLOP on the vector ALU (fp32 has no place on the bf16 matrix path): ten short launches
-    whose contraction loops are bound by load latency, not arithmetic; time only."""
+    forward and backward.  0.8 GFLOP in ten short launches whose contraction loops (fp32 matrix instructions) are bound by
+    load latency, not arithmetic; time only."""
     import torch
     from paper_2511_11641_amd import binding as B, synth
     from paper_2511_11641_amd.layer import FfnBlock
