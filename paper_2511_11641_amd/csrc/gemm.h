@@ -113,29 +113,34 @@ int ecospa_aux_launch(ecospa_ctx* ctx, const AuxBatch& b);
 
 // Activation helpers shared by the epilogues and the elementwise kernels.
 #ifdef __HIPCC__
-// Standard normal CDF by the rational approximation 7.1.26 of Abramowitz & Stegun for erfc
-// (absolute error about 3e-7 in Phi when evaluated in fp32: far below bf16 resolution, and a relative Frobenius error near 1e-7 on GELU outputs), written on the
-// tail Phi(-|x|) so that negative arguments lose nothing to cancellation: one reciprocal, one
-// exponential and a degree-5 Horner chain instead of the library erf.  `e` returns exp(-x^2 / 2),
-// which the derivative needs as well.
-__device__ __forceinline__ float act_norm_cdf(float x, float& e) {
-  const float z = fabsf(x) * 0.7071067811865476f;
-  const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3275911f, z, 1.f));
-  float p = __builtin_fmaf(1.061405429f, t, -1.453152027f);
-  p = __builtin_fmaf(p, t, 1.421413741f);
-  p = __builtin_fmaf(p, t, -0.284496736f);
-  p = __builtin_fmaf(p, t, 0.254829592f);
-  e = __expf(-z * z);
-  const float tail = 0.5f * p * t * e;   // Phi(-|x|)
-  return x < 0.f ? tail : 1.f - tail;
+// Tail of the standard normal distribution, Phi(-|x|), by the rational approximation 7.1.26 of Abramowitz & Stegun for erfc (absolute
+// error about 3e-7 when evaluated in fp32: far below bf16 resolution, and a relative Frobenius error near 1e-7 on GELU outputs): one
+// reciprocal, one exponential and a degree-5 Horner chain instead of the library erf, the factors 1/sqrt(2) and 1/2 folded into the
+// constants.  `e` returns exp(-x^2 / 2), which the derivative needs as well.  What follows from the tail without a comparison:
+// x Phi(x) = max(x, 0) - |x| Phi(-|x|),  Phi(x) = 1/2 + sign(x) (1/2 - Phi(-|x|)).
+// Vector instructions bound the activation epilogues: 15 and two transcendentals per element where the form with Phi itself took 20 (forward
+// and backward of a 384-wide GELU layer on 12017 tokens 256.1 -> 253.4 us, 1024-wide layer step on 8192 tokens 569.5 -> 565.5 us).
+__device__ __forceinline__ float act_tail_t(float x) { return __builtin_amdgcn_rcpf(__builtin_fmaf(fabsf(x), 0.23164188f, 1.f)); }
+__device__ __forceinline__ float act_gauss(float x) { return __builtin_amdgcn_exp2f(x * (x * -0.72134752f)); }
+__device__ __forceinline__ float act_norm_tail(float x, float& e) {
+  const float t = act_tail_t(x);
+  float p = __builtin_fmaf(0.5307027145f, t, -0.7265760135f);
+  p = __builtin_fmaf(p, t, 0.7107068705f);
+  p = __builtin_fmaf(p, t, -0.142248368f);
+  p = __builtin_fmaf(p, t, 0.127414796f);
+  e = act_gauss(x);
+  return p * t * e;
 }
+// (the bound keeps infinity times a tail of zero out)
+__device__ __forceinline__ float act_gelu_of_tail(float x, float tail) { return __builtin_fmaf(-fminf(fabsf(x), 1e30f), tail, fmaxf(x, 0.f)); }
 __device__ __forceinline__ float act_gelu(float x, int act) {
   if (act == ECOSPA_ACT_GELU_TANH) {
     const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
     return 0.5f * x * (1.f + tanhf(u));
   }
   float e;
-  return x * act_norm_cdf(x, e);
+  const float tail = act_norm_tail(x, e);
+  return act_gelu_of_tail(x, tail);
 }
 __device__ __forceinline__ float act_gelu_grad(float x, int act) {
   if (act == ECOSPA_ACT_GELU_TANH) {
@@ -144,8 +149,11 @@ __device__ __forceinline__ float act_gelu_grad(float x, int act) {
     return 0.5f * (1.f + th) + 0.5f * x * (1.f - th * th) * 0.7978845608028654f * (1.f + 0.134145f * x * x);
   }
   float e;
-  const float cdf = act_norm_cdf(x, e);
-  return cdf + x * (0.3989422804014327f * e);
+  const float tail = act_norm_tail(x, e);
+  return __builtin_fmaf(x * 0.3989422804014327f, e, 0.5f + __builtin_copysignf(0.5f - tail, x));
 }
 __device__ __forceinline__ float act_sigmoid(float x) { return 1.f / (1.f + __expf(-x)); }
+// The same with the hardware's reciprocal (1 ulp) in place of the IEEE division (nine instructions more): for results that are
+// rounded to bf16.
+__device__ __forceinline__ float act_sigmoid_rcp(float x) { return __builtin_amdgcn_rcpf(1.f + __expf(-x)); }
 #endif

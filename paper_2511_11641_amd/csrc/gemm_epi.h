@@ -141,7 +141,7 @@ __device__ __forceinline__ void epi_math_k(int act, float (&v)[8], const EpiSide
     typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
     floatx4 a;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = v[2 * i] * act_sigmoid(v[2 * i]) * v[2 * i + 1];
+    for (int i = 0; i < 4; ++i) a[i] = v[2 * i] * act_sigmoid_rcp(v[2 * i]) * v[2 * i + 1];
     const uint2 p = __builtin_bit_cast(uint2, __builtin_convertvector(a, bf16x4_t));
     out.a2.x = p.x; out.a2.y = p.y;
   } else {  // EPI_DSWIGLU: units n .. n+7, their (gate, up) pairs in columns 2n .. 2n+15 of h and of c
@@ -152,7 +152,7 @@ __device__ __forceinline__ void epi_math_k(int act, float (&v)[8], const EpiSide
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const float g = p[i >> 2][2 * (i & 3)], u = p[i >> 2][2 * (i & 3) + 1];
-      const float sg = act_sigmoid(g);
+      const float sg = act_sigmoid_rcp(g);
       o[i >> 2][2 * (i & 3)] = v[i] * u * sg * (1.f + g * (1.f - sg));
       o[i >> 2][2 * (i & 3) + 1] = v[i] * g * sg;
     }
