@@ -87,6 +87,18 @@ static inline bool ring_wide(const GemmDesc& d) {
   const long long lim = 1ll << 23;
   return d.lda >= lim || d.ldb >= lim || d.epi.ldc >= lim || d.epi.ldc2 >= lim || d.epi.ldh >= lim;
 }
+// The kernel of resident workgroups (gemm_flow.h): x W^T with every epilogue but the tanh GELU, dY^T X without column sums; more tiles
+// than compute units, whole slabs of K and enough of them to carry a tile's epilogue.
+#define GEMM_FLOW_TILE 192
+#define GEMM_FLOW_MIN_SLABS 16
+static inline bool gemm_flow_takes(const GemmDesc& d) {
+  const long long tiles = static_cast<long long>((d.M + GEMM_FLOW_TILE - 1) / GEMM_FLOW_TILE) * ((d.N + GEMM_FLOW_TILE - 1) / GEMM_FLOW_TILE);
+  const bool act = d.epi.kind == EPI_BIAS_ACT || d.epi.kind == EPI_ACT || d.epi.kind == EPI_DACT;
+  return d.splits <= 1 && !d.colsum && (d.trans_a != 0) == (d.trans_b != 0) && !(d.trans_a && d.epi.bias) && tiles > 256 && tiles < (1 << 24) &&
+         d.K % 64 == 0 && d.K / 64 >= GEMM_FLOW_MIN_SLABS && !(act && d.epi.act != ECOSPA_ACT_GELU_ERF) && !ring_wide(d);
+}
+hipError_t gemm_flow_launch_nt(ecospa_ctx* ctx, const GemmDesc& d);
+hipError_t gemm_flow_launch_tt(ecospa_ctx* ctx, const GemmDesc& d);
 hipError_t gemm_ring_launch_nt(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk);
 hipError_t gemm_ring_launch_tt(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk);
 hipError_t gemm_ring_launch_mixed(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk);

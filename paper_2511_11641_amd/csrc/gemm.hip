@@ -1,7 +1,7 @@
 // Dense contractions of the reduced forward/backward pass: choice of kernel, tile shape and K split, the fp32 kernel, and the
 // reductions of split contractions.
 //
-// bf16: the kernel of gemm_ring.h (MFMA, direct global -> LDS loads).
+// bf16: the kernels of gemm_ring.h and, for several rounds of tiles, gemm_flow.h (MFMA, direct global -> LDS loads).
 // fp32: MFMA on fragments loaded straight from memory (the fp32 configuration is small and latency bound).
 // Split-K writes fp32 partials that a second kernel adds in a fixed order (deterministic dW).
 #include "gemm_epi.h"
@@ -160,30 +160,42 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_vec8_kernel(const Gemm
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tile shape and K split of a bf16 contraction.
+// Kernel, tile shape and K split of a bf16 contraction.
 //
-// One workgroup per compute unit: a launch takes rounds = ceil(tiles * splits / 256) of (slabs of 64 k) * slab + rest, with both
-// times measured per shape on full rounds of 256 tiles (us; `rest`: first slabs from memory and the epilogue; 2 us more once
-// per launch).  The K-slow forms read 8 bytes per LDS instruction instead of 16, which the narrow tiles feel most.  A split adds
-// its partial sums: 3 us and their bytes at 4 TB/s; a split keeps at least 4 slabs.  The times are of operands that the L2s hold and
-// of a plain store: with operands from memory a slab of the K-slow 64x128 shape takes 0.47-0.54 us, and an epilogue with an activation
-// adds 15-25 us to a round of the largest tiles.
+// One workgroup per compute unit: a launch of the ring kernel takes rounds = ceil(tiles * splits / 256) of (slabs of 64 k) * slab + rest +
+// epilogue, with slab and rest measured per shape on full rounds of 256 tiles (us; `rest`: first slabs from memory and the stores; 2 us
+// more once per launch).  The K-slow forms read 8 bytes per LDS instruction instead of 16, which the narrow tiles feel most.  A split adds
+// its partial sums: 3 us and their bytes at 4 TB/s; a split keeps at least 4 slabs.  The kernel of resident workgroups hides most of
+// the rest and the epilogue of every tile but a workgroup's last.  The times are of operands that the L2s hold: with operands from
+// memory a slab of the K-slow 64x128 shape takes 0.47-0.54 us.
 struct RingShape {
   int bm, bn;
   float slab_nt, slab_tt, rest;
 };
 static const RingShape RING_SHAPES[GEMM_RING_NSHAPES] = {
-    {256, 256, 1.50f, 1.37f, 6.5f}, {192, 256, 1.10f, 1.03f, 6.0f}, {256, 192, 1.07f, 1.02f, 6.5f}, {128, 256, 0.73f, 0.74f, 5.2f},
+    {256, 256, 1.33f, 1.30f, 8.5f}, {192, 256, 1.05f, 1.03f, 6.5f}, {256, 192, 1.04f, 1.02f, 6.8f}, {128, 256, 0.73f, 0.74f, 5.2f},
     {256, 128, 0.71f, 0.73f, 5.4f}, {192, 192, 0.80f, 0.81f, 5.5f}, {128, 192, 0.54f, 0.57f, 4.3f}, {192, 128, 0.54f, 0.57f, 4.1f},
     {128, 128, 0.39f, 0.40f, 3.1f}, {64, 128, 0.26f, 0.29f, 2.2f},  {128, 64, 0.25f, 0.29f, 2.2f},  {64, 64, 0.165f, 0.20f, 1.7f}};
+// Kernel of resident workgroups: per slab, per round beside it, and once.
+static const float FLOW_SLAB_NT = 0.775f, FLOW_SLAB_TT = 0.79f, FLOW_ROUND = 2.3f, FLOW_REST = 6.0f;
+// What an epilogue adds to a plain store, us per 1000 columns x rows of a tile (vector instructions and further outputs).
+static float epi_us(int kind) {
+  switch (kind) {
+    case EPI_BIAS_ACT: case EPI_ACT: case EPI_DACT: return 0.20f;
+    case EPI_SWIGLU: return 0.27f;
+    case EPI_DSWIGLU: return 0.50f;
+    case EPI_ROPE: return 0.15f;
+    default: return 0.f;
+  }
+}
 // Shapes that are built per form (bit i: shape i); see gemm_ring_*.hip.
 static unsigned ring_shapes_built(int trans_a, int trans_b) {
   if (!trans_a && !trans_b) return 0xfffu;
   if (trans_a && trans_b) return 0x3ffu;        // at least 128 columns: the partial column sums have a row per tile column
   return trans_b ? 0x391u : 0x101u;
 }
-// Shape and split that finish soonest; splits > 0: that many, else 1 .. max_splits.
-static void ring_plan(int trans_a, int trans_b, int M, int N, int K, int splits, int max_splits, int* shape_out, int* splits_out) {
+// Shape and split that finish soonest; splits > 0: that many, else 1 .. max_splits.  Returns the time (us).
+static double ring_plan(int trans_a, int trans_b, int M, int N, int K, int kind, int splits, int max_splits, int* shape_out, int* splits_out) {
   const int slabs = (K + 63) / 64;
   const unsigned built = ring_shapes_built(trans_a, trans_b);
   double best = 0.0;
@@ -193,29 +205,37 @@ static void ring_plan(int trans_a, int trans_b, int M, int N, int K, int splits,
     const RingShape& r = RING_SHAPES[q];
     const long long tiles = static_cast<long long>((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn);
     const double slab = trans_a || trans_b ? r.slab_tt : r.slab_nt;
+    const double epi = epi_us(kind) * r.bm * r.bn / 1000.0;
     for (int sp = splits > 0 ? splits : 1; sp <= (splits > 0 ? splits : max_splits); ++sp) {
       const int per = (slabs + sp - 1) / sp;                 // slabs of the first splits; the last one takes the rest
       if (splits <= 0 && sp > 1 && (per < 4 || per * (sp - 1) >= slabs)) break;
       const double mn = static_cast<double>(M) * N;
       const double red = sp > 1 ? 3.0 + (sp * mn * 4.0 + mn * 2.0) / 4.0e6 : 0.0;
-      const double t = static_cast<double>((tiles * sp + 255) / 256) * (per * slab + r.rest) + red;
+      const double t = 2.0 + static_cast<double>((tiles * sp + 255) / 256) * (per * slab + r.rest + (sp > 1 ? 0.0 : epi)) + red;
       if (bs < 0 || t < best) { best = t; bs = q; bq = sp; }
     }
   }
   *shape_out = bs;
   *splits_out = bq;
+  return best;
+}
+static double flow_time(const GemmDesc& d) {
+  const long long tiles = static_cast<long long>((d.M + GEMM_FLOW_TILE - 1) / GEMM_FLOW_TILE) * ((d.N + GEMM_FLOW_TILE - 1) / GEMM_FLOW_TILE);
+  const double rounds = static_cast<double>(((tiles + 7) / 8 + 31) / 32);
+  const double epi = epi_us(d.epi.kind) * GEMM_FLOW_TILE * GEMM_FLOW_TILE / 1000.0;
+  return FLOW_REST + rounds * (d.K / 64 * (d.trans_a ? FLOW_SLAB_TT : FLOW_SLAB_NT) + FLOW_ROUND) + epi * (1.0 + 0.2 * (rounds - 1.0));
 }
 
 int ecospa_gemm_splits(int dtype, int M, int N, int K) {
   if (dtype != ECOSPA_BF16) return 1;      // the fp32 kernel shares K out inside a workgroup
   int shape, sp;
-  ring_plan(1, 1, M, N, K, 0, 8, &shape, &sp);
+  ring_plan(1, 1, M, N, K, EPI_STORE, 0, 8, &shape, &sp);
   return sp;
 }
 
 int ecospa_gemm_token_splits(int M, int N, int K) {
   int shape, sp;
-  ring_plan(0, 0, M, N, K, 0, 8, &shape, &sp);
+  ring_plan(0, 0, M, N, K, EPI_STORE, 0, 8, &shape, &sp);
   return sp;
 }
 
@@ -232,14 +252,16 @@ static void ring_forced_tile(int tile, int* bm, int* bn) {
   else if (tile >= 30 && tile < 42) { *bm = wg[tile - 30][0]; *bn = wg[tile - 30][1]; }
 }
 
-static int ring_route(const GemmDesc& d, int splits) {
+// Shape of the ring kernel for d and the time it is expected to take (us; 0: not a choice of time).
+static int ring_shape(const GemmDesc& d, int splits, double* t) {
   int shape, sp, bm, bn;
+  *t = 0.0;
   if (ring_wide(d)) return GEMM_RING_WIDE_SHAPE;
   ring_forced_tile(d.tile, &bm, &bn);
   const unsigned built = ring_shapes_built(d.trans_a, d.trans_b);
   for (int q = 0; q < GEMM_RING_NSHAPES && bm; ++q)
     if (((built >> q) & 1) && RING_SHAPES[q].bm == bm && RING_SHAPES[q].bn == bn) return q;
-  ring_plan(d.trans_a, d.trans_b, d.M, d.N, d.K, splits, splits, &shape, &sp);
+  *t = ring_plan(d.trans_a, d.trans_b, d.M, d.N, d.K, d.epi.kind, splits, splits, &shape, &sp);
   return shape;
 }
 
@@ -248,7 +270,8 @@ static int ring_route(const GemmDesc& d, int splits) {
 int ecospa_gemm_colsum_rows(const GemmDesc& d) {
   const int splits = d.splits > 1 ? d.splits : 1;
   if (d.dtype != ECOSPA_BF16) return splits;
-  const int bn = RING_SHAPES[ring_route(d, splits)].bn;
+  double t;
+  const int bn = RING_SHAPES[ring_shape(d, splits, &t)].bn;
   return splits * ((d.N + bn - 1) / bn);
 }
 
@@ -279,9 +302,11 @@ int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d) {
     if (prof) (void)hipEventRecord(ctx->prof_ev[2 * ctx->prof_n], ctx->stream);
     // K range of a split: whole 64-deep slabs, the last split takes what is left
     const int k_chunk = ((d.K + 63) / 64 + splits - 1) / splits * 64;
-    const int shape = ring_route(d, splits);
+    double t;
+    const int shape = ring_shape(d, splits, &t);
     hipError_t le;
-    if (d.trans_a && d.trans_b) le = gemm_ring_launch_tt(ctx, d, shape, k_chunk);
+    if (gemm_flow_takes(d) && flow_time(d) < t) le = d.trans_a ? gemm_flow_launch_tt(ctx, d) : gemm_flow_launch_nt(ctx, d);
+    else if (d.trans_a && d.trans_b) le = gemm_ring_launch_tt(ctx, d, shape, k_chunk);
     else if (d.trans_a || d.trans_b) le = gemm_ring_launch_mixed(ctx, d, shape, k_chunk);
     else le = gemm_ring_launch_nt(ctx, d, shape, k_chunk);
     if (le != hipSuccess) return hip_fail(ctx, le, "gemm launch");

@@ -134,3 +134,25 @@ def test_matrix_instructions_follow_vector_writes_of_their_operands_at_a_distanc
                     states += 1
                     j -= 1
     assert seen > 5000
+
+
+def test_waits_of_the_resident_workgroups_cover_the_next_slab(code_objects):
+    """The kernel of resident workgroups names, in front of each barrier, how many memory operations may still be under way: at most the
+    loads of the slabs behind the next one.  The stores and side inputs it counts beside them must really have been issued since."""
+    seen = 0
+    for f in code_objects:
+        for name, ins in _functions(f).items():
+            m = re.search(r"gemm_bf16_flow_kernelILi(\d+)ELi(\d+)ELi(\d+)E", name)
+            if not m:
+                continue
+            bm, bn, bufs = map(int, m.groups())
+            behind = (bufs - 2) * (bm + bn) * 128 // 4096
+            for i, (_, op, _, _) in enumerate(ins):
+                if op != "s_barrier":
+                    continue
+                j = next(j for j in range(i - 1, -1, -1) if ins[j][1] == "s_waitcnt" and "vmcnt" in ins[j][2])
+                left = int(re.search(r"vmcnt\((\d+)\)", ins[j][2])[1])
+                memory = [o for _, o, *_ in ins[:j] if o.startswith(("global_", "buffer_", "flat_"))][-left:]
+                assert sum("lds" in o for o in memory) <= behind, name
+                seen += 1
+    assert seen > 100

@@ -1,0 +1,85 @@
+"""The contraction kernel of resident workgroups (csrc/gemm_flow.h) against the kernel of one tile per workgroup: every epilogue, tiles cut
+off at both edges, two and three tiles per workgroup, the shortest K it takes and one that is no multiple of the ring's three slabs."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2511_11641_amd import binding as B
+from util import GemmDesc
+
+pytestmark = pytest.mark.gpu
+STORE, BIAS_ACT, DACT, DSWIGLU, ACT, ROPE, SWIGLU = range(7)
+FLOW = ("_Z19gemm_flow_launch_ntP10ecospa_ctxRK8GemmDesc", "_Z19gemm_flow_launch_ttP10ecospa_ctxRK8GemmDesc")
+RING_192 = 35          # tile code: 192 x 192, one tile per workgroup
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    return B.Context("cuda:0")
+
+
+def _rnd(gen, *shape):
+    return torch.randn(*shape, device="cuda", generator=gen).bfloat16()
+
+
+def _desc(kind, tt, M, N, K, gen):
+    """A descriptor, its two outputs inside larger buffers of a marker value, and what has to stay alive."""
+    a, b = _rnd(gen, K, M) if tt else _rnd(gen, M, K), _rnd(gen, K, N) if tt else _rnd(gen, N, K)
+    b *= K ** -0.5
+    wide = 2 * N if kind == DSWIGLU else N
+    c, c2 = torch.full((M + 3, wide + 8), 7.0, device="cuda").bfloat16(), torch.full((M + 3, N + 8), 7.0, device="cuda").bfloat16()
+    g = GemmDesc(B.BF16, M, N, K, a.data_ptr(), a.stride(0), int(tt), b.data_ptr(), b.stride(0), int(tt), 0, 1, None)
+    g.epi.kind, g.epi.act, g.epi.c, g.epi.ldc = kind, B.ACT_GELU_ERF, c.data_ptr(), c.stride(0)
+    keep = [a, b]
+    if not tt and kind not in (DACT, DSWIGLU):
+        keep.append(_rnd(gen, N))
+        g.epi.bias = keep[-1].data_ptr()
+    if kind in (BIAS_ACT, SWIGLU):
+        g.epi.c2, g.epi.ldc2 = c2.data_ptr(), c2.stride(0)
+    if kind in (DACT, DSWIGLU):
+        keep.append(_rnd(gen, M, wide))
+        g.epi.h, g.epi.ldh, g.epi.kp = keep[-1].data_ptr(), wide, N
+    if kind == ROPE:      # 24-wide heads: four query heads on two key heads' tables, then a part that is not turned
+        kp, hkv, L = 24, 2 * max(1, N // 240), 190
+        hq = 2 * hkv
+        cs, sn = (torch.rand(hkv, L, kp // 2, device="cuda", generator=gen) for _ in range(2))
+        keep += [cs, sn]
+        g.epi.rope_cos, g.epi.rope_sin, g.epi.rope_cols, g.epi.rope_kp, g.epi.rope_L, g.epi.rope_hq, g.epi.rope_qpk = (
+            cs.data_ptr(), sn.data_ptr(), (hq + hkv) * kp, kp, L, hq, hq // hkv)
+    return g, c, c2, keep
+
+
+@pytest.mark.parametrize("M,N,K", [(3265, 3080, 1024), (3256, 6136, 1088), (8, 51400, 1152), (49160, 200, 1024)])
+@pytest.mark.parametrize("kind,tt", [(STORE, False), (BIAS_ACT, False), (ACT, False), (DACT, False), (DSWIGLU, False), (ROPE, False), (SWIGLU, False), (STORE, True)])
+def test_resident_workgroups_give_what_one_tile_per_workgroup_gives(ctx, kind, tt, M, N, K):
+    if tt:
+        M -= M % 8
+    gen = torch.Generator(device="cuda").manual_seed(71)
+    g, c, c2, keep = _desc(kind, tt, M, N, K, gen)
+    assert getattr(ctx.lib, FLOW[tt])(ctx.h, C.byref(g)) == 0
+    got, got2 = c.clone(), c2.clone()
+    c.fill_(7.0)
+    c2.fill_(7.0)
+    g.tile = RING_192
+    assert ctx.lib._Z11ecospa_gemmP10ecospa_ctxRK8GemmDesc(ctx.h, C.byref(g)) == B.OK
+    for x, y in ((got, c), (got2, c2)):
+        # products are added in the same order; the epilogues' arithmetic may be contracted differently: fp32 roundings of values below
+        # 16 (1e-6, where a difference cancels), which here and there, in far fewer than one of a thousand values, move the rounding to
+        # bf16 by one step (at most 2^-7 of the value)
+        x, y = x.float(), y.float()
+        assert bool(((x - y).abs() <= 2 ** -7 * y.abs() + 4e-6).all()) and float((x != y).float().mean()) < 1e-3
+        assert bool((x[M:] == 7).all()) and bool((x[:, -8:] == 7).all()), "written beyond the matrix"
+
+
+def test_the_rule_takes_it_and_refuses_what_it_is_not_built_for(ctx):
+    gen = torch.Generator(device="cuda").manual_seed(72)
+    g, c, c2, keep = _desc(BIAS_ACT, False, 6140, 3064, 1024, gen)
+    run = lambda: ctx.lib._Z11ecospa_gemmP10ecospa_ctxRK8GemmDesc(ctx.h, C.byref(g))
+    for act in (B.ACT_GELU_ERF, B.ACT_GELU_TANH):       # the tanh form stays with the other kernel
+        g.epi.act, g.tile = act, 0
+        assert run() == B.OK
+        got = c2.clone()
+        g.tile = RING_192
+        assert run() == B.OK
+        assert torch.equal(got, c2) or float((got != c2).float().mean()) < 1e-3
