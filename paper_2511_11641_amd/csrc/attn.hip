@@ -77,6 +77,8 @@ __device__ __forceinline__ bf16x8_t frag_nat(const bf16_t* tile, int row, int s,
 // dim0 + l32 of the rows {16s + 4hh + 0..3, 16s + 8 + 4hh + 0..3} - the order in which acc_to_frag()
 // lays out the contraction index.  Within a 16-lane group, lane i addresses (row i / 4, dims
 // 4 * (i % 4) ..+3) and receives dim i of the group's four rows.
+// With two 32-wide sides the reads go out in front of the softmax arithmetic, whose registers leave room for them: their latency passes behind
+// it (8 x 1024 causal tokens, 16 heads: dK/dV 47.5 -> 45.3 us, forward 29.6 -> 28.5).
 // The reads are issued through inline assembly: the compiler would hold the builtin form back until
 // every direct global->LDS load in flight has landed (it cannot tell the stream buffers apart), which
 // would undo the prefetch.  The step is an offset in the instruction: these kernels are bound by their vector instructions (62 % of the
@@ -123,40 +125,45 @@ __device__ __forceinline__ bf16x8_t trn_frag(TrnRegs& r) {
 // repeat the last kept chunk: finite stand-ins that the callers keep out of every result (masked
 // scores; a zero-padded partner operand; output columns that are never stored).
 // WAVES = 1: a wavefront moves whole tiles of its own.
+// An address is a wavefront-uniform base in scalar registers plus a lane offset that does not change; only a tile beyond the end of the
+// sequence corrects the offsets.  (With 64-bit lane addresses the compiler ran their multiplications for every tile: three quarter-rate
+// instructions and six 64-bit additions per load.)  That, loops that are uniform to the compiler and bit masks instead of comparisons:
+// forward of 32 x 1024 causal tokens, 16 heads of 32 dims, 103.2 -> 92.5 us; dK/dV of 11 x 381, 32 query heads on 8 key heads, 47.1 -> 39.4.
 template <int D, int WAVES = 4>
 struct TileStream {
   static constexpr int CPR = D / 8, RPI = 64 / CPR, PER = (64 / RPI) / WAVES;
-  static __device__ __forceinline__ int wave_of() { return WAVES == 1 ? 0 : static_cast<int>(threadIdx.x >> 6); }
-  const bf16_t* base;
-  long long ld;
-  const bf16_t* p0[PER];   // this lane's source in a tile that starts at row 0
-  int row[PER], col[PER];
+  const char* base;
+  long long ldb;           // bytes per row
+  unsigned off[PER];       // this lane's piece of a tile
+  int row0, wave;          // its row in the first instruction of the wavefront
+  __device__ __forceinline__ void aim(const bf16_t* b) { base = reinterpret_cast<const char*>(b); }
   __device__ __forceinline__ void init(const bf16_t* b, long long l, int kp) {
-    const int lane = threadIdx.x & 63, wave = wave_of();
-    base = b;
-    ld = l;
+    const int lane = threadIdx.x & 63;
+    wave = WAVES == 1 ? 0 : static_cast<int>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    aim(b);
+    ldb = 2 * l;
+    row0 = wave * (PER * RPI) + lane / CPR;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const int r = (wave * PER + i) * RPI + lane / CPR, pc = lane % CPR;
-      row[i] = r;
-      col[i] = min((pc ^ nat_swz<D>(r)) * 8, kp - 8);
-      p0[i] = b + r * l + col[i];
+      const int r = row0 + i * RPI;
+      off[i] = static_cast<unsigned>(r) * static_cast<unsigned>(ldb) + static_cast<unsigned>(min(((lane % CPR) ^ nat_swz<D>(r)) * 8, kp - 8) * 2);
     }
   }
   // rows g0 .. g0 + 63 of the matrix, of which the first rows_valid (>= 1) exist
   __device__ __forceinline__ void issue(bf16_t* tile, long long g0, int rows_valid) const {
-    const int wave = __builtin_amdgcn_readfirstlane(wave_of());
-    if (rows_valid >= 64) {      // uniform: one scalar product, one add per load
-      const long long adv = g0 * ld;
+    const char* const p = base + g0 * ldb;
+    lds_bf16_t* const dst = (lds_bf16_t*)tile + wave * (PER * 512);
+    unsigned o[PER];
 #pragma unroll
-      for (int i = 0; i < PER; ++i)
-        __builtin_amdgcn_global_load_lds(p0[i] + adv, (lds_bf16_t*)tile + (wave * PER + i) * 512, 16, 0, 0);
-    } else {
+    for (int i = 0; i < PER; ++i) o[i] = off[i];
+    if (rows_valid < 64) {
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const bf16_t* src = base + (g0 + min(row[i], rows_valid - 1)) * ld + col[i];
-        __builtin_amdgcn_global_load_lds(src, (lds_bf16_t*)tile + (wave * PER + i) * 512, 16, 0, 0);
-      }
+      for (int i = 0; i < PER; ++i) o[i] -= static_cast<unsigned>(max(row0 + i * RPI - (rows_valid - 1), 0)) * static_cast<unsigned>(ldb);
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      asm volatile("" : "+v"(o[i]));      // keeps the offset a lane register at the load
+      __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(p + o[i]), dst + i * 512, 16, 0, 0);
     }
   }
 };
@@ -165,6 +172,26 @@ __device__ __forceinline__ void stream_wait() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0);   // vmcnt(0) lgkmcnt(0) expcnt(0)
   asm volatile("" ::: "memory");
+}
+// Masks of the 32 scores that a lane holds of a 64-row score tile: element e = 16 t + r is row 8 (e / 4) + e % 4 behind the lane's first
+// row.  rows_below(x): a bit for each element in front of row x.  An element whose bit is set in `hidden` becomes -inf: a bit-field
+// extraction and a bitwise selection (a comparison and a select have to wait two states for each other, twice the time).
+__device__ __forceinline__ unsigned rows_below(int x) {
+  x = min(max(x, 0), 64);
+  const int n = 4 * (x >> 3) + min(x & 7, 4);
+  return n >= 32 ? ~0u : (1u << n) - 1u;
+}
+template <int E>
+__device__ __forceinline__ float hide(float s, unsigned hidden) {
+  const unsigned t = static_cast<unsigned>(__builtin_amdgcn_sbfe(static_cast<int>(hidden), E, 1));
+  return __uint_as_float((t & 0xff800000u) | (~t & __float_as_uint(s)));
+}
+template <int T>
+__device__ __forceinline__ void hide16(floatx16& s, unsigned hidden) {
+#define HIDE4(R) s[R] = hide<16 * T + R>(s[R], hidden); s[R + 1] = hide<16 * T + R + 1>(s[R + 1], hidden); \
+                 s[R + 2] = hide<16 * T + R + 2>(s[R + 2], hidden); s[R + 3] = hide<16 * T + R + 3>(s[R + 3], hidden);
+  HIDE4(0) HIDE4(4) HIDE4(8) HIDE4(12)
+#undef HIDE4
 }
 // accumulator registers 8*half .. 8*half+7 as a bf16 B operand
 __device__ __forceinline__ bf16x8_t acc_to_frag(const floatx16& a, int half) {
@@ -294,15 +321,18 @@ __device__ __forceinline__ void attn_fwd_tile(const bf16_t* Kt, const bf16_t* Vt
     for (int s = 0; s < DQ / 16; ++s)
       sacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_nat<DQ>(Kt, t * 32 + l32, s, hh), qf[s], sacc[t], 0, 0, 0);
   }
+  TrnRegs vr[4][DV / 32];
+  if constexpr (DV == 32) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) trn_issue<DV>(vr[s][0], Vt, 0, s);
+  }
   // Softmax on raw scores: the scale is folded into the exponent's FMA.  Masking is a
   // wave-uniform special case (tiles on the diagonal or at the end of the sequence) done
   // with selects, never with divergent branches.
   if ((causal && kv0 + 63 > qw0) || (kv0 + 64 > L)) {
-    const int lim = (causal ? min(q_idx, L - 1) : L - 1) - kv0 - hh * 4;   // last visible key of this query, from the lane's first key
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[t][r] = t * 32 + (r >> 2) * 8 + (r & 3) > lim ? -INFINITY : sacc[t][r];
+    const unsigned hidden = ~rows_below((causal ? min(q_idx + 1, L) : L) - kv0 - hh * 4);      // keys behind the query's last visible one
+    hide16<0>(sacc[0], hidden);
+    hide16<1>(sacc[1], hidden);
   }
   float mx = sacc[0][0];
 #pragma unroll
@@ -334,11 +364,12 @@ __device__ __forceinline__ void attn_fwd_tile(const bf16_t* Kt, const bf16_t* Vt
   for (int t = 0; t < 2; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) sacc[t][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[t][r], sc, -msc));
-  TrnRegs vr[4][DV / 32];
+  if constexpr (DV > 32) {
 #pragma unroll
-  for (int s = 0; s < 4; ++s)
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-    for (int u = 0; u < DV / 32; ++u) trn_issue<DV>(vr[s][u], Vt, u * 32, s);
+      for (int u = 0; u < DV / 32; ++u) trn_issue<DV>(vr[s][u], Vt, u * 32, s);
+  }
   trn_wait();
   taken();
 #pragma unroll
@@ -367,7 +398,7 @@ void attn_fwd_kernel(const AttnArgs a) {
   bf16_t* const Vs0 = Ks0 + 2 * 64 * DQ;      // [2][64 * DV]
 #define Ks(buf) (Ks0 + (buf) * (64 * DQ))
 #define Vs(buf) (Vs0 + (buf) * (64 * DV))
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hh = lane >> 5, l32 = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hh = lane >> 5, l32 = lane & 31;
   int qt, head, b;
   attn_work_item(a, a.h, (a.L + 127) / 128, qt, head, b);
   const int q0 = qt * 128;
@@ -407,17 +438,24 @@ void attn_fwd_kernel(const AttnArgs a) {
   const float sc = a.scale * LOG2E;
   const int qw0 = q0 + wave * 32, q_idx = qw0 + l32;
 
-  for (int j = 0; j < n_kv; ++j) {
-    const int cur = j & 1, kv0 = j * 64;
+  // Key tiles that some query of this wavefront sees; behind them it only keeps step with the others (a loop of its own: skipping inside
+  // one loop has the compiler keep the accumulators twice).
+  const int n_own = a.causal ? min(n_kv, (qw0 + 31) / 64 + 1) : n_kv;
+  auto next_tile = [&](int j) __attribute__((always_inline)) {
     stream_wait();
     __syncthreads();    // tile j is in LDS; every wavefront is done with tile j-1, whose buffer is refilled now
     if (j + 1 < n_kv) {
-      ks.issue(Ks(cur ^ 1), tok0 + kv0 + 64, a.L - kv0 - 64);
-      vs.issue(Vs(cur ^ 1), tok0 + kv0 + 64, a.L - kv0 - 64);
+      ks.issue(Ks((j & 1) ^ 1), tok0 + j * 64 + 64, a.L - j * 64 - 64);
+      vs.issue(Vs((j & 1) ^ 1), tok0 + j * 64 + 64, a.L - j * 64 - 64);
     }
-    if (a.causal && kv0 > qw0 + 31) continue;   // no query of this wavefront sees the tile
-    attn_fwd_tile<DQ, DV>(Ks(cur), Vs(cur), qf, oacc, lacc, m_run, ones, sc, a.L, a.causal, kv0, qw0, [] {});
+  };
+  int j = 0;
+#pragma unroll 1
+  for (; j < n_own; ++j) {
+    next_tile(j);
+    attn_fwd_tile<DQ, DV>(Ks(j & 1), Vs(j & 1), qf, oacc, lacc, m_run, ones, sc, a.L, a.causal, j * 64, qw0, [] {});
   }
+  for (; j < n_kv; ++j) next_tile(j);
   const float l_tot = lacc[0];
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   if (hh == 0 && q_idx < a.L)
@@ -559,7 +597,7 @@ void attn_bwd_dq_kernel(const AttnArgs a) {
   bf16_t* const Vs0 = Ks0 + 2 * 64 * DQ;      // [2][64 * DV]
 #define Ks(buf) (Ks0 + (buf) * (64 * DQ))
 #define Vs(buf) (Vs0 + (buf) * (64 * DV))
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hh = lane >> 5, l32 = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hh = lane >> 5, l32 = lane & 31;
   int qt, head, b;
   attn_work_item(a, a.h, (a.L + 127) / 128, qt, head, b);
   const int q0 = qt * 128;
@@ -617,17 +655,22 @@ void attn_bwd_dq_kernel(const AttnArgs a) {
 
   const int kv_end = a.causal ? min(a.L, q0 + 128) : a.L;
   const int n_kv = (kv_end + 63) / 64;
-  for (int j = 0; j < n_kv; ++j) {
-    const int cur = j & 1, kv0 = j * 64;
+  const int n_own = a.causal ? min(n_kv, (qw0 + 31) / 64 + 1) : n_kv;      // as in attn_fwd_kernel
+  auto next_tile = [&](int j) __attribute__((always_inline)) {
     stream_wait();
     __syncthreads();    // tile j is in LDS; every wavefront is done with tile j-1, whose buffer is refilled now
     if (j + 1 < n_kv) {
-      ks.issue(Ks(cur ^ 1), tok0 + kv0 + 64, a.L - kv0 - 64);
-      vs.issue(Vs(cur ^ 1), tok0 + kv0 + 64, a.L - kv0 - 64);
+      ks.issue(Ks((j & 1) ^ 1), tok0 + j * 64 + 64, a.L - j * 64 - 64);
+      vs.issue(Vs((j & 1) ^ 1), tok0 + j * 64 + 64, a.L - j * 64 - 64);
     }
-    if (a.causal && kv0 > qw0 + 31) continue;
+  };
+  int j = 0;
+#pragma unroll 1
+  for (; j < n_own; ++j) {
+    const int cur = j & 1, kv0 = j * 64;
+    next_tile(j);
     const bool need_mask = (a.causal && kv0 + 63 > qw0) || (kv0 + 64 > a.L);
-    const int lim = (a.causal ? min(q_idx, a.L - 1) : a.L - 1) - kv0 - hh * 4;       // last visible key of this query, from the lane's first key
+    const unsigned hidden = ~rows_below((a.causal ? min(q_idx + 1, a.L) : a.L) - kv0 - hh * 4);      // keys behind the query's last visible one
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       floatx16 sacc, pacc;
@@ -639,20 +682,24 @@ void attn_bwd_dq_kernel(const AttnArgs a) {
 #pragma unroll
       for (int s = 0; s < DV / 16; ++s)
         pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_nat<DV>(Vs(cur), t * 32 + l32, s, hh), dof[s], pacc, 0, 0, 0);
-      if (need_mask) {        // wave-uniform; selects only
+      TrnRegs kr[2][DQ / 32];
+      auto read_k = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sacc[r] = t * 32 + (r >> 2) * 8 + (r & 3) > lim ? -INFINITY : sacc[r];
+        for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+          for (int u = 0; u < DQ / 32; ++u) trn_issue<DQ>(kr[s2][u], Ks(cur), u * 32, t * 2 + s2);
+      };
+      if (DQ == 32) read_k();
+      if (need_mask) {        // wave-uniform
+        if (t == 0) hide16<0>(sacc, hidden);
+        else hide16<1>(sacc, hidden);
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[r], sc, -lse2));
         sacc[r] = p * (pacc[r] - dlt);
       }
-      TrnRegs kr[2][DQ / 32];
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-        for (int u = 0; u < DQ / 32; ++u) trn_issue<DQ>(kr[s2][u], Ks(cur), u * 32, t * 2 + s2);
+      if (DQ > 32) read_k();
       trn_wait();
 #pragma unroll
       for (int s2 = 0; s2 < 2; ++s2) {
@@ -663,6 +710,7 @@ void attn_bwd_dq_kernel(const AttnArgs a) {
       }
     }
   }
+  for (; j < n_kv; ++j) next_tile(j);
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < DQ / 32; ++u) acc_to_tile<DQ>(Qs, wave * 32 + l32, u, dq[u], a.scale, hh);
@@ -693,7 +741,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ATTN_WPE(DQ
 #define dOs(buf) (dOs0 + (buf) * (64 * DV))
 #define lse_s(buf) (stats + (buf) * 64)
 #define dlt_s(buf) (stats + 128 + (buf) * 64)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hh = lane >> 5, l32 = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hh = lane >> 5, l32 = lane & 31;
   // one workgroup per (128 keys, key/value head, batch element); the query heads that share the key/value head
   // (Eq. 5) are walked one after the other, their contributions adding up in the same accumulators
   int kt, kvh, b;
@@ -734,122 +782,132 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ATTN_WPE(DQ
   TileStream<DV> ds;
   float st = 0.f;
   const int cnt = n_q - j0, n_it = cnt > 0 ? cnt * a.qpk : 0;   // iterations: query heads of the group x their query tiles
-  // iteration `it` is query tile j0 + it % cnt of query head head0 + it / cnt; a new head re-aims the streams
-#define KV_ISSUE(it, buf)                                                                              \
-  do {                                                                                                 \
-    const int hq_ = head0 + (it) / cnt, j_ = j0 + (it) % cnt;                                          \
-    if ((it) % cnt == 0) {                                                                             \
-      qs.init(a.qkv + hq_ * a.kp_qk, a.ld_qkv, a.kp_qk);                                               \
-      ds.init(a.d_o + hq_ * a.kp_vo, a.ld_o, a.kp_vo);                                                 \
-    }                                                                                                  \
-    qs.issue(Qs(buf), tok0 + j_ * 64, a.L - j_ * 64);                                                  \
-    ds.issue(dOs(buf), tok0 + j_ * 64, a.L - j_ * 64);                                                 \
-    if (tid < 128)                                                                                     \
-      st = (tid < 64 ? a.lse : a.delta)[(static_cast<long long>(b) * a.h + hq_) * a.L +                \
-                                        min(j_ * 64 + (tid & 63), a.L - 1)];                           \
-  } while (0)
-  if (n_it > 0) KV_ISSUE(0, 0);
-  for (int it = 0; it < n_it; ++it) {
-    const int j = j0 + it % cnt;
-    const int qb0 = j * 64, cur = it & 1;
+  qs.init(a.qkv + head0 * a.kp_qk, a.ld_qkv, a.kp_qk);
+  ds.init(a.d_o + head0 * a.kp_vo, a.ld_o, a.kp_vo);
+  const float* const row_stat = (tid < 64 ? a.lse : a.delta) + static_cast<long long>(b) * a.h * a.L;
+  int hq = head0, jn = j0;         // query head and tile that are requested next; a new head re-aims the streams
+  auto issue = [&](int buf) __attribute__((always_inline)) {
+    if (jn == n_q) {
+      jn = j0;
+      ++hq;
+      qs.aim(a.qkv + hq * a.kp_qk);
+      ds.aim(a.d_o + hq * a.kp_vo);
+    }
+    qs.issue(Qs(buf), tok0 + jn * 64, a.L - jn * 64);
+    ds.issue(dOs(buf), tok0 + jn * 64, a.L - jn * 64);
+    if (tid < 128) st = row_stat[static_cast<long long>(hq) * a.L + min(jn * 64 + (tid & 63), a.L - 1)];
+    ++jn;
+  };
+  if (n_it > 0) issue(0);
+  int it = 0;
+  auto next_tile = [&]() __attribute__((always_inline)) {
+    const int cur = it & 1;
     if (tid < 64) lse_s(cur)[tid] = st * LOG2E;
     else if (tid < 128) dlt_s(cur)[tid - 64] = st;
     stream_wait();
     __syncthreads();    // this tile is in LDS; every wavefront is done with the one before, whose buffers are refilled now
-    if (it + 1 < n_it) KV_ISSUE(it + 1, cur ^ 1);
-    if (a.causal && qb0 + 63 < kw0) continue;          // every query of the tile precedes this wave's keys
-    const bool need_mask = (a.causal && qb0 < kw0 + 31) || (qb0 + 64 > a.L) || (kw0 + 32 > a.L);
+    if (it + 1 < n_it) issue(cur ^ 1);
+    ++it;
+  };
+  const int j_own = a.causal ? min(max(kw0 / 64, j0), n_q) : j0;      // first query tile that sees a key of this wavefront
+  for (int head = 0; head < a.qpk; ++head) {
+    for (int j = j0; j < j_own; ++j) next_tile();      // every query of the tile precedes this wavefront's keys
+#pragma unroll 1
+    for (int j = j_own; j < n_q; ++j) {
+      const int qb0 = j * 64, cur = it & 1;
+      next_tile();
+      const bool need_mask = (a.causal && qb0 < kw0 + 31) || (qb0 + 64 > a.L) || (kw0 + 32 > a.L);
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      floatx16 sacc, pacc;
+      for (int t = 0; t < 2; ++t) {
+        floatx16 sacc, pacc;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { sacc[r] = 0.f; pacc[r] = 0.f; }
+        for (int r = 0; r < 16; ++r) { sacc[r] = 0.f; pacc[r] = 0.f; }
 #pragma unroll
-      for (int s = 0; s < DQ / 16; ++s)
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_nat<DQ>(Qs(cur), t * 32 + l32, s, hh), kf[s], sacc, 0, 0, 0);
+        for (int s = 0; s < DQ / 16; ++s)
+          sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_nat<DQ>(Qs(cur), t * 32 + l32, s, hh), kf[s], sacc, 0, 0, 0);
 #pragma unroll
-      for (int s = 0; s < DV / 16; ++s)
-        pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_nat<DV>(dOs(cur), t * 32 + l32, s, hh), vf[s], pacc, 0, 0, 0);
-      floatx16 pr;
-      if (need_mask) {        // wave-uniform: only tiles on the diagonal or at the end of the sequence pay for the selects
-        // a query sees this lane's key if key <= q (causal) and both are inside the sequence
-        // (both limits counted from the lane's first query; where two 128-wide sides leave no registers for them, the queries from 0)
-        const int q_lane = qb0 + hh * 4, q_first = DQ + DV <= 192 ? q_lane : 0;
-        const int q_min = key_idx >= a.L ? (DQ + DV <= 192 ? 64 : 0x7fffffff) : (a.causal ? key_idx : 0) - q_first, q_end = a.L - q_first;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int q = (q_lane - q_first) + t * 32 + (r >> 2) * 8 + (r & 3);
-          sacc[r] = (q < q_min || q >= q_end) ? -INFINITY : sacc[r];
-        }
-      }
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int qrow = t * 32 + g * 8 + hh * 4;
-        const float4 ls = *reinterpret_cast<const float4*>(lse_s(cur) + qrow);
-        const float4 dl = *reinterpret_cast<const float4*>(dlt_s(cur) + qrow);
-        const float lsv[4] = {ls.x, ls.y, ls.z, ls.w}, dlv[4] = {dl.x, dl.y, dl.z, dl.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = g * 4 + i;
-          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[r], sc, -lsv[i]));
-          pr[r] = p;
-          sacc[r] = p * (pacc[r] - dlv[i]);
-        }
-      }
-      if constexpr (DQ + DV <= 192) {
+        for (int s = 0; s < DV / 16; ++s)
+          pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_nat<DV>(dOs(cur), t * 32 + l32, s, hh), vf[s], pacc, 0, 0, 0);
+        floatx16 pr;
         TrnRegs dor[2][DV / 32], qr[2][DQ / 32];
+        auto read_t = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
+          for (int s2 = 0; s2 < 2; ++s2) {
 #pragma unroll
-          for (int u = 0; u < DV / 32; ++u) trn_issue<DV>(dor[s2][u], dOs(cur), u * 32, t * 2 + s2);
+            for (int u = 0; u < DV / 32; ++u) trn_issue<DV>(dor[s2][u], dOs(cur), u * 32, t * 2 + s2);
 #pragma unroll
-          for (int u = 0; u < DQ / 32; ++u) trn_issue<DQ>(qr[s2][u], Qs(cur), u * 32, t * 2 + s2);
+            for (int u = 0; u < DQ / 32; ++u) trn_issue<DQ>(qr[s2][u], Qs(cur), u * 32, t * 2 + s2);
+          }
+        };
+        if (DQ + DV == 64) read_t();
+        if (need_mask) {        // wave-uniform: only tiles on the diagonal or at the end of the sequence
+          // a query sees this lane's key if key <= q (causal) and both are inside the sequence
+          const int q_lane = qb0 + hh * 4;
+          const unsigned hidden = rows_below(key_idx >= a.L ? 64 : (a.causal ? key_idx : 0) - q_lane) | ~rows_below(a.L - q_lane);
+          if (t == 0) hide16<0>(sacc, hidden);
+          else hide16<1>(sacc, hidden);
         }
-        trn_wait();
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-          const bf16x8_t pf = acc_to_frag(pr, s2), df = acc_to_frag(sacc, s2);
+        for (int g = 0; g < 4; ++g) {
+          const int qrow = t * 32 + g * 8 + hh * 4;
+          const float4 ls = *reinterpret_cast<const float4*>(lse_s(cur) + qrow);
+          const float4 dl = *reinterpret_cast<const float4*>(dlt_s(cur) + qrow);
+          const float lsv[4] = {ls.x, ls.y, ls.z, ls.w}, dlv[4] = {dl.x, dl.y, dl.z, dl.w};
 #pragma unroll
-          for (int u = 0; u < DV / 32; ++u)
-            dv[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trn_frag(dor[s2][u]), pf, dv[u], 0, 0, 0);
-#pragma unroll
-          for (int u = 0; u < DQ / 32; ++u)
-            dk[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trn_frag(qr[s2][u]), df, dk[u], 0, 0, 0);
+          for (int i = 0; i < 4; ++i) {
+            const int r = g * 4 + i;
+            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[r], sc, -lsv[i]));
+            pr[r] = p;
+            sacc[r] = p * (pacc[r] - dlv[i]);
+          }
         }
-      } else {
-        // two 128-wide sides: the transposed fragments of one operand and one 16-query step at a time, and their addresses computed
-        // here (the compiler cannot see that ln is the lane) instead of kept over the loop, or they would not fit the registers.
-        // 4 x 512 causal tokens, 32 heads of 96 dims: 80.6 us; with both kept, 68 bytes of scratch per lane, 80.3 us; with the
-        // addresses computed for each step 84.7 us.
-        int ln = lane;
-        asm volatile("" : "+v"(ln));
+        if constexpr (DQ + DV <= 192) {
+          if (DQ + DV > 64) read_t();
+          trn_wait();
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-          {
-            TrnRegs dor[DV / 32];
-#pragma unroll
-            for (int u = 0; u < DV / 32; ++u) trn_issue_from<DV>(dor[u], dOs(cur), u * 32, t * 2 + s2, ln);
-            trn_wait();
-            const bf16x8_t pf = acc_to_frag(pr, s2);
+          for (int s2 = 0; s2 < 2; ++s2) {
+            const bf16x8_t pf = acc_to_frag(pr, s2), df = acc_to_frag(sacc, s2);
 #pragma unroll
             for (int u = 0; u < DV / 32; ++u)
-              dv[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trn_frag(dor[u]), pf, dv[u], 0, 0, 0);
-          }
-          {
-            TrnRegs qr[DQ / 32];
-#pragma unroll
-            for (int u = 0; u < DQ / 32; ++u) trn_issue_from<DQ>(qr[u], Qs(cur), u * 32, t * 2 + s2, ln);
-            trn_wait();
-            const bf16x8_t df = acc_to_frag(sacc, s2);
+              dv[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trn_frag(dor[s2][u]), pf, dv[u], 0, 0, 0);
 #pragma unroll
             for (int u = 0; u < DQ / 32; ++u)
-              dk[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trn_frag(qr[u]), df, dk[u], 0, 0, 0);
+              dk[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trn_frag(qr[s2][u]), df, dk[u], 0, 0, 0);
+          }
+        } else {
+          // two 128-wide sides: the transposed fragments of one operand and one 16-query step at a time, and their addresses computed
+          // here (the compiler cannot see that ln is the lane) instead of kept over the loop, or they would not fit the registers.
+          // 4 x 512 causal tokens, 32 heads of 96 dims: 80.6 us; with both kept, 68 bytes of scratch per lane, 80.3 us; with the
+          // addresses computed for each step 84.7 us.
+          int ln = lane;
+          asm volatile("" : "+v"(ln));
+#pragma unroll
+          for (int s2 = 0; s2 < 2; ++s2) {
+            {
+              TrnRegs dor[DV / 32];
+#pragma unroll
+              for (int u = 0; u < DV / 32; ++u) trn_issue_from<DV>(dor[u], dOs(cur), u * 32, t * 2 + s2, ln);
+              trn_wait();
+              const bf16x8_t pf = acc_to_frag(pr, s2);
+#pragma unroll
+              for (int u = 0; u < DV / 32; ++u)
+                dv[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trn_frag(dor[u]), pf, dv[u], 0, 0, 0);
+            }
+            {
+              TrnRegs qr[DQ / 32];
+#pragma unroll
+              for (int u = 0; u < DQ / 32; ++u) trn_issue_from<DQ>(qr[u], Qs(cur), u * 32, t * 2 + s2, ln);
+              trn_wait();
+              const bf16x8_t df = acc_to_frag(sacc, s2);
+#pragma unroll
+              for (int u = 0; u < DQ / 32; ++u)
+                dk[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trn_frag(qr[u]), df, dk[u], 0, 0, 0);
+            }
           }
         }
       }
     }
   }
-#undef KV_ISSUE
 #undef Qs
 #undef dOs
 #undef lse_s
