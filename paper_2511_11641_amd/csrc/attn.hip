@@ -1069,10 +1069,10 @@ static int attn_backward_body(ecospa_ctx* ctx, const ecospa_block_desc& d, const
   // the bias gradients are column sums of dY and dQKV, the K-slow operands of the two weight-gradient
   // contractions: those add them up on the way
   if (gr.dw_o && gr.db_o) go.colsum = w.colsum;
-  if (gr.dw_o && (rc = ecospa_gemm(ctx, go))) return rc;
-  if ((rc = token_gemm(ctx, w, d.w_o_t ? mk_gemm(d.dtype, T, nvo, dm, dy, dm, 0, d.w_o_t, d.ld_wot, 0, w.d_o, nvo, nullptr)   // transposed copy [nvo, d_model]
-                                     : mk_gemm(d.dtype, T, nvo, dm, dy, dm, 0, d.w_o, d.ld_wo, 1, w.d_o, nvo, nullptr))))
-    return rc;
+  GemmDesc gd = d.w_o_t ? mk_gemm(d.dtype, T, nvo, dm, dy, dm, 0, d.w_o_t, d.ld_wot, 0, w.d_o, nvo, nullptr)   // transposed copy [nvo, d_model]
+                        : mk_gemm(d.dtype, T, nvo, dm, dy, dm, 0, d.w_o, d.ld_wo, 1, w.d_o, nvo, nullptr);
+  block_token_split(gd, w);
+  if ((rc = gr.dw_o ? ecospa_gemm_pair(ctx, go, gd) : ecospa_gemm(ctx, gd))) return rc;
 
   AttnArgs a;
   memset(&a, 0, sizeof(a));
@@ -1090,12 +1090,15 @@ static int attn_backward_body(ecospa_ctx* ctx, const ecospa_block_desc& d, const
   GemmDesc gq = mk_gemm(d.dtype, nqkv, dm, T, w.dqkv, nqkv, 1, x, dm, 1, gr.dw_qkv, gr.ld_dwqkv, nullptr);
   gq.splits = ecospa_gemm_splits(d.dtype, nqkv, dm, T); gq.partial = w.partial2; gq.defer_reduce = 1;
   if (gr.dw_qkv && gr.db_qkv) gq.colsum = w.colsum2;
-  if (gr.dw_qkv && (rc = ecospa_gemm(ctx, gq))) return rc;
-
-  // dX = dQKV W_qkv
-  if (dx && (rc = token_gemm(ctx, w, d.w_qkv_t ? mk_gemm(d.dtype, T, dm, nqkv, w.dqkv, nqkv, 0, d.w_qkv_t, d.ld_wqkvt, 0, dx, dm, nullptr)   // [d_model, nqkv]
-                                             : mk_gemm(d.dtype, T, dm, nqkv, w.dqkv, nqkv, 0, d.w_qkv, d.ld_wqkv, 1, dx, dm, nullptr))))
+  // dX = dQKV W_qkv, beside it
+  if (dx) {
+    GemmDesc gx = d.w_qkv_t ? mk_gemm(d.dtype, T, dm, nqkv, w.dqkv, nqkv, 0, d.w_qkv_t, d.ld_wqkvt, 0, dx, dm, nullptr)   // [d_model, nqkv]
+                            : mk_gemm(d.dtype, T, dm, nqkv, w.dqkv, nqkv, 0, d.w_qkv, d.ld_wqkv, 1, dx, dm, nullptr);
+    block_token_split(gx, w);
+    if ((rc = gr.dw_qkv ? ecospa_gemm_pair(ctx, gq, gx) : ecospa_gemm(ctx, gx))) return rc;
+  } else if (gr.dw_qkv && (rc = ecospa_gemm(ctx, gq))) {
     return rc;
+  }
   AuxBatch aux;
   memset(&aux, 0, sizeof(aux));
   if (gr.dw_o && go.splits > 1) aux.reduce[aux.n_reduce++] = go;

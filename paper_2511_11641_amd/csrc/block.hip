@@ -198,15 +198,15 @@ static int ffn_backward_body(ecospa_ctx* ctx, const ecospa_block_desc& d, const 
   g1.splits = ecospa_gemm_splits(d.dtype, nh, dm, T); g1.partial = w.partial2; g1.defer_reduce = 1;
   g1.epi.kind = EPI_STORE; g1.epi.c = gr.dw_1; g1.epi.ldc = gr.ld_dw1;
   if (fused_db && gr.dw_1 && gr.db_1) g1.colsum = w.colsum2;
-  if (gr.dw_1 && (rc = ecospa_gemm(ctx, g1))) return rc;
-
-  // dX = dH W_1
+  // dX = dH W_1, beside dW_1
   if (dx) {
     GemmDesc g = d.w_1_t ? gemm_desc(d.dtype, T, dm, nh, w.dh, nh, 0, d.w_1_t, d.ld_w1t, 0)   // transposed copy [d_model, nh]
                          : gemm_desc(d.dtype, T, dm, nh, w.dh, nh, 0, d.w_1, d.ld_w1, 1);
     g.epi.kind = EPI_STORE; g.epi.c = dx; g.epi.ldc = dm;
     block_token_split(g, w);
-    if ((rc = ecospa_gemm(ctx, g))) return rc;
+    if ((rc = gr.dw_1 ? ecospa_gemm_pair(ctx, g1, g) : ecospa_gemm(ctx, g))) return rc;
+  } else if (gr.dw_1 && (rc = ecospa_gemm(ctx, g1))) {
+    return rc;
   }
   AuxBatch aux;
   memset(&aux, 0, sizeof(aux));

@@ -58,6 +58,9 @@ struct GemmDesc {
 
 // Launch on ctx->stream.  bf16 and fp32 both run on MFMA tiles.
 int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d);
+// Two contractions that do not depend on each other: w a weight gradient (dY^T X, bf16 or fp32; its reduction deferred where K is split), x
+// over the same tokens.  One launch where that is built for the two, otherwise w, then x.
+int ecospa_gemm_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x);
 // Rows (of M floats) of the partial column sums that the launch of d writes to d.colsum.
 int ecospa_gemm_colsum_rows(const GemmDesc& d);
 // Second half of a split-K contraction launched with defer_reduce: fixed-order sum of the partials,
@@ -102,6 +105,12 @@ hipError_t gemm_flow_launch_tt(ecospa_ctx* ctx, const GemmDesc& d);
 hipError_t gemm_ring_launch_nt(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk);
 hipError_t gemm_ring_launch_tt(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk);
 hipError_t gemm_ring_launch_mixed(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk);
+// Pairs (see ecospa_gemm_pair): by the weight gradient's tile rows; x on one of the shapes of GEMM_PAIR_X.
+#define GEMM_PAIR_X ((1u << 4) | (1u << 5) | (1u << 7) | (1u << 8))
+hipError_t gemm_pair_launch_64(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int x_shape, int w_k_chunk);
+hipError_t gemm_pair_launch_128(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int x_shape, int w_k_chunk);
+hipError_t gemm_pair_launch_192(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int x_shape, int w_k_chunk);
+hipError_t gemm_pair_launch_256(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int x_shape, int w_k_chunk);
 
 // The small jobs that follow the contractions of a backward pass, batched into ONE launch (each of
 // them alone would be bound by the fixed cost of a launch): fixed-order reductions of split-K

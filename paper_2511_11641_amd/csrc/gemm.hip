@@ -275,33 +275,54 @@ int ecospa_gemm_colsum_rows(const GemmDesc& d) {
   return splits * ((d.N + bn - 1) / bn);
 }
 
-int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d) {
+// What a descriptor has to satisfy before anything is launched.
+static int gemm_check(const GemmDesc& d) {
   if (d.M < 1 || d.N < 1 || d.K < 1) return ECOSPA_ERR_SHAPE;
   if (!d.A || !d.B || (!d.epi.c && d.epi.kind != EPI_SWIGLU)) return ECOSPA_ERR_NULL;      // the gated epilogue may skip its first output
   if (d.splits > 1 && !d.partial) return ECOSPA_ERR_WORKSPACE;
   if (d.colsum && !(d.dtype == ECOSPA_BF16 && d.trans_a && d.trans_b)) return ECOSPA_ERR_SHAPE;      // column sums of A: the dY^T X form
+  if (d.dtype == ECOSPA_F32) return d.epi.kind < EPI_STORE || d.epi.kind > EPI_ACT ? ECOSPA_ERR_DTYPE : ECOSPA_OK;      // the rotary and gated forms are bf16 only
+  if (d.dtype != ECOSPA_BF16) return ECOSPA_ERR_DTYPE;
+  // 16-byte vector loads along the contiguous axis of each operand
+  const int ca = d.trans_a ? d.M : d.K, cb = d.trans_b ? d.N : d.K;
+  if (ca % 8 || cb % 8 || d.lda % 8 || d.ldb % 8) return ECOSPA_ERR_ALIGN;
+  if (!aligned16(d.A) || !aligned16(d.B)) return ECOSPA_ERR_ALIGN;
+  // the epilogue moves 8 columns at a time
+  if (d.N % 8 || d.epi.ldc % 8 || !aligned16(d.epi.c)) return ECOSPA_ERR_ALIGN;
+  if (d.epi.kind == EPI_SWIGLU && (!d.epi.c2 || d.epi.ldc2 % 4 || (reinterpret_cast<uintptr_t>(d.epi.c2) & 7u))) return ECOSPA_ERR_ALIGN;
+  if (d.epi.kind == EPI_ROPE && (!d.epi.rope_cos || !d.epi.rope_sin || !aligned16(d.epi.rope_cos) || !aligned16(d.epi.rope_sin) ||
+                                 d.epi.rope_kp % 8 || d.epi.rope_cols % 8 || d.epi.rope_L < 1 || d.epi.rope_qpk < 1)) return ECOSPA_ERR_ALIGN;
+  if (d.epi.bias && !aligned16(d.epi.bias)) return ECOSPA_ERR_ALIGN;
+  if (d.epi.kind == EPI_BIAS_ACT && (!d.epi.c2 || d.epi.ldc2 % 8 || !aligned16(d.epi.c2))) return ECOSPA_ERR_ALIGN;
+  if ((d.epi.kind == EPI_DACT || d.epi.kind == EPI_DSWIGLU) && (!d.epi.h || d.epi.ldh % 8 || !aligned16(d.epi.h)))
+    return ECOSPA_ERR_ALIGN;
+  if (d.epi.kind == EPI_DSWIGLU && d.epi.kp % 8) return ECOSPA_ERR_ALIGN;
+  if (d.splits > 1 && !aligned16(d.partial)) return ECOSPA_ERR_ALIGN;
+  if (!gemm_epi_built(d.splits > 1 ? 0 : d.trans_a, d.splits > 1 ? 0 : d.trans_b, d.epi.kind)) return ECOSPA_ERR_DTYPE;
+  return ECOSPA_OK;
+}
+
+// K range of a split: whole 64-deep slabs, the last split takes what is left
+static int ring_chunk(const GemmDesc& d, int splits) { return ((d.K + 63) / 64 + splits - 1) / splits * 64; }
+
+// Timing window of ecospa_profile_gemm: events around a launch and the operations it does.
+static bool prof_begin(ecospa_ctx* ctx) {
+  const bool on = ctx->prof_on && ctx->prof_n < ctx->prof_cap;
+  if (on) (void)hipEventRecord(ctx->prof_ev[2 * ctx->prof_n], ctx->stream);
+  return on;
+}
+static void prof_end(ecospa_ctx* ctx, double flop) {
+  (void)hipEventRecord(ctx->prof_ev[2 * ctx->prof_n + 1], ctx->stream);
+  ctx->prof_flop[ctx->prof_n++] = flop;
+}
+
+int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d) {
+  const int bad = gemm_check(d);
+  if (bad) return bad;
   const int splits = d.splits > 1 ? d.splits : 1;
   if (d.dtype == ECOSPA_BF16) {
-    // 16-byte vector loads along the contiguous axis of each operand
-    const int ca = d.trans_a ? d.M : d.K, cb = d.trans_b ? d.N : d.K;
-    if (ca % 8 || cb % 8 || d.lda % 8 || d.ldb % 8) return ECOSPA_ERR_ALIGN;
-    if (!aligned16(d.A) || !aligned16(d.B)) return ECOSPA_ERR_ALIGN;
-    // the epilogue moves 8 columns at a time
-    if (d.N % 8 || d.epi.ldc % 8 || !aligned16(d.epi.c)) return ECOSPA_ERR_ALIGN;
-    if (d.epi.kind == EPI_SWIGLU && (!d.epi.c2 || d.epi.ldc2 % 4 || (reinterpret_cast<uintptr_t>(d.epi.c2) & 7u))) return ECOSPA_ERR_ALIGN;
-    if (d.epi.kind == EPI_ROPE && (!d.epi.rope_cos || !d.epi.rope_sin || !aligned16(d.epi.rope_cos) || !aligned16(d.epi.rope_sin) ||
-                                   d.epi.rope_kp % 8 || d.epi.rope_cols % 8 || d.epi.rope_L < 1 || d.epi.rope_qpk < 1)) return ECOSPA_ERR_ALIGN;
-    if (d.epi.bias && !aligned16(d.epi.bias)) return ECOSPA_ERR_ALIGN;
-    if (d.epi.kind == EPI_BIAS_ACT && (!d.epi.c2 || d.epi.ldc2 % 8 || !aligned16(d.epi.c2))) return ECOSPA_ERR_ALIGN;
-    if ((d.epi.kind == EPI_DACT || d.epi.kind == EPI_DSWIGLU) && (!d.epi.h || d.epi.ldh % 8 || !aligned16(d.epi.h)))
-      return ECOSPA_ERR_ALIGN;
-    if (d.epi.kind == EPI_DSWIGLU && d.epi.kp % 8) return ECOSPA_ERR_ALIGN;
-    if (d.splits > 1 && !aligned16(d.partial)) return ECOSPA_ERR_ALIGN;
-    if (!gemm_epi_built(splits > 1 ? 0 : d.trans_a, splits > 1 ? 0 : d.trans_b, d.epi.kind)) return ECOSPA_ERR_DTYPE;
-    const bool prof = ctx->prof_on && ctx->prof_n < ctx->prof_cap;
-    if (prof) (void)hipEventRecord(ctx->prof_ev[2 * ctx->prof_n], ctx->stream);
-    // K range of a split: whole 64-deep slabs, the last split takes what is left
-    const int k_chunk = ((d.K + 63) / 64 + splits - 1) / splits * 64;
+    const bool prof = prof_begin(ctx);
+    const int k_chunk = ring_chunk(d, splits);
     double t;
     const int shape = ring_shape(d, splits, &t);
     hipError_t le;
@@ -310,23 +331,81 @@ int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d) {
     else if (d.trans_a || d.trans_b) le = gemm_ring_launch_mixed(ctx, d, shape, k_chunk);
     else le = gemm_ring_launch_nt(ctx, d, shape, k_chunk);
     if (le != hipSuccess) return hip_fail(ctx, le, "gemm launch");
-    if (prof) {
-      (void)hipEventRecord(ctx->prof_ev[2 * ctx->prof_n + 1], ctx->stream);
-      ctx->prof_flop[ctx->prof_n++] = 2.0 * d.M * d.N * d.K;
-    }
+    if (prof) prof_end(ctx, 2.0 * d.M * d.N * d.K);
     ECOSPA_CHECK_LAUNCH(ctx, "gemm_bf16_ring_kernel");
-  } else if (d.dtype == ECOSPA_F32) {
-    if (d.epi.kind < EPI_STORE || d.epi.kind > EPI_ACT) return ECOSPA_ERR_DTYPE;      // the rotary and gated forms are bf16 only
+  } else {
     if (!d.trans_a && !d.trans_b) launch_f32<false, false>(ctx, d, splits);
     else if (!d.trans_a) launch_f32<false, true>(ctx, d, splits);
     else if (d.trans_b) launch_f32<true, true>(ctx, d, splits);
     else launch_f32<true, false>(ctx, d, splits);
     ECOSPA_CHECK_LAUNCH(ctx, "gemm_f32_kernel");
-  } else {
-    return ECOSPA_ERR_DTYPE;
   }
   if (splits > 1 && !d.defer_reduce) return ecospa_gemm_reduce(ctx, d);
   return ECOSPA_OK;
+}
+
+// Byte ranges that a descriptor reads and writes.
+struct GemmRange {
+  uintptr_t lo, hi;
+  bool apart(const GemmRange& o) const { return hi <= o.lo || o.hi <= lo; }
+};
+static GemmRange mat_range(const void* p, long long rows, long long ld, long long cols, int bytes) {
+  const uintptr_t lo = reinterpret_cast<uintptr_t>(p);
+  return {lo, p ? lo + static_cast<uintptr_t>(((rows - 1) * ld + cols) * bytes) : lo};
+}
+// Neither reads what the other writes, nor do they write the same (a caller may pass one buffer for an input and a gradient: then they
+// have to run in order).
+static bool gemm_independent(const GemmDesc& w, const GemmDesc& x) {
+  const int es = static_cast<int>(dtype_size(w.dtype)), splits = w.splits > 1 ? w.splits : 1;
+  const GemmRange in_w[2] = {mat_range(w.A, w.K, w.lda, w.M, es), mat_range(w.B, w.K, w.ldb, w.N, es)};
+  const GemmRange in_x[2] = {x.trans_a ? mat_range(x.A, x.K, x.lda, x.M, es) : mat_range(x.A, x.M, x.lda, x.K, es),
+                             x.trans_b ? mat_range(x.B, x.K, x.ldb, x.N, es) : mat_range(x.B, x.N, x.ldb, x.K, es)};
+  const GemmRange out_x = mat_range(x.epi.c, x.M, x.epi.ldc, x.N, es);
+  const GemmRange out_w[2] = {splits > 1 ? mat_range(w.partial, splits, static_cast<long long>(w.M) * w.N, static_cast<long long>(w.M) * w.N, 4)
+                                         : mat_range(w.epi.c, w.M, w.epi.ldc, w.N, es),
+                              mat_range(w.colsum, w.colsum ? ecospa_gemm_colsum_rows(w) : 1, w.M, w.M, 4)};
+  bool ok = true;
+  for (int i = 0; i < 2; ++i) {
+    ok = ok && out_x.apart(in_w[i]) && out_x.apart(out_w[i]);
+    for (int j = 0; j < 2; ++j) ok = ok && out_w[i].apart(in_x[j]);
+  }
+  return ok;
+}
+
+// Whether one launch is the better way for two contractions of these shapes: where together they leave a good part of a round of compute
+// units (64 of 512) to nobody, which the other's tiles then take.  Forward and backward of a 384-wide layer on 12017 tokens (252 + 189, 96
+// + 188 and 216 + 189 workgroups) 251 -> 242 us; pairs of full rounds gain nothing (256 + 256 workgroups: -0.6 .. +5 us, the tiles
+// that share operands no longer run side by side).
+static bool pair_pays(const GemmDesc& w, int splits, int ws, const GemmDesc& x, int xs) {
+  const auto idle = [](const GemmDesc& d, int sp, const RingShape& r) {
+    const long long n = static_cast<long long>((d.M + r.bm - 1) / r.bm) * ((d.N + r.bn - 1) / r.bn) * sp;
+    return static_cast<int>((256 - n % 256) % 256);
+  };
+  return idle(w, splits, RING_SHAPES[ws]) + idle(x, 1, RING_SHAPES[xs]) >= 64;
+}
+
+int ecospa_gemm_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x) {
+  int rc;
+  if ((rc = gemm_check(w)) || (rc = gemm_check(x))) return rc;
+  if (w.dtype == ECOSPA_BF16 && x.dtype == ECOSPA_BF16 && w.trans_a && w.trans_b && !x.trans_a && !x.trans_b && x.splits <= 1 &&
+      x.epi.kind == EPI_STORE && (w.splits <= 1 || w.defer_reduce) && !ring_wide(w) && !ring_wide(x) && gemm_independent(w, x)) {
+    const int splits = w.splits > 1 ? w.splits : 1;
+    double tw, tx;
+    const int ws = ring_shape(w, splits, &tw), xs = ring_shape(x, 1, &tx);
+    const RingShape& r = RING_SHAPES[ws];
+    if (r.bn == 128 && ((GEMM_PAIR_X >> xs) & 1) && pair_pays(w, splits, ws, x, xs) && !(gemm_flow_takes(w) && flow_time(w) < tw) && !(gemm_flow_takes(x) && flow_time(x) < tx)) {
+      const bool prof = prof_begin(ctx);
+      const int k_chunk = ring_chunk(w, splits);
+      const hipError_t le = r.bm == 64 ? gemm_pair_launch_64(ctx, w, x, xs, k_chunk) : r.bm == 128 ? gemm_pair_launch_128(ctx, w, x, xs, k_chunk)
+                          : r.bm == 192 ? gemm_pair_launch_192(ctx, w, x, xs, k_chunk) : gemm_pair_launch_256(ctx, w, x, xs, k_chunk);
+      if (le != hipSuccess) return hip_fail(ctx, le, "gemm pair launch");
+      if (prof) prof_end(ctx, 2.0 * w.M * w.N * w.K + 2.0 * x.M * x.N * x.K);
+      ECOSPA_CHECK_LAUNCH(ctx, "gemm_bf16_pair_kernel");
+      return ECOSPA_OK;
+    }
+  }
+  if ((rc = ecospa_gemm(ctx, w))) return rc;
+  return ecospa_gemm(ctx, x);
 }
 
 int ecospa_gemm_reduce(ecospa_ctx* ctx, const GemmDesc& d) {

@@ -155,8 +155,8 @@ __device__ __forceinline__ void ring_mfma(ring_f4& c, const bf16x8_t& a, const b
 // range of tile ids, and with split K the splits are spread over the XCDs first (8 / splits XCDs per split,
 // or splits / 8 splits per XCD): the tiles of one split read one K range of both operands, so an XCD's L2
 // then holds that range once instead of every XCD fetching all of K for its share of the tiles.
-__device__ __forceinline__ void gemm_work_item(int splits, int& tile, int& z) {
-  const int id = blockIdx.x, nb = gridDim.x, tiles = nb / splits;
+__device__ __forceinline__ void gemm_work_item(int id, int nb, int splits, int& tile, int& z) {      // workgroup id of nb
+  const int tiles = nb / splits;
   if (nb & 7) {                                   // no even deal: plain order
     z = id / tiles;
     tile = id - z * tiles;
@@ -178,10 +178,10 @@ __device__ __forceinline__ void gemm_work_item(int splits, int& tile, int& z) {
   }
 }
 
+// One output tile (of one K split): that of workgroup `block` of `blocks`.
 // EPIS: bit mask of the epilogue kinds the instantiation carries; CS: column sums of a K-slow A (GemmDesc::colsum); WIDE: see ring_off.
-template <int BM, int BN, int NS, bool TA, bool TB, bool CS, int EPIS, bool WIDE = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void gemm_bf16_ring_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
+template <int BM, int BN, int NS, bool TA, bool TB, bool CS, int EPIS, bool WIDE>
+__device__ __forceinline__ void ring_tile(const GemmDesc& d, int tiles_n, int k_chunk, int block, int blocks) {
   constexpr int WTM = BM / 2, WTN = BN / 2, FM = WTM / 16, FN = WTN / 16, S = RING_BK / 32, NM = FM * FN, NR = FM + FN;
   constexpr int STAGE = (BM + BN) * RING_BK;
   static_assert(FN % 2 == 0, "the epilogue pairs column blocks");
@@ -195,9 +195,9 @@ void gemm_bf16_ring_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
   // near-square block of C and share operand rows in its L2
   int id, zsplit;
   const int nsplit = d.splits > 1 ? d.splits : 1;
-  gemm_work_item(nsplit, id, zsplit);
+  gemm_work_item(block, blocks, nsplit, id, zsplit);
   constexpr int GROUP_M = BM >= 192 ? 4 : (BM >= 128 ? 8 : 16);
-  const int tiles_m = static_cast<int>(gridDim.x) / nsplit / tiles_n;
+  const int tiles_m = blocks / nsplit / tiles_n;
   const int band = id / (GROUP_M * tiles_n), in_band = id - band * (GROUP_M * tiles_n);
   const int band_rows = min(GROUP_M, tiles_m - band * GROUP_M);
   const int tile_col = in_band / band_rows;
@@ -546,6 +546,12 @@ void gemm_bf16_ring_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
   });
 }
 
+template <int BM, int BN, int NS, bool TA, bool TB, bool CS, int EPIS, bool WIDE = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void gemm_bf16_ring_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
+  ring_tile<BM, BN, NS, TA, TB, CS, EPIS, WIDE>(d, tiles_n, k_chunk, blockIdx.x, gridDim.x);
+}
+
 // ---------------------------------------------------------------------------------------------
 // launch
 template <int BM, int BN, int NS, bool TA, bool TB, bool CS, int EPIS, bool WIDE = false>
@@ -561,5 +567,29 @@ static hipError_t ring_launch_shape(ecospa_ctx* ctx, const GemmDesc& d, int k_ch
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(kern, dim3(tm * tn * splits), dim3(256), lds_bytes, ctx->stream, d, tn, k_chunk);
+  return hipGetLastError();
+}
+
+// Two contractions that do not depend on each other, a weight gradient dY^T X and an x W^T with a plain store, in one launch: the first
+// n_tt workgroups take the tiles of the first.  Alone, each of the two pays for its launch (2.5 us), its first slabs (2 us) and its last
+// stores with the matrix units idle, and often fills a part of the compute units only (when it is taken: pair_pays() in gemm.hip).
+template <int TM, int TN, int TS, bool CS, int XM, int XN, int XS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void gemm_bf16_pair_kernel(const GemmDesc w, const GemmDesc x, int w_tiles_n, int w_k_chunk, int n_tt, int x_tiles_n) {
+  const int block = blockIdx.x;
+  if (block < n_tt) ring_tile<TM, TN, TS, true, true, CS, GEMM_EPIS_TX, false>(w, w_tiles_n, w_k_chunk, block, n_tt);
+  else ring_tile<XM, XN, XS, false, false, false, 1 << EPI_STORE, false>(x, x_tiles_n, (x.K + 63) / 64 * 64, block - n_tt, gridDim.x - n_tt);
+}
+template <int TM, int TN, int TS, bool CS, int XM, int XN, int XS>
+static hipError_t ring_launch_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int w_k_chunk) {
+  const int splits = w.splits > 1 ? w.splits : 1, wn = (w.N + TN - 1) / TN, xn = (x.N + XN - 1) / XN;
+  const int n_tt = (w.M + TM - 1) / TM * wn * splits, n_nt = (x.M + XM - 1) / XM * xn;
+  constexpr int lds_w = TS * (TM + TN) * RING_BK * 2, lds_x = XS * (XM + XN) * RING_BK * 2, lds_bytes = lds_w > lds_x ? lds_w : lds_x;
+  static_assert(lds_bytes > 64 * 1024 && lds_bytes <= 160 * 1024, "LDS of a compute unit");
+  auto kern = gemm_bf16_pair_kernel<TM, TN, TS, CS, XM, XN, XS>;
+  static LdsAttrOnce attr_once;
+  const hipError_t e = attr_once.ensure(reinterpret_cast<const void*>(kern), lds_bytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(n_tt + n_nt), dim3(256), lds_bytes, ctx->stream, w, x, wn, w_k_chunk, n_tt, xn);
   return hipGetLastError();
 }
