@@ -176,28 +176,30 @@ static int ffn_backward_body(ecospa_ctx* ctx, const ecospa_block_desc& d, const 
                              const ecospa_saved& sv, void* dx, const ecospa_grads& gr) {
   const int T = d.B * d.L, kp = d.kp_ff, nh = is_gated(d) ? 2 * kp : kp, dm = d.d_model;
   int rc;
-  // dH = (dY W_2) * act'(H)
-  {
-    GemmDesc g = d.w_2_t ? gemm_desc(d.dtype, T, kp, dm, dy, dm, 0, d.w_2_t, d.ld_w2t, 0)     // transposed copy [kp, d_model]
-                         : gemm_desc(d.dtype, T, kp, dm, dy, dm, 0, d.w_2, d.ld_w2, 1);
-    g.epi.c = w.dh; g.epi.ldc = nh; g.epi.h = sv.hpre; g.epi.ldh = nh; g.epi.act = d.act; g.epi.kp = kp;
-    g.epi.kind = is_gated(d) ? EPI_DSWIGLU : EPI_DACT;
-    block_token_split(g, w);
-    if ((rc = ecospa_gemm(ctx, g))) return rc;
-  }
-  // dW_2 = dY^T A,  dW_1 = dH^T X
+  // dH = (dY W_2) * act'(H)  and  dW_2 = dY^T A, which does not need it
+  GemmDesc gh = d.w_2_t ? gemm_desc(d.dtype, T, kp, dm, dy, dm, 0, d.w_2_t, d.ld_w2t, 0)     // transposed copy [kp, d_model]
+                        : gemm_desc(d.dtype, T, kp, dm, dy, dm, 0, d.w_2, d.ld_w2, 1);
+  gh.epi.c = w.dh; gh.epi.ldc = nh; gh.epi.h = sv.hpre; gh.epi.ldh = nh; gh.epi.act = d.act; gh.epi.kp = kp;
+  gh.epi.kind = is_gated(d) ? EPI_DSWIGLU : EPI_DACT;
+  block_token_split(gh, w);
   GemmDesc g2 = gemm_desc(d.dtype, dm, kp, T, dy, dm, 1, sv.act, kp, 1);
   g2.splits = ecospa_gemm_splits(d.dtype, dm, kp, T); g2.partial = w.partial; g2.defer_reduce = 1;
   g2.epi.kind = EPI_STORE; g2.epi.c = gr.dw_2; g2.epi.ldc = gr.ld_dw2;
-  // the bias gradients are column sums of dY and dH: the weight-gradient contractions read exactly these as
-  // their K-slow operand and add them up on the way (bf16 kernels; otherwise a column-sum job below)
-  const bool fused_db = d.dtype == ECOSPA_BF16;
-  if (fused_db && gr.dw_2 && gr.db_2) g2.colsum = w.colsum;
-  if (gr.dw_2 && (rc = ecospa_gemm(ctx, g2))) return rc;
+  // the bias gradients are column sums of dY and dH: the weight-gradient contractions read exactly these as their K-slow operand and add
+  // them up on the way - bf16 in partial rows that the tail launch adds, fp32 to the end
+  const bool bf = d.dtype == ECOSPA_BF16;
+  if (gr.dw_2 && gr.db_2) g2.colsum = bf ? w.colsum : static_cast<float*>(gr.db_2);
+  if (gr.dw_2 && !bf) {
+    if ((rc = ecospa_gemm_pair(ctx, g2, gh, 1))) return rc;
+  } else {
+    if ((rc = ecospa_gemm(ctx, gh))) return rc;
+    if (gr.dw_2 && (rc = ecospa_gemm(ctx, g2))) return rc;
+  }
+  // dW_1 = dH^T X
   GemmDesc g1 = gemm_desc(d.dtype, nh, dm, T, w.dh, nh, 1, x, dm, 1);
   g1.splits = ecospa_gemm_splits(d.dtype, nh, dm, T); g1.partial = w.partial2; g1.defer_reduce = 1;
   g1.epi.kind = EPI_STORE; g1.epi.c = gr.dw_1; g1.epi.ldc = gr.ld_dw1;
-  if (fused_db && gr.dw_1 && gr.db_1) g1.colsum = w.colsum2;
+  if (gr.dw_1 && gr.db_1) g1.colsum = bf ? w.colsum2 : static_cast<float*>(gr.db_1);
   // dX = dH W_1, beside dW_1
   if (dx) {
     GemmDesc g = d.w_1_t ? gemm_desc(d.dtype, T, dm, nh, w.dh, nh, 0, d.w_1_t, d.ld_w1t, 0)   // transposed copy [d_model, nh]
@@ -212,9 +214,10 @@ static int ffn_backward_body(ecospa_ctx* ctx, const ecospa_block_desc& d, const 
   memset(&aux, 0, sizeof(aux));
   if (gr.dw_2 && g2.splits > 1) aux.reduce[aux.n_reduce++] = g2;
   if (gr.dw_1 && g1.splits > 1) aux.reduce[aux.n_reduce++] = g1;
-  if (gr.db_2) aux.colsum[aux.n_colsum++] = g2.colsum ? AuxColsum{g2.colsum, dm, ecospa_gemm_colsum_rows(g2), dm, ECOSPA_F32, gr.db_2, d.dtype}
+  const bool summed_2 = g2.colsum && !bf, summed_1 = g1.colsum && !bf;
+  if (gr.db_2 && !summed_2) aux.colsum[aux.n_colsum++] = g2.colsum ? AuxColsum{g2.colsum, dm, ecospa_gemm_colsum_rows(g2), dm, ECOSPA_F32, gr.db_2, d.dtype}
                                                        : AuxColsum{dy, dm, T, dm, d.dtype, gr.db_2, 0};
-  if (gr.db_1) aux.colsum[aux.n_colsum++] = g1.colsum ? AuxColsum{g1.colsum, nh, ecospa_gemm_colsum_rows(g1), nh, ECOSPA_F32, gr.db_1, d.dtype}
+  if (gr.db_1 && !summed_1) aux.colsum[aux.n_colsum++] = g1.colsum ? AuxColsum{g1.colsum, nh, ecospa_gemm_colsum_rows(g1), nh, ECOSPA_F32, gr.db_1, d.dtype}
                                                        : AuxColsum{w.dh, nh, T, nh, d.dtype, gr.db_1, 0};
   return ecospa_aux_launch(ctx, aux);
 }

@@ -50,7 +50,7 @@ struct GemmDesc {
   int splits;        // > 1: split K, fp32 partials in `partial`, reduced in a fixed order
   float* partial;    // [splits][M][N] when splits > 1
   int defer_reduce;  // splits > 1: only write the partials; the caller runs ecospa_gemm_reduce later
-  float* colsum;     // optional, bf16 contractions with a K-slow A operand (dY^T X): [ecospa_gemm_colsum_rows(d)][M] partial
+  float* colsum;     // optional, contractions with a K-slow A operand (dY^T X; fp32: K unsplit): [ecospa_gemm_colsum_rows(d)][M] partial
                      // column sums of A, sum_k A(m, k) over disjoint parts of K - the bias gradient that belongs to the
                      // weight gradient, added up from the operand's fragments; the rows add up to the sums
   GemmEpi epi;
@@ -59,8 +59,8 @@ struct GemmDesc {
 // Launch on ctx->stream.  bf16 and fp32 both run on MFMA tiles.
 int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d);
 // Two contractions that do not depend on each other: w a weight gradient (dY^T X, bf16 or fp32; its reduction deferred where K is split), x
-// over the same tokens.  One launch where that is built for the two, otherwise w, then x.
-int ecospa_gemm_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x);
+// over the same tokens.  One launch where that is built for the two and pays, otherwise w, then x (x_first: the other way round).
+int ecospa_gemm_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int x_first = 0);
 // Rows (of M floats) of the partial column sums that the launch of d writes to d.colsum.
 int ecospa_gemm_colsum_rows(const GemmDesc& d);
 // Second half of a split-K contraction launched with defer_reduce: fixed-order sum of the partials,
@@ -137,8 +137,8 @@ int ecospa_aux_launch(ecospa_ctx* ctx, const AuxBatch& b);
 // Tail of the standard normal distribution, Phi(-|x|), by the rational approximation 7.1.26 of Abramowitz & Stegun for erfc (absolute
 // error about 3e-7 when evaluated in fp32: far below bf16 resolution, and a relative Frobenius error near 1e-7 on GELU outputs): one
 // reciprocal, one exponential and a degree-5 Horner chain instead of the library erf, the factors 1/sqrt(2) and 1/2 folded into the
-// constants.  `e` returns exp(-x^2 / 2), which the derivative needs as well.  What follows from the tail without a comparison:
-// x Phi(x) = max(x, 0) - |x| Phi(-|x|),  Phi(x) = 1/2 + sign(x) (1/2 - Phi(-|x|)).
+// constants.  `e` returns exp(-x^2 / 2), which the derivative needs as well.  GELU needs no comparison: x Phi(x) = max(x, 0) - |x| Phi(-|x|);
+// the derivative's Phi(x) keeps one, or negative arguments would lose to cancellation.
 // Vector instructions bound the activation epilogues: 15 and two transcendentals per element where the form with Phi itself took 20 (forward
 // and backward of a 384-wide GELU layer on 12017 tokens 256.1 -> 253.4 us, 1024-wide layer step on 8192 tokens 569.5 -> 565.5 us).
 __device__ __forceinline__ float act_tail_t(float x) { return __builtin_amdgcn_rcpf(__builtin_fmaf(fabsf(x), 0.23164188f, 1.f)); }
@@ -171,7 +171,7 @@ __device__ __forceinline__ float act_gelu_grad(float x, int act) {
   }
   float e;
   const float tail = act_norm_tail(x, e);
-  return __builtin_fmaf(x * 0.3989422804014327f, e, 0.5f + __builtin_copysignf(0.5f - tail, x));
+  return __builtin_fmaf(x, 0.3989422804014327f * e, x < 0.f ? tail : 1.f - tail);
 }
 __device__ __forceinline__ float act_sigmoid(float x) { return 1.f / (1.f + __expf(-x)); }
 // The same with the hardware's reciprocal (1 ulp) in place of the IEEE division (nine instructions more): for results that are

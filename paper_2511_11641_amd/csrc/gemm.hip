@@ -52,13 +52,15 @@ struct F32Frags {
 
 #define F32_CHAIN 256
 
+// One output tile of K split z.  A K-slow A (dY^T X) also gives its column sums (GemmDesc::colsum, the bias gradient; K unsplit): the
+// workgroups of the first tile column add the operand's values up as they pass, sixteen at a time in a tree, the sums of those with what their additions round away.
 template <int WM, int WN, int WK, bool TA, bool TB>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
+__device__ __forceinline__ void f32_tile(const GemmDesc& d, int tiles_n, int k_chunk, int block, int z) {
   static_assert(WM * WN * WK == 4 && (WK == 1 || WK == 4), "four wavefronts");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hh = lane >> 5;
   const int wk = wave % WK, wmn = wave / WK, wm = wmn / WN, wn = wmn % WN;
-  const int m0 = (static_cast<int>(blockIdx.x) / tiles_n) * (32 * WM) + wm * 32, n0 = (static_cast<int>(blockIdx.x) % tiles_n) * (32 * WN) + wn * 32;
-  const int z0 = blockIdx.z * k_chunk, z1 = min(d.K, z0 + k_chunk);
+  const int m0 = (block / tiles_n) * (32 * WM) + wm * 32, n0 = (block % tiles_n) * (32 * WN) + wn * 32;
+  const int z0 = z * k_chunk, z1 = min(d.K, z0 + k_chunk);
   const int per = ((z1 - z0 + WK - 1) / WK + 31) / 32 * 32;       // K range of a wavefront: whole groups of 32
   const int k_begin = min(z0 + wk * per, z1), k_end = min(k_begin + per, z1);
   F32Frags<TA> fa;
@@ -70,9 +72,19 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmDesc d, int til
   for (int r = 0; r < 16; ++r) acc[r] = sum[r] = 0.f;
   float a[2][16], b[2][16];
   const int nc = (k_end - k_begin) / 32;
+  const bool sums = TA && TB && d.colsum && n0 == 0;
+  float cs = 0.f, cs_lost = 0.f;
   auto products = [&](const float (&x)[16], const float (&y)[16]) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[j], y[j], acc, 0, 0, 0);
+    if (TA && TB && sums) {
+      float t[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = x[2 * j] + x[2 * j + 1];
+      const float v = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7])), sum2 = cs + v, got = sum2 - cs;
+      cs_lost += (cs - (sum2 - got)) + (v - got);       // what the addition rounded away
+      cs = sum2;
+    }
   };
   if (nc > 0) { fa.load(a[0], k_begin, hh); fb.load(b[0], k_begin, hh); }
   int c = 0;
@@ -97,7 +109,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmDesc d, int til
   }
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] += sum[r];
-  float* part = d.splits > 1 ? d.partial + static_cast<long long>(blockIdx.z) * d.M * d.N : nullptr;
+  float* part = d.splits > 1 ? d.partial + static_cast<long long>(z) * d.M * d.N : nullptr;
+  if constexpr (TA && TB) {
+    cs += cs_lost;
+    cs += __shfl_xor(cs, 32, 64);      // the other half of the k
+  }
   auto put = [&](int m, int n, float v) __attribute__((always_inline)) {
     if (m < d.M && n < d.N) {
       if (part) part[static_cast<long long>(m) * d.N + n] = v;
@@ -106,10 +122,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmDesc d, int til
   };
   // accumulator layout: column lane % 32, row 8 (r / 4) + 4 (lane / 32) + r % 4
   if constexpr (WK == 4) {
-    __shared__ float red[4][32][33];
+    __shared__ float red[4][32][33], red_cs[4][32];
 #pragma unroll
     for (int r = 0; r < 16; ++r) red[wave][8 * (r / 4) + 4 * hh + r % 4][l32] = acc[r];
+    if (TA && TB && hh == 0) red_cs[wave][l32] = cs;
     __syncthreads();
+    if (TA && TB && sums && threadIdx.x < 32 && m0 + static_cast<int>(threadIdx.x) < d.M)
+      d.colsum[m0 + threadIdx.x] = (red_cs[0][threadIdx.x] + red_cs[1][threadIdx.x]) + (red_cs[2][threadIdx.x] + red_cs[3][threadIdx.x]);
     const int n = threadIdx.x & 31;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -119,15 +138,33 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmDesc d, int til
   } else {
 #pragma unroll
     for (int r = 0; r < 16; ++r) put(m0 + 8 * (r / 4) + 4 * hh + r % 4, n0 + l32, acc[r]);
+    if (TA && TB && sums && hh == 0 && m0 + l32 < d.M) d.colsum[m0 + l32] = cs;
   }
+}
+
+template <int WM, int WN, int WK, bool TA, bool TB>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
+  f32_tile<WM, WN, WK, TA, TB>(d, tiles_n, k_chunk, blockIdx.x, blockIdx.z);
+}
+// A weight gradient and a contraction over the tokens that do not depend on each other, in one launch: the first n_w workgroups take the
+// tiles of the first.  Launches of this size last as long as one of their workgroups does, 6 - 8 us.
+template <bool XTB>
+__global__ __launch_bounds__(256) void gemm_f32_pair_kernel(const GemmDesc w, const GemmDesc x, int w_tiles_n, int n_w, int x_tiles_n) {
+  const int block = blockIdx.x;
+  if (block < n_w) f32_tile<1, 1, 4, true, true>(w, w_tiles_n, w.K, block, 0);
+  else f32_tile<1, 1, 4, false, XTB>(x, x_tiles_n, x.K, block - n_w, 0);
+}
+
+// 64 x 64 tiles once they fill the compute units (half the operand traffic per product); below that K is what there is to share out
+static bool f32_wide_tiles(const GemmDesc& d, int splits) {
+  return static_cast<long long>((d.M + 63) / 64) * ((d.N + 63) / 64) * splits >= 512;
 }
 
 template <bool TA, bool TB>
 static void launch_f32(ecospa_ctx* ctx, const GemmDesc& d, int splits) {
   const int k_chunk = (d.K + splits - 1) / splits;
   const int tm = (d.M + 63) / 64, tn = (d.N + 63) / 64, sm = (d.M + 31) / 32, sn = (d.N + 31) / 32;
-  // 64 x 64 tiles once they fill the compute units (half the operand traffic per product); below that K is what there is to share out
-  if (static_cast<long long>(tm) * tn * splits >= 512)
+  if (f32_wide_tiles(d, splits))
     hipLaunchKernelGGL((gemm_f32_kernel<2, 2, 1, TA, TB>), dim3(tm * tn, 1, splits), dim3(256), 0, ctx->stream, d, tn, k_chunk);
   else
     hipLaunchKernelGGL((gemm_f32_kernel<1, 1, 4, TA, TB>), dim3(sm * sn, 1, splits), dim3(256), 0, ctx->stream, d, sn, k_chunk);
@@ -280,7 +317,7 @@ static int gemm_check(const GemmDesc& d) {
   if (d.M < 1 || d.N < 1 || d.K < 1) return ECOSPA_ERR_SHAPE;
   if (!d.A || !d.B || (!d.epi.c && d.epi.kind != EPI_SWIGLU)) return ECOSPA_ERR_NULL;      // the gated epilogue may skip its first output
   if (d.splits > 1 && !d.partial) return ECOSPA_ERR_WORKSPACE;
-  if (d.colsum && !(d.dtype == ECOSPA_BF16 && d.trans_a && d.trans_b)) return ECOSPA_ERR_SHAPE;      // column sums of A: the dY^T X form
+  if (d.colsum && !(d.trans_a && d.trans_b && (d.dtype == ECOSPA_BF16 || d.splits <= 1))) return ECOSPA_ERR_SHAPE;      // column sums of A: the dY^T X form
   if (d.dtype == ECOSPA_F32) return d.epi.kind < EPI_STORE || d.epi.kind > EPI_ACT ? ECOSPA_ERR_DTYPE : ECOSPA_OK;      // the rotary and gated forms are bf16 only
   if (d.dtype != ECOSPA_BF16) return ECOSPA_ERR_DTYPE;
   // 16-byte vector loads along the contiguous axis of each operand
@@ -360,13 +397,14 @@ static bool gemm_independent(const GemmDesc& w, const GemmDesc& x) {
   const GemmRange in_w[2] = {mat_range(w.A, w.K, w.lda, w.M, es), mat_range(w.B, w.K, w.ldb, w.N, es)};
   const GemmRange in_x[2] = {x.trans_a ? mat_range(x.A, x.K, x.lda, x.M, es) : mat_range(x.A, x.M, x.lda, x.K, es),
                              x.trans_b ? mat_range(x.B, x.K, x.ldb, x.N, es) : mat_range(x.B, x.N, x.ldb, x.K, es)};
-  const GemmRange out_x = mat_range(x.epi.c, x.M, x.epi.ldc, x.N, es);
+  const long long wide = x.epi.kind == EPI_DSWIGLU ? 2ll * x.N : x.N;
+  const GemmRange out_x = mat_range(x.epi.c, x.M, x.epi.ldc, wide, es), side_x = mat_range(x.epi.h, x.M, x.epi.ldh, wide, es);
   const GemmRange out_w[2] = {splits > 1 ? mat_range(w.partial, splits, static_cast<long long>(w.M) * w.N, static_cast<long long>(w.M) * w.N, 4)
                                          : mat_range(w.epi.c, w.M, w.epi.ldc, w.N, es),
                               mat_range(w.colsum, w.colsum ? ecospa_gemm_colsum_rows(w) : 1, w.M, w.M, 4)};
   bool ok = true;
   for (int i = 0; i < 2; ++i) {
-    ok = ok && out_x.apart(in_w[i]) && out_x.apart(out_w[i]);
+    ok = ok && out_x.apart(in_w[i]) && out_x.apart(out_w[i]) && side_x.apart(out_w[i]);
     for (int j = 0; j < 2; ++j) ok = ok && out_w[i].apart(in_x[j]);
   }
   return ok;
@@ -384,7 +422,7 @@ static bool pair_pays(const GemmDesc& w, int splits, int ws, const GemmDesc& x, 
   return idle(w, splits, RING_SHAPES[ws]) + idle(x, 1, RING_SHAPES[xs]) >= 64;
 }
 
-int ecospa_gemm_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x) {
+int ecospa_gemm_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int x_first) {
   int rc;
   if ((rc = gemm_check(w)) || (rc = gemm_check(x))) return rc;
   if (w.dtype == ECOSPA_BF16 && x.dtype == ECOSPA_BF16 && w.trans_a && w.trans_b && !x.trans_a && !x.trans_b && x.splits <= 1 &&
@@ -404,8 +442,18 @@ int ecospa_gemm_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x) {
       return ECOSPA_OK;
     }
   }
-  if ((rc = ecospa_gemm(ctx, w))) return rc;
-  return ecospa_gemm(ctx, x);
+  // fp32: while both are on tiles that share out K, that is bound by the latency of their launches (forward and backward of 512 tokens,
+  // 256 -> 512 units: 71.4 -> 57.4 us with two pairs and the bias gradients out of the weight gradients, eight launches instead of eleven)
+  if (w.dtype == ECOSPA_F32 && x.dtype == ECOSPA_F32 && w.trans_a && w.trans_b && !x.trans_a && w.splits <= 1 && x.splits <= 1 &&
+      !f32_wide_tiles(w, 1) && !f32_wide_tiles(x, 1) && gemm_independent(w, x)) {
+    const int wn = (w.N + 31) / 32, xn = (x.N + 31) / 32, n_w = (w.M + 31) / 32 * wn, n_x = (x.M + 31) / 32 * xn;
+    if (x.trans_b) hipLaunchKernelGGL((gemm_f32_pair_kernel<true>), dim3(n_w + n_x), dim3(256), 0, ctx->stream, w, x, wn, n_w, xn);
+    else hipLaunchKernelGGL((gemm_f32_pair_kernel<false>), dim3(n_w + n_x), dim3(256), 0, ctx->stream, w, x, wn, n_w, xn);
+    ECOSPA_CHECK_LAUNCH(ctx, "gemm_f32_pair_kernel");
+    return ECOSPA_OK;
+  }
+  if ((rc = ecospa_gemm(ctx, x_first ? x : w))) return rc;
+  return ecospa_gemm(ctx, x_first ? w : x);
 }
 
 int ecospa_gemm_reduce(ecospa_ctx* ctx, const GemmDesc& d) {

@@ -99,10 +99,10 @@ struct FlowEpi {
       if constexpr (ST == 6) p[q] = p[q] * t[q];
       if constexpr (ST == 7) p[q] = p[q] * e[q];
       if constexpr (ST == 8) {
-        if constexpr (KIND == EPI_DACT) z[q] = 0.5f + __builtin_copysignf(0.5f - p[q], a);
+        if constexpr (KIND == EPI_DACT) z[q] = a < 0.f ? p[q] : 1.f - p[q];
         else z[q] = act_gelu_of_tail(a, p[q]);
       }
-      if constexpr (ST == 9) x[q] *= __builtin_fmaf(a * 0.3989422804014327f, e[q], z[q]);
+      if constexpr (ST == 9) x[q] *= __builtin_fmaf(a, 0.3989422804014327f * e[q], z[q]);
     } else if constexpr (KIND == EPI_SWIGLU) {
       // columns are (gate, up) pairs: four units, two steps per stage
       const int u = q & 3;

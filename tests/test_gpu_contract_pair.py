@@ -9,7 +9,7 @@ from paper_2511_11641_amd import binding as B
 from util import GemmDesc
 
 pytestmark = pytest.mark.gpu
-ONE, PAIR, ROWS = "_Z11ecospa_gemmP10ecospa_ctxRK8GemmDesc", "_Z16ecospa_gemm_pairP10ecospa_ctxRK8GemmDescS3_", "_Z23ecospa_gemm_colsum_rowsRK8GemmDesc"
+ONE, PAIR, ROWS = "_Z11ecospa_gemmP10ecospa_ctxRK8GemmDesc", "_Z16ecospa_gemm_pairP10ecospa_ctxRK8GemmDescS3_i", "_Z23ecospa_gemm_colsum_rowsRK8GemmDesc"
 
 
 @pytest.fixture(scope="module")
@@ -42,7 +42,7 @@ def test_one_launch_gives_what_two_give(ctx, w_tile, x_tile, T, d, n, splits, su
             w.colsum = cs.data_ptr()
         g, dx = _desc(T, d, n, dh, wt, False, x_tile)
         if pair:
-            assert getattr(ctx.lib, PAIR)(ctx.h, C.byref(w), C.byref(g)) == B.OK
+            assert getattr(ctx.lib, PAIR)(ctx.h, C.byref(w), C.byref(g), 0) == B.OK
         else:
             assert getattr(ctx.lib, ONE)(ctx.h, C.byref(w)) == B.OK and getattr(ctx.lib, ONE)(ctx.h, C.byref(g)) == B.OK
         out.append((dw, part, cs, dx))
@@ -59,6 +59,22 @@ def test_an_input_that_the_other_overwrites_is_read_first(ctx):
     w, dw = _desc(392, 264, 1379, dh, x, True, 0)
     g, _ = _desc(1379, 264, 392, dh, wt, False, 0)
     g.epi.c = x.data_ptr()                    # the input gradient goes where the weight gradient's input is
-    assert getattr(ctx.lib, PAIR)(ctx.h, C.byref(w), C.byref(g)) == B.OK
+    assert getattr(ctx.lib, PAIR)(ctx.h, C.byref(w), C.byref(g), 0) == B.OK
     # bf16 rounding of the result: 2^-9 of each element at most
     assert float((dw.float() - want).norm() / want.norm()) < 2 ** -8
+
+
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("T,d,n", [(512, 256, 512), (61, 40, 72), (1, 8, 33), (701, 96, 1500)])
+def test_fp32_pair_and_column_sums(ctx, T, d, n, tb):
+    """fp32: the same two contractions, x with W stored either way, and the column sums of the weight gradient's first operand."""
+    gen = torch.Generator(device="cuda").manual_seed(83)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen)
+    dh, x, wm = rnd(T, n), rnd(T, d), rnd(*((n, d) if tb else (d, n)))
+    dw, dx, cs = (torch.full(s, 7.0, device="cuda") for s in ((n, d), (T, d), (n,)))
+    w = GemmDesc(B.F32, n, d, T, dh.data_ptr(), n, 1, x.data_ptr(), d, 1, 0, 1, None)
+    g = GemmDesc(B.F32, T, d, n, dh.data_ptr(), n, 0, wm.data_ptr(), wm.stride(0), tb, 0, 1, None)
+    w.epi.c, w.epi.ldc, w.colsum, g.epi.c, g.epi.ldc = dw.data_ptr(), d, cs.data_ptr(), dx.data_ptr(), d
+    assert getattr(ctx.lib, PAIR)(ctx.h, C.byref(w), C.byref(g), 0) == B.OK
+    for got, want in ((dw, dh.double().t() @ x.double()), (dx, dh.double() @ (wm.double() if tb else wm.double().t())), (cs, dh.double().sum(0))):
+        assert float((got - want).norm() / want.norm()) < 2e-6      # chains of at most 256 fp32 additions
