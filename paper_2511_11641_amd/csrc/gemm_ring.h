@@ -156,23 +156,17 @@ __device__ __forceinline__ void ring_mfma(ring_f4& c, const bf16x8_t& a, const b
 // or splits / 8 splits per XCD): the tiles of one split read one K range of both operands, so an XCD's L2
 // then holds that range once instead of every XCD fetching all of K for its share of the tiles.
 __device__ __forceinline__ void gemm_work_item(int id, int nb, int splits, int& tile, int& z) {      // workgroup id of nb
-  const int tiles = nb / splits;
-  if (nb & 7) {                                   // no even deal: plain order
-    z = id / tiles;
-    tile = id - z * tiles;
-    return;
-  }
-  const int xcd = id & 7, j = id >> 3;            // j: index inside the XCD's share of nb / 8 workgroups
-  if (splits <= 8 && (8 % splits) == 0 && tiles % (8 / splits) == 0) {
+  const int tiles = nb / splits, xcd = id & 7, j = id >> 3, per = nb >> 3, more = nb & 7;      // j: index inside the XCD's share
+  if (more == 0 && splits <= 8 && (8 % splits) == 0 && tiles % (8 / splits) == 0) {
     const int p = 8 / splits;                     // XCDs per split
     z = xcd / p;
     tile = (xcd % p) * (tiles / p) + j;
-  } else if ((splits & 7) == 0) {
+  } else if (more == 0 && (splits & 7) == 0) {
     const int q = splits >> 3;                    // splits per XCD
     z = xcd * q + j / tiles;
     tile = j % tiles;
   } else {
-    const int lin = xcd * (nb >> 3) + j;          // contiguous range per XCD over (split, tile)
+    const int lin = xcd * per + min(xcd, more) + j;      // contiguous range per XCD over (split, tile); the first `more` XCDs have one more
     z = lin / tiles;
     tile = lin - z * tiles;
   }
