@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch of the MFMA contraction kernels, averaged over the contraction launches of one sparse
 # step of the headline workload, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (see profiles/):
 # (sha256 prefix of csrc/gemm*, bytes).  Reported only while the kernel sources still have that hash; otherwise null.
-GEMM_TRAFFIC = ("e6cb08a98703f552", 143.8e6)
+GEMM_TRAFFIC = ("f819751e371fca13", 141.9e6)
 HEADLINE = "c3_llama1b_layer"
 SECOND = "c2_gpt2m_layer"
 
@@ -746,7 +746,7 @@ def main():
         "speedup_whole_step_vs_dense_fwd_bwd": main_wl["speedup_whole_step_vs_dense_fwd_bwd"],
         "parts_ms": main_wl["parts_ms"], "attention_core": main_wl["attention_core"],
         "score_gbs": main_wl["score_gbs"], "compact_gbs": main_wl["compact_gbs"],
-        "roofline": {"bound": "mfma", "kernel": "gemm_bf16_ring_kernel", "achieved": gm["achieved"],
+        "roofline": {"bound": "mfma", "kernel": "gemm_bf16_ring_kernel, gemm_bf16_flow_kernel", "achieved": gm["achieved"],
                      "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": gm["frac"], "traffic": gemm_traffic(),
                      "launches": gm["launches"], "launches_per_step": gm["launches_per_step"], "avg_launch_us": gm["avg_launch_us"],
                      "flop_per_launch_avg": gm["flop_per_launch_avg"],

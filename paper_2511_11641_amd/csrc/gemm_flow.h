@@ -14,8 +14,8 @@
 // own, and the loop is as fast as the unrolled one (0.77 us per slab of 192x192).  Stores dealt over four slabs instead of twelve cost 0.7 us
 // a slab: their acknowledgements come back in order with the loads that the ring waits for.
 // 192x192 because it has the best rate of the tiles whose two accumulator sets fit.  N(0,1) operands, x W^T, 2048 tiles, kernel of one tile
-// per workgroup -> this one: K = 1024 135 -> 119 us, 2048 229 -> 219, 4096 423 -> 417; layer launches (operands and outputs cold):
-// 4096x11008x2048 with SwiGLU 208 -> 160 us, 4096x6144x2048 with rotation 118 -> 105, dY^T X 4096x8256x2048 150 -> 124.
+// per workgroup -> this one: K = 1024 135 -> 119 us, 2048 229 -> 219, 4096 423 -> 417; in a layer's pass (operands and outputs cold):
+// 4096x11008x2048 with SwiGLU 219 -> 170 us, 4096x6144x2048 with rotation 118 -> 104, dY^T X 4096x8256x2048 151 -> 123.
 //
 // Every store is issued whatever the tile's edge: rows and columns beyond the matrix repeat its last ones in the operand tiles, so their
 // values are equal to those of the rows and columns they repeat and are written there once more.  That keeps the count of memory
