@@ -204,13 +204,14 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_vec8_kernel(const Gemm
 // more once per launch).  The K-slow forms read 8 bytes per LDS instruction instead of 16, which the narrow tiles feel most.  A split adds
 // its partial sums: 3 us and their bytes at 4 TB/s; a split keeps at least 4 slabs.  The kernel of resident workgroups hides most of
 // the rest and the epilogue of every tile but a workgroup's last.  The times are of operands that the L2s hold: with operands from
-// memory a slab of the K-slow 64x128 shape takes 0.47-0.54 us.
+// memory a slab of the K-slow 64x128 shape takes 0.47-0.54 us.  (x W^T on 256x256 tiles: 1.30-1.34 us on N(0,1) operands, 1.27 as activations
+// and weights draw power; 8192x32000x2048 takes 75 us less on these tiles than on resident workgroups.)
 struct RingShape {
   int bm, bn;
   float slab_nt, slab_tt, rest;
 };
 static const RingShape RING_SHAPES[GEMM_RING_NSHAPES] = {
-    {256, 256, 1.33f, 1.30f, 8.5f}, {192, 256, 1.05f, 1.03f, 6.5f}, {256, 192, 1.04f, 1.02f, 6.8f}, {128, 256, 0.73f, 0.74f, 5.2f},
+    {256, 256, 1.27f, 1.30f, 8.5f}, {192, 256, 1.05f, 1.03f, 6.5f}, {256, 192, 1.04f, 1.02f, 6.8f}, {128, 256, 0.73f, 0.74f, 5.2f},
     {256, 128, 0.71f, 0.73f, 5.4f}, {192, 192, 0.80f, 0.81f, 5.5f}, {128, 192, 0.54f, 0.57f, 4.3f}, {192, 128, 0.54f, 0.57f, 4.1f},
     {128, 128, 0.39f, 0.40f, 3.1f}, {64, 128, 0.26f, 0.29f, 2.2f},  {128, 64, 0.25f, 0.29f, 2.2f},  {64, 64, 0.165f, 0.20f, 1.7f}};
 // Kernel of resident workgroups: per slab, per round beside it, and once.
@@ -218,7 +219,7 @@ static const float FLOW_SLAB_NT = 0.775f, FLOW_SLAB_TT = 0.79f, FLOW_ROUND = 2.3
 // What an epilogue adds to a plain store, us per 1000 columns x rows of a tile (vector instructions and further outputs).
 static float epi_us(int kind) {
   switch (kind) {
-    case EPI_BIAS_ACT: case EPI_ACT: case EPI_DACT: return 0.20f;
+    case EPI_BIAS_ACT: case EPI_ACT: case EPI_DACT: return 0.23f;
     case EPI_SWIGLU: return 0.27f;
     case EPI_DSWIGLU: return 0.50f;
     case EPI_ROPE: return 0.15f;
