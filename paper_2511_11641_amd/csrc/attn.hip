@@ -14,6 +14,8 @@
 // floating-point atomics are needed.
 #include "block.h"
 
+#include <type_traits>
+
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float floatx8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
@@ -129,12 +131,14 @@ __device__ __forceinline__ bf16x8_t trn_frag(TrnRegs& r) {
 // sequence corrects the offsets.  (With 64-bit lane addresses the compiler ran their multiplications for every tile: three quarter-rate
 // instructions and six 64-bit additions per load.)  That, loops that are uniform to the compiler and bit masks instead of comparisons:
 // forward of 32 x 1024 causal tokens, 16 heads of 32 dims, 103.2 -> 92.5 us; dK/dV of 11 x 381, 32 query heads on 8 key heads, 47.1 -> 39.4.
-template <int D, int WAVES = 4>
+// WIDE: 64-bit lane offsets, for rows of which 64 reach over 4 GB (attn_wide()).
+template <int D, int WAVES = 4, bool WIDE = false>
 struct TileStream {
   static constexpr int CPR = D / 8, RPI = 64 / CPR, PER = (64 / RPI) / WAVES;
+  typedef std::conditional_t<WIDE, unsigned long long, unsigned> off_t;
   const char* base;
   long long ldb;           // bytes per row
-  unsigned off[PER];       // this lane's piece of a tile
+  off_t off[PER];          // this lane's piece of a tile
   int row0, wave;          // its row in the first instruction of the wavefront
   __device__ __forceinline__ void aim(const bf16_t* b) { base = reinterpret_cast<const char*>(b); }
   __device__ __forceinline__ void init(const bf16_t* b, long long l, int kp) {
@@ -146,19 +150,19 @@ struct TileStream {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int r = row0 + i * RPI;
-      off[i] = static_cast<unsigned>(r) * static_cast<unsigned>(ldb) + static_cast<unsigned>(min(((lane % CPR) ^ nat_swz<D>(r)) * 8, kp - 8) * 2);
+      off[i] = static_cast<off_t>(r) * static_cast<off_t>(ldb) + static_cast<off_t>(min(((lane % CPR) ^ nat_swz<D>(r)) * 8, kp - 8) * 2);
     }
   }
   // rows g0 .. g0 + 63 of the matrix, of which the first rows_valid (>= 1) exist
   __device__ __forceinline__ void issue(bf16_t* tile, long long g0, int rows_valid) const {
     const char* const p = base + g0 * ldb;
     lds_bf16_t* const dst = (lds_bf16_t*)tile + wave * (PER * 512);
-    unsigned o[PER];
+    off_t o[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) o[i] = off[i];
     if (rows_valid < 64) {
 #pragma unroll
-      for (int i = 0; i < PER; ++i) o[i] -= static_cast<unsigned>(max(row0 + i * RPI - (rows_valid - 1), 0)) * static_cast<unsigned>(ldb);
+      for (int i = 0; i < PER; ++i) o[i] -= static_cast<off_t>(max(row0 + i * RPI - (rows_valid - 1), 0)) * static_cast<off_t>(ldb);
     }
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
@@ -385,7 +389,7 @@ __device__ __forceinline__ void attn_fwd_tile(const bf16_t* Kt, const bf16_t* Vt
 // ---------------------------------------------------------------------------------------------
 // forward: one workgroup per (128 queries, head, batch); 4 wavefronts x 32 queries
 // ---------------------------------------------------------------------------------------------
-template <int DQ, int DV>
+template <int DQ, int DV, bool WIDE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ATTN_WPE(DQ, DV, 4), ATTN_WPE(DQ, DV, 4))))
 void attn_fwd_kernel(const AttnArgs a) {
   constexpr int DMAX = DQ > DV ? DQ : DV;
@@ -406,8 +410,8 @@ void attn_fwd_kernel(const AttnArgs a) {
   const bf16_t* Qg = a.qkv + head * a.kp_qk;
 
   // key/value tiles stream straight into LDS, one tile ahead of the one being used
-  TileStream<DQ> ks;
-  TileStream<DV> vs;
+  TileStream<DQ, 4, WIDE> ks;
+  TileStream<DV, 4, WIDE> vs;
   ks.init(a.qkv + k_col(a, head / a.qpk), a.ld_qkv, a.kp_qk);
   vs.init(a.qkv + v_col(a, head / a.qpk), a.ld_qkv, a.kp_vo);
   ks.issue(Ks(0), tok0, a.L);
@@ -587,7 +591,7 @@ void attn_fwd_split_kernel(const AttnArgs a) {
 // backward, dQ: one workgroup per (128 queries, head, batch), loop over key tiles
 //   S^T = K Q^T, dP^T = V dO^T, dS^T = P^T * (dP^T - delta), dQ^T += K^T dS^T
 // ---------------------------------------------------------------------------------------------
-template <int DQ, int DV>
+template <int DQ, int DV, bool WIDE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ATTN_WPE(DQ, DV, 4), ATTN_WPE(DQ, DV, 4))))
 void attn_bwd_dq_kernel(const AttnArgs a) {
   constexpr int DMAX = DQ > DV ? DQ : DV;
@@ -606,8 +610,8 @@ void attn_bwd_dq_kernel(const AttnArgs a) {
   const bf16_t* dOg = a.d_o + head * a.kp_vo;
 
   // key/value tiles stream straight into LDS, one tile ahead of the one being used
-  TileStream<DQ> ks;
-  TileStream<DV> vs;
+  TileStream<DQ, 4, WIDE> ks;
+  TileStream<DV, 4, WIDE> vs;
   ks.init(a.qkv + k_col(a, head / a.qpk), a.ld_qkv, a.kp_qk);
   vs.init(a.qkv + v_col(a, head / a.qpk), a.ld_qkv, a.kp_vo);
   ks.issue(Ks(0), tok0, a.L);
@@ -729,7 +733,7 @@ void attn_bwd_dq_kernel(const AttnArgs a) {
 // backward, dK and dV: one workgroup per (128 keys, head, batch), loop over query tiles
 //   S = Q K^T, dP = dO V^T, dS = P * (dP - delta), dV^T += dO^T P, dK^T += Q^T dS
 // ---------------------------------------------------------------------------------------------
-template <int DQ, int DV>
+template <int DQ, int DV, bool WIDE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ATTN_WPE(DQ, DV, 3), ATTN_WPE(DQ, DV, 3)))) void attn_bwd_dkdv_kernel(const AttnArgs a) {
   constexpr int DMAX = DQ > DV ? DQ : DV;
   extern __shared__ __attribute__((aligned(16))) bf16_t lds_all[];     // one object: see attn_fwd_kernel; attn_lds_bytes<DQ, DV>(2)
@@ -778,8 +782,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ATTN_WPE(DQ
   const int j0 = a.causal ? k0 / 64 : 0;     // first query tile that can see a key of this tile
   // Query tiles (Q and dO) stream straight into LDS, one tile ahead; the tile's 64 log-sum-exp and
   // delta values travel through a register of threads 0..127 and are parked in LDS one iteration later.
-  TileStream<DQ> qs;
-  TileStream<DV> ds;
+  TileStream<DQ, 4, WIDE> qs;
+  TileStream<DV, 4, WIDE> ds;
   float st = 0.f;
   const int cnt = n_q - j0, n_it = cnt > 0 ? cnt * a.qpk : 0;   // iterations: query heads of the group x their query tiles
   qs.init(a.qkv + head0 * a.kp_qk, a.ld_qkv, a.kp_qk);
@@ -935,11 +939,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ATTN_WPE(DQ
 
 // The head-width combinations that are built, instantiated explicitly (left to implicit instantiation
 // from the launch code, the host side of this compiler can drop some of the kernel stubs).
+#define ATTN_INSTANTIATE_CORE(DQ, DV, WIDE)                                   \
+  template __global__ void attn_fwd_kernel<DQ, DV, WIDE>(const AttnArgs);     \
+  template __global__ void attn_bwd_dq_kernel<DQ, DV, WIDE>(const AttnArgs);  \
+  template __global__ void attn_bwd_dkdv_kernel<DQ, DV, WIDE>(const AttnArgs);
 #define ATTN_INSTANTIATE(DQ, DV)                                              \
-  template __global__ void attn_fwd_kernel<DQ, DV>(const AttnArgs);           \
   template __global__ void attn_fwd_split_kernel<DQ, DV>(const AttnArgs);     \
-  template __global__ void attn_bwd_dq_kernel<DQ, DV>(const AttnArgs);        \
-  template __global__ void attn_bwd_dkdv_kernel<DQ, DV>(const AttnArgs);
+  ATTN_INSTANTIATE_CORE(DQ, DV, false)
 ATTN_INSTANTIATE(32, 32)
 ATTN_INSTANTIATE(32, 64)
 ATTN_INSTANTIATE(64, 32)
@@ -950,6 +956,10 @@ ATTN_INSTANTIATE(128, 32)
 ATTN_INSTANTIATE(128, 64)
 ATTN_INSTANTIATE(128, 128)
 #undef ATTN_INSTANTIATE
+ATTN_INSTANTIATE_CORE(32, 32, true)
+ATTN_INSTANTIATE_CORE(64, 64, true)
+ATTN_INSTANTIATE_CORE(128, 128, true)
+#undef ATTN_INSTANTIATE_CORE
 
 // Whether the forward pass shares a query tile's keys out over the wavefronts (attn_fwd_split_kernel).  It needs 4 times the workgroups
 // and reads every key tile from memory once per 32 queries, so it pays while all of its workgroups are resident at once (two per
@@ -971,11 +981,15 @@ static constexpr int attn_lds_bytes(int which) {
   return (128 * (DQ > DV ? DQ : DV) + 2 * 64 * DQ + 2 * 64 * DV + (which == 2 ? 512 : 0)) * 2;
 }
 
+// Rows from 2^25 elements on: 64 of them reach over 4 GB, beyond the 32-bit lane offsets of TileStream (that is 87382 heads at least, so
+// the kernels run on their 64-bit form for equal widths of both sides alone).
+static bool attn_wide(const AttnArgs& a) { return a.ld_qkv >= (1ll << 25) || a.ld_o >= (1ll << 25); }
+
 template <int DQ, int DV>
 static hipError_t launch_core(int which, const AttnArgs& a, hipStream_t st) {
   const unsigned tiles = static_cast<unsigned>((a.L + 127) / 128);
   const dim3 grid(tiles * a.h * a.B), grid_kv(tiles * a.h_kv * a.B);
-  const bool split = which == 0 && attn_fwd_splits_keys(a, DQ, DV);
+  const bool wide = attn_wide(a), split = which == 0 && !wide && attn_fwd_splits_keys(a, DQ, DV);
   const int lds = split ? attn_split_lds_bytes<DQ, DV>() : attn_lds_bytes<DQ, DV>(which);
 #define ATTN_LAUNCH(kern, g)                                                                      \
   do {                                                                                            \
@@ -987,9 +1001,14 @@ static hipError_t launch_core(int which, const AttnArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(kern, g, dim3(256), lds, st, a);                                           \
   } while (0)
   if (split) ATTN_LAUNCH((attn_fwd_split_kernel<DQ, DV>), dim3(static_cast<unsigned>((a.L + 31) / 32) * a.h * a.B));
-  else if (which == 0) ATTN_LAUNCH((attn_fwd_kernel<DQ, DV>), grid);
-  else if (which == 1) ATTN_LAUNCH((attn_bwd_dq_kernel<DQ, DV>), grid);
-  else ATTN_LAUNCH((attn_bwd_dkdv_kernel<DQ, DV>), grid_kv);
+  else if (!wide && which == 0) ATTN_LAUNCH((attn_fwd_kernel<DQ, DV, false>), grid);
+  else if (!wide && which == 1) ATTN_LAUNCH((attn_bwd_dq_kernel<DQ, DV, false>), grid);
+  else if (!wide) ATTN_LAUNCH((attn_bwd_dkdv_kernel<DQ, DV, false>), grid_kv);
+  else if constexpr (DQ == DV) {
+    if (which == 0) ATTN_LAUNCH((attn_fwd_kernel<DQ, DV, true>), grid);
+    else if (which == 1) ATTN_LAUNCH((attn_bwd_dq_kernel<DQ, DV, true>), grid);
+    else ATTN_LAUNCH((attn_bwd_dkdv_kernel<DQ, DV, true>), grid_kv);
+  }
 #undef ATTN_LAUNCH
   return hipGetLastError();
 }
@@ -998,7 +1017,8 @@ static hipError_t launch_core(int which, const AttnArgs& a, hipStream_t st) {
 static int attn_width(int kp) { return kp <= 32 ? 32 : (kp <= 64 ? 64 : 128); }
 static int dispatch_core(ecospa_ctx* ctx, int which, const AttnArgs& a) {
   if (a.kp_qk > 128 || a.kp_vo > 128) return ECOSPA_ERR_SHAPE;   // rejected by the block validation before anything is launched
-  const int dq = attn_width(a.kp_qk), dv = attn_width(a.kp_vo);
+  int dq = attn_width(a.kp_qk), dv = attn_width(a.kp_vo);
+  if (attn_wide(a)) dq = dv = dq > dv ? dq : dv;
   hipError_t e = hipSuccess;
 #define ATTN_CASE(Q, V) if (dq == Q && dv == V) e = launch_core<Q, V>(which, a, ctx->stream);
   ATTN_CASE(32, 32) else ATTN_CASE(32, 64) else ATTN_CASE(64, 32) else ATTN_CASE(64, 64)
