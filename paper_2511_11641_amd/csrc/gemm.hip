@@ -111,7 +111,7 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& d, int tiles_n, int k_c
   for (int r = 0; r < 16; ++r) acc[r] += sum[r];
   float* part = d.splits > 1 ? d.partial + static_cast<long long>(z) * d.M * d.N : nullptr;
   if constexpr (TA && TB) {
-    cs += cs_lost;
+    cs += fabsf(cs_lost) < INFINITY ? cs_lost : 0.f;      // (not a number behind an infinite sum, which stands as it is)
     cs += __shfl_xor(cs, 32, 64);      // the other half of the k
   }
   auto put = [&](int m, int n, float v) __attribute__((always_inline)) {

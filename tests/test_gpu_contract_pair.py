@@ -78,3 +78,27 @@ def test_fp32_pair_and_column_sums(ctx, T, d, n, tb):
     assert getattr(ctx.lib, PAIR)(ctx.h, C.byref(w), C.byref(g), 0) == B.OK
     for got, want in ((dw, dh.double().t() @ x.double()), (dx, dh.double() @ (wm.double() if tb else wm.double().t())), (cs, dh.double().sum(0))):
         assert float((got - want).norm() / want.norm()) < 2e-6      # chains of at most 256 fp32 additions
+
+
+@pytest.mark.parametrize("T,d,n", [(512, 256, 512), (61, 40, 72), (70, 1024, 2048)])      # K shared out over the wavefronts; 64 x 64 tiles
+def test_fp32_column_sums_of_infinities(ctx, T, d, n):
+    """One infinite gradient, an overflow, both signs, not a number: as a plain sum has them, and the other columns as without."""
+    gen = torch.Generator(device="cuda").manual_seed(84)
+    dh, x, dw = (torch.randn(s, device="cuda", generator=gen) for s in ((T, n), (T, d), (n, d)))
+    sums = []
+    for special in (False, True):
+        if special:
+            dh[3, 5], dh[T - 1, 7], dh[0, 9] = float("inf"), float("-inf"), float("nan")
+            dh[4, 11], dh[T - 2, 11] = float("inf"), float("-inf")
+            dh[1, 13], dh[2, 13] = 3e38, 3e38
+        cs = torch.full((n,), 7.0, device="cuda")
+        w = GemmDesc(B.F32, n, d, T, dh.data_ptr(), n, 1, x.data_ptr(), d, 1, 0, 1, None)
+        w.epi.c, w.epi.ldc, w.colsum = dw.data_ptr(), d, cs.data_ptr()
+        assert getattr(ctx.lib, ONE)(ctx.h, C.byref(w)) == B.OK
+        sums.append(cs)
+    plain, cs = sums
+    assert float(cs[5]) == float("inf") and float(cs[7]) == float("-inf") and float(cs[13]) == float("inf")
+    assert bool(torch.isnan(cs[[9, 11]]).all())
+    rest = torch.ones(n, dtype=torch.bool, device="cuda")
+    rest[[5, 7, 9, 11, 13]] = False
+    assert torch.equal(cs[rest], plain[rest])
