@@ -152,8 +152,8 @@ __device__ __forceinline__ float act_norm_tail(float x, float& e) {
   e = act_gauss(x);
   return p * t * e;
 }
-// (the bound keeps infinity times a tail of zero out)
-__device__ __forceinline__ float act_gelu_of_tail(float x, float tail) { return __builtin_fmaf(-fminf(fabsf(x), 1e30f), tail, fmaxf(x, 0.f)); }
+// (the bound keeps infinity times a tail of zero out of the positive side; x = -inf gives NaN, as x Phi(x) does)
+__device__ __forceinline__ float act_gelu_of_tail(float x, float tail) { return __builtin_fmaf(-fabsf(fminf(x, 1e30f)), tail, fmaxf(x, 0.f)); }
 __device__ __forceinline__ float act_gelu(float x, int act) {
   if (act == ECOSPA_ACT_GELU_TANH) {
     const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
