@@ -73,7 +73,7 @@ struct FlowLoads {
 // accumulators, two that add the bias, then the kind's own stages on four values at a time, and one that packs and stores.
 template <int KIND>
 struct FlowEpi {
-  static constexpr int STAGES = KIND == EPI_BIAS_ACT || KIND == EPI_ACT ? 9 : KIND == EPI_DACT ? 10 : KIND == EPI_SWIGLU ? 2 : KIND == EPI_DSWIGLU ? 6 : KIND == EPI_ROPE ? 2 : 0;
+  static constexpr int STAGES = KIND == EPI_BIAS_ACT || KIND == EPI_ACT ? 9 : KIND == EPI_DACT ? 10 : KIND == EPI_SWIGLU ? 3 : KIND == EPI_DSWIGLU ? 8 : KIND == EPI_ROPE ? 2 : 0;
   static constexpr bool BIAS = KIND != EPI_DACT && KIND != EPI_DSWIGLU;
   static constexpr int P0 = 4, P1 = P0 + (BIAS ? 2 : 0), PIECES = P1 + 2 * STAGES + 1;
   static constexpr int SIDES = KIND == EPI_DACT ? 1 : KIND == EPI_DSWIGLU || KIND == EPI_ROPE ? 2 : 0;      // side inputs per group: loads
@@ -104,25 +104,31 @@ struct FlowEpi {
       }
       if constexpr (ST == 9) x[q] *= __builtin_fmaf(a, 0.3989422804014327f * e[q], z[q]);
     } else if constexpr (KIND == EPI_SWIGLU) {
-      // columns are (gate, up) pairs: four units, two steps per stage
+      // columns are (gate, up) pairs: four units, two steps per stage; e: denominator of the sigmoid, t: its reciprocal
       const int u = q & 3;
       if constexpr (ST == 0) {
-        if (q < 4) e[u] = __expf(-x[2 * u]);
-        else t[u] = __builtin_amdgcn_rcpf(1.f + e[u]);
+        if (q < 4) e[u] = act_sigmoid_den(__expf(-x[2 * u]));
+        else t[u] = __builtin_amdgcn_rcpf(e[u]);
       }
       if constexpr (ST == 1) {
+        if (q < 4) t[u] = act_sigmoid_step(e[u], t[u]);
+        else t[u] = act_sigmoid_end(e[u], t[u]);
+      }
+      if constexpr (ST == 2) {
         if (q < 4) z[u] = x[2 * u] * t[u];
         else z[u] = z[u] * x[2 * u + 1];
       }
     } else if constexpr (KIND == EPI_DSWIGLU) {
       const uint32_t w[8] = {sd.a.x, sd.a.y, sd.a.z, sd.a.w, sd.b.x, sd.b.y, sd.b.z, sd.b.w};
       const float g = __uint_as_float(w[q] << 16), u = __uint_as_float(w[q] & 0xffff0000u);
-      if constexpr (ST == 0) e[q] = __expf(-g);
-      if constexpr (ST == 1) t[q] = __builtin_amdgcn_rcpf(1.f + e[q]);
-      if constexpr (ST == 2) z[q] = x[q] * u * t[q];
-      if constexpr (ST == 3) p[q] = 1.f + g * (1.f - t[q]);
-      if constexpr (ST == 4) z[q] *= p[q];
-      if constexpr (ST == 5) p[q] = x[q] * g * t[q];
+      if constexpr (ST == 0) e[q] = act_sigmoid_den(__expf(-g));
+      if constexpr (ST == 1) t[q] = __builtin_amdgcn_rcpf(e[q]);
+      if constexpr (ST == 2) t[q] = act_sigmoid_step(e[q], t[q]);
+      if constexpr (ST == 3) t[q] = act_sigmoid_end(e[q], t[q]);
+      if constexpr (ST == 4) z[q] = x[q] * u * t[q];
+      if constexpr (ST == 5) p[q] = 1.f + g * (1.f - t[q]);
+      if constexpr (ST == 6) z[q] *= p[q];
+      if constexpr (ST == 7) p[q] = x[q] * g * t[q];
     } else if constexpr (KIND == EPI_ROPE) {
       const float4 c4 = __builtin_bit_cast(float4, sd.a), s4 = __builtin_bit_cast(float4, sd.b);
       const float cv[4] = {c4.x, c4.y, c4.z, c4.w}, sv[4] = {s4.x, s4.y, s4.z, s4.w};

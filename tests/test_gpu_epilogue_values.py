@@ -57,3 +57,32 @@ def test_gelu(ctx, route, kind):
     assert bool((torch.isinf(c) == torch.isinf(want))[ok].all())
     ok &= ~torch.isinf(want)
     assert float(((c - want).abs() - 2 ** -8 * want.abs())[ok].max()) <= 1e-30
+
+
+@pytest.mark.parametrize("route", ["ring", "split", "flow"])
+def test_gates_whose_sigmoid_is_below_the_normal_range(ctx, route):
+    """exp(88) is a number, so gates down to -88.5 have a sigmoid (subnormal) and the products with it a value in the normal range."""
+    gate = torch.tensor([-86.5, -87.5, -88.0, -88.5, -3.0, 90.0, 0.0, -100.0], device="cuda")
+    sig = 1.0 / (1.0 + torch.exp(-gate.double()))
+    sig[-1] = 0.0                                   # exp(100) overflows in fp32
+
+    def fwd(g, M, N, dt):
+        h = torch.stack((gate, torch.full_like(gate, 2.0)), 1).flatten().to(dt).repeat((N + 15) // 16)[:N].contiguous()
+        act = torch.full((M, N // 2), 7.0, device="cuda", dtype=dt)
+        g.epi.bias, g.epi.c2, g.epi.ldc2 = h.data_ptr(), act.data_ptr(), N // 2
+        return h, act
+    _, (_, act) = _launch(ctx, route, SWIGLU, 2, fwd)
+    n = act.shape[1]
+    want = (gate.double() * sig * 2.0).repeat((n + 7) // 8)[:n]
+    # exp() of an argument of 88 is good to 88 * 2^-24, the bf16 rounding to 2^-9
+    assert bool(((act.double() - want).abs() <= 2 ** -8 * want.abs()).all())
+
+    def bwd(g, M, N, dt):
+        h = torch.stack((gate, torch.full_like(gate, 2.0)), 1).flatten().to(dt).repeat((N + 7) // 8)[:2 * N].expand(M, 2 * N).contiguous()
+        g.epi.h, g.epi.ldh, g.epi.kp = h.data_ptr(), 2 * N, N
+        return h
+    dh, _ = _launch(ctx, route, DSWIGLU, 4, bwd)
+    n = dh.shape[1] // 2
+    for half, w in ((0, 2.0 * sig * (1.0 + gate.double() * (1.0 - sig))), (1, gate.double() * sig)):
+        want = w.repeat((n + 7) // 8)[:n]
+        assert bool(((dh[:, half::2].double() - want).abs() <= 2 ** -8 * want.abs()).all())
