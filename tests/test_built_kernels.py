@@ -136,9 +136,43 @@ def test_matrix_instructions_follow_vector_writes_of_their_operands_at_a_distanc
     assert seen > 5000
 
 
+def _loads_in_flight(ins):
+    """{index of a barrier: most direct loads to LDS that may still be under way there}, over all paths to it.  Memory operations end in the
+    order they were issued, so a load is done where a wait allows no more operations than were issued since; on the path with the fewest."""
+    at = {a: i for i, (a, *_) in enumerate(ins)}
+    succ = [[j for j in ([] if op in ("s_endpgm", "s_branch") else [i + 1]) + ([at[t]] if t is not None else []) if j < len(ins)]
+            for i, (_, op, _, t) in enumerate(ins)]
+    joins = {j for i, s in enumerate(succ) for j in s if s != [i + 1]} | {i + 1 for i, s in enumerate(succ) if s != [i + 1]}
+    state, work, found, most = {0: ()}, [0], {}, 48       # operations issued since each direct load, the latest load first; 48 and more are let go
+    while work:
+        i = work.pop()
+        st = list(state[i])
+        while True:
+            _, op, args, _ = ins[i]
+            if op.startswith(("global_", "buffer_", "flat_")):
+                st = ([0] if "lds" in op else []) + [n + 1 for n in st if n + 1 < most]
+            elif op == "s_waitcnt" and "vmcnt" in args:
+                left = int(re.search(r"vmcnt\((\d+)\)", args)[1])
+                assert left <= most
+                st = [n for n in st if n < left]
+            elif op == "s_barrier":
+                found[i] = max(found.get(i, 0), len(st))
+            if succ[i] == [i + 1] and i + 1 not in joins:
+                i += 1
+                continue
+            for j in succ[i]:
+                old = state.get(j)
+                new = tuple(st) if old is None else tuple(min(p) for p in zip(st, old)) + (tuple(st) if len(st) > len(old) else old)[min(len(st), len(old)):]
+                if new != old:
+                    state[j] = new
+                    work.append(j)
+            break
+    return found
+
+
 def test_waits_of_the_resident_workgroups_cover_the_next_slab(code_objects):
     """The kernel of resident workgroups names, in front of each barrier, how many memory operations may still be under way: at most the
-    loads of the slabs behind the next one.  The stores and side inputs it counts beside them must really have been issued since."""
+    loads of the slabs behind the next one.  The stores and side inputs it counts beside them must have been issued since on every path."""
     seen = 0
     for f in code_objects:
         for name, ins in _functions(f).items():
@@ -147,12 +181,9 @@ def test_waits_of_the_resident_workgroups_cover_the_next_slab(code_objects):
                 continue
             bm, bn, bufs = map(int, m.groups())
             behind = (bufs - 2) * (bm + bn) * 128 // 4096
-            for i, (_, op, _, _) in enumerate(ins):
-                if op != "s_barrier":
-                    continue
-                j = next(j for j in range(i - 1, -1, -1) if ins[j][1] == "s_waitcnt" and "vmcnt" in ins[j][2])
-                left = int(re.search(r"vmcnt\((\d+)\)", ins[j][2])[1])
-                memory = [o for _, o, *_ in ins[:j] if o.startswith(("global_", "buffer_", "flat_"))][-left:]
-                assert sum("lds" in o for o in memory) <= behind, name
-                seen += 1
+            found = _loads_in_flight(ins)
+            assert max(found.values()) <= behind, (name, sorted(found.values())[-3:])
+            # the check itself: without the waits there are more
+            assert max(_loads_in_flight([(a, "s_nop" if op == "s_waitcnt" else op, args, t) for a, op, args, t in ins]).values()) > behind
+            seen += len(found)
     assert seen > 100
