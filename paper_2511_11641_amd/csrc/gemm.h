@@ -61,6 +61,11 @@ int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d);
 // Two contractions that do not depend on each other: w a weight gradient (dY^T X, bf16 or fp32; its reduction deferred where K is split), x
 // over the same tokens.  One launch where that is built for the two and pays, otherwise w, then x (x_first: the other way round).
 int ecospa_gemm_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int x_first = 0);
+// What the two above choose (host arithmetic only; they launch by it).  A bf16 contraction: the tile shape of the ring kernel, or GEMM_ROUTE_FLOW
+// for the kernel of resident workgroups.  A pair: one launch or two, and for one of bf16 the tile shapes.
+int ecospa_gemm_route(const GemmDesc& d);
+enum { GEMM_PAIR_NONE = 0, GEMM_PAIR_BF16 = 1, GEMM_PAIR_F32 = 2 };
+int ecospa_gemm_pair_route(const GemmDesc& w, const GemmDesc& x, int* w_shape, int* x_shape);
 // Rows (of M floats) of the partial column sums that the launch of d writes to d.colsum.
 int ecospa_gemm_colsum_rows(const GemmDesc& d);
 // Second half of a split-K contraction launched with defer_reduce: fixed-order sum of the partials,
@@ -75,6 +80,7 @@ int ecospa_gemm_token_splits(int M, int N, int K);
 // The bf16 kernel (gemm_ring.h): launch of tile shape `shape` (index into the table in gemm.hip; not every shape is built for every
 // form).  k_chunk: K range of a split, a multiple of 64.
 #define GEMM_RING_NSHAPES 12
+#define GEMM_ROUTE_FLOW GEMM_RING_NSHAPES
 // Epilogue kinds that are built, as bit masks: x W^T carries all of them, dY W the activation derivatives, the forms with a K-slow A
 // only the plain store.  (A split contraction leaves partial sums; the reduction behind it knows every kind.)
 #define GEMM_EPIS_NT 0x7f

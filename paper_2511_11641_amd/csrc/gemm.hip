@@ -354,17 +354,21 @@ static void prof_end(ecospa_ctx* ctx, double flop) {
   ctx->prof_flop[ctx->prof_n++] = flop;
 }
 
+int ecospa_gemm_route(const GemmDesc& d) {
+  double t;
+  const int shape = ring_shape(d, d.splits > 1 ? d.splits : 1, &t);
+  return gemm_flow_takes(d) && flow_time(d) < t ? GEMM_ROUTE_FLOW : shape;
+}
+
 int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d) {
   const int bad = gemm_check(d);
   if (bad) return bad;
   const int splits = d.splits > 1 ? d.splits : 1;
   if (d.dtype == ECOSPA_BF16) {
     const bool prof = prof_begin(ctx);
-    const int k_chunk = ring_chunk(d, splits);
-    double t;
-    const int shape = ring_shape(d, splits, &t);
+    const int k_chunk = ring_chunk(d, splits), shape = ecospa_gemm_route(d);
     hipError_t le;
-    if (gemm_flow_takes(d) && flow_time(d) < t) le = d.trans_a ? gemm_flow_launch_tt(ctx, d) : gemm_flow_launch_nt(ctx, d);
+    if (shape == GEMM_ROUTE_FLOW) le = d.trans_a ? gemm_flow_launch_tt(ctx, d) : gemm_flow_launch_nt(ctx, d);
     else if (d.trans_a && d.trans_b) le = gemm_ring_launch_tt(ctx, d, shape, k_chunk);
     else if (d.trans_a || d.trans_b) le = gemm_ring_launch_mixed(ctx, d, shape, k_chunk);
     else le = gemm_ring_launch_nt(ctx, d, shape, k_chunk);
@@ -423,30 +427,37 @@ static bool pair_pays(const GemmDesc& w, int splits, int ws, const GemmDesc& x, 
   return idle(w, splits, RING_SHAPES[ws]) + idle(x, 1, RING_SHAPES[xs]) >= 64;
 }
 
-int ecospa_gemm_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int x_first) {
-  int rc;
-  if ((rc = gemm_check(w)) || (rc = gemm_check(x))) return rc;
-  if (w.dtype == ECOSPA_BF16 && x.dtype == ECOSPA_BF16 && w.trans_a && w.trans_b && !x.trans_a && !x.trans_b && x.splits <= 1 &&
-      x.epi.kind == EPI_STORE && (w.splits <= 1 || w.defer_reduce) && !ring_wide(w) && !ring_wide(x) && gemm_independent(w, x)) {
-    const int splits = w.splits > 1 ? w.splits : 1;
-    double tw, tx;
-    const int ws = ring_shape(w, splits, &tw), xs = ring_shape(x, 1, &tx);
-    const RingShape& r = RING_SHAPES[ws];
-    if (r.bn == 128 && ((GEMM_PAIR_X >> xs) & 1) && pair_pays(w, splits, ws, x, xs) && !(gemm_flow_takes(w) && flow_time(w) < tw) && !(gemm_flow_takes(x) && flow_time(x) < tx)) {
-      const bool prof = prof_begin(ctx);
-      const int k_chunk = ring_chunk(w, splits);
-      const hipError_t le = r.bm == 64 ? gemm_pair_launch_64(ctx, w, x, xs, k_chunk) : r.bm == 128 ? gemm_pair_launch_128(ctx, w, x, xs, k_chunk)
-                          : r.bm == 192 ? gemm_pair_launch_192(ctx, w, x, xs, k_chunk) : gemm_pair_launch_256(ctx, w, x, xs, k_chunk);
-      if (le != hipSuccess) return hip_fail(ctx, le, "gemm pair launch");
-      if (prof) prof_end(ctx, 2.0 * w.M * w.N * w.K + 2.0 * x.M * x.N * x.K);
-      ECOSPA_CHECK_LAUNCH(ctx, "gemm_bf16_pair_kernel");
-      return ECOSPA_OK;
-    }
+int ecospa_gemm_pair_route(const GemmDesc& w, const GemmDesc& x, int* w_shape, int* x_shape) {
+  *w_shape = *x_shape = -1;
+  if (w.dtype != x.dtype || !w.trans_a || !w.trans_b || x.trans_a || x.splits > 1 || !gemm_independent(w, x)) return GEMM_PAIR_NONE;
+  const int splits = w.splits > 1 ? w.splits : 1;
+  if (w.dtype == ECOSPA_BF16) {
+    if (x.trans_b || x.epi.kind != EPI_STORE || (splits > 1 && !w.defer_reduce) || ring_wide(w) || ring_wide(x)) return GEMM_PAIR_NONE;
+    const int ws = *w_shape = ecospa_gemm_route(w), xs = *x_shape = ecospa_gemm_route(x);
+    if (ws == GEMM_ROUTE_FLOW || xs == GEMM_ROUTE_FLOW) return GEMM_PAIR_NONE;
+    return RING_SHAPES[ws].bn == 128 && ((GEMM_PAIR_X >> xs) & 1) && pair_pays(w, splits, ws, x, xs) ? GEMM_PAIR_BF16 : GEMM_PAIR_NONE;
   }
   // fp32: while both are on tiles that share out K, that is bound by the latency of their launches (forward and backward of 512 tokens,
   // 256 -> 512 units: 71.4 -> 57.4 us with two pairs and the bias gradients out of the weight gradients, eight launches instead of eleven)
-  if (w.dtype == ECOSPA_F32 && x.dtype == ECOSPA_F32 && w.trans_a && w.trans_b && !x.trans_a && w.splits <= 1 && x.splits <= 1 &&
-      !f32_wide_tiles(w, 1) && !f32_wide_tiles(x, 1) && gemm_independent(w, x)) {
+  return splits == 1 && !f32_wide_tiles(w, 1) && !f32_wide_tiles(x, 1) ? GEMM_PAIR_F32 : GEMM_PAIR_NONE;
+}
+
+int ecospa_gemm_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int x_first) {
+  int rc;
+  if ((rc = gemm_check(w)) || (rc = gemm_check(x))) return rc;
+  int ws, xs;
+  const int route = ecospa_gemm_pair_route(w, x, &ws, &xs);
+  if (route == GEMM_PAIR_BF16) {
+    const int k_chunk = ring_chunk(w, w.splits > 1 ? w.splits : 1), bm = RING_SHAPES[ws].bm;
+    const bool prof = prof_begin(ctx);
+    const hipError_t le = bm == 64 ? gemm_pair_launch_64(ctx, w, x, xs, k_chunk) : bm == 128 ? gemm_pair_launch_128(ctx, w, x, xs, k_chunk)
+                        : bm == 192 ? gemm_pair_launch_192(ctx, w, x, xs, k_chunk) : gemm_pair_launch_256(ctx, w, x, xs, k_chunk);
+    if (le != hipSuccess) return hip_fail(ctx, le, "gemm pair launch");
+    if (prof) prof_end(ctx, 2.0 * w.M * w.N * w.K + 2.0 * x.M * x.N * x.K);
+    ECOSPA_CHECK_LAUNCH(ctx, "gemm_bf16_pair_kernel");
+    return ECOSPA_OK;
+  }
+  if (route == GEMM_PAIR_F32) {
     const int wn = (w.N + 31) / 32, xn = (x.N + 31) / 32, n_w = (w.M + 31) / 32 * wn, n_x = (x.M + 31) / 32 * xn;
     if (x.trans_b) hipLaunchKernelGGL((gemm_f32_pair_kernel<true>), dim3(n_w + n_x), dim3(256), 0, ctx->stream, w, x, wn, n_w, xn);
     else hipLaunchKernelGGL((gemm_f32_pair_kernel<false>), dim3(n_w + n_x), dim3(256), 0, ctx->stream, w, x, wn, n_w, xn);

@@ -11,6 +11,13 @@ from util import GemmDesc
 pytestmark = pytest.mark.gpu
 ONE, PAIR, ROWS = "_Z11ecospa_gemmP10ecospa_ctxRK8GemmDesc", "_Z16ecospa_gemm_pairP10ecospa_ctxRK8GemmDescS3_i", "_Z23ecospa_gemm_colsum_rowsRK8GemmDesc"
 
+PAIR_ROUTE = "_Z22ecospa_gemm_pair_routeRK8GemmDescS1_PiS2_"      # 0: two launches, 1: one of bf16, 2: one of fp32
+
+
+def _route(ctx, w, x):
+    ws, xs = C.c_int(), C.c_int()
+    return getattr(ctx.lib, PAIR_ROUTE)(C.byref(w), C.byref(x), C.byref(ws), C.byref(xs)), ws.value, xs.value
+
 
 @pytest.fixture(scope="module")
 def ctx():
@@ -42,6 +49,8 @@ def test_one_launch_gives_what_two_give(ctx, w_tile, x_tile, T, d, n, splits, su
             w.colsum = cs.data_ptr()
         g, dx = _desc(T, d, n, dh, wt, False, x_tile)
         if pair:
+            # tile codes 30 .. 41 in the order of the shapes
+            assert _route(ctx, w, g) == (1, w_tile - 30, x_tile - 30)
             assert getattr(ctx.lib, PAIR)(ctx.h, C.byref(w), C.byref(g), 0) == B.OK
         else:
             assert getattr(ctx.lib, ONE)(ctx.h, C.byref(w)) == B.OK and getattr(ctx.lib, ONE)(ctx.h, C.byref(g)) == B.OK
@@ -56,9 +65,11 @@ def test_an_input_that_the_other_overwrites_is_read_first(ctx):
     rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen).bfloat16()
     dh, x, wt = rnd(1379, 392), rnd(1379, 264), rnd(264, 392)
     want = dh.float().t() @ x.float()
-    w, dw = _desc(392, 264, 1379, dh, x, True, 0)
-    g, _ = _desc(1379, 264, 392, dh, wt, False, 0)
+    w, dw = _desc(392, 264, 1379, dh, x, True, 39)
+    g, _ = _desc(1379, 264, 392, dh, wt, False, 38)
+    assert _route(ctx, w, g)[0] == 1
     g.epi.c = x.data_ptr()                    # the input gradient goes where the weight gradient's input is
+    assert _route(ctx, w, g)[0] == 0
     assert getattr(ctx.lib, PAIR)(ctx.h, C.byref(w), C.byref(g), 0) == B.OK
     # bf16 rounding of the result: 2^-9 of each element at most
     assert float((dw.float() - want).norm() / want.norm()) < 2 ** -8
@@ -75,6 +86,7 @@ def test_fp32_pair_and_column_sums(ctx, T, d, n, tb):
     w = GemmDesc(B.F32, n, d, T, dh.data_ptr(), n, 1, x.data_ptr(), d, 1, 0, 1, None)
     g = GemmDesc(B.F32, T, d, n, dh.data_ptr(), n, 0, wm.data_ptr(), wm.stride(0), tb, 0, 1, None)
     w.epi.c, w.epi.ldc, w.colsum, g.epi.c, g.epi.ldc = dw.data_ptr(), d, cs.data_ptr(), dx.data_ptr(), d
+    assert _route(ctx, w, g)[0] == 2
     assert getattr(ctx.lib, PAIR)(ctx.h, C.byref(w), C.byref(g), 0) == B.OK
     for got, want in ((dw, dh.double().t() @ x.double()), (dx, dh.double() @ (wm.double() if tb else wm.double().t())), (cs, dh.double().sum(0))):
         assert float((got - want).norm() / want.norm()) < 2e-6      # chains of at most 256 fp32 additions
