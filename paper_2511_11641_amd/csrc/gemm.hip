@@ -204,8 +204,13 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_vec8_kernel(const Gemm
 // more once per launch).  The K-slow forms read 8 bytes per LDS instruction instead of 16, which the narrow tiles feel most.  A split adds
 // its partial sums: 3 us and their bytes at 4 TB/s; a split keeps at least 4 slabs.  The kernel of resident workgroups hides most of
 // the rest and the epilogue of every tile but a workgroup's last.  The times are of operands that the L2s hold: with operands from
-// memory a slab of the K-slow 64x128 shape takes 0.47-0.54 us.  (x W^T on 256x256 tiles: 1.30-1.34 us on N(0,1) operands, 1.27 as activations
-// and weights draw power; 8192x32000x2048 takes 75 us less on these tiles than on resident workgroups.)
+// memory a slab of the K-slow 64x128 shape takes 0.47-0.54 us.
+//
+// How good the choice is: 680 contractions x W^T of random kinds and sizes (512 .. 32768 x 64 .. 52000 x 256 .. 8300; activations just written, the rest
+// from memory), every shape and the resident workgroups timed.  The sum over the choices is 1.0 - 1.4 % above the sum of the fastest, the worst
+// single ones (fewer than 256 tiles, K beyond 3000) 1.4 times.  A slab of 256x256 is 1.28 us by least squares over the plain stores; with 1.30 or 1.33 in
+// the table the sum is 0.1 - 0.7 % larger, with 0.79 - 0.83 for the resident workgroups' it is no smaller.  Outputs of more than 30000 columns
+// cost those up to 3 us a round that the rule does not see (6144x24576x2048: 484 us, 440 on 256x256 tiles).
 struct RingShape {
   int bm, bn;
   float slab_nt, slab_tt, rest;
@@ -418,7 +423,8 @@ static bool gemm_independent(const GemmDesc& w, const GemmDesc& x) {
 // Whether one launch is the better way for two contractions of these shapes: where together they leave a good part of a round of compute
 // units (64 of 512) to nobody, which the other's tiles then take.  Forward and backward of a 384-wide layer on 12017 tokens (252 + 189, 96
 // + 188 and 216 + 189 workgroups) 251 -> 242 us; pairs of full rounds gain nothing (256 + 256 workgroups: -0.6 .. +5 us, the tiles
-// that share operands no longer run side by side).
+// that share operands no longer run side by side).  200 pairs of random sizes that the rule takes, on 15 of the 16 shape pairs: 1.18x in the geometric
+// mean against the two launches one behind the other (1.29x with 64x128 weight-gradient tiles, 1.01 - 1.10x with larger ones), one slower (0.974x).
 static bool pair_pays(const GemmDesc& w, int splits, int ws, const GemmDesc& x, int xs) {
   const auto idle = [](const GemmDesc& d, int sp, const RingShape& r) {
     const long long n = static_cast<long long>((d.M + r.bm - 1) / r.bm) * ((d.N + r.bn - 1) / r.bn) * sp;
