@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch of the MFMA contraction kernels, averaged over the contraction launches of one sparse
 # step of the headline workload, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (see profiles/):
 # (sha256 prefix of csrc/gemm*, bytes).  Reported only while the kernel sources still have that hash; otherwise null.
-GEMM_TRAFFIC = ("28a144224bd67e9c", 141.9e6)
+GEMM_TRAFFIC = ("9ec2346a611e2db6", 141.9e6)
 HEADLINE = "c3_llama1b_layer"
 SECOND = "c2_gpt2m_layer"
 
@@ -284,7 +284,7 @@ def prune_stack(ctx, cfg, n_layers, keep_num, keep_den, steps, rows=True, extras
 
 def fp32_pair_workload(ctx, steps):
     """The fp32 single FFN pair (512 tokens, d = 256, 1024 inner dimensions, half kept): score, select, gather,
-    forward and backward.  0.8 GFLOP in ten short launches whose contraction loops (fp32 matrix instructions) are bound by
+    forward and backward.  0.8 GFLOP in eight short launches whose contraction loops (fp32 matrix instructions) are bound by
     load latency, not arithmetic; time only."""
     import torch
     from paper_2511_11641_amd import binding as B, synth
@@ -314,7 +314,7 @@ def fp32_pair_workload(ctx, steps):
 
     ms = timed(torch, step, steps, 3)
     return {"workload": "c1_ffn_f32", "dtype": "f32", "tokens": T, "keep": f"{k}/{n}", "ms_per_step": ms,
-            "tokens_per_s": T / (ms * 1e-3), "note": "0.8 GFLOP in ten short launches: latency-bound, reported as a time only"}
+            "tokens_per_s": T / (ms * 1e-3), "note": "0.8 GFLOP in eight short launches: latency-bound, reported as a time only"}
 
 
 def layer_workload(ctx, name, steps, warmup, h_kv=None, detail=True, keep=(1, 2)):
