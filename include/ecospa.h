@@ -56,6 +56,7 @@ const char* ecospa_last_error(const ecospa_ctx* ctx);
  * recorded on the context's own stream.  enable != 0 starts a new window (at most 4096 launches
  * are kept); ecospa_profile_gemm_read waits for the recorded events and returns the number of
  * launches, the sum of their durations in ms and the sum of their 2*M*N*K flops (host pointers).
+ * Two contractions of a backward pass that share a launch are one launch with the flops of both.
  * The events add a few microseconds per launch, so time throughput with profiling off. */
 int ecospa_profile_gemm(ecospa_ctx* ctx, int enable);
 int ecospa_profile_gemm_read(ecospa_ctx* ctx, int* launches, double* total_ms, double* total_flop);
