@@ -60,18 +60,14 @@ __device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
   const bf16x8_t b = __builtin_convertvector(v, bf16x8_t);   // round to nearest even (v_cvt_pk_bf16_f32)
   return __builtin_bit_cast(uint4, b);
 }
-// Rotary turn of an adjacent pair (x0, x1) by the angle of (c, s).  Which product is fused is written out: left to the compiler, two kernels
-// give results that differ in the last bit.
-__device__ __forceinline__ float rope_even(float x0, float x1, float c, float s) { return __builtin_fmaf(x0, c, -(x1 * s)); }
-__device__ __forceinline__ float rope_odd(float x0, float x1, float c, float s) { return __builtin_fmaf(x1, c, x0 * s); }
-// The four pairs in v (columns n .. n+7 of row m).
-__device__ __forceinline__ void rope_turn8(const float4& c4, const float4& s4, float (&v)[8]) {
+// Rotary turn of the four adjacent pairs in v (columns n .. n+7 of row m), sign = +1 forward, -1 for gradients.
+__device__ __forceinline__ void rope_turn8(const float4& c4, const float4& s4, float sign, float (&v)[8]) {
   const float cv[4] = {c4.x, c4.y, c4.z, c4.w}, sv[4] = {s4.x, s4.y, s4.z, s4.w};
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const float x0 = v[2 * i], x1 = v[2 * i + 1];
-    v[2 * i] = rope_even(x0, x1, cv[i], sv[i]);
-    v[2 * i + 1] = rope_odd(x0, x1, cv[i], sv[i]);
+    const float x0 = v[2 * i], x1 = v[2 * i + 1], s = sign * sv[i];
+    v[2 * i] = x0 * cv[i] - x1 * s;
+    v[2 * i + 1] = x0 * s + x1 * cv[i];
   }
 }
 
@@ -112,7 +108,7 @@ struct EpiOut { uint4 o[2]; uint4 a2; };
 template <int KIND>
 __device__ __forceinline__ void epi_math_k(int act, float (&v)[8], const EpiSide& sd, bool rope_on, EpiOut& out) {
   if constexpr (KIND == EPI_ROPE) {
-    if (rope_on) rope_turn8(__builtin_bit_cast(float4, sd.a), __builtin_bit_cast(float4, sd.b), v);
+    if (rope_on) rope_turn8(__builtin_bit_cast(float4, sd.a), __builtin_bit_cast(float4, sd.b), 1.f, v);
     out.o[0] = pack8(v);
   } else if constexpr (KIND == EPI_STORE) {
     out.o[0] = pack8(v);

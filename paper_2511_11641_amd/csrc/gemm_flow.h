@@ -133,7 +133,8 @@ struct FlowEpi {
       const float4 c4 = __builtin_bit_cast(float4, sd.a), s4 = __builtin_bit_cast(float4, sd.b);
       const float cv[4] = {c4.x, c4.y, c4.z, c4.w}, sv[4] = {s4.x, s4.y, s4.z, s4.w};
       const int i = q >> 1;
-      if constexpr (ST == 0) z[q] = q & 1 ? rope_odd(x[q - 1], x[q], cv[i], sv[i]) : rope_even(x[q], x[q + 1], cv[i], sv[i]);
+      // which product is fused is written out: as in the wide tile shapes of the other kernel, so that the route does not decide the last bit
+      if constexpr (ST == 0) z[q] = q & 1 ? __builtin_fmaf(x[q], cv[i], x[q - 1] * sv[i]) : __builtin_fmaf(x[q], cv[i], -(x[q + 1] * sv[i]));
       if constexpr (ST == 1) x[q] = rope_on ? z[q] : x[q];
     }
   }
