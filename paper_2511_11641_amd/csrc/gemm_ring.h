@@ -72,23 +72,33 @@ struct RingLoads {
   // first slab: kv (1 .. 64) of k, loaded here into `tile`; single: there is no other slab (the offsets then stay the clamped ones)
   __device__ __forceinline__ void init(const bf16_t* mat, long long ld, int r0, int R, int k0, int kv, bool single, bf16_t* tile) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    lds_bf16_t* const dst = (lds_bf16_t*)tile + wave * PER * 512;
     base = reinterpret_cast<const char*>(KSLOW ? mat + static_cast<long long>(k0) * ld + r0 : mat + static_cast<long long>(r0) * ld + k0);
+    const int last = R - r0 - (KSLOW ? 8 : 1);       // rows beyond the matrix repeat its last ones (never stored)
+    const ring_off<WIDE> ldo = static_cast<ring_off<WIDE>>(ld);
+    ring_off<WIDE> back[PER];        // how far the clamped address of the first slab lies behind that of a whole one
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int p = (wave * PER + i) * 64 + lane;      // physical chunk of the tile
-      int r, k;
       if constexpr (!KSLOW) {
-        r = p / 8;
-        k = ((p % 8) ^ (r & 7)) * 8;
+        const int k = ((lane & 7) ^ (lane >> 3)) * 8;
+        off[i] = (static_cast<ring_off<WIDE>>(min(p / 8, last)) * ldo + static_cast<ring_off<WIDE>>(k)) * 2u;
+        back[i] = static_cast<ring_off<WIDE>>(max(k + 8 - kv, 0)) * 2u;
       } else {
-        k = p / (RT / 8);
-        r = ((p % (RT / 8)) ^ ring_ks_swz<RT>(k)) * 8;
+        const int k = p / (RT / 8);
+        off[i] = (static_cast<ring_off<WIDE>>(k) * ldo + static_cast<ring_off<WIDE>>(min(((p % (RT / 8)) ^ ring_ks_swz<RT>(k)) * 8, last))) * 2u;
+        back[i] = static_cast<ring_off<WIDE>>(max(k + 1 - kv, 0)) * ldo * 2u;
       }
-      const int gr = min(r0 + r, KSLOW ? R - 8 : R - 1) - r0;          // rows beyond the matrix repeat its last ones (never stored)
-      const int gk = min(k, KSLOW ? kv - 1 : kv - 8);
-      const ring_off<WIDE> o0 = static_cast<ring_off<WIDE>>((KSLOW ? static_cast<long long>(gk) * ld + gr : static_cast<long long>(gr) * ld + gk) * 2);
-      off[i] = single ? o0 : static_cast<ring_off<WIDE>>((KSLOW ? static_cast<long long>(k) * ld + gr : static_cast<long long>(gr) * ld + k) * 2);
-      __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(base + o0), (lds_bf16_t*)tile + (wave * PER + i) * 512, 16, 0, 0);
+    }
+    if (kv == RING_BK) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i) __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(base + off[i]), dst + i * 512, 16, 0, 0);
+    } else {
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(base + (off[i] - back[i])), dst + i * 512, 16, 0, 0);
+        if (single) off[i] -= back[i];
+      }
     }
     if (!single) base += KSLOW ? static_cast<long long>(kv) * ld * 2 : kv * 2;
     step = KSLOW ? static_cast<long long>(RING_BK) * ld * 2 : RING_BK * 2;
@@ -150,32 +160,60 @@ __device__ __forceinline__ void ring_mfma(ring_f4& c, const bf16x8_t& a, const b
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 
-// Work item of a workgroup on a 1-D grid of tiles * splits: which output tile and which K split.
-// Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own.  Every XCD gets a contiguous
-// range of tile ids, and with split K the splits are spread over the XCDs first (8 / splits XCDs per split,
-// or splits / 8 splits per XCD): the tiles of one split read one K range of both operands, so an XCD's L2
-// then holds that range once instead of every XCD fetching all of K for its share of the tiles.
-__device__ __forceinline__ void gemm_work_item(int id, int nb, int splits, int& tile, int& z) {      // workgroup id of nb
-  const int tiles = nb / splits, xcd = id & 7, j = id >> 3, per = nb >> 3, more = nb & 7;      // j: index inside the XCD's share
-  if (more == 0 && splits <= 8 && (8 % splits) == 0 && tiles % (8 / splits) == 0) {
-    const int p = 8 / splits;                     // XCDs per split
-    z = xcd / p;
-    tile = (xcd % p) * (tiles / p) + j;
-  } else if (more == 0 && (splits & 7) == 0) {
-    const int q = splits >> 3;                    // splits per XCD
-    z = xcd * q + j / tiles;
-    tile = j % tiles;
-  } else {
-    const int lin = xcd * per + min(xcd, more) + j;      // contiguous range per XCD over (split, tile); the first `more` XCDs have one more
-    z = lin / tiles;
-    tile = lin - z * tiles;
+// The grid of a launch, worked out on the host: a workgroup finds its tile with multiplications.  What bounds a launch of few slabs is the
+// time to its first load and what its XCD fetches from memory: six divisions one behind the other were 0.3 us of the 1.3 us to a workgroup's
+// last first-round load, and bands of a fixed 16 tile rows had an XCD of 1024x1024x2048 on 64x64 tiles fetch 1152 operand rows where 768 do.
+// The four contractions of a layer on 1024 tokens, 1024 wide, weights from memory: 41.5 -> 39.9 us with both and the bias asked for early.
+// Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own.  Every XCD gets a contiguous range of (K split, tile), so the
+// tiles of one split, which read one K range of both operands, are on as few XCDs as there are.  Inside a split the tiles are ordered in
+// bands of tile rows walked column by column, so that the tiles an XCD works on at a time form a block of C and share operand rows in
+// its L2; the height of a band is the one whose blocks have the fewest operand rows.
+struct RingGrid {
+  int tiles_n, k_chunk;
+  int per, more;                  // workgroups per XCD; the first `more` XCDs have one more
+  int tiles, group, band, last_band, last_rows;      // tiles of a split; rows and tiles of a band; where the last band starts, its rows
+  unsigned tiles_inv, band_inv, group_inv, last_inv;
+};
+static inline unsigned ring_inverse(unsigned d) { return d <= 1 ? ~0u : static_cast<unsigned>((1ull << 32) / d); }
+static inline RingGrid ring_grid(int M, int N, int bm, int bn, int splits, int k_chunk) {
+  RingGrid g;
+  const int tiles_m = (M + bm - 1) / bm;
+  g.tiles_n = (N + bn - 1) / bn;
+  g.k_chunk = k_chunk;
+  g.tiles = tiles_m * g.tiles_n;
+  const int nb = g.tiles * splits;
+  g.per = nb >> 3;
+  g.more = nb & 7;
+  const int at_once = g.per < 1 ? 1 : (g.per < 32 ? g.per : 32);      // tiles that an XCD's 32 compute units work on at a time
+  long long fewest = 0;
+  g.group = 1;
+  for (int r = 1; r <= 16 && r <= tiles_m; ++r) {
+    const long long rows = static_cast<long long>(r) * bm + static_cast<long long>((at_once + r - 1) / r) * bn;
+    if (r == 1 || rows < fewest) { fewest = rows; g.group = r; }
   }
+  const int bands = (tiles_m + g.group - 1) / g.group;
+  g.group = (tiles_m + bands - 1) / bands;           // bands of equal height
+  g.band = g.group * g.tiles_n;
+  g.last_band = (tiles_m - 1) / g.group;
+  g.last_rows = tiles_m - g.last_band * g.group;
+  g.tiles_inv = ring_inverse(g.tiles);
+  g.band_inv = ring_inverse(g.band);
+  g.group_inv = ring_inverse(g.group);
+  g.last_inv = ring_inverse(g.last_rows);
+  return g;
+}
+// a / d with d's ring_inverse(): the product's high half falls short by one at most
+__device__ __forceinline__ int ring_div(int a, int d, unsigned inv, int& rest) {
+  int q = static_cast<int>(__umulhi(static_cast<unsigned>(a), inv));
+  rest = a - q * d;
+  if (rest >= d) { ++q; rest -= d; }
+  return q;
 }
 
-// One output tile (of one K split): that of workgroup `block` of `blocks`.
+// One output tile (of one K split): that of workgroup `block` of the grid w.
 // EPIS: bit mask of the epilogue kinds the instantiation carries; CS: column sums of a K-slow A (GemmDesc::colsum); WIDE: see ring_off.
 template <int BM, int BN, int NS, bool TA, bool TB, bool CS, int EPIS, bool WIDE>
-__device__ __forceinline__ void ring_tile(const GemmDesc& d, int tiles_n, int k_chunk, int block, int blocks) {
+__device__ __forceinline__ void ring_tile(const GemmDesc& d, const RingGrid& w, int block) {
   constexpr int WTM = BM / 2, WTN = BN / 2, FM = WTM / 16, FN = WTN / 16, S = RING_BK / 32, NM = FM * FN, NR = FM + FN;
   constexpr int STAGE = (BM + BN) * RING_BK;
   static_assert(FN % 2 == 0, "the epilogue pairs column blocks");
@@ -185,19 +223,15 @@ __device__ __forceinline__ void ring_tile(const GemmDesc& d, int tiles_n, int k_
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 1, wn = __builtin_amdgcn_readfirstlane(wave & 1);
 
-  // tile order: bands of GROUP_M tile rows walked column by column, so that the tiles an XCD works on at a time form a
-  // near-square block of C and share operand rows in its L2
-  int id, zsplit;
-  const int nsplit = d.splits > 1 ? d.splits : 1;
-  gemm_work_item(block, blocks, nsplit, id, zsplit);
-  constexpr int GROUP_M = BM >= 192 ? 4 : (BM >= 128 ? 8 : 16);
-  const int tiles_m = blocks / nsplit / tiles_n;
-  const int band = id / (GROUP_M * tiles_n), in_band = id - band * (GROUP_M * tiles_n);
-  const int band_rows = min(GROUP_M, tiles_m - band * GROUP_M);
-  const int tile_col = in_band / band_rows;
-  const int m0 = (band * GROUP_M + in_band % band_rows) * BM, n0 = tile_col * BN;
-  const int k_begin = zsplit * k_chunk;
-  const int k_end = min(d.K, k_begin + k_chunk);
+  const int xcd = block & 7, tiles_n = w.tiles_n;
+  int id = xcd * w.per + min(xcd, w.more) + (block >> 3), zsplit = 0, in_band, tile_row;
+  if (d.splits > 1) zsplit = ring_div(id, w.tiles, w.tiles_inv, id);
+  const int band = ring_div(id, w.band, w.band_inv, in_band);
+  const bool last_band = band == w.last_band;
+  const int tile_col = ring_div(in_band, last_band ? w.last_rows : w.group, last_band ? w.last_inv : w.group_inv, tile_row);
+  const int m0 = (band * w.group + tile_row) * BM, n0 = tile_col * BN;
+  const int k_begin = zsplit * w.k_chunk;
+  const int k_end = min(d.K, k_begin + w.k_chunk);
   const int nk = (k_end - k_begin + RING_BK - 1) / RING_BK;
   const int kv = (k_end - k_begin) - (nk - 1) * RING_BK;         // k of the first slab
 
@@ -233,6 +267,23 @@ __device__ __forceinline__ void ring_tile(const GemmDesc& d, int tiles_n, int k_
   static_assert(LPW * (NS - 1) < 64, "vmcnt range");
   la.init(static_cast<const bf16_t*>(d.A), d.lda, m0, d.M, k_begin, kv, nk == 1, lds);
   lb.init(static_cast<const bf16_t*>(d.B), d.ldb, n0, d.N, k_begin, kv, nk == 1, lds + BM * RING_BK);
+  // A lane keeps its columns (see the epilogue) for every row: their bias is loaded once.  Tiles that leave registers for it ask for it here,
+  // behind the first slab; asked for behind the loop it comes from memory while everything waits (stores out 0.75 -> 0.5 us behind the loop's end).
+  const int l16 = lane & 15, g = lane >> 4, nw = n0 + wn * WTN + 16 * (g & 1) + 8 * (g >> 1);
+  constexpr int JP = FN / 2;
+  constexpr bool BIAS_EARLY = NM <= 24;      // (256x256 tiles: 32 x 1024 tokens, 1024 -> 1536 columns, 80 -> 87 us with the loop's registers so much fewer)
+  uint4 braw[JP];
+  const bool has_bias = d.splits <= 1 && d.epi.bias != nullptr && d.epi.kind != EPI_DACT && d.epi.kind != EPI_DSWIGLU;
+  auto load_bias = [&]() __attribute__((always_inline)) {
+    if (has_bias) {
+#pragma unroll
+      for (int j = 0; j < JP; ++j) braw[j] = *reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(d.epi.bias) + min(nw + j * 32, d.N - 8));
+    }
+  };
+  if constexpr (BIAS_EARLY) {
+    load_bias();
+    asm volatile("" ::: "memory");
+  }
   auto issue = [&](auto q_, auto buf_, bool adv) __attribute__((always_inline)) {
     constexpr int q = decltype(q_)::value, buf = decltype(buf_)::value;
     if constexpr (q < PA) la.issue(q, lds3 + buf * STAGE, adv ? la.step : 0);
@@ -360,7 +411,6 @@ __device__ __forceinline__ void ring_tile(const GemmDesc& d, int tiles_n, int k_
     for (int j = 0; j < FN; ++j) asm volatile("" : "+a"(acc[i][j]));
   __builtin_amdgcn_sched_barrier(0);
 
-  const int l16 = lane & 15, g = lane >> 4;
   if constexpr (CS) {
     // lanes of one l16 hold the sums over different k; the two wavefront columns took different slabs
     __syncthreads();                            // everyone's loads have landed: LDS is free
@@ -380,8 +430,7 @@ __device__ __forceinline__ void ring_tile(const GemmDesc& d, int tiles_n, int k_
   // Epilogue straight from the accumulators.  acc[i][j] of lane (l16, g): row i * 16 + l16, columns j * 16 + 4 g + 0..3; two
   // neighbouring column blocks swap their odd and even lane groups, so that a lane holds 8 consecutive columns (16-byte stores,
   // 64 bytes per row and instruction; staging the tile through LDS instead costs 4 us more on a 256x256 tile).
-  const int mw = m0 + wm * WTM + l16, nw = n0 + wn * WTN + 16 * (g & 1) + 8 * (g >> 1);
-  constexpr int JP = FN / 2;
+  const int mw = m0 + wm * WTM + l16;
   auto vals = [&](auto i_, auto jp_, float (&v)[8]) __attribute__((always_inline)) {
     constexpr int i = decltype(i_)::value, jp = decltype(jp_)::value;
 #pragma unroll
@@ -408,13 +457,7 @@ __device__ __forceinline__ void ring_tile(const GemmDesc& d, int tiles_n, int k_
     });
     return;
   }
-  // A lane keeps its columns for every row: their bias is loaded once.
-  uint4 braw[JP];
-  const bool has_bias = d.epi.bias != nullptr && d.epi.kind != EPI_DACT && d.epi.kind != EPI_DSWIGLU;
-  if (has_bias) {
-#pragma unroll
-    for (int j = 0; j < JP; ++j) braw[j] = *reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(d.epi.bias) + min(nw + j * 32, d.N - 8));
-  }
+  if constexpr (!BIAS_EARLY) load_bias();
   auto add_bias = [&](int jp, float (&v)[8]) __attribute__((always_inline)) {
     if (has_bias) {
       float b[8];
@@ -542,16 +585,16 @@ __device__ __forceinline__ void ring_tile(const GemmDesc& d, int tiles_n, int k_
 
 template <int BM, int BN, int NS, bool TA, bool TB, bool CS, int EPIS, bool WIDE = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void gemm_bf16_ring_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
-  ring_tile<BM, BN, NS, TA, TB, CS, EPIS, WIDE>(d, tiles_n, k_chunk, blockIdx.x, gridDim.x);
+void gemm_bf16_ring_kernel(const RingGrid w, const GemmDesc d) {
+  ring_tile<BM, BN, NS, TA, TB, CS, EPIS, WIDE>(d, w, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------
 // launch
 template <int BM, int BN, int NS, bool TA, bool TB, bool CS, int EPIS, bool WIDE = false>
 static hipError_t ring_launch_shape(ecospa_ctx* ctx, const GemmDesc& d, int k_chunk) {
-  const int tm = (d.M + BM - 1) / BM, tn = (d.N + BN - 1) / BN;
   const int splits = d.splits > 1 ? d.splits : 1;
+  const RingGrid w = ring_grid(d.M, d.N, BM, BN, splits, k_chunk);
   constexpr int lds_bytes = NS * (BM + BN) * RING_BK * static_cast<int>(sizeof(bf16_t));
   static_assert(lds_bytes <= 160 * 1024, "LDS of a compute unit");
   auto kern = gemm_bf16_ring_kernel<BM, BN, NS, TA, TB, CS, EPIS, WIDE>;
@@ -560,7 +603,7 @@ static hipError_t ring_launch_shape(ecospa_ctx* ctx, const GemmDesc& d, int k_ch
     const hipError_t e = attr_once.ensure(reinterpret_cast<const void*>(kern), lds_bytes);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kern, dim3(tm * tn * splits), dim3(256), lds_bytes, ctx->stream, d, tn, k_chunk);
+  hipLaunchKernelGGL(kern, dim3(w.tiles * splits), dim3(256), lds_bytes, ctx->stream, w, d);
   return hipGetLastError();
 }
 
@@ -569,21 +612,22 @@ static hipError_t ring_launch_shape(ecospa_ctx* ctx, const GemmDesc& d, int k_ch
 // stores with the matrix units idle, and often fills a part of the compute units only (when it is taken: pair_pays() in gemm.hip).
 template <int TM, int TN, int TS, bool CS, int XM, int XN, int XS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void gemm_bf16_pair_kernel(const GemmDesc w, const GemmDesc x, int w_tiles_n, int w_k_chunk, int n_tt, int x_tiles_n) {
+void gemm_bf16_pair_kernel(const RingGrid wg, const RingGrid xg, int n_tt, const GemmDesc w, const GemmDesc x) {
   const int block = blockIdx.x;
-  if (block < n_tt) ring_tile<TM, TN, TS, true, true, CS, GEMM_EPIS_TX, false>(w, w_tiles_n, w_k_chunk, block, n_tt);
-  else ring_tile<XM, XN, XS, false, false, false, 1 << EPI_STORE, false>(x, x_tiles_n, (x.K + 63) / 64 * 64, block - n_tt, gridDim.x - n_tt);
+  if (block < n_tt) ring_tile<TM, TN, TS, true, true, CS, GEMM_EPIS_TX, false>(w, wg, block);
+  else ring_tile<XM, XN, XS, false, false, false, 1 << EPI_STORE, false>(x, xg, block - n_tt);
 }
 template <int TM, int TN, int TS, bool CS, int XM, int XN, int XS>
 static hipError_t ring_launch_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int w_k_chunk) {
-  const int splits = w.splits > 1 ? w.splits : 1, wn = (w.N + TN - 1) / TN, xn = (x.N + XN - 1) / XN;
-  const int n_tt = (w.M + TM - 1) / TM * wn * splits, n_nt = (x.M + XM - 1) / XM * xn;
+  const int splits = w.splits > 1 ? w.splits : 1;
+  const RingGrid wg = ring_grid(w.M, w.N, TM, TN, splits, w_k_chunk), xg = ring_grid(x.M, x.N, XM, XN, 1, (x.K + 63) / 64 * 64);
+  const int n_tt = wg.tiles * splits;
   constexpr int lds_w = TS * (TM + TN) * RING_BK * 2, lds_x = XS * (XM + XN) * RING_BK * 2, lds_bytes = lds_w > lds_x ? lds_w : lds_x;
   static_assert(lds_bytes > 64 * 1024 && lds_bytes <= 160 * 1024, "LDS of a compute unit");
   auto kern = gemm_bf16_pair_kernel<TM, TN, TS, CS, XM, XN, XS>;
   static LdsAttrOnce attr_once;
   const hipError_t e = attr_once.ensure(reinterpret_cast<const void*>(kern), lds_bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(n_tt + n_nt), dim3(256), lds_bytes, ctx->stream, w, x, wn, w_k_chunk, n_tt, xn);
+  hipLaunchKernelGGL(kern, dim3(n_tt + xg.tiles), dim3(256), lds_bytes, ctx->stream, wg, xg, n_tt, w, x);
   return hipGetLastError();
 }
