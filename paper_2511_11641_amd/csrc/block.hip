@@ -238,9 +238,8 @@ extern "C" int ecospa_coupled_fwd(ecospa_ctx* ctx, const ecospa_block_desc* desc
   if (rc) return rc;
   if (!aligned16(x) || !aligned16(y)) return ECOSPA_ERR_ALIGN;
   BlockWs w;
-  block_ws_layout(*desc, nullptr, w);
-  if (!ctx->ws || ctx->ws_bytes < w.total) return ECOSPA_ERR_WORKSPACE;
   block_ws_layout(*desc, ctx->ws, w);
+  if (!ctx->ws || ctx->ws_bytes < w.total) return ECOSPA_ERR_WORKSPACE;
   if (desc->block == ECOSPA_BLOCK_FFN) return ffn_forward(ctx, *desc, w, x, y, saved);
   return attn_forward(ctx, *desc, w, x, y, saved);
 }
@@ -252,9 +251,8 @@ extern "C" int ecospa_coupled_bwd(ecospa_ctx* ctx, const ecospa_block_desc* desc
   if (rc) return rc;
   if (!aligned16(x) || !aligned16(dy) || (dx && !aligned16(dx))) return ECOSPA_ERR_ALIGN;
   BlockWs w;
-  block_ws_layout(*desc, nullptr, w);
-  if (!ctx->ws || ctx->ws_bytes < w.total) return ECOSPA_ERR_WORKSPACE;
   block_ws_layout(*desc, ctx->ws, w);
+  if (!ctx->ws || ctx->ws_bytes < w.total) return ECOSPA_ERR_WORKSPACE;
   if (desc->block == ECOSPA_BLOCK_FFN) return ffn_backward(ctx, *desc, w, x, dy, *saved, dx, *grads);
   return attn_backward(ctx, *desc, w, x, dy, *saved, dx, *grads);
 }

@@ -238,7 +238,7 @@ static unsigned ring_shapes_built(int trans_a, int trans_b) {
   return trans_b ? 0x391u : 0x101u;
 }
 // Shape and split that finish soonest; splits > 0: that many, else 1 .. max_splits.  Returns the time (us).
-static double ring_plan(int trans_a, int trans_b, int M, int N, int K, int kind, int splits, int max_splits, int* shape_out, int* splits_out) {
+static double ring_plan_search(int trans_a, int trans_b, int M, int N, int K, int kind, int splits, int max_splits, int* shape_out, int* splits_out) {
   const int slabs = (K + 63) / 64;
   const unsigned built = ring_shapes_built(trans_a, trans_b);
   double best = 0.0;
@@ -261,6 +261,28 @@ static double ring_plan(int trans_a, int trans_b, int M, int N, int K, int kind,
   *shape_out = bs;
   *splits_out = bq;
   return best;
+}
+// The same from a table that each thread keeps of its latest questions (a function of the eight numbers alone).  A forward or backward call of a
+// block asks thirty times - its workspace is laid out from the same answers - and 0.3 us each were half of the host time of such a call, which
+// is what a few tokens wait for: attention and FFN block on 61 tokens, 2048 wide: enqueued in 23 us, with the table in 15.
+static double ring_plan(int trans_a, int trans_b, int M, int N, int K, int kind, int splits, int max_splits, int* shape_out, int* splits_out) {
+  struct Answer {
+    int q[8];
+    int shape, splits;
+    double t;
+  };
+  static thread_local Answer table[128];      // all zeros: M = 0 is nobody's question
+  const int q[8] = {trans_a, trans_b, M, N, K, kind, splits, max_splits};
+  unsigned h = 0;
+  for (int i = 0; i < 8; ++i) h = (h ^ static_cast<unsigned>(q[i])) * 0x9e3779b1u;
+  Answer& a = table[h >> 25];
+  if (memcmp(a.q, q, sizeof(q)) != 0) {
+    a.t = ring_plan_search(trans_a, trans_b, M, N, K, kind, splits, max_splits, &a.shape, &a.splits);
+    memcpy(a.q, q, sizeof(q));
+  }
+  *shape_out = a.shape;
+  *splits_out = a.splits;
+  return a.t;
 }
 static double flow_time(const GemmDesc& d) {
   const long long tiles = static_cast<long long>((d.M + GEMM_FLOW_TILE - 1) / GEMM_FLOW_TILE) * ((d.N + GEMM_FLOW_TILE - 1) / GEMM_FLOW_TILE);
