@@ -27,7 +27,7 @@ struct BlockWs {           // pieces carved from the caller's workspace
 // K split of a contraction over few tokens (x W^T, dY W): partials from the workspace, reduced right after the launch.
 static inline void block_token_split(GemmDesc& g, const BlockWs& w) {
   const int s = g.dtype == ECOSPA_BF16 ? ecospa_gemm_token_splits(g.M, g.N, g.K) : 1;
-  if (s > 1 && w.partial_x) { g.splits = s; g.partial = w.partial_x; }
+  if (s > 1 && w.partial_x && !ecospa_gemm_shares_k(g)) { g.splits = s; g.partial = w.partial_x; }
 }
 static inline size_t block_token_split_bytes(int M, int N, int K) {
   const int s = ecospa_gemm_token_splits(M, N, K);

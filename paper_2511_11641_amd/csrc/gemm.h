@@ -46,7 +46,7 @@ struct GemmDesc {
   const void* B;
   long long ldb;
   int trans_b;
-  int tile;          // 0 = choose, otherwise a tile code of ecospa_contract, or 39 .. 41 (64x128, 128x64, 64x64)
+  int tile;          // 0 = choose, otherwise a tile code of ecospa_contract, 39 .. 41 (64x128, 128x64, 64x64) or 50 .. 53 (gemm_share.h)
   int splits;        // > 1: split K, fp32 partials in `partial`, reduced in a fixed order
   float* partial;    // [splits][M][N] when splits > 1
   int defer_reduce;  // splits > 1: only write the partials; the caller runs ecospa_gemm_reduce later
@@ -61,8 +61,8 @@ int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d);
 // Two contractions that do not depend on each other: w a weight gradient (dY^T X, bf16 or fp32; its reduction deferred where K is split), x
 // over the same tokens.  One launch where that is built for the two and pays, otherwise w, then x (x_first: the other way round).
 int ecospa_gemm_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int x_first = 0);
-// What the two above choose (host arithmetic only; they launch by it).  A bf16 contraction: the tile shape of the ring kernel, or GEMM_ROUTE_FLOW
-// for the kernel of resident workgroups.  A pair: one launch or two, and for one of bf16 the tile shapes.
+// What the two above choose (host arithmetic only; they launch by it).  A bf16 contraction: the tile shape of the ring kernel, GEMM_ROUTE_FLOW
+// for the kernel of resident workgroups, or GEMM_ROUTE_SHARE and a shape of the kernel that shares K out inside a workgroup.  A pair: one launch or two, and for one of bf16 the tile shapes.
 int ecospa_gemm_route(const GemmDesc& d);
 enum { GEMM_PAIR_NONE = 0, GEMM_PAIR_BF16 = 1, GEMM_PAIR_F32 = 2 };
 int ecospa_gemm_pair_route(const GemmDesc& w, const GemmDesc& x, int* w_shape, int* x_shape);
@@ -76,11 +76,15 @@ int ecospa_gemm_splits(int dtype, int M, int N, int K);
 // The same question for the contractions whose M is the token count (x W^T and dY W): with few tokens (inference
 // at batch 1) their output has too few tiles for the chip; 1 for the training shapes.
 int ecospa_gemm_token_splits(int M, int N, int K);
+// Whether a contraction of few tokens is done sooner with K shared out inside the workgroups (gemm_share.h) than split over them.
+bool ecospa_gemm_shares_k(const GemmDesc& d);
 
 // The bf16 kernel (gemm_ring.h): launch of tile shape `shape` (index into the table in gemm.hip; not every shape is built for every
 // form).  k_chunk: K range of a split, a multiple of 64.
 #define GEMM_RING_NSHAPES 12
 #define GEMM_ROUTE_FLOW GEMM_RING_NSHAPES
+#define GEMM_ROUTE_SHARE (GEMM_RING_NSHAPES + 1)
+#define GEMM_SHARE_NSHAPES 4
 // Epilogue kinds that are built, as bit masks: x W^T carries all of them, dY W the activation derivatives, the forms with a K-slow A
 // only the plain store.  (A split contraction leaves partial sums; the reduction behind it knows every kind.)
 #define GEMM_EPIS_NT 0x7f
@@ -106,6 +110,7 @@ static inline bool gemm_flow_takes(const GemmDesc& d) {
   return d.splits <= 1 && !d.colsum && (d.trans_a != 0) == (d.trans_b != 0) && !(d.trans_a && d.epi.bias) && tiles > 256 && tiles < (1 << 24) &&
          d.K % 64 == 0 && d.K / 64 >= GEMM_FLOW_MIN_SLABS && !(act && d.epi.act != ECOSPA_ACT_GELU_ERF) && !ring_wide(d);
 }
+hipError_t gemm_share_launch_nt(ecospa_ctx* ctx, const GemmDesc& d, int shape);
 hipError_t gemm_flow_launch_nt(ecospa_ctx* ctx, const GemmDesc& d);
 hipError_t gemm_flow_launch_tt(ecospa_ctx* ctx, const GemmDesc& d);
 hipError_t gemm_ring_launch_nt(ecospa_ctx* ctx, const GemmDesc& d, int shape, int k_chunk);

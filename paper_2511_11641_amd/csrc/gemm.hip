@@ -1,7 +1,7 @@
 // Dense contractions of the reduced forward/backward pass: choice of kernel, tile shape and K split, the fp32 kernel, and the
 // reductions of split contractions.
 //
-// bf16: the kernels of gemm_ring.h and, for several rounds of tiles, gemm_flow.h (MFMA, direct global -> LDS loads).
+// bf16: the kernels of gemm_ring.h and, for several rounds of tiles, gemm_flow.h, for few tokens gemm_share.h (MFMA, direct global -> LDS loads).
 // fp32: MFMA on fragments loaded straight from memory (the fp32 configuration is small and latency bound).
 // Split-K writes fp32 partials that a second kernel adds in a fixed order (deterministic dW).
 #include "gemm_epi.h"
@@ -291,6 +291,31 @@ static double flow_time(const GemmDesc& d) {
   return FLOW_REST + rounds * (d.K / 64 * (d.trans_a ? FLOW_SLAB_TT : FLOW_SLAB_NT) + FLOW_ROUND) + epi * (1.0 + 0.2 * (rounds - 1.0));
 }
 
+// Kernel that shares K out inside a workgroup: time of a round (us, weights from memory) and per unit of 64 k.  Single rounds fit to 0.5 us from K = 768
+// to 4096 and 17 to 256 rows; a further round costs about as much as the first (512 tiles of 64x32 at K = 512: 7.3 us, 64x64 of the ring kernel 4.9).
+struct ShareShape {
+  int bm, bn;
+  float round, unit;
+};
+static const ShareShape SHARE_SHAPES[GEMM_SHARE_NSHAPES] = {{32, 16, 2.3f, 0.11f}, {32, 32, 2.2f, 0.155f}, {64, 16, 2.0f, 0.18f}, {64, 32, 2.3f, 0.215f}};
+static bool gemm_share_takes(const GemmDesc& d) {
+  return d.dtype == ECOSPA_BF16 && !d.trans_a && !d.trans_b && d.splits <= 1 && !d.colsum && !ring_wide(d);
+}
+static double share_plan(const GemmDesc& d, int* shape_out) {
+  const int units = (d.K + 63) / 64;
+  double best = 0.0;
+  for (int q = 0; q < GEMM_SHARE_NSHAPES; ++q) {
+    const ShareShape& r = SHARE_SHAPES[q];
+    const long long tiles = static_cast<long long>((d.M + r.bm - 1) / r.bm) * ((d.N + r.bn - 1) / r.bn);
+    const double t = static_cast<double>((tiles + 255) / 256) * (r.round + units * r.unit + epi_us(d.epi.kind) * r.bm * r.bn / 1000.0);
+    if (q == 0 || t < best) { best = t; *shape_out = q; }
+  }
+  return best;
+}
+// What the ring kernel takes beyond its table on 64-wide tiles, whose slabs the table has from L2: with weights from memory, 61 to 256 rows, 64x64
+// unsplit, it takes 5.2 us at K = 768, 6.3 at 1024, 11.5 at 2048 and 20.5 at 4096 (table 5.7, 6.3, 9.0, 14.3).
+static double ring_cold(int shape, int slabs) { return shape >= 9 ? 0.065 * slabs - 0.6 : 0.0; }
+
 int ecospa_gemm_splits(int dtype, int M, int N, int K) {
   if (dtype != ECOSPA_BF16) return 1;      // the fp32 kernel shares K out inside a workgroup
   int shape, sp;
@@ -302,6 +327,13 @@ int ecospa_gemm_token_splits(int M, int N, int K) {
   int shape, sp;
   ring_plan(0, 0, M, N, K, EPI_STORE, 0, 8, &shape, &sp);
   return sp;
+}
+
+bool ecospa_gemm_shares_k(const GemmDesc& d) {
+  if (!gemm_share_takes(d)) return false;
+  int shape, sp, share;
+  const double t = ring_plan(0, 0, d.M, d.N, d.K, d.epi.kind, 0, 8, &shape, &sp);
+  return share_plan(d, &share) < t + ring_cold(shape, ((d.K + 63) / 64 + sp - 1) / sp);
 }
 
 // Workgroup tile that a tile code names, or 0: those of the contraction entry point, and 39 .. 41 for the 64-wide shapes.
@@ -381,10 +413,19 @@ static void prof_end(ecospa_ctx* ctx, double flop) {
   ctx->prof_flop[ctx->prof_n++] = flop;
 }
 
+// Ring kernel or resident workgroups.
+static int tiled_route(const GemmDesc& d, double* t) {
+  const int shape = ring_shape(d, d.splits > 1 ? d.splits : 1, t);
+  return gemm_flow_takes(d) && flow_time(d) < *t ? GEMM_ROUTE_FLOW : shape;
+}
+
 int ecospa_gemm_route(const GemmDesc& d) {
   double t;
-  const int shape = ring_shape(d, d.splits > 1 ? d.splits : 1, &t);
-  return gemm_flow_takes(d) && flow_time(d) < t ? GEMM_ROUTE_FLOW : shape;
+  int share;
+  if (d.tile >= 50 && d.tile < 50 + GEMM_SHARE_NSHAPES && gemm_share_takes(d)) return GEMM_ROUTE_SHARE + d.tile - 50;
+  const int route = tiled_route(d, &t);
+  if (d.tile == 0 && route != GEMM_ROUTE_FLOW && gemm_share_takes(d) && share_plan(d, &share) < t + ring_cold(route, (d.K + 63) / 64)) return GEMM_ROUTE_SHARE + share;
+  return route;
 }
 
 int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d) {
@@ -395,7 +436,8 @@ int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d) {
     const bool prof = prof_begin(ctx);
     const int k_chunk = ring_chunk(d, splits), shape = ecospa_gemm_route(d);
     hipError_t le;
-    if (shape == GEMM_ROUTE_FLOW) le = d.trans_a ? gemm_flow_launch_tt(ctx, d) : gemm_flow_launch_nt(ctx, d);
+    if (shape >= GEMM_ROUTE_SHARE) le = gemm_share_launch_nt(ctx, d, shape - GEMM_ROUTE_SHARE);
+    else if (shape == GEMM_ROUTE_FLOW) le = d.trans_a ? gemm_flow_launch_tt(ctx, d) : gemm_flow_launch_nt(ctx, d);
     else if (d.trans_a && d.trans_b) le = gemm_ring_launch_tt(ctx, d, shape, k_chunk);
     else if (d.trans_a || d.trans_b) le = gemm_ring_launch_mixed(ctx, d, shape, k_chunk);
     else le = gemm_ring_launch_nt(ctx, d, shape, k_chunk);
@@ -461,7 +503,10 @@ int ecospa_gemm_pair_route(const GemmDesc& w, const GemmDesc& x, int* w_shape, i
   const int splits = w.splits > 1 ? w.splits : 1;
   if (w.dtype == ECOSPA_BF16) {
     if (x.trans_b || x.epi.kind != EPI_STORE || (splits > 1 && !w.defer_reduce) || ring_wide(w) || ring_wide(x)) return GEMM_PAIR_NONE;
-    const int ws = *w_shape = ecospa_gemm_route(w), xs = *x_shape = ecospa_gemm_route(x);
+    // x on its tiles of the ring kernel - but not where so few tokens would have it split along K, and it runs by itself with K shared out
+    if (ecospa_gemm_shares_k(x) && ecospa_gemm_token_splits(x.M, x.N, x.K) > 1) return GEMM_PAIR_NONE;
+    double t;
+    const int ws = *w_shape = ecospa_gemm_route(w), xs = *x_shape = tiled_route(x, &t);
     if (ws == GEMM_ROUTE_FLOW || xs == GEMM_ROUTE_FLOW) return GEMM_PAIR_NONE;
     return RING_SHAPES[ws].bn == 128 && ((GEMM_PAIR_X >> xs) & 1) && pair_pays(w, splits, ws, x, xs) ? GEMM_PAIR_BF16 : GEMM_PAIR_NONE;
   }

@@ -1,0 +1,44 @@
+"""The contraction kernel that shares K out over the wavefronts of a workgroup (csrc/gemm_share.h) against the kernel whose wavefronts share every
+slab: every tile shape and epilogue, rows and columns off every tile, K from one part of a unit to more units than there are buffers, and
+wavefronts without any."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2511_11641_amd import binding as B
+from test_gpu_contract_flow import ACT, BIAS_ACT, DACT, DSWIGLU, ROPE, STORE, SWIGLU, _desc
+
+pytestmark = pytest.mark.gpu
+GEMM = "_Z11ecospa_gemmP10ecospa_ctxRK8GemmDesc"
+RING_128 = 38          # tile code: 128 x 128 of the other kernel
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    return B.Context("cuda:0")
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (33, 40, 56), (31, 72, 64), (65, 248, 520), (64, 96, 1608), (130, 24, 2048)])
+@pytest.mark.parametrize("tile", [50, 51, 52, 53])
+@pytest.mark.parametrize("kind,act,bias", [(STORE, 0, True), (STORE, 0, False), (BIAS_ACT, 0, True), (ACT, 0, False), (ACT, 1, True), (DACT, 0, True),
+                                           (DSWIGLU, 0, True), (ROPE, 0, True), (SWIGLU, 0, True), (SWIGLU, 0, False)])
+def test_shared_k_gives_what_shared_slabs_give(ctx, kind, act, bias, tile, M, N, K):
+    if kind == ROPE and N < 144:
+        N = 144          # four query and two key heads of 24
+    gen = torch.Generator(device="cuda").manual_seed(81)
+    g, c, c2, keep = _desc(kind, False, M, N, K, gen, bias, keep_c=bias or kind != SWIGLU)
+    g.epi.act = (B.ACT_GELU_ERF, B.ACT_GELU_TANH)[act]
+    out = []
+    for g.tile in (tile, RING_128):
+        c.fill_(7.0)
+        c2.fill_(7.0)
+        assert getattr(ctx.lib, GEMM)(ctx.h, C.byref(g)) == B.OK
+        out.append((c.clone(), c2.clone()))
+    for x, y in zip(*out):
+        assert bool((x[M:] == 7).all()) and bool((x[:, -8:] == 7).all()), "written beyond the matrix"
+        # fp32 sums of up to 2048 products of size 1, in another order, differ by less than 2048^0.5 2^-24 4 = 1e-5; behind it bf16 rounds to a
+        # neighbour at most (2^-7 of a value), of few values: a sum lies within 1e-5 of a rounding boundary 2^-8 apart
+        assert bool(((x.float() - y.float()).abs() <= y.float().abs() * 2.0 ** -7 + 4e-5).all())
+        assert float((x != y).float().mean()) < 0.03
+    del keep
