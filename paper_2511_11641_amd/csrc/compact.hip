@@ -29,23 +29,23 @@ struct MapArgs {
 // Kept count of group g: the ragged count is clamped to what the destination and the index list hold.
 __device__ __forceinline__ int map_kept(const MapArgs& m, int g) {
   if (!m.k_group) return m.k;
-  const int kg = m.k_group[g / m.idx_div], cap = m.kp < m.ld_idx ? m.kp : m.ld_idx;
+  const int kg = m.k_group[static_cast<unsigned>(g) / static_cast<unsigned>(m.idx_div)], cap = m.kp < m.ld_idx ? m.kp : m.ld_idx;
   return kg < 0 ? 0 : (kg < cap ? kg : cap);
 }
 
-__device__ __forceinline__ long long map_slot(const MapArgs& m, long long s) {
+// Slots are counted in 32 bits (a destination has fewer than 2^31): with 64-bit divisions the few of a slot were longer than the copy of a small
+// matrix (256x1024 fp32 columns and 1024x256 rows, half kept, with the window's atomics replaced as well: 9.5 -> 5.1 us).  No branches
+// round divisors of one: they cost the 24-layer gather 0.4 %.
+__device__ __forceinline__ long long map_slot(const MapArgs& m, long long slot) {
+  const unsigned s = static_cast<unsigned>(slot), unit = static_cast<unsigned>(m.unit);
+  const unsigned per = static_cast<unsigned>(m.scatter ? m.n : m.kp * m.unit);      // slots of a group
+  const unsigned g = s / per, rem = s - g * per, i = rem / unit, u = rem - i * unit;
+  const int* list = m.idx + static_cast<long long>(g / static_cast<unsigned>(m.idx_div)) * m.ld_idx;
+  const int kg = map_kept(m, static_cast<int>(g)), q = static_cast<int>(i);
   if (!m.scatter) {
-    const int per = m.kp * m.unit;
-    const int g = static_cast<int>(s / per), rem = static_cast<int>(s % per);
-    const int i = rem / m.unit, u = rem % m.unit;
-    if (i >= map_kept(m, g)) return -1;
-    return static_cast<long long>(g) * m.n +
-           static_cast<long long>(m.idx[static_cast<long long>(g / m.idx_div) * m.ld_idx + i]) * m.unit + u;
+    if (q >= kg) return -1;
+    return static_cast<long long>(g) * m.n + static_cast<long long>(list[q]) * m.unit + u;
   }
-  const int g = static_cast<int>(s / m.n), rem = static_cast<int>(s % m.n);
-  const int q = rem / m.unit, u = rem % m.unit;
-  const int* list = m.idx + static_cast<long long>(g / m.idx_div) * m.ld_idx;
-  const int kg = map_kept(m, g);
   int lo = 0, hi = kg;   // first position with list[pos] >= q
   while (lo < hi) {
     const int mid = (lo + hi) >> 1;
@@ -285,6 +285,14 @@ __device__ __forceinline__ void map_cols_block(const MapItemDev& t, int blk) {
 // wider than the LDS tile (kept indices far apart: below a quarter kept) the region falls back to element-wise
 // gathers.  Measured: 16 column groups x 16 rows per pass beat 32 x 8 (1.5 % on a 24-layer launch, 12 % on a
 // single layer's) and 8 x 32; 64 x 4 is a third slower.
+// least of the 64 lanes' values, by lane permutations (see row16_sum)
+__device__ __forceinline__ int wave_min(int v) {
+  v = min(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true));
+  v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true));
+  v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true));
+  v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, true));
+  return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)), min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
 #define MAP_LDS_GROUPS 16          // 16-byte column groups per workgroup
 #define MAP_LDS_ROWS (256 / MAP_LDS_GROUPS)   // rows per pass (MAP_LDS_GROUPS * MAP_LDS_ROWS = 256 threads)
 #define MAP_LDS_ROWS_TOTAL 64      // rows per workgroup
@@ -295,7 +303,7 @@ __device__ __forceinline__ void map_cols_lds_block(const MapItemDev& t, int blk,
   constexpr int CB = MAP_LDS_GROUPS * V;
   E* tile = reinterpret_cast<E*>(lds_raw);                                   // [MAP_LDS_ROWS][MAP_LDS_CHUNKS * V]
   int* smap = reinterpret_cast<int*>(lds_raw + MAP_LDS_ROWS * MAP_LDS_CHUNKS * 16);   // [CB]
-  int* lim = smap + CB;                                                      // [2]: min, max source column
+  int* lim = smap + CB;                                                      // [CB / 64][2]: least and greatest source column of 64 destination columns
   const E* __restrict__ src = static_cast<const E*>(t.src);
   E* __restrict__ dst = static_cast<E*>(t.dst);
   const int tid = threadIdx.x;
@@ -303,15 +311,17 @@ __device__ __forceinline__ void map_cols_lds_block(const MapItemDev& t, int blk,
   const long long c0 = static_cast<long long>(bx) * CB;
   const long long r_begin = static_cast<long long>(by) * t.rpb;
   const long long r_end = r_begin + t.rpb < t.other ? r_begin + t.rpb : t.other;
-  if (tid == 0) { lim[0] = 0x7fffffff; lim[1] = -1; }
-  __syncthreads();
-  for (int c = tid; c < CB; c += 256) {
-    const long long sc = (c0 + c < t.dst_slots) ? map_slot(t.m, c0 + c) : -1;
-    smap[c] = static_cast<int>(sc);
-    if (sc >= 0) { atomicMin(&lim[0], static_cast<int>(sc)); atomicMax(&lim[1], static_cast<int>(sc)); }
+  static_assert(CB % 64 == 0 && CB <= 256, "a destination column per thread of the first wavefronts");
+  if (tid < CB) {
+    const int sc = c0 + tid < t.dst_slots ? static_cast<int>(map_slot(t.m, c0 + tid)) : -1;
+    smap[tid] = sc;
+    const int lo = wave_min(sc >= 0 ? sc : 0x7fffffff), hi = ~wave_min(~sc);      // (no source: -1, the smallest)
+    if ((tid & 63) == 0) { lim[2 * (tid >> 6)] = lo; lim[2 * (tid >> 6) + 1] = hi; }
   }
   __syncthreads();
-  const int smin = lim[0], smax = lim[1];
+  int smin = lim[0], smax = lim[1];
+#pragma unroll
+  for (int w = 1; w < CB / 64; ++w) { smin = min(smin, lim[2 * w]); smax = max(smax, lim[2 * w + 1]); }
   const int w0 = smin & ~(V - 1);                            // window start, 16-byte aligned
   const int chunks = smax >= 0 ? (smax - w0) / V + 1 : 0;    // 16-byte chunks per row
   const int grp = tid % MAP_LDS_GROUPS, rr = tid / MAP_LDS_GROUPS;   // this thread's column group and row slot
@@ -390,7 +400,7 @@ __device__ __forceinline__ void map_cols_lds_block(const MapItemDev& t, int blk,
 }
 
 __global__ __launch_bounds__(256) void map_batch_kernel(const MapBatch b) {
-  constexpr int LDS_COLS = MAP_LDS_ROWS * MAP_LDS_CHUNKS * 16 + (MAP_LDS_GROUPS * 8 + 2) * 4, LDS_TR = 64 * 65 * 4 + 64 * 8;
+  constexpr int LDS_COLS = MAP_LDS_ROWS * MAP_LDS_CHUNKS * 16 + (MAP_LDS_GROUPS * 8 + 4) * 4, LDS_TR = 64 * 65 * 4 + 64 * 8;
   __shared__ __attribute__((aligned(16))) unsigned char lds_raw[LDS_COLS > LDS_TR ? LDS_COLS : LDS_TR];
   const int blk = blockIdx.x;
   if (b.rope_blk0 >= 0 && blk >= b.rope_blk0) {
