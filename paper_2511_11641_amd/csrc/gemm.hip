@@ -52,6 +52,26 @@ struct F32Frags {
 
 #define F32_CHAIN 256
 
+// Output (m, n): its sum with the bias already added; h, u: what the activation derivatives read beside it.
+__device__ __forceinline__ void f32_put(const GemmEpi& e, int m, int n, float acc, float h, float u) {
+  float* const c = static_cast<float*>(e.c) + static_cast<long long>(m) * e.ldc;
+  switch (e.kind) {
+    case EPI_STORE: c[n] = acc; break;
+    case EPI_BIAS_ACT:
+      c[n] = acc;
+      static_cast<float*>(e.c2)[static_cast<long long>(m) * e.ldc2 + n] = act_gelu(acc, e.act);
+      break;
+    case EPI_ACT: c[n] = act_gelu(acc, e.act); break;
+    case EPI_DACT: c[n] = acc * act_gelu_grad(h, e.act); break;
+    case EPI_DSWIGLU: {
+      const float sg = act_sigmoid(h);
+      c[2 * n] = acc * u * sg * (1.f + h * (1.f - sg));
+      c[2 * n + 1] = acc * h * sg;
+    } break;
+    default: break;          // the rotary and gated forms are bf16 only
+  }
+}
+
 // One output tile of K split z.  A K-slow A (dY^T X) also gives its column sums (GemmDesc::colsum, the bias gradient; K unsplit): the
 // workgroups of the first tile column add the operand's values up as they pass, sixteen at a time in a tree, the sums of those with what their additions round away.
 template <int WM, int WN, int WK, bool TA, bool TB>
@@ -87,14 +107,35 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& d, int tiles_n, int k_c
     }
   };
   if (nc > 0) { fa.load(a[0], k_begin, hh); fb.load(b[0], k_begin, hh); }
+  // The outputs that this lane writes: one column, NOUT rows.  What their epilogue reads besides the sums is asked for here; behind the
+  // loop every output's saved pre-activation was a trip to memory of its own.
+  constexpr int NOUT = WK == 4 ? 4 : 16;
+  auto row_out = [](int q) __attribute__((always_inline)) { return WK == 4 ? 8 * q : 8 * (q / 4) + q % 4; };
+  const int m_out = m0 + (WK == 4 ? threadIdx.x >> 5 : 4 * hh), n_out = n0 + (WK == 4 ? threadIdx.x & 31 : l32);
+  const bool derivative = d.epi.kind == EPI_DACT || d.epi.kind == EPI_DSWIGLU, biased = d.splits <= 1 && d.epi.bias && !derivative;
+  float bias = 0.f, eh[NOUT], eu[NOUT];
+#pragma unroll
+  for (int q = 0; q < NOUT; ++q) eh[q] = eu[q] = 0.f;
+  if (biased) bias = static_cast<const float*>(d.epi.bias)[min(n_out, d.N - 1)];
+  if (derivative && d.splits <= 1) {
+    const int per = d.epi.kind == EPI_DSWIGLU ? 2 : 1;
+    const float* const col = static_cast<const float*>(d.epi.h) + static_cast<long long>(min(n_out, d.N - 1)) * per;
+#pragma unroll
+    for (int q = 0; q < NOUT; ++q) {
+      const float* const at = col + static_cast<long long>(min(m_out + row_out(q), d.M - 1)) * d.epi.ldh;
+      eh[q] = at[0];
+      eu[q] = at[per - 1];
+    }
+  }
   int c = 0;
   for (; c + 2 <= nc; c += 2) {
     fa.load(a[1], k_begin + (c + 1) * 32, hh);
     fb.load(b[1], k_begin + (c + 1) * 32, hh);
     products(a[0], b[0]);
-    const int kn = k_begin + min(c + 2, nc - 1) * 32;       // the last group again when there is no further one
-    fa.load(a[0], kn, hh);
-    fb.load(b[0], kn, hh);
+    if (c + 2 < nc) {
+      fa.load(a[0], k_begin + (c + 2) * 32, hh);
+      fb.load(b[0], k_begin + (c + 2) * 32, hh);
+    }
     products(a[1], b[1]);
     if ((c + 2) % (F32_CHAIN / 32) == 0) {
 #pragma unroll
@@ -114,10 +155,10 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& d, int tiles_n, int k_c
     cs += fabsf(cs_lost) < INFINITY ? cs_lost : 0.f;      // (not a number behind an infinite sum, which stands as it is)
     cs += __shfl_xor(cs, 32, 64);      // the other half of the k
   }
-  auto put = [&](int m, int n, float v) __attribute__((always_inline)) {
-    if (m < d.M && n < d.N) {
-      if (part) part[static_cast<long long>(m) * d.N + n] = v;
-      else epi_apply<float>(d.epi, m, n, v);
+  auto put = [&](int m, float v, float h, float u) __attribute__((always_inline)) {
+    if (m < d.M && n_out < d.N) {
+      if (part) part[static_cast<long long>(m) * d.N + n_out] = v;
+      else f32_put(d.epi, m, n_out, biased ? v + bias : v, h, u);
     }
   };
   // accumulator layout: column lane % 32, row 8 (r / 4) + 4 (lane / 32) + r % 4
@@ -133,11 +174,11 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& d, int tiles_n, int k_c
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int m = (threadIdx.x >> 5) + 8 * q;
-      put(m0 + m, n0 + n, (red[0][m][n] + red[1][m][n]) + (red[2][m][n] + red[3][m][n]));
+      put(m0 + m, (red[0][m][n] + red[1][m][n]) + (red[2][m][n] + red[3][m][n]), eh[q], eu[q]);
     }
   } else {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) put(m0 + 8 * (r / 4) + 4 * hh + r % 4, n0 + l32, acc[r]);
+    for (int r = 0; r < 16; ++r) put(m_out + row_out(r), acc[r], eh[r % NOUT], eu[r % NOUT]);
     if (TA && TB && sums && hh == 0 && m0 + l32 < d.M) d.colsum[m0 + l32] = cs;
   }
 }
