@@ -127,21 +127,26 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& d, int tiles_n, int k_c
       eu[q] = at[per - 1];
     }
   }
+  // Groups in pairs; the last pair by itself, so that nothing is loaded twice and no load sits behind a branch (the products of a pair would
+  // wait for it as well).
   int c = 0;
-  for (; c + 2 <= nc; c += 2) {
+  auto pair = [&](bool more) __attribute__((always_inline)) {
     fa.load(a[1], k_begin + (c + 1) * 32, hh);
     fb.load(b[1], k_begin + (c + 1) * 32, hh);
     products(a[0], b[0]);
-    if (c + 2 < nc) {
+    if (more) {
       fa.load(a[0], k_begin + (c + 2) * 32, hh);
       fb.load(b[0], k_begin + (c + 2) * 32, hh);
     }
     products(a[1], b[1]);
-    if ((c + 2) % (F32_CHAIN / 32) == 0) {
+    c += 2;
+    if (c % (F32_CHAIN / 32) == 0) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) { sum[r] += acc[r]; acc[r] = 0.f; }
     }
-  }
+  };
+  while (c + 2 < nc) pair(true);
+  if (c + 2 == nc) pair(false);
   if (c < nc) products(a[0], b[0]);
   if (k_begin + nc * 32 < k_end) {
     fa.load_tail(a[0], k_begin + nc * 32, k_end, hh);
