@@ -651,6 +651,13 @@ void attn_bwd_dq_kernel(const AttnArgs a) {
   }
   const float sc = a.scale * LOG2E;
 
+  // dP - delta comes out of the matrix unit: the accumulators of dP start at -delta (a subtraction per score was an eighth of the loop's
+  // vector instructions: 8 x 1024 causal tokens, 16 heads of 32 dims, 34.7 -> 32.6 us; 11 x 381, 32 heads, 23.5 -> 23.1).  Not in the
+  // kernel over query tiles, where delta changes along the accumulator: there it comes from LDS in front of the products, 37.7 -> 39.7 us.
+  floatx16 neg_dlt;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) neg_dlt[r] = -dlt;
+
   floatx16 dq[DQ / 32];
 #pragma unroll
   for (int u = 0; u < DQ / 32; ++u)
@@ -677,9 +684,9 @@ void attn_bwd_dq_kernel(const AttnArgs a) {
     const unsigned hidden = ~rows_below((a.causal ? min(q_idx + 1, a.L) : a.L) - kv0 - hh * 4);      // keys behind the query's last visible one
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      floatx16 sacc, pacc;
+      floatx16 sacc, pacc = neg_dlt;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { sacc[r] = 0.f; pacc[r] = 0.f; }
+      for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
 #pragma unroll
       for (int s = 0; s < DQ / 16; ++s)
         sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_nat<DQ>(Ks(cur), t * 32 + l32, s, hh), qf[s], sacc, 0, 0, 0);
@@ -701,7 +708,7 @@ void attn_bwd_dq_kernel(const AttnArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[r], sc, -lse2));
-        sacc[r] = p * (pacc[r] - dlt);
+        sacc[r] = p * pacc[r];
       }
       if (DQ > 32) read_k();
       trn_wait();
