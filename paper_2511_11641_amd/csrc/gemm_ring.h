@@ -25,10 +25,12 @@
 // LDS layout: 16-byte chunks, XOR-swizzled on the GLOBAL side of the direct load (the lane that owns a physical chunk fetches the
 // logical chunk that maps there):
 //   K-contiguous tile [rows][64]:  chunk ^ (row % 8): the lanes of an access fall on different banks (no conflicts counted)
-//   K-slow tile [64][rows]:        chunk ^ 4 (k % 4), or chunk ^ 4 (k / 2 % 2) for rows of 192 (which start half-way round the banks
-//                                  for odd k, and whose 24 chunks only allow a swizzle inside groups of eight), chunk ^ 4 (k % 2)
-//                                  for rows of 64.  This parts the four k of one group of 16 lanes; groups read 8 k apart from each
-//                                  other and still meet on the same banks (conflicts counted in 49-62 % of the LDS cycles).
+//   K-slow tile [64][rows]:        the transposing reads of half a wavefront (32 lanes, one pass over the 64 banks) take 32 bytes of eight
+//                                  rows, k .. k + 3 and k + 8 .. k + 11.  Rows of 128 and 256 start at the same bank: chunk ^ 4 (k % 4) ^ 2 (k / 8 % 2)
+//                                  puts the eight pieces on eight bank groups; rows of 64 and 192 start half-way round the banks for odd k: chunk ^ 2 (k / 2 % 2)
+//                                  ^ 4 (k / 8 % 2), inside groups of eight chunks.  No conflicts counted either (with the rows k + 8 on the banks
+//                                  of the rows k, 49-62 % of these launches' LDS cycles were conflicts: 768x384x12017 16.5 -> 14.3 us on 64x128,
+//                                  2048x1024x8192 in two parts 41.7 -> 39.8 us on 128x128; launches on larger tiles, which power bounds, 0 - 2 %).
 #pragma once
 #include "gemm_epi.h"
 
@@ -56,7 +58,9 @@ __host__ __device__ constexpr int ring_waitcnt(int vm, bool lgkm0) {
 }
 
 template <int RT>
-__device__ __forceinline__ int ring_ks_swz(int k) { return RT % 128 == 0 ? ((k & 3) << 2) : RT == 64 ? ((k & 1) << 2) : (((k >> 1) & 1) << 2); }
+__device__ __forceinline__ int ring_ks_swz(int k) {
+  return RT % 128 == 0 ? ((k & 3) << 2) | (((k >> 3) & 1) << 1) : (((k >> 3) & 1) << 2) | (((k >> 1) & 1) << 1);
+}
 
 // Direct loads of one operand tile of RT rows: PER instructions per slab and wavefront, each moving 64 x 16 bytes to consecutive LDS.
 // Addresses are a wavefront-uniform base (scalar registers, advanced by scalar adds) plus a lane offset that never changes: 32 bits, or
