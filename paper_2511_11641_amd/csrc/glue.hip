@@ -19,11 +19,16 @@ __device__ __forceinline__ void glue_unpack8(const uint4& u, float (&f)[8]) {
     f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
   }
 }
+// round to nearest even by the conversion instruction, two values each (in integer arithmetic six instructions a value: 1024 x 1024 with the
+// residual, LayerNorm, a wavefront per SIMD and nothing to hide them behind: 5.4 -> 4.4 us; 8192 x 2048: forward 24.9 -> 22.2, backward
+// 32.7 -> 29.5; cross-entropy 8192 x 32000 230 -> 205)
 __device__ __forceinline__ uint4 glue_pack8(const float (&f)[8]) {
-  uint32_t w[4];
+  typedef float floatx8 __attribute__((ext_vector_type(8)));
+  typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+  floatx8 v;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) w[i] = static_cast<uint32_t>(f32_to_bf16(f[2 * i])) | (static_cast<uint32_t>(f32_to_bf16(f[2 * i + 1])) << 16);
-  return make_uint4(w[0], w[1], w[2], w[3]);
+  for (int i = 0; i < 8; ++i) v[i] = f[i];
+  return __builtin_bit_cast(uint4, __builtin_convertvector(v, bf16x8));
 }
 
 // ---------------------------------------------------------------------------------------------
