@@ -62,7 +62,8 @@ int ecospa_gemm(ecospa_ctx* ctx, const GemmDesc& d);
 // over the same tokens.  One launch where that is built for the two and pays, otherwise w, then x (x_first: the other way round).
 int ecospa_gemm_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int x_first = 0);
 // What the two above choose (host arithmetic only; they launch by it).  A bf16 contraction: the tile shape of the ring kernel, GEMM_ROUTE_FLOW
-// for the kernel of resident workgroups, or GEMM_ROUTE_SHARE and a shape of the kernel that shares K out inside a workgroup.  A pair: one launch or two, and for one of bf16 the tile shapes.
+// for the kernel of resident workgroups, or GEMM_ROUTE_SHARE and a shape of the kernel that shares K out inside a workgroup.  A pair: one launch
+// or two, and for one of bf16 the tile shapes.
 int ecospa_gemm_route(const GemmDesc& d);
 enum { GEMM_PAIR_NONE = 0, GEMM_PAIR_BF16 = 1, GEMM_PAIR_F32 = 2 };
 int ecospa_gemm_pair_route(const GemmDesc& w, const GemmDesc& x, int* w_shape, int* x_shape);

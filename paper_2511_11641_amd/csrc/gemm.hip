@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_vec8_kernel(const Gemm
 // more once per launch).  The K-slow forms read 8 bytes per LDS instruction instead of 16, which the narrow tiles feel most.  A split adds
 // its partial sums: 3 us and their bytes at 4 TB/s; a split keeps at least 4 slabs.  The kernel of resident workgroups hides most of
 // the rest and the epilogue of every tile but a workgroup's last.  The times are of operands that the L2s hold: with operands from
-// memory a slab of the K-slow 64x128 shape takes 0.47-0.54 us.
+// memory a slab of the K-slow 64x128 shape takes 0.38-0.46 us.
 //
 // How good the choice is: 680 contractions x W^T of random kinds and sizes (512 .. 32768 x 64 .. 52000 x 256 .. 8300; activations just written, the rest
 // from memory), every shape and the resident workgroups timed.  The sum over the choices is 1.0 - 1.4 % above the sum of the fastest, the worst
