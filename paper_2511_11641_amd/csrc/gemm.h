@@ -111,6 +111,21 @@ static inline bool gemm_flow_takes(const GemmDesc& d) {
   return d.splits <= 1 && !d.colsum && (d.trans_a != 0) == (d.trans_b != 0) && !(d.trans_a && d.epi.bias) && tiles > 256 && tiles < (1 << 24) &&
          d.K % 64 == 0 && d.K / 64 >= GEMM_FLOW_MIN_SLABS && !(act && d.epi.act != ECOSPA_ACT_GELU_ERF) && !ring_wide(d);
 }
+// The grid of a launch, worked out on the host: a workgroup finds its tile with multiplications.  What bounds a launch of few slabs is the
+// time to its first load and what its XCD fetches from memory: six divisions one behind the other were 0.3 us of the 1.3 us to a workgroup's
+// last first-round load, and bands of a fixed 16 tile rows had an XCD of 1024x1024x2048 on 64x64 tiles fetch 1152 operand rows where 768 do.
+// The four contractions of a layer on 1024 tokens, 1024 wide, weights from memory: 41.5 -> 39.9 us with both and the bias asked for early.
+// Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own.  Every XCD gets a contiguous range of (K split, tile), so the
+// tiles of one split, which read one K range of both operands, are on as few XCDs as there are.  Inside a split the tiles are ordered in
+// bands of tile rows walked column by column, so that the tiles an XCD works on at a time form a block of C and share operand rows in
+// its L2.
+struct RingGrid {
+  int tiles_n, k_chunk;
+  int per, more;                  // workgroups per XCD; the first `more` XCDs have one more
+  int tiles, group, band, last_band, last_rows;      // tiles of a split; rows and tiles of a band; where the last band starts, its rows
+  unsigned tiles_inv, band_inv, group_inv, last_inv;
+};
+RingGrid gemm_ring_grid(int M, int N, int bm, int bn, int splits, int k_chunk);
 hipError_t gemm_share_launch_nt(ecospa_ctx* ctx, const GemmDesc& d, int shape);
 hipError_t gemm_flow_launch_nt(ecospa_ctx* ctx, const GemmDesc& d);
 hipError_t gemm_flow_launch_tt(ecospa_ctx* ctx, const GemmDesc& d);

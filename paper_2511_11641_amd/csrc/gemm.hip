@@ -382,6 +382,48 @@ bool ecospa_gemm_shares_k(const GemmDesc& d) {
   return share_plan(d, &share) < t + ring_cold(shape, ((d.K + 63) / 64 + sp - 1) / sp);
 }
 
+// Rows of a band of tiles (gemm.h).  A launch of one round (256 tiles or fewer): an XCD's tiles of it are all under way together, and the height
+// taken has the fewest operand rows per tile, the lower last band weighed in; heights up to 16, equal bands, the lowest of equals.  Without the
+// last band 548x3200x3504 on 128x64 tiles, five tile rows, ran in bands of three and two: 32.9 us, 29.7 in one band; some 600 random launches of one
+// round take 0.6 % less than in bands of 4, 8 or 16 (by tile height).  Those stay for several rounds, where the count says nothing of what the
+// L2s keep from one to the next: 3632x5648x584 on 192x256 tiles 41.9 us in bands of 4, 46.1 of 7; 16345x1560x1496 on 256x256 88.2 of 4, 105 of 8.
+static int ring_band_rows(int tiles_m, int bm, int bn, int blocks) {
+  if (blocks > 256) {
+    const int rows = bm >= 192 ? 4 : (bm >= 128 ? 8 : 16);
+    return rows < tiles_m ? rows : tiles_m;
+  }
+  const int at_once = blocks < 8 ? 1 : blocks >> 3;
+  const auto fetched = [&](int rows) { return rows * (rows * bm + (at_once + rows - 1) / rows * bn); };      // by the tile rows of a band
+  int best = 1, fewest = 0;
+  for (int rows = 1; rows <= 16 && rows <= tiles_m; ++rows) {
+    const int bands = (tiles_m + rows - 1) / rows;
+    if ((tiles_m + bands - 1) / bands != rows) continue;
+    const int sum = (bands - 1) * fetched(rows) + fetched(tiles_m - (bands - 1) * rows);
+    if (fewest == 0 || sum < fewest) { fewest = sum; best = rows; }
+  }
+  return best;
+}
+static unsigned ring_inverse(unsigned d) { return d <= 1 ? ~0u : static_cast<unsigned>((1ull << 32) / d); }
+RingGrid gemm_ring_grid(int M, int N, int bm, int bn, int splits, int k_chunk) {
+  RingGrid g;
+  const int tiles_m = (M + bm - 1) / bm;
+  g.tiles_n = (N + bn - 1) / bn;
+  g.k_chunk = k_chunk;
+  g.tiles = tiles_m * g.tiles_n;
+  const int nb = g.tiles * splits;
+  g.per = nb >> 3;
+  g.more = nb & 7;
+  g.group = ring_band_rows(tiles_m, bm, bn, nb);
+  g.band = g.group * g.tiles_n;
+  g.last_band = (tiles_m - 1) / g.group;
+  g.last_rows = tiles_m - g.last_band * g.group;
+  g.tiles_inv = ring_inverse(g.tiles);
+  g.band_inv = ring_inverse(g.band);
+  g.group_inv = ring_inverse(g.group);
+  g.last_inv = ring_inverse(g.last_rows);
+  return g;
+}
+
 // Workgroup tile that a tile code names, or 0: those of the contraction entry point, and 39 .. 41 for the 64-wide shapes.
 static void ring_forced_tile(int tile, int* bm, int* bn) {
   static const int cfg[11][2] = {{256, 256}, {256, 256}, {256, 128}, {128, 256}, {128, 128}, {256, 256}, {128, 128}, {256, 256}, {256, 256}, {256, 128}, {256, 192}};

@@ -164,49 +164,7 @@ __device__ __forceinline__ void ring_mfma(ring_f4& c, const bf16x8_t& a, const b
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 
-// The grid of a launch, worked out on the host: a workgroup finds its tile with multiplications.  What bounds a launch of few slabs is the
-// time to its first load and what its XCD fetches from memory: six divisions one behind the other were 0.3 us of the 1.3 us to a workgroup's
-// last first-round load, and bands of a fixed 16 tile rows had an XCD of 1024x1024x2048 on 64x64 tiles fetch 1152 operand rows where 768 do.
-// The four contractions of a layer on 1024 tokens, 1024 wide, weights from memory: 41.5 -> 39.9 us with both and the bias asked for early.
-// Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own.  Every XCD gets a contiguous range of (K split, tile), so the
-// tiles of one split, which read one K range of both operands, are on as few XCDs as there are.  Inside a split the tiles are ordered in
-// bands of tile rows walked column by column, so that the tiles an XCD works on at a time form a block of C and share operand rows in
-// its L2; the height of a band is the one whose blocks have the fewest operand rows.
-struct RingGrid {
-  int tiles_n, k_chunk;
-  int per, more;                  // workgroups per XCD; the first `more` XCDs have one more
-  int tiles, group, band, last_band, last_rows;      // tiles of a split; rows and tiles of a band; where the last band starts, its rows
-  unsigned tiles_inv, band_inv, group_inv, last_inv;
-};
-static inline unsigned ring_inverse(unsigned d) { return d <= 1 ? ~0u : static_cast<unsigned>((1ull << 32) / d); }
-static inline RingGrid ring_grid(int M, int N, int bm, int bn, int splits, int k_chunk) {
-  RingGrid g;
-  const int tiles_m = (M + bm - 1) / bm;
-  g.tiles_n = (N + bn - 1) / bn;
-  g.k_chunk = k_chunk;
-  g.tiles = tiles_m * g.tiles_n;
-  const int nb = g.tiles * splits;
-  g.per = nb >> 3;
-  g.more = nb & 7;
-  const int at_once = g.per < 1 ? 1 : (g.per < 32 ? g.per : 32);      // tiles that an XCD's 32 compute units work on at a time
-  long long fewest = 0;
-  g.group = 1;
-  for (int r = 1; r <= 16 && r <= tiles_m; ++r) {
-    const long long rows = static_cast<long long>(r) * bm + static_cast<long long>((at_once + r - 1) / r) * bn;
-    if (r == 1 || rows < fewest) { fewest = rows; g.group = r; }
-  }
-  const int bands = (tiles_m + g.group - 1) / g.group;
-  g.group = (tiles_m + bands - 1) / bands;           // bands of equal height
-  g.band = g.group * g.tiles_n;
-  g.last_band = (tiles_m - 1) / g.group;
-  g.last_rows = tiles_m - g.last_band * g.group;
-  g.tiles_inv = ring_inverse(g.tiles);
-  g.band_inv = ring_inverse(g.band);
-  g.group_inv = ring_inverse(g.group);
-  g.last_inv = ring_inverse(g.last_rows);
-  return g;
-}
-// a / d with d's ring_inverse(): the product's high half falls short by one at most
+// a / d with the inverse of d that RingGrid has beside it: the product's high half falls short by one at most
 __device__ __forceinline__ int ring_div(int a, int d, unsigned inv, int& rest) {
   int q = static_cast<int>(__umulhi(static_cast<unsigned>(a), inv));
   rest = a - q * d;
@@ -611,7 +569,7 @@ void gemm_bf16_ring_kernel(const RingGrid w, const GemmDesc d) {
 template <int BM, int BN, int NS, bool TA, bool TB, bool CS, int EPIS, bool WIDE = false>
 static hipError_t ring_launch_shape(ecospa_ctx* ctx, const GemmDesc& d, int k_chunk) {
   const int splits = d.splits > 1 ? d.splits : 1;
-  const RingGrid w = ring_grid(d.M, d.N, BM, BN, splits, k_chunk);
+  const RingGrid w = gemm_ring_grid(d.M, d.N, BM, BN, splits, k_chunk);
   constexpr int lds_bytes = NS * (BM + BN) * RING_BK * static_cast<int>(sizeof(bf16_t));
   static_assert(lds_bytes <= 160 * 1024, "LDS of a compute unit");
   auto kern = gemm_bf16_ring_kernel<BM, BN, NS, TA, TB, CS, EPIS, WIDE>;
@@ -637,7 +595,7 @@ void gemm_bf16_pair_kernel(const RingGrid wg, const RingGrid xg, int n_tt, const
 template <int TM, int TN, int TS, bool CS, int XM, int XN, int XS>
 static hipError_t ring_launch_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int w_k_chunk) {
   const int splits = w.splits > 1 ? w.splits : 1;
-  const RingGrid wg = ring_grid(w.M, w.N, TM, TN, splits, w_k_chunk), xg = ring_grid(x.M, x.N, XM, XN, 1, (x.K + 63) / 64 * 64);
+  const RingGrid wg = gemm_ring_grid(w.M, w.N, TM, TN, splits, w_k_chunk), xg = gemm_ring_grid(x.M, x.N, XM, XN, 1, (x.K + 63) / 64 * 64);
   const int n_tt = wg.tiles * splits;
   constexpr int lds_w = TS * (TM + TN) * RING_BK * 2, lds_x = XS * (XM + XN) * RING_BK * 2, lds_bytes = lds_w > lds_x ? lds_w : lds_x;
   static_assert(lds_bytes > 64 * 1024 && lds_bytes <= 160 * 1024, "LDS of a compute unit");

@@ -221,7 +221,7 @@ void gemm_bf16_share_kernel(const RingGrid w, const GemmDesc d) {
 
 template <int BM, int BN, int W, int D>
 static hipError_t share_launch_shape(ecospa_ctx* ctx, const GemmDesc& d) {
-  const RingGrid w = ring_grid(d.M, d.N, BM, BN, 1, 0);
+  const RingGrid w = gemm_ring_grid(d.M, d.N, BM, BN, 1, 0);
   constexpr int lds_bytes = W * ShareTile<BM, BN, W, D>::AREA;
   auto kern = gemm_bf16_share_kernel<BM, BN, W, D>;
   static LdsAttrOnce attr_once;
