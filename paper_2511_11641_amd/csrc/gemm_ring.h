@@ -458,12 +458,14 @@ __device__ __forceinline__ void ring_tile(const GemmDesc& d, const RingGrid& w, 
   // every wavefront fetches once (GELU with two outputs on 8192x2048x1024, 256x256 tiles: 72 us).  Instead the accumulators
   // are parked in LDS, each lane's own values in its own slots (no exchange, no barrier), and a loop over the row blocks takes
   // them back.  Up to four groups go straight from the registers: their code is short, and the barrier and the trip through LDS stood behind a
-  // short loop (24-layer forward on 1024 tokens, one GELU contraction on 128x64 tiles per layer: 1468 -> 1457 us).
+  // short loop (24-layer forward on 1024 tokens, one GELU contraction on 128x64 tiles per layer: 1468 -> 1457 us).  Not the tanh form of GELU,
+  // whose code is long (tanhf has two branches): its derivative on 128x64 tiles, 1400x520x720: 14.2 us from the registers, 13.5 through LDS.
   constexpr int SLOT_ROWS = NS * (BM + BN) * RING_BK * 2 / 4 / (JP * 2048);      // row blocks that a wavefront's share of LDS holds
   constexpr int CH = SLOT_ROWS >= FM ? FM : FM / 2;
   static_assert(CH >= 1 && CH <= SLOT_ROWS && FM % CH == 0, "LDS holds a whole chunk");
   constexpr bool PARK = FM * JP > 4;
-  if constexpr (PARK) __syncthreads();                  // everyone's loads have landed
+  const bool park = PARK || (d.epi.act == ECOSPA_ACT_GELU_TANH && (d.epi.kind == EPI_BIAS_ACT || d.epi.kind == EPI_ACT || d.epi.kind == EPI_DACT));
+  if (park) __syncthreads();                  // everyone's loads have landed
   char* const slots = reinterpret_cast<char*>(lds) + wave * (CH * JP * 2048) + lane * 16;
   epi_dispatch(d.epi.kind, [&](auto kind_) __attribute__((always_inline)) {
     constexpr int KIND = decltype(kind_)::value;
@@ -499,22 +501,14 @@ __device__ __forceinline__ void ring_tile(const GemmDesc& d, const RingGrid& w, 
         }
       };
       if constexpr (epi_has_side(KIND)) request(0);
-      auto row_block = [&](int i, auto&& value) __attribute__((always_inline)) {      // value(jp, v): the sums of its group jp
-        const int row = row_l + i * 16;
-        EpiSide sd[JP];
+      auto side = [&](int i, EpiSide (&sd)[JP]) __attribute__((always_inline)) {
         if constexpr (epi_has_side(KIND)) {
 #pragma unroll
           for (int jp = 0; jp < JP; ++jp) sd[jp] = nxt[jp];
           request(i + 1);            // behind the last block: its row is clamped, the values are not used
         }
-        EpiOut out[JP];
-        ring_for<0, JP>([&](auto jp_) __attribute__((always_inline)) {
-          constexpr int jp = decltype(jp_)::value;
-          float v[8];
-          value(jp_, v);
-          add_bias(jp, v);
-          epi_math_k<KIND>(d.epi.act, v, sd[jp], KIND == EPI_ROPE && rope_on[jp], out[jp]);
-        });
+      };
+      auto store = [&](int row, const EpiOut (&out)[JP]) __attribute__((always_inline)) {
         const off_t off = static_cast<off_t>(row) * ldc2b + nl * CM;
         if (row < rows_in) {
 #pragma unroll
@@ -530,11 +524,27 @@ __device__ __forceinline__ void ring_tile(const GemmDesc& d, const RingGrid& w, 
           }
         }
       };
+      constexpr bool GELU = KIND == EPI_BIAS_ACT || KIND == EPI_ACT || KIND == EPI_DACT;
       if constexpr (!PARK) {
-        ring_for<0, FM>([&](auto i_) __attribute__((always_inline)) {
-          row_block(decltype(i_)::value, [&](auto jp_, float (&v)[8]) __attribute__((always_inline)) { vals(i_, jp_, v); });
-        });
-      } else {
+        if (!GELU || !park) {
+          ring_for<0, FM>([&](auto i_) __attribute__((always_inline)) {
+            constexpr int i = decltype(i_)::value;
+            EpiSide sd[JP];
+            side(i, sd);
+            EpiOut out[JP];
+            ring_for<0, JP>([&](auto jp_) __attribute__((always_inline)) {
+              constexpr int jp = decltype(jp_)::value;
+              float v[8];
+              vals(i_, jp_, v);
+              add_bias(jp, v);
+              epi_math_k<KIND>(ECOSPA_ACT_GELU_ERF, v, sd[jp], KIND == EPI_ROPE && rope_on[jp], out[jp]);
+            });
+            store(row_l + i * 16, out);
+          });
+          return;
+        }
+      }
+      if constexpr (PARK || GELU) {
         ring_for<0, FM / CH>([&](auto ch_) __attribute__((always_inline)) {
           ring_for<0, CH>([&](auto i_) __attribute__((always_inline)) {
             ring_for<0, JP>([&](auto jp_) __attribute__((always_inline)) {
@@ -546,12 +556,21 @@ __device__ __forceinline__ void ring_tile(const GemmDesc& d, const RingGrid& w, 
             });
           });
 #pragma unroll 1
-          for (int il = 0; il < CH; ++il)
-            row_block(decltype(ch_)::value * CH + il, [&](auto jp_, float (&v)[8]) __attribute__((always_inline)) {
-              const float4* s4 = reinterpret_cast<const float4*>(slots + (il * JP + decltype(jp_)::value) * 2048);
+          for (int il = 0; il < CH; ++il) {
+            const int i = decltype(ch_)::value * CH + il;
+            EpiSide sd[JP];
+            side(i, sd);
+            EpiOut out[JP];
+#pragma unroll
+            for (int jp = 0; jp < JP; ++jp) {
+              const float4* s4 = reinterpret_cast<const float4*>(slots + (il * JP + jp) * 2048);
               const float4 lo = s4[0], hi = s4[64];
-              v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w; v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
-            });
+              float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+              add_bias(jp, v);
+              epi_math_k<KIND>(PARK ? d.epi.act : ECOSPA_ACT_GELU_TANH, v, sd[jp], KIND == EPI_ROPE && rope_on[jp], out[jp]);
+            }
+            store(row_l + i * 16, out);
+          }
         });
       }
     }

@@ -29,6 +29,12 @@ def test_shared_k_gives_what_shared_slabs_give(ctx, kind, act, bias, tile, M, N,
     gen = torch.Generator(device="cuda").manual_seed(81)
     g, c, c2, keep = _desc(kind, False, M, N, K, gen, bias, keep_c=bias or kind != SWIGLU)
     g.epi.act = (B.ACT_GELU_ERF, B.ACT_GELU_TANH)[act]
+    _compare(ctx, g, c, c2, tile, M)
+    del keep
+
+
+def _compare(ctx, g, c, c2, tile, M):
+    """The launch of g on `tile` and on 128 x 128 tiles of the other kernel."""
     out = []
     for g.tile in (tile, RING_128):
         c.fill_(7.0)
@@ -41,4 +47,22 @@ def test_shared_k_gives_what_shared_slabs_give(ctx, kind, act, bias, tile, M, N,
         # neighbour at most (2^-7 of a value), of few values: a sum lies within 1e-5 of a rounding boundary 2^-8 apart
         assert bool(((x.float() - y.float()).abs() <= y.float().abs() * 2.0 ** -7 + 4e-5).all())
         assert float((x != y).float().mean()) < 0.03
+
+
+# The 64-wide tiles of the other kernel take their activations straight from the registers, the tanh form of GELU through LDS
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (33, 40, 56), (130, 24, 200), (65, 248, 520)])
+@pytest.mark.parametrize("tile", [39, 40, 41])
+@pytest.mark.parametrize("kind,act,bias", [(BIAS_ACT, 0, True), (BIAS_ACT, 1, False), (ACT, 0, True), (ACT, 1, True), (DACT, 0, True), (DACT, 1, True),
+                                           (DSWIGLU, 0, True), (ROPE, 0, True), (SWIGLU, 0, True), (SWIGLU, 0, False)])
+def test_64_wide_tiles_give_what_128_square_ones_give(ctx, kind, act, bias, tile, M, N, K):
+    if kind == ROPE and N < 144:
+        N = 144
+    gen = torch.Generator(device="cuda").manual_seed(82)
+    g, c, c2, keep = _desc(kind, False, M, N, K, gen, bias, keep_c=bias or kind != SWIGLU)
+    g.epi.act = (B.ACT_GELU_ERF, B.ACT_GELU_TANH)[act]
+    _compare(ctx, g, c, c2, tile, M)
+    if kind in (DACT, DSWIGLU) and tile == 39:      # dY W, whose second operand is K-slow: the only 64-wide shape of that form
+        b = keep[1].t().contiguous()
+        g.B, g.ldb, g.trans_b = b.data_ptr(), N, 1
+        _compare(ctx, g, c, c2, tile, M)
     del keep
