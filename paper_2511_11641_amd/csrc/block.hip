@@ -137,32 +137,32 @@ static int ffn_forward(ecospa_ctx* ctx, const ecospa_block_desc& d, const BlockW
   int rc;
   GemmDesc g = gemm_desc(d.dtype, T, nh, d.d_model, x, d.d_model, 0, d.w_1, d.ld_w1, 0);
   g.epi.c = hpre; g.epi.ldc = nh; g.epi.bias = d.b_1;
-  block_token_split(g, w);
-  if (is_gated(d) && d.dtype == ECOSPA_BF16) {
+  const bool gated_f32 = is_gated(d) && d.dtype != ECOSPA_BF16;
+  if (gated_f32) {
+    g.epi.kind = EPI_STORE;
+  } else if (is_gated(d)) {
     // gate and up rows alternate in w_1, so every output tile holds whole (gate, up) pairs: the product is formed in
     // the epilogue; forward only (no saved activations) the pre-activations are not written at all
     g.epi.kind = EPI_SWIGLU;
     g.epi.c = saved ? hpre : nullptr;
     g.epi.c2 = act; g.epi.ldc2 = kp;
     if (!aligned16(hpre) || (reinterpret_cast<uintptr_t>(act) & 7u)) return ECOSPA_ERR_ALIGN;
-    if ((rc = ecospa_gemm(ctx, g))) return rc;
-  } else if (is_gated(d)) {
-    g.epi.kind = EPI_STORE;
-    if ((rc = ecospa_gemm(ctx, g))) return rc;
+  } else if (!saved) {
+    // forward only: nothing will ask for the activation's input, so it is not written
+    g.epi.kind = EPI_ACT; g.epi.act = d.act;
+    g.epi.c = act; g.epi.ldc = kp;
+  } else {
+    g.epi.kind = EPI_BIAS_ACT; g.epi.act = d.act;
+    g.epi.c2 = act; g.epi.ldc2 = kp;
+  }
+  block_token_split(g, w);
+  if ((rc = ecospa_gemm(ctx, g))) return rc;
+  if (gated_f32) {
     const long long tot = static_cast<long long>(T) * kp;
     hipLaunchKernelGGL((swiglu_kernel<float>), dim3(static_cast<unsigned>((tot + 255) / 256)), dim3(256), 0, ctx->stream,
                        static_cast<const float*>(hpre), static_cast<long long>(nh), static_cast<float*>(act),
                        static_cast<long long>(kp), static_cast<long long>(T), kp);
     ECOSPA_CHECK_LAUNCH(ctx, "swiglu_kernel");
-  } else if (!saved) {
-    // forward only: nothing will ask for the activation's input, so it is not written
-    g.epi.kind = EPI_ACT; g.epi.act = d.act;
-    g.epi.c = act; g.epi.ldc = kp;
-    if ((rc = ecospa_gemm(ctx, g))) return rc;
-  } else {
-    g.epi.kind = EPI_BIAS_ACT; g.epi.act = d.act;
-    g.epi.c2 = act; g.epi.ldc2 = kp;
-    if ((rc = ecospa_gemm(ctx, g))) return rc;
   }
   GemmDesc g2 = gemm_desc(d.dtype, T, d.d_model, kp, act, kp, 0, d.w_2, d.ld_w2, 0);
   g2.epi.kind = EPI_STORE; g2.epi.c = y; g2.epi.ldc = d.d_model; g2.epi.bias = d.b_2;

@@ -347,13 +347,13 @@ static const ShareShape SHARE_SHAPES[GEMM_SHARE_NSHAPES] = {{32, 16, 2.3f, 0.11f
 static bool gemm_share_takes(const GemmDesc& d) {
   return d.dtype == ECOSPA_BF16 && !d.trans_a && !d.trans_b && d.splits <= 1 && !d.colsum && !ring_wide(d);
 }
-static double share_plan(const GemmDesc& d, int* shape_out) {
+static double share_plan(const GemmDesc& d, int kind, int* shape_out) {
   const int units = (d.K + 63) / 64;
   double best = 0.0;
   for (int q = 0; q < GEMM_SHARE_NSHAPES; ++q) {
     const ShareShape& r = SHARE_SHAPES[q];
     const long long tiles = static_cast<long long>((d.M + r.bm - 1) / r.bm) * ((d.N + r.bn - 1) / r.bn);
-    const double t = static_cast<double>((tiles + 255) / 256) * (r.round + units * r.unit + epi_us(d.epi.kind) * r.bm * r.bn / 1000.0);
+    const double t = static_cast<double>((tiles + 255) / 256) * (r.round + units * r.unit + epi_us(kind) * r.bm * r.bn / 1000.0);
     if (q == 0 || t < best) { best = t; *shape_out = q; }
   }
   return best;
@@ -375,11 +375,14 @@ int ecospa_gemm_token_splits(int M, int N, int K) {
   return sp;
 }
 
+// A question of the sizes alone, like that for the split: both sides have the epilogue behind their sums, spread over the chip.  (The table prices
+// none behind a split.  With its price on this side only, about one contraction in sixty with another epilogue than the plain store was split, K 2500 to
+// 4800: 80 of those of every kind take 1.04 - 1.59 times as long in parts, 1.32 in the geometric mean; 61x2480x2736 with GELU' 13.1 us, shared 10.8.)
 bool ecospa_gemm_shares_k(const GemmDesc& d) {
   if (!gemm_share_takes(d)) return false;
   int shape, sp, share;
-  const double t = ring_plan(0, 0, d.M, d.N, d.K, d.epi.kind, 0, 8, &shape, &sp);
-  return share_plan(d, &share) < t + ring_cold(shape, ((d.K + 63) / 64 + sp - 1) / sp);
+  const double t = ring_plan(0, 0, d.M, d.N, d.K, EPI_STORE, 0, 8, &shape, &sp);
+  return share_plan(d, EPI_STORE, &share) < t + ring_cold(shape, ((d.K + 63) / 64 + sp - 1) / sp);
 }
 
 // Rows of a band of tiles (gemm.h).  A launch of one round (256 tiles or fewer): an XCD's tiles of it are all under way together, and the height
@@ -512,7 +515,7 @@ int ecospa_gemm_route(const GemmDesc& d) {
   int share;
   if (d.tile >= 50 && d.tile < 50 + GEMM_SHARE_NSHAPES && gemm_share_takes(d)) return GEMM_ROUTE_SHARE + d.tile - 50;
   const int route = tiled_route(d, &t);
-  if (d.tile == 0 && route != GEMM_ROUTE_FLOW && gemm_share_takes(d) && share_plan(d, &share) < t + ring_cold(route, (d.K + 63) / 64)) return GEMM_ROUTE_SHARE + share;
+  if (d.tile == 0 && route != GEMM_ROUTE_FLOW && gemm_share_takes(d) && share_plan(d, d.epi.kind, &share) < t + ring_cold(route, (d.K + 63) / 64)) return GEMM_ROUTE_SHARE + share;
   return route;
 }
 

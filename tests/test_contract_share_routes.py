@@ -32,3 +32,16 @@ def test_no_pair_where_k_would_be_split(lib):      # noqa: F811
     x.tile = 0
     assert _route(lib, x) >= SHARE and lib._Z24ecospa_gemm_token_splitsiii(T, d, n) > 1
     assert lib._Z22ecospa_gemm_pair_routeRK8GemmDescS1_PiS2_(C.byref(w), C.byref(x), C.byref(C.c_int()), C.byref(C.c_int())) == 0
+
+
+@pytest.mark.parametrize("M,N,K", [(17, 240, 2960), (61, 64, 2952), (61, 2480, 2736), (200, 1040, 3888), (33, 128, 2960), (61, 3072, 2048), (61, 512, 11008)])
+def test_shared_or_in_parts_is_a_question_of_the_sizes(lib, M, N, K):      # noqa: F811
+    """A block asks before it launches, where the epilogue may not be filled in yet: every kind has the answer of the plain store, and what is
+    not split because it shares K does share it."""
+    shares = getattr(lib, SHARES_K)
+    want = shares(C.byref(_big(STORE, M=M, N=N, K=K))) & 1
+    assert lib._Z24ecospa_gemm_token_splitsiii(M, N, K) > 1 and want == (K < 4096)
+    for kind in range(7):
+        g = _big(kind, M=M, N=N, K=K)
+        assert shares(C.byref(g)) & 1 == want, kind
+        assert not want or _route(lib, g) >= SHARE, kind
