@@ -11,6 +11,8 @@ from paper_2511_11641_amd import binding as B
 from paper_2511_11641_amd import synth
 from test_gpu_attn import run_attn_case
 from test_gpu_ffn import run_ffn_case
+from test_gpu_contract_flow import ACT, BIAS_ACT, DACT, DSWIGLU, ROPE, STORE, SWIGLU, _desc
+from test_gpu_contract_share import _compare
 from util import GemmDesc, assert_close, dev
 
 pytestmark = pytest.mark.gpu
@@ -81,9 +83,18 @@ def test_few_rows(ctx, M, N, K, split):
     assert_close(ctx.ecospa_contract(ga, False, gb, False), want, "bf16", "library's choice")
 
 
-# a layer of 61 tokens: the contractions over the tokens' rows are split along K, so every epilogue runs behind the sum of the parts
+def _shares(lib, M, N, K):
+    f = lib._Z20ecospa_gemm_shares_kRK8GemmDesc
+    g = GemmDesc(B.BF16, M, N, K, 1 << 32, K, 0, 2 << 32, K, 0, 0, 1, None)
+    g.epi.ldc = N
+    return f(C.byref(g)) & 1 == 1
+
+
+# Layers of few tokens, whose contractions would be split along K: x W^T (and dY W from a transposed copy) shares K inside its workgroups where that
+# is faster - all of a layer 2048 wide with 61 tokens - and goes in parts where K is long.  dY W from the matrix itself goes in parts either way.
 def test_few_tokens_rotary_projection_in_parts(ctx):
     assert min(ctx.lib._Z24ecospa_gemm_token_splitsiii(61, n, k) for n, k in ((3072, 2048), (1024, 2048), (2048, 3072))) > 1
+    assert _shares(ctx.lib, 61, 3072, 2048)
     run_attn_case(ctx, 75, 1, 61, 2048, 32, 64, 32, 32, rope=True, causal=True, bias=False, structure="pretrained", transposed=True)
     run_attn_case(ctx, 76, 1, 61, 2048, 32, 64, 32, 32, rope=False, causal=True, structure="pretrained")
 
@@ -93,8 +104,36 @@ def test_few_tokens_activations_in_parts(ctx, act, n, k):
     kp = (k + 63) // 64 * 64
     nh = 2 * kp if act == "swiglu" else kp
     assert min(ctx.lib._Z24ecospa_gemm_token_splitsiii(61, *nk) for nk in ((nh, 2048), (kp, 2048), (2048, nh))) > 1
+    assert _shares(ctx.lib, 61, nh, 2048)
     run_ffn_case(ctx, 77, 1, 61, 2048, n, k, act, "bf16", structure="pretrained")
     run_ffn_case(ctx, 78, 1, 61, 2048, n, k, act, "bf16", structure="pretrained", transposed=True)
+
+
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("block", ["swiglu", "gelu", "attention"])
+def test_layers_with_long_k_in_parts(ctx, block, transposed):
+    """8192 wide, 33 tokens: Q|K|V with the rotation, W_1 with the activation and dY W_2 with its derivative, the epilogue behind the sum of the parts."""
+    for n in {"swiglu": (128, 64), "gelu": (64,), "attention": (384,)}[block]:
+        assert ctx.lib._Z24ecospa_gemm_token_splitsiii(33, n, 8192) > 1 and not _shares(ctx.lib, 33, n, 8192)
+    if block == "attention":
+        run_attn_case(ctx, 83, 1, 33, 8192, 4, 64, 32, 32, rope=True, causal=True, bias=False, structure="pretrained", transposed=transposed)
+    else:
+        run_ffn_case(ctx, 84, 1, 33, 8192, 160, 64, block, "bf16", structure="pretrained", transposed=transposed)
+
+
+@pytest.mark.parametrize("splits", [2, 3, 8])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 520), (33, 40, 1032), (70, 144, 520)])
+@pytest.mark.parametrize("kind,act,bias", [(STORE, 0, True), (BIAS_ACT, 0, True), (BIAS_ACT, 1, False), (ACT, 0, True), (ACT, 1, True), (DACT, 0, True),
+                                           (DACT, 1, True), (DSWIGLU, 0, True), (ROPE, 0, True), (SWIGLU, 0, True), (SWIGLU, 0, False)])
+def test_epilogues_behind_the_sum_of_parts(ctx, kind, act, bias, M, N, K, splits):
+    """K in parts and the reduction that knows every epilogue, against the contraction in one part."""
+    if kind == ROPE:
+        M, N = max(M, 33), 144          # four query and two key heads of 24
+    gen = torch.Generator(device="cuda").manual_seed(85)
+    g, c, c2, keep = _desc(kind, False, M, N, K, gen, bias, keep_c=bias or kind != SWIGLU)
+    g.epi.act = (B.ACT_GELU_ERF, B.ACT_GELU_TANH)[act]
+    _compare(ctx, g, c, c2, 0, M, splits)
+    del keep
 
 
 # 32 x 32 tiles with K shared out over a workgroup, and 64 x 64 tiles once 512 of them exist; K below, at and beyond the groups of 32

@@ -33,20 +33,46 @@ def test_shared_k_gives_what_shared_slabs_give(ctx, kind, act, bias, tile, M, N,
     del keep
 
 
-def _compare(ctx, g, c, c2, tile, M):
-    """The launch of g on `tile` and on 128 x 128 tiles of the other kernel."""
+def _compare(ctx, g, c, c2, tile, M, splits=1):
+    """The launch of g on `tile`, K in `splits` parts, and on 128 x 128 tiles of the other kernel with K whole."""
     out = []
-    for g.tile in (tile, RING_128):
+    parts = torch.full((splits * g.M * g.N + 64,), 7.0, device="cuda")
+    for g.tile, g.splits, g.partial in ((tile, splits, parts.data_ptr() if splits > 1 else None), (RING_128, 1, None)):
         c.fill_(7.0)
         c2.fill_(7.0)
         assert getattr(ctx.lib, GEMM)(ctx.h, C.byref(g)) == B.OK
         out.append((c.clone(), c2.clone()))
+    assert bool((parts[-64:] == 7).all()), "written beyond the partial sums"
     for x, y in zip(*out):
         assert bool((x[M:] == 7).all()) and bool((x[:, -8:] == 7).all()), "written beyond the matrix"
         # fp32 sums of up to 2048 products of size 1, in another order, differ by less than 2048^0.5 2^-24 4 = 1e-5; behind it bf16 rounds to a
         # neighbour at most (2^-7 of a value), of few values: a sum lies within 1e-5 of a rounding boundary 2^-8 apart
         assert bool(((x.float() - y.float()).abs() <= y.float().abs() * 2.0 ** -7 + 4e-5).all())
         assert float((x != y).float().mean()) < 0.03
+
+
+@pytest.mark.parametrize("M,N,K", [(37, 40, 8), (37, 40, 56), (37, 72, 520), (37, 72, 1608)])
+@pytest.mark.parametrize("tile", [50, 51, 52, 53, 38, 39, 40, 41])
+def test_infinities_and_nan_stay_in_their_rows_and_columns(ctx, tile, M, N, K):
+    """The k that fill the first unit up to 64 are zeroed behind the load, on both sides: nothing of them may meet an infinity or a NaN of the k that
+    they repeat.  Every other output is as without them."""
+    gen = torch.Generator(device="cuda").manual_seed(86)
+    g, c, c2, (a, b, *keep) = _desc(STORE, False, M, N, K, gen)
+    kv = (K - 1) % 64 + 1                        # k of the first unit
+    for r, k, v in ((0, 0, float("inf")), (5, kv - 1, float("-inf")), (17, min(kv, K - 1), float("nan")), (36, K - 1, float("inf"))):
+        a[r, k] = v
+    for r, k, v in ((1, kv - 1, float("nan")), (8, 0, float("inf")), (N - 1, K - 1, float("-inf"))):
+        b[r, k] = v
+    g.tile = tile
+    assert getattr(ctx.lib, GEMM)(ctx.h, C.byref(g)) == B.OK
+    want = (a.double().cpu() @ b.double().cpu().T + keep[0].double().cpu()).cuda()
+    got = c[:M, :N].double()
+    assert bool((torch.isnan(got) == torch.isnan(want)).all())
+    sure = ~torch.isnan(want)
+    assert bool((got == want)[sure & torch.isinf(want)].all())
+    sure &= ~torch.isinf(want)
+    assert bool(((got - want).abs() <= want.abs() * 2.0 ** -8 + 4e-5)[sure].all())
+    assert bool((c[M:] == 7).all()) and bool((c[:, -8:] == 7).all())
 
 
 # The 64-wide tiles of the other kernel take their activations straight from the registers, the tanh form of GELU through LDS

@@ -169,3 +169,25 @@ def test_cross_entropy_target_outside_the_vocabulary(ctx):
     assert_close(rows, want_rows, "f32", "row losses")
     assert abs(float(loss) - want_rows.mean()) <= 1e-5 * want_rows.mean()
     each_element_rounded(dl, want_dl, "dlogits")
+
+
+@pytest.mark.parametrize("other", ["zero", "near", "any"])
+def test_rounding_of_a_sum_bit_for_bit(ctx, other):
+    """Every bf16 value plus zero (infinities, NaN with any payload, subnormals come back as they are), plus one of nearly its size (ties and
+    subnormal sums) and plus any other: the fp32 sum to nearest even, in integers."""
+    bits = np.arange(65536, dtype=np.uint32)
+    rng = np.random.default_rng(5)
+    o = {"zero": np.zeros_like(bits), "near": bits ^ rng.integers(0, 0x480, bits.size, dtype=np.uint32) ^ (rng.integers(0, 2, bits.size, dtype=np.uint32) << 15),
+         "any": rng.permutation(bits)}[other]
+    dev = lambda b: torch.from_numpy(b.astype(np.uint16).view(np.int16).reshape(16, 4096)).cuda().view(torch.bfloat16)
+    x, res, x_out, y = dev(bits), dev(o), dev(bits), dev(bits)
+    ctx.ecospa_norm_fwd(B.NORM_RMS, x, torch.ones_like(x[0]), None, 1e-6, y, res=res, x_out=x_out)
+    got = x_out.view(torch.int16).cpu().numpy().reshape(-1).view(np.uint16).astype(np.uint32)
+    with np.errstate(invalid="ignore", over="ignore"):
+        s = ((bits << 16).view(np.float32) + (o << 16).view(np.float32)).view(np.uint32)
+    want = (s + 0x7fff + ((s >> 16) & 1)) >> 16
+    nan = (s & 0x7fffffff) > 0x7f800000
+    assert np.array_equal(got[~nan], want[~nan])
+    assert ((got[nan] & 0x7fff) > 0x7f80).all()
+    if other == "zero":
+        assert np.array_equal(got[nan], bits[nan] | 0x40)
