@@ -107,6 +107,17 @@ __device__ __forceinline__ float wave_sum(float v) {
   const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 48));
   return (r0 + r1) + (r2 + r3);
 }
+// Least of the 64 lanes' values: inside the rows of 16 by lane permutations (see row16_sum), then of the four rows.
+__device__ __forceinline__ uint32_t wave_umin(uint32_t v) {
+#define ECOSPA_DPP_UMIN(v, ctrl) min((v), static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), (ctrl), 0xF, 0xF, true)))
+  v = ECOSPA_DPP_UMIN(v, 0xB1);
+  v = ECOSPA_DPP_UMIN(v, 0x4E);
+  v = ECOSPA_DPP_UMIN(v, 0x141);
+  v = ECOSPA_DPP_UMIN(v, 0x140);
+#undef ECOSPA_DPP_UMIN
+  const auto row = [&](int l) __attribute__((always_inline)) { return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), l)); };
+  return min(min(row(0), row(16)), min(row(32), row(48)));
+}
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));

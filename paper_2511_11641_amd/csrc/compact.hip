@@ -285,14 +285,6 @@ __device__ __forceinline__ void map_cols_block(const MapItemDev& t, int blk) {
 // wider than the LDS tile (kept indices far apart: below a quarter kept) the region falls back to element-wise
 // gathers.  Measured: 16 column groups x 16 rows per pass beat 32 x 8 (1.5 % on a 24-layer launch, 12 % on a
 // single layer's) and 8 x 32; 64 x 4 is a third slower.
-// least of the 64 lanes' values, by lane permutations (see row16_sum)
-__device__ __forceinline__ int wave_min(int v) {
-  v = min(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true));
-  v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true));
-  v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true));
-  v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, true));
-  return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)), min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
-}
 #define MAP_LDS_GROUPS 16          // 16-byte column groups per workgroup
 #define MAP_LDS_ROWS (256 / MAP_LDS_GROUPS)   // rows per pass (MAP_LDS_GROUPS * MAP_LDS_ROWS = 256 threads)
 #define MAP_LDS_ROWS_TOTAL 64      // rows per workgroup
@@ -315,8 +307,8 @@ __device__ __forceinline__ void map_cols_lds_block(const MapItemDev& t, int blk,
   if (tid < CB) {
     const int sc = c0 + tid < t.dst_slots ? static_cast<int>(map_slot(t.m, c0 + tid)) : -1;
     smap[tid] = sc;
-    const int lo = wave_min(sc >= 0 ? sc : 0x7fffffff), hi = ~wave_min(~sc);      // (no source: -1, the smallest)
-    if ((tid & 63) == 0) { lim[2 * (tid >> 6)] = lo; lim[2 * (tid >> 6) + 1] = hi; }
+    const uint32_t lo = wave_umin(sc >= 0 ? sc : 0x7fffffff), past = ~wave_umin(~static_cast<uint32_t>(sc + 1));      // (no source: 0, the smallest)
+    if ((tid & 63) == 0) { lim[2 * (tid >> 6)] = static_cast<int>(lo); lim[2 * (tid >> 6) + 1] = static_cast<int>(past) - 1; }
   }
   __syncthreads();
   int smin = lim[0], smax = lim[1];

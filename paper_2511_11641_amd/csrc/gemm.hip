@@ -52,26 +52,6 @@ struct F32Frags {
 
 #define F32_CHAIN 256
 
-// Output (m, n): its sum with the bias already added; h, u: what the activation derivatives read beside it.
-__device__ __forceinline__ void f32_put(const GemmEpi& e, int m, int n, float acc, float h, float u) {
-  float* const c = static_cast<float*>(e.c) + static_cast<long long>(m) * e.ldc;
-  switch (e.kind) {
-    case EPI_STORE: c[n] = acc; break;
-    case EPI_BIAS_ACT:
-      c[n] = acc;
-      static_cast<float*>(e.c2)[static_cast<long long>(m) * e.ldc2 + n] = act_gelu(acc, e.act);
-      break;
-    case EPI_ACT: c[n] = act_gelu(acc, e.act); break;
-    case EPI_DACT: c[n] = acc * act_gelu_grad(h, e.act); break;
-    case EPI_DSWIGLU: {
-      const float sg = act_sigmoid(h);
-      c[2 * n] = acc * u * sg * (1.f + h * (1.f - sg));
-      c[2 * n + 1] = acc * h * sg;
-    } break;
-    default: break;          // the rotary and gated forms are bf16 only
-  }
-}
-
 // One output tile of K split z.  A K-slow A (dY^T X) also gives its column sums (GemmDesc::colsum, the bias gradient; K unsplit): the
 // workgroups of the first tile column add the operand's values up as they pass, sixteen at a time in a tree, the sums of those with what their additions round away.
 template <int WM, int WN, int WK, bool TA, bool TB>
@@ -163,7 +143,7 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& d, int tiles_n, int k_c
   auto put = [&](int m, float v, float h, float u) __attribute__((always_inline)) {
     if (m < d.M && n_out < d.N) {
       if (part) part[static_cast<long long>(m) * d.N + n_out] = v;
-      else f32_put(d.epi, m, n_out, biased ? v + bias : v, h, u);
+      else epi_put<float>(d.epi, m, n_out, biased ? v + bias : v, h, u);
     }
   };
   // accumulator layout: column lane % 32, row 8 (r / 4) + 4 (lane / 32) + r % 4

@@ -9,38 +9,38 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // ---------------------------------------------------------------------------------------------
 // epilogue
 // ---------------------------------------------------------------------------------------------
+// Output (m, n): its sum with the bias already added; h, u: what the activation derivatives read beside it.
 template <typename T>
-__device__ __forceinline__ void epi_apply(const GemmEpi& e, int m, int n, float acc) {
-  T* c = static_cast<T*>(e.c);
-  const long long off = static_cast<long long>(m) * e.ldc + n;
+__device__ __forceinline__ void epi_put(const GemmEpi& e, int m, int n, float acc, float h, float u) {
+  T* const c = static_cast<T*>(e.c) + static_cast<long long>(m) * e.ldc;
   switch (e.kind) {
-    case EPI_STORE: {
-      if (e.bias) acc += load_f32<T>(static_cast<const T*>(e.bias) + n);
-      store_f32<T>(c + off, acc);
-    } break;
-    case EPI_BIAS_ACT: {
-      if (e.bias) acc += load_f32<T>(static_cast<const T*>(e.bias) + n);
-      store_f32<T>(c + off, acc);
+    case EPI_STORE: store_f32<T>(c + n, acc); break;
+    case EPI_BIAS_ACT:
+      store_f32<T>(c + n, acc);
       store_f32<T>(static_cast<T*>(e.c2) + static_cast<long long>(m) * e.ldc2 + n, act_gelu(acc, e.act));
-    } break;
-    case EPI_ACT: {
-      if (e.bias) acc += load_f32<T>(static_cast<const T*>(e.bias) + n);
-      store_f32<T>(c + off, act_gelu(acc, e.act));
-    } break;
-    case EPI_DACT: {
-      const float h = load_f32<T>(static_cast<const T*>(e.h) + static_cast<long long>(m) * e.ldh + n);
-      store_f32<T>(c + off, acc * act_gelu_grad(h, e.act));
-    } break;
+      break;
+    case EPI_ACT: store_f32<T>(c + n, act_gelu(acc, e.act)); break;
+    case EPI_DACT: store_f32<T>(c + n, acc * act_gelu_grad(h, e.act)); break;
     case EPI_DSWIGLU: {      // unit n: gate and up pre-activations in columns 2n and 2n + 1 of h, their gradients likewise in c
-      const T* hp = static_cast<const T*>(e.h) + static_cast<long long>(m) * e.ldh + 2 * n;
-      const float g = load_f32<T>(hp), u = load_f32<T>(hp + 1);
-      const float sg = act_sigmoid(g);
-      T* cp = c + static_cast<long long>(m) * e.ldc + 2 * n;
-      store_f32<T>(cp, acc * u * sg * (1.f + g * (1.f - sg)));
-      store_f32<T>(cp + 1, acc * g * sg);
+      const float sg = act_sigmoid(h);
+      store_f32<T>(c + 2 * n, acc * u * sg * (1.f + h * (1.f - sg)));
+      store_f32<T>(c + 2 * n + 1, acc * h * sg);
     } break;
     default: break;          // EPI_ROPE, EPI_SWIGLU: bf16 only (vector epilogue)
   }
+}
+template <typename T>
+__device__ __forceinline__ void epi_apply(const GemmEpi& e, int m, int n, float acc) {
+  float h = 0.f, u = 0.f;
+  if (e.kind == EPI_DACT || e.kind == EPI_DSWIGLU) {
+    const int per = e.kind == EPI_DSWIGLU ? 2 : 1;
+    const T* const at = static_cast<const T*>(e.h) + static_cast<long long>(m) * e.ldh + static_cast<long long>(n) * per;
+    h = load_f32<T>(at);
+    u = load_f32<T>(at + per - 1);
+  } else if (e.bias) {
+    acc += load_f32<T>(static_cast<const T*>(e.bias) + n);
+  }
+  epi_put<T>(e, m, n, acc, h, u);
 }
 
 // 8 consecutive columns of one row, bf16 storage, 16-byte aligned (N, ld* multiples of 8)

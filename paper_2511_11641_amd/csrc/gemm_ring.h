@@ -172,6 +172,18 @@ __device__ __forceinline__ int ring_div(int a, int d, unsigned inv, int& rest) {
   return q;
 }
 
+// Tile (row, column) and K split of workgroup `block`.
+__device__ __forceinline__ void ring_place(const RingGrid& w, int block, bool split, int& zsplit, int& row, int& col) {
+  const int xcd = block & 7;
+  int id = xcd * w.per + min(xcd, w.more) + (block >> 3), in_band;
+  zsplit = 0;
+  if (split) zsplit = ring_div(id, w.tiles, w.tiles_inv, id);
+  const int band = ring_div(id, w.band, w.band_inv, in_band);
+  const bool last_band = band == w.last_band;
+  col = ring_div(in_band, last_band ? w.last_rows : w.group, last_band ? w.last_inv : w.group_inv, row);
+  row += band * w.group;
+}
+
 // One output tile (of one K split): that of workgroup `block` of the grid w.
 // EPIS: bit mask of the epilogue kinds the instantiation carries; CS: column sums of a K-slow A (GemmDesc::colsum); WIDE: see ring_off.
 template <int BM, int BN, int NS, bool TA, bool TB, bool CS, int EPIS, bool WIDE>
@@ -185,13 +197,10 @@ __device__ __forceinline__ void ring_tile(const GemmDesc& d, const RingGrid& w, 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 1, wn = __builtin_amdgcn_readfirstlane(wave & 1);
 
-  const int xcd = block & 7, tiles_n = w.tiles_n;
-  int id = xcd * w.per + min(xcd, w.more) + (block >> 3), zsplit = 0, in_band, tile_row;
-  if (d.splits > 1) zsplit = ring_div(id, w.tiles, w.tiles_inv, id);
-  const int band = ring_div(id, w.band, w.band_inv, in_band);
-  const bool last_band = band == w.last_band;
-  const int tile_col = ring_div(in_band, last_band ? w.last_rows : w.group, last_band ? w.last_inv : w.group_inv, tile_row);
-  const int m0 = (band * w.group + tile_row) * BM, n0 = tile_col * BN;
+  const int tiles_n = w.tiles_n;
+  int zsplit, tile_row, tile_col;
+  ring_place(w, block, d.splits > 1, zsplit, tile_row, tile_col);
+  const int m0 = tile_row * BM, n0 = tile_col * BN;
   const int k_begin = zsplit * w.k_chunk;
   const int k_end = min(d.K, k_begin + w.k_chunk);
   const int nk = (k_end - k_begin + RING_BK - 1) / RING_BK;

@@ -5,7 +5,7 @@
 // Here narrow tiles fill it, down to 32x16, and what a narrow tile lacks in products per byte does not matter at this size; the chain is
 // shared out: every wavefront of a workgroup computes the whole BM x BN tile over its own units of 64 k, dealt round the W wavefronts.  It
 // streams them global -> LDS into D buffers of its own (128 bytes of a row at a time: 64 are 10 % slower), so the main loop has no barrier, and
-// 96 - 160 KB per compute unit are on their way from the start.  The W partial tiles meet in LDS at the end and are added in wavefront order.
+// 128 - 160 KB per compute unit are on their way from the start where K has a unit for every buffer (64 W D: from 1536 on for 32x16, 768 for 64x32).  The W partial tiles meet in LDS at the end and are added in wavefront order.
 //
 // Weights from memory, kernel with K split over workgroups (or unsplit) -> this one, us: 61x3072x2048 10.6 -> 7.5 (32x32), 61x2048x1024 6.3 -> 3.9
 // (32x16), 61x5504x2048 with SwiGLU 13.2 -> 10.4 (64x32), 61x2048x2752 11.4 -> 7.4, 17x2048x2752 9.9 -> 6.6, 200x2048x2752 13.4 -> 10.3, 512x768x768
@@ -40,11 +40,9 @@ void gemm_bf16_share_kernel(const RingGrid w, const GemmDesc d) {
   const int block = blockIdx.x, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, g = lane >> 4;
 
-  int id = (block & 7) * w.per + min(block & 7, w.more) + (block >> 3), in_band, tile_row;
-  const int band = ring_div(id, w.band, w.band_inv, in_band);
-  const bool last_band = band == w.last_band;
-  const int tile_col = ring_div(in_band, last_band ? w.last_rows : w.group, last_band ? w.last_inv : w.group_inv, tile_row);
-  const int m0 = (band * w.group + tile_row) * BM, n0 = tile_col * BN;
+  int zsplit, tile_row, tile_col;
+  ring_place(w, block, false, zsplit, tile_row, tile_col);
+  const int m0 = tile_row * BM, n0 = tile_col * BN;
 
   // units of this wavefront: wave, wave + W, ..; unit 0 takes the remainder of K (kv of its 64 k)
   const int units = (d.K + 63) >> 6, kv = d.K - (units - 1) * 64;

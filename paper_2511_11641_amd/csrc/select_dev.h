@@ -42,18 +42,6 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
   return v;
 }
 
-// Least of the 64 lanes' values: inside the rows of 16 by lane permutations (see row16_sum), then of the four rows.
-__device__ __forceinline__ uint32_t wave_umin(uint32_t v) {
-#define ECOSPA_DPP_UMIN(v, ctrl) min((v), static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), (ctrl), 0xF, 0xF, true)))
-  v = ECOSPA_DPP_UMIN(v, 0xB1);
-  v = ECOSPA_DPP_UMIN(v, 0x4E);
-  v = ECOSPA_DPP_UMIN(v, 0x141);
-  v = ECOSPA_DPP_UMIN(v, 0x140);
-#undef ECOSPA_DPP_UMIN
-  const auto row = [&](int l) __attribute__((always_inline)) { return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), l)); };
-  return min(min(row(0), row(16)), min(row(32), row(48)));
-}
-
 // Exclusive prefix sums of `a` and of `b` over the block's threads in thread order (one pass for both).
 // `wave_tot` holds 2 x (SELECT_THREADS / 64) ints and must not be in use by another scan one barrier earlier.
 __device__ __forceinline__ void block_exclusive_scan2(int a, int b, int* wave_tot, int& a_before, int& b_before) {
