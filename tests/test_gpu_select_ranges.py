@@ -28,6 +28,9 @@ SCORES = {
     "spread norms": lambda n, g: np.exp(0.7 * g.standard_normal(n)).astype(np.float32) * np.float32(0.01),
     "every sign": lambda n, g: np.concatenate([[np.nan, np.inf, -np.inf, 0.0, -0.0, 1e-45, -1e-45], g.standard_normal(n - 7)]).astype(np.float32),
     "pairs": lambda n, g: np.repeat(g.standard_normal((n + 1) // 2), 2)[:n].astype(np.float32),
+    "six in ten zero": lambda n, g: (np.exp(0.5 * g.standard_normal(n)) * (g.random(n) > 0.6)).astype(np.float32),
+    "five values": lambda n, g: g.integers(0, 5, n).astype(np.float32),
+    "two neighbours among others": lambda n, g: np.where(g.random(n) < 0.9, _neighbours(n, g, 1), 10.0 ** g.uniform(-30, 30, n) * g.choice((-1, 1), n)).astype(np.float32),
     "one above": lambda n, g: np.where(np.arange(n) == n // 2, 3e38, 1e-30).astype(np.float32),
 }
 
