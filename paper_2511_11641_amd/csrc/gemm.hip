@@ -54,7 +54,9 @@ struct F32Frags {
 
 // One output tile of K split z.  A K-slow A (dY^T X) also gives its column sums (GemmDesc::colsum, the bias gradient; K unsplit): the
 // workgroups of the first tile column add the operand's values up as they pass, sixteen at a time in a tree, the sums of those with what their additions round away.
-template <int WM, int WN, int WK, bool TA, bool TB>
+// FEW: for launches whose workgroups are all resident at once (f32_few), which last as long as one workgroup does.  The last pair of K groups then
+// stands by itself, so that nothing is loaded twice; that takes 16 - 36 registers more, a workgroup less per compute unit.
+template <int WM, int WN, int WK, bool TA, bool TB, bool FEW>
 __device__ __forceinline__ void f32_tile(const GemmDesc& d, int tiles_n, int k_chunk, int block, int z) {
   static_assert(WM * WN * WK == 4 && (WK == 1 || WK == 4), "four wavefronts");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hh = lane >> 5;
@@ -88,45 +90,64 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& d, int tiles_n, int k_c
   };
   if (nc > 0) { fa.load(a[0], k_begin, hh); fb.load(b[0], k_begin, hh); }
   // The outputs that this lane writes: one column, NOUT rows.  What their epilogue reads besides the sums is asked for here; behind the
-  // loop every output's saved pre-activation was a trip to memory of its own.
+  // loop every output's saved pre-activation was a trip to memory of its own.  (Not for the 16 outputs of a lane of a 64 x 64 tile: 32 registers
+  // more through the loop leave a SIMD two wavefronts where it has five; 1027x2448x192 with GELU' 32.5 us, 36.0 with them.)
   constexpr int NOUT = WK == 4 ? 4 : 16;
+  constexpr bool AHEAD = WK == 4;
   auto row_out = [](int q) __attribute__((always_inline)) { return WK == 4 ? 8 * q : 8 * (q / 4) + q % 4; };
   const int m_out = m0 + (WK == 4 ? threadIdx.x >> 5 : 4 * hh), n_out = n0 + (WK == 4 ? threadIdx.x & 31 : l32);
-  const bool derivative = d.epi.kind == EPI_DACT || d.epi.kind == EPI_DSWIGLU, biased = d.splits <= 1 && d.epi.bias && !derivative;
+  const bool derivative = (d.epi.kind == EPI_DACT || d.epi.kind == EPI_DSWIGLU) && d.splits <= 1, biased = d.splits <= 1 && d.epi.bias && !derivative;
+  const int per_unit = d.epi.kind == EPI_DSWIGLU ? 2 : 1;
   float bias = 0.f, eh[NOUT], eu[NOUT];
 #pragma unroll
   for (int q = 0; q < NOUT; ++q) eh[q] = eu[q] = 0.f;
   if (biased) bias = static_cast<const float*>(d.epi.bias)[min(n_out, d.N - 1)];
-  if (derivative && d.splits <= 1) {
-    const int per = d.epi.kind == EPI_DSWIGLU ? 2 : 1;
-    const float* const col = static_cast<const float*>(d.epi.h) + static_cast<long long>(min(n_out, d.N - 1)) * per;
+  auto side_column = [&]() __attribute__((always_inline)) { return static_cast<const float*>(d.epi.h) + static_cast<long long>(min(n_out, d.N - 1)) * per_unit; };
+  if (AHEAD && derivative) {
+    const float* const col = side_column();
 #pragma unroll
     for (int q = 0; q < NOUT; ++q) {
       const float* const at = col + static_cast<long long>(min(m_out + row_out(q), d.M - 1)) * d.epi.ldh;
       eh[q] = at[0];
-      eu[q] = at[per - 1];
+      eu[q] = at[per_unit - 1];
     }
   }
-  // Groups in pairs; the last pair by itself, so that nothing is loaded twice and no load sits behind a branch (the products of a pair would
-  // wait for it as well).
+  // groups in pairs, no load behind a branch (the products of a pair would wait for it as well)
   int c = 0;
-  auto pair = [&](bool more) __attribute__((always_inline)) {
-    fa.load(a[1], k_begin + (c + 1) * 32, hh);
-    fb.load(b[1], k_begin + (c + 1) * 32, hh);
-    products(a[0], b[0]);
-    if (more) {
-      fa.load(a[0], k_begin + (c + 2) * 32, hh);
-      fb.load(b[0], k_begin + (c + 2) * 32, hh);
-    }
-    products(a[1], b[1]);
-    c += 2;
+  auto chain_end = [&]() __attribute__((always_inline)) {
     if (c % (F32_CHAIN / 32) == 0) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) { sum[r] += acc[r]; acc[r] = 0.f; }
     }
   };
-  while (c + 2 < nc) pair(true);
-  if (c + 2 == nc) pair(false);
+  if constexpr (FEW) {
+    auto pair = [&](bool more) __attribute__((always_inline)) {
+      fa.load(a[1], k_begin + (c + 1) * 32, hh);
+      fb.load(b[1], k_begin + (c + 1) * 32, hh);
+      products(a[0], b[0]);
+      if (more) {
+        fa.load(a[0], k_begin + (c + 2) * 32, hh);
+        fb.load(b[0], k_begin + (c + 2) * 32, hh);
+      }
+      products(a[1], b[1]);
+      c += 2;
+      chain_end();
+    };
+    while (c + 2 < nc) pair(true);
+    if (c + 2 == nc) pair(false);
+  } else {
+    while (c + 2 <= nc) {
+      fa.load(a[1], k_begin + (c + 1) * 32, hh);
+      fb.load(b[1], k_begin + (c + 1) * 32, hh);
+      products(a[0], b[0]);
+      const int kn = k_begin + min(c + 2, nc - 1) * 32;       // the last group again when there is no further one
+      fa.load(a[0], kn, hh);
+      fb.load(b[0], kn, hh);
+      products(a[1], b[1]);
+      c += 2;
+      chain_end();
+    }
+  }
   if (c < nc) products(a[0], b[0]);
   if (k_begin + nc * 32 < k_end) {
     fa.load_tail(a[0], k_begin + nc * 32, k_end, hh);
@@ -140,10 +161,16 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& d, int tiles_n, int k_c
     cs += fabsf(cs_lost) < INFINITY ? cs_lost : 0.f;      // (not a number behind an infinite sum, which stands as it is)
     cs += __shfl_xor(cs, 32, 64);      // the other half of the k
   }
-  auto put = [&](int m, float v, float h, float u) __attribute__((always_inline)) {
+  auto put = [&](int q, float v) __attribute__((always_inline)) {
+    const int m = m_out + row_out(q);
     if (m < d.M && n_out < d.N) {
+      if (!AHEAD && derivative) {
+        const float* const at = side_column() + static_cast<long long>(m) * d.epi.ldh;
+        eh[q] = at[0];
+        eu[q] = at[per_unit - 1];
+      }
       if (part) part[static_cast<long long>(m) * d.N + n_out] = v;
-      else epi_put<float>(d.epi, m, n_out, biased ? v + bias : v, h, u);
+      else epi_put<float>(d.epi, m, n_out, biased ? v + bias : v, eh[q], eu[q]);
     }
   };
   // accumulator layout: column lane % 32, row 8 (r / 4) + 4 (lane / 32) + r % 4
@@ -157,28 +184,28 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& d, int tiles_n, int k_c
       d.colsum[m0 + threadIdx.x] = (red_cs[0][threadIdx.x] + red_cs[1][threadIdx.x]) + (red_cs[2][threadIdx.x] + red_cs[3][threadIdx.x]);
     const int n = threadIdx.x & 31;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < NOUT; ++q) {
       const int m = (threadIdx.x >> 5) + 8 * q;
-      put(m0 + m, (red[0][m][n] + red[1][m][n]) + (red[2][m][n] + red[3][m][n]), eh[q], eu[q]);
+      put(q, (red[0][m][n] + red[1][m][n]) + (red[2][m][n] + red[3][m][n]));
     }
   } else {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) put(m_out + row_out(r), acc[r], eh[r % NOUT], eu[r % NOUT]);
+    for (int r = 0; r < NOUT; ++r) put(r, acc[r]);
     if (TA && TB && sums && hh == 0 && m0 + l32 < d.M) d.colsum[m0 + l32] = cs;
   }
 }
 
-template <int WM, int WN, int WK, bool TA, bool TB>
+template <int WM, int WN, int WK, bool TA, bool TB, bool FEW>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmDesc d, int tiles_n, int k_chunk) {
-  f32_tile<WM, WN, WK, TA, TB>(d, tiles_n, k_chunk, blockIdx.x, blockIdx.z);
+  f32_tile<WM, WN, WK, TA, TB, FEW>(d, tiles_n, k_chunk, blockIdx.x, blockIdx.z);
 }
 // A weight gradient and a contraction over the tokens that do not depend on each other, in one launch: the first n_w workgroups take the
 // tiles of the first.  Launches of this size last as long as one of their workgroups does, 6 - 8 us.
-template <bool XTB>
+template <bool XTB, bool FEW>
 __global__ __launch_bounds__(256) void gemm_f32_pair_kernel(const GemmDesc w, const GemmDesc x, int w_tiles_n, int n_w, int x_tiles_n) {
   const int block = blockIdx.x;
-  if (block < n_w) f32_tile<1, 1, 4, true, true>(w, w_tiles_n, w.K, block, 0);
-  else f32_tile<1, 1, 4, false, XTB>(x, x_tiles_n, x.K, block - n_w, 0);
+  if (block < n_w) f32_tile<1, 1, 4, true, true, FEW>(w, w_tiles_n, w.K, block, 0);
+  else f32_tile<1, 1, 4, false, XTB, FEW>(x, x_tiles_n, x.K, block - n_w, 0);
 }
 
 // 64 x 64 tiles once they fill the compute units (half the operand traffic per product); below that K is what there is to share out
@@ -186,14 +213,21 @@ static bool f32_wide_tiles(const GemmDesc& d, int splits) {
   return static_cast<long long>((d.M + 63) / 64) * ((d.N + 63) / 64) * splits >= 512;
 }
 
+// Whether a compute unit takes all its workgroups of the launch at once in the FEW form as well: three by its registers, two of a pair.  512x512x256 with two
+// outputs 6.0 us in the other form, 5.6 in this one; with more workgroups than are resident it is the other way round: dW_2 | dH of 512 tokens, 256 to 1024
+// wide, 768 workgroups: 13.0 us, 15.8 in this one.
+static bool f32_few(long long blocks, bool pair) { return blocks <= (pair ? 2 : 3) * 256; }
+
 template <bool TA, bool TB>
 static void launch_f32(ecospa_ctx* ctx, const GemmDesc& d, int splits) {
   const int k_chunk = (d.K + splits - 1) / splits;
   const int tm = (d.M + 63) / 64, tn = (d.N + 63) / 64, sm = (d.M + 31) / 32, sn = (d.N + 31) / 32;
   if (f32_wide_tiles(d, splits))
-    hipLaunchKernelGGL((gemm_f32_kernel<2, 2, 1, TA, TB>), dim3(tm * tn, 1, splits), dim3(256), 0, ctx->stream, d, tn, k_chunk);
+    hipLaunchKernelGGL((gemm_f32_kernel<2, 2, 1, TA, TB, false>), dim3(tm * tn, 1, splits), dim3(256), 0, ctx->stream, d, tn, k_chunk);
+  else if (f32_few(static_cast<long long>(sm) * sn * splits, false))
+    hipLaunchKernelGGL((gemm_f32_kernel<1, 1, 4, TA, TB, true>), dim3(sm * sn, 1, splits), dim3(256), 0, ctx->stream, d, sn, k_chunk);
   else
-    hipLaunchKernelGGL((gemm_f32_kernel<1, 1, 4, TA, TB>), dim3(sm * sn, 1, splits), dim3(256), 0, ctx->stream, d, sn, k_chunk);
+    hipLaunchKernelGGL((gemm_f32_kernel<1, 1, 4, TA, TB, false>), dim3(sm * sn, 1, splits), dim3(256), 0, ctx->stream, d, sn, k_chunk);
 }
 
 // fixed-order sum of the K-split partials, then the epilogue
@@ -603,8 +637,9 @@ int ecospa_gemm_pair(ecospa_ctx* ctx, const GemmDesc& w, const GemmDesc& x, int 
   }
   if (route == GEMM_PAIR_F32) {
     const int wn = (w.N + 31) / 32, xn = (x.N + 31) / 32, n_w = (w.M + 31) / 32 * wn, n_x = (x.M + 31) / 32 * xn;
-    if (x.trans_b) hipLaunchKernelGGL((gemm_f32_pair_kernel<true>), dim3(n_w + n_x), dim3(256), 0, ctx->stream, w, x, wn, n_w, xn);
-    else hipLaunchKernelGGL((gemm_f32_pair_kernel<false>), dim3(n_w + n_x), dim3(256), 0, ctx->stream, w, x, wn, n_w, xn);
+    const auto kern = f32_few(n_w + n_x, true) ? (x.trans_b ? gemm_f32_pair_kernel<true, true> : gemm_f32_pair_kernel<false, true>)
+                                               : (x.trans_b ? gemm_f32_pair_kernel<true, false> : gemm_f32_pair_kernel<false, false>);
+    hipLaunchKernelGGL(kern, dim3(n_w + n_x), dim3(256), 0, ctx->stream, w, x, wn, n_w, xn);
     ECOSPA_CHECK_LAUNCH(ctx, "gemm_f32_pair_kernel");
     return ECOSPA_OK;
   }
