@@ -263,11 +263,13 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_vec8_kernel(const Gemm
 // epilogue, with slab and rest measured per shape on full rounds of 256 tiles (us; `rest`: first slabs from memory and the stores; 2 us
 // more once per launch).  The K-slow forms read 8 bytes per LDS instruction instead of 16, which the narrow tiles feel most.  A split adds
 // its partial sums: 3 us and their bytes at 4 TB/s; a split keeps at least 4 slabs.  The kernel of resident workgroups hides most of
-// the rest and the epilogue of every tile but a workgroup's last.  The times are of operands that the L2s hold: with operands from
-// memory a slab of the K-slow 64x128 shape takes 0.38-0.46 us.
+// the rest and the epilogue of every tile but a workgroup's last.  The times are of operands that the L2s hold.  Those of the K-slow
+// forms were taken when their LDS tiles still had bank conflicts; without, a slab takes 1.26 us on 256x256 tiles, 0.99 (192x256), 1.00, 0.72, 0.71, 0.79, 0.55,
+// 0.56, 0.41 (128x128) and 0.31 (64x128), what lies beside the slabs up to 2 us less, and 0.80 with resident workgroups.  With operands from
+// memory it takes 1.35, 1.19, 1.21, 0.74, 0.77, 0.78, 0.63, 0.64, 0.54 and 0.41.
 //
-// How good the choice is: 680 contractions x W^T of random kinds and sizes (512 .. 32768 x 64 .. 52000 x 256 .. 8300; activations just written, the rest
-// from memory), every shape and the resident workgroups timed.  The sum over the choices is 1.0 - 1.4 % above the sum of the fastest, the worst
+// How good the choice is (the K-slow forms have not been tried like this): 680 contractions x W^T of random kinds and sizes (512 .. 32768 x 64 .. 52000
+// x 256 .. 8300; activations just written, the rest from memory), every shape and the resident workgroups timed.  The sum over the choices is 1.0 - 1.4 % above the sum of the fastest, the worst
 // single ones (fewer than 256 tiles, K beyond 3000) 1.4 times.  A slab of 256x256 is 1.28 us by least squares over the plain stores; with 1.30 or 1.33 in
 // the table the sum is 0.1 - 0.7 % larger, with 0.79 - 0.83 for the resident workgroups' it is no smaller.  Outputs of more than 30000 columns
 // cost those up to 3 us a round that the rule does not see (6144x24576x2048: 484 us, 440 on 256x256 tiles).
@@ -351,8 +353,10 @@ static double flow_time(const GemmDesc& d) {
   return FLOW_REST + rounds * (d.K / 64 * (d.trans_a ? FLOW_SLAB_TT : FLOW_SLAB_NT) + FLOW_ROUND) + epi * (1.0 + 0.2 * (rounds - 1.0));
 }
 
-// Kernel that shares K out inside a workgroup: time of a round (us, weights from memory) and per unit of 64 k.  Single rounds fit to 0.5 us from K = 768
-// to 4096 and 17 to 256 rows; a further round costs about as much as the first (512 tiles of 64x32 at K = 512: 7.3 us, 64x64 of the ring kernel 4.9).
+// Kernel that shares K out inside a workgroup: time of a round (us, weights from memory) and per unit of 64 k.  Against 1000 random contractions of 1 to
+// 1100 rows, N and K 64 to 12000, every kind and shape: the time of a single round comes out 0.6 - 1.0 us short below K = 256, 0 - 0.4 short (spread
+// 0.5) from 640 to 2048, 0.1 - 1.2 long (0.9 - 1.7) up to 4096 and 0.7 - 4 long beyond; a further round costs about as much as the first (512 tiles of 64x32
+// at K = 512: 7.3 us, 64x64 of the ring kernel 4.9).
 struct ShareShape {
   int bm, bn;
   float round, unit;
@@ -372,8 +376,11 @@ static double share_plan(const GemmDesc& d, int kind, int* shape_out) {
   }
   return best;
 }
-// What the ring kernel takes beyond its table on 64-wide tiles, whose slabs the table has from L2: with weights from memory, 61 to 256 rows, 64x64
-// unsplit, it takes 5.2 us at K = 768, 6.3 at 1024, 11.5 at 2048 and 20.5 at 4096 (table 5.7, 6.3, 9.0, 14.3).
+// What the ring kernel takes beyond its table on 64-wide tiles, whose slabs the table has from L2.  Of the same contractions, weights from memory, 64x64
+// tiles take nothing more below 4 slabs, 0.3 us at 4 - 8, 0.9 at 8 - 16, 2.1 at 16 - 24, 4.5 at 32 - 48 and 8.6 at 64 - 96, in parts 1.7 at 4 - 8 slabs, 2.5 at
+// 8 - 16 and 4.1 at 16 - 24.  About half of that is counted: the kernel that shares K is then taken where it is faster and nowhere else - 830 of the 1000
+// go to it, none of which the ring kernel, in parts or not, does sooner, weights in the caches or not; 40 with K from 2900 to 6700 stay in parts that would take 0.7 -
+// 0.9 of the time.  The sum over the choices is 2 % above the sum of the fastest, 35 % without the kernel.
 static double ring_cold(int shape, int slabs) { return shape >= 9 ? 0.065 * slabs - 0.6 : 0.0; }
 
 int ecospa_gemm_splits(int dtype, int M, int N, int K) {
